@@ -782,7 +782,7 @@ __global__ void k_trial_shortcut(const double *__restrict__ ghat, const double *
     }
 }
 
-__global__ void k_zero_count(int32_t *count) { *count = 0; }
+__global__ void k_zero_count(int32_t *count) { count[threadIdx.x] = 0; }
 
 size_t dtfm_hk_exchange_bytes(const dtfm_problem *pr)
 {
@@ -818,7 +818,8 @@ dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t ro
     }
     b.pp = ar.take<double>(rows);
     b.list = ar.take<int32_t>(rows);
-    b.count = ar.take<int32_t>(1);
+    b.dense = lean || pr->D_pp <= DTFM_HK_LDS_MAX_DPP ? b.list : ar.take<int32_t>(rows);
+    b.count = ar.take<int32_t>(2);
     return b;
 }
 
@@ -878,9 +879,11 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     }
     if (cost == nullptr) return DTFM_OK;
     const int32_t *list = nullptr, *count = nullptr;
-    if (ref != nullptr) {   // trials of the local search: Held-Karp only where the coarsened graph does not settle the trial
-        hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(1), 0, st, b.count);
+    if (ref != nullptr || n > DTFM_HK_LDS_MAX_DPP) {
+        hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(2), 0, st, b.count);
         DTFM_HIP(hipGetLastError());
+    }
+    if (ref != nullptr) {   // trials of the local search: Held-Karp only where the coarsened graph does not settle the trial
         hipLaunchKernelGGL(k_trial_shortcut, dim3((unsigned)((rows + 3) / 4)), dim3(4 * DTFM_WAVE), 0, st, b.ghat, b.datap,
                            n * n, ref->ghat_cur, ref->pp_cur, ref->cur, cost, b.pp, b.list, b.count, rows, ref->trials_per_row);
         DTFM_HIP(hipGetLastError());
@@ -896,6 +899,9 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         hipLaunchKernelGGL(k_held_karp<true>, dim3((unsigned)rows), dim3(bt), lds, st, b.ghat, b.datap, n,
                            pr->hk_subsets, pr->hk_off, (double *)nullptr, cost, rows, list, count, b.pp);
     } else {
+        // the pruned recursion first; the dense one for what it left (usually nothing)
+        const int rc = dtfm_tour_enqueue(pr, b, rows, cost, list, ref, st);
+        if (rc != DTFM_OK) return rc;
         size_t grid = b.hk_grid;
         constexpr int NL = DTFM_HK_BLOCK_LOW;
         // rows, Ghat, and the low parts in layer order with two more turns of entries behind them (read ahead, never used)
@@ -903,8 +909,8 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         auto kern = n <= 12 ? k_held_karp_blocked<NL, 6> : n <= 14 ? k_held_karp_blocked<NL, 7> : k_held_karp_blocked<NL, 8>;
         DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds));
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1 << NL), lds, st, b.ghat, b.datap, n, b.hk_tab, cost, rows, list,
-                           count, b.pp);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1 << NL), lds, st, b.ghat, b.datap, n, b.hk_tab, cost, rows, b.dense,
+                           b.count + 1, b.pp);
     }
     DTFM_HIP(hipGetLastError());
     return DTFM_OK;

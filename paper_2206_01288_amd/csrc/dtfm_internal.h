@@ -85,7 +85,8 @@ struct dtfm_eval_bufs {
     size_t hk_grid;  // workgroups of the blocked Held-Karp kernel (each owns one exchange area)
     double *pp;      // rows: PipelineP-Cost (the Held-Karp value) of every row whose Held-Karp was run
     int32_t *list;   // rows: the rows whose Held-Karp is still to run (trial evaluations, see dtfm_trial_ref)
-    int32_t *count;  // 1: length of list
+    int32_t *dense;  // rows: the rows the pruned recursion leaves to the dense one (lean: the buffer of `list`)
+    int32_t *count;  // 2: lengths of list and dense
 };
 // What a trial evaluation of the local search knows about the rows its trials were made from: with it, a trial
 // whose coarsened graph equals its current row's, or is nowhere below it while DataP + the current PipelineP
@@ -109,6 +110,10 @@ int dtfm_eval_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int
 // inc_j < inc_jp (inc_j < 0: plain evaluation): only the edges of those two stages are matched again
 int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int32_t *perm, size_t rows,
                           double *cost, int inc_j, int inc_jp, hipStream_t st, const dtfm_trial_ref *ref = nullptr);
+// Eq. 4 by pruned subset recursion (dtfm_tour.hip): cost and b.pp of the rows (with list: list[0 .. b.count[0])); appends
+// the rows it cannot settle to b.dense, b.count[1] of them. D_pp from 3 to 16.
+int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t rows, double *cost, const int32_t *list,
+                      const dtfm_trial_ref *ref, hipStream_t st);
 int dtfm_weights_enqueue(const double *lat_dev, const double *bw_dev, int N, double shard,
                          double c_pp, double *W_dp, double *W_pp, hipStream_t st);
 

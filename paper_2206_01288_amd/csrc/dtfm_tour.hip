@@ -1,0 +1,534 @@
+// Eq. 4 for many stages by pruned subset recursion (the open-loop TSP over the coarsened graph, exact to the bit).
+//
+// Held-Karp fills tab[S][v] for all 2^n subsets (n = 16: 524,288 entries, 3.9 million relaxations a candidate). Nearly
+// all of them belong to no path that comes near the optimum: with a lower bound on what the stages outside S still
+// cost, some 50 to 200 entries per candidate are left (bounds and thresholds below; measured on coarsened graphs of
+// region, cluster and independent networks at n = 14 and 16, where the dense recursion is the whole cost).
+//   bound      node potentials pi turn an edge (i, j) into C_ij = g_ij + pi_i + pi_j. A path visits every inner stage
+//              with degree 2, so the cheapest completion of a path over S that ends in v costs at least
+//              MST_C(rest) + (cheapest edge into the rest is priced exactly, edge by edge) - 2 sum pi(rest) + the
+//              smallest pi an end can have. Good potentials make this tight to some 1e-4 of the optimum; they come from
+//              a few subgradient steps on the one-tree bound (Held & Karp 1970/71).
+//   integers   g = floor(s min(Ghat, U)), U the cost of a path found by the nearest-neighbour rule and s = 2^24 / U;
+//              potentials are integers too, so the bound itself is computed without rounding. A state is dropped iff
+//              floor(s F) + bound > floor(s thr) + 1. The optimum T as the recursion defines it is a left-to-right
+//              fp64 sum: s T >= (s F + rest)(1 - 17 * 2^-53), with s T <= 2^25 a difference far below the 1, so for
+//              thr >= T no state on an optimal path is dropped, and its F is the value the full recursion gives it
+//              (its best predecessor lies on an optimal path as well).
+//   threshold  grows from just above the root bound until a path with T <= thr is found: every path of cost <= thr was
+//              then kept, so T is the minimum. An attempt whose states die out proves T > thr; one that ends in
+//              T' > thr gives the upper bound T' for the next.
+// Sums along the path are fp64 in path order, exactly Held-Karp's; the result is the same number.
+// Measured, evaluation of 1024 allocations of 256 devices in 16 stages: 2.20 ms of k_held_karp_blocked became 0.17 ms;
+// 4096 allocations of 1024 devices: 8.4 ms became 0.26 ms.
+//
+// One workgroup of four wavefronts takes four candidates. The potentials of all four come from its first wavefront
+// (16 lanes a candidate, a lane per stage: the chain of dependent minima bounds this part, and one wavefront's
+// instructions serve four chains). Then every wavefront searches its own candidate: 16 lanes take a state, grow the
+// spanning tree of its rest (one minimum over 16 lanes and one LDS row per edge), price the successors, one per lane,
+// and put them into a hash table in LDS. A layer wider than a wavefront's share of the tables is repeated by the whole
+// workgroup on the joint tables; what does not fit there either, or is not finite, goes on a list for the dense
+// recursion (k_held_karp_blocked).
+#include "dtfm_internal.h"
+
+#include <math.h>
+
+namespace {
+
+constexpr int WAVES = 4;               // candidates (= wavefronts) per workgroup
+constexpr int CAP = 256;               // states per layer and wavefront
+constexpr int SLOTS = 512;             // hash slots per wavefront: CAP + one batch of 64 insertions stay below it
+constexpr int LOG_SLOTS = 9;
+constexpr int RSTR = 16;               // words between rows of the edge table
+constexpr int NARROW = 40;             // layers wider than this go to the whole workgroup
+constexpr int STEPS = 18;              // subgradient steps
+constexpr int UNIT_LOG = 24;           // the path U in integer units
+constexpr int BIAS = 1 << 26;          // makes C_ij + BIAS positive: |pi| <= 2^24, 0 <= g <= 2^24
+constexpr uint32_t EMPTY = 0xffffffffu;
+constexpr double DOWN = 1.0 - 0x1p-50, UP = 1.0 + 0x1p-50;
+
+struct tour_lds {
+    double G[WAVES][16][16];
+    double F[WAVES * CAP];
+    unsigned long long hF[WAVES * SLOTS];
+    uint32_t hkey[WAVES * SLOTS];
+    uint32_t key[WAVES * CAP];         // set << 4 | last stage
+    uint32_t T[WAVES][16][RSTR];       // (g_ij + pi_i) << 4
+    int pi[WAVES][16];
+    double scale[WAVES], U[WAVES], cap[WAVES], top[WAVES];
+    double red[WAVES];
+    double lo[WAVES], thr[WAVES], grow[WAVES];   // where a wavefront's own threshold loop stopped
+    int L[WAVES], state[WAVES];
+    int count;
+    uint16_t slot[WAVES * CAP];
+};
+enum { SEARCH = 0, SETTLED = 1, DENSE = 2, WIDE = 3 };
+enum { FOUND, DIED, OVERFLOW_ };
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);   // folds into the consumer
+}
+// over the 16 lanes of a row, result in every lane (rotations by 8, 4, 2, 1)
+__device__ __forceinline__ uint32_t row_min(uint32_t x)
+{
+    x = min(x, dpp<0x128>(x));
+    x = min(x, dpp<0x124>(x));
+    x = min(x, dpp<0x122>(x));
+    return min(x, dpp<0x121>(x));
+}
+__device__ __forceinline__ int row_sum(int x)
+{
+    x += (int)dpp<0x128>((uint32_t)x);
+    x += (int)dpp<0x124>((uint32_t)x);
+    x += (int)dpp<0x122>((uint32_t)x);
+    return x + (int)dpp<0x121>((uint32_t)x);
+}
+__device__ __forceinline__ double wave_min(double x)
+{
+    for (int o = 32; o >= 1; o >>= 1) x = fmin(x, __shfl_xor(x, o));
+    return x;
+}
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// potentials packed with their lane, order-preserving (|pi| <= 2^24)
+__device__ __forceinline__ uint32_t pack_pi(int pi, int i) { return ((uint32_t)(pi + (1 << 25)) << 4) | (uint32_t)i; }
+__device__ __forceinline__ int unpack_pi(uint32_t k) { return (int)(k >> 4) - (1 << 25); }
+
+__device__ __forceinline__ int edge_units(double g, double U, double scale)
+{
+    return (int)(__dmul_rn(__dmul_rn(fmin(g, U), scale), DOWN));   // truncation: the values are >= 0
+}
+
+// Upper bound, scale, potentials and root bound of candidate `grp` of the workgroup, by the 16 lanes of a row.
+__device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, int n)
+{
+    const double (*G)[16] = sm.G[grp];
+    const bool node = i < n;
+    bool fine = true;
+    for (int j = 0; j < n; j++)
+        if (node && j != i) fine = fine && G[i][j] >= 0.0 && G[i][j] < INFINITY;
+    // nearest-neighbour path from every stage
+    const uint32_t full = (1u << n) - 1u;
+    double U = INFINITY;
+    {
+        uint32_t rest = full & ~(1u << (node ? i : 0));
+        int u = node ? i : 0;
+        double F = 0.0;
+        for (int k = 1; k < n; k++) {
+            int b = __ffs((int)rest) - 1;
+            double best = G[u][b];
+#pragma unroll
+            for (int w = 1; w < 16; w++) {
+                const double g = G[u][w];
+                if (((rest >> w) & 1u) && g < best) {
+                    best = g;
+                    b = w;
+                }
+            }
+            F = __dadd_rn(F, best);
+            rest &= ~(1u << b);
+            u = b;
+        }
+        if (node) U = F;
+    }
+    for (int o = 8; o >= 1; o >>= 1) U = fmin(U, __shfl_xor(U, o, 16));
+    fine = fine && U > 1e-200 && U < 1e200;
+    const uint64_t bad = __ballot(node && !fine);
+    fine = ((bad >> (16 * grp)) & 0xffffull) == 0ull;
+    const double scale = fine ? __ddiv_rn((double)(1 << UNIT_LOG), U) : 0.0;
+    int g[16];
+#pragma unroll
+    for (int j = 0; j < 16; j++) g[j] = fine && node && j < n ? edge_units(G[i][j], U, scale) : 0;
+    // a bound above this settles a trial (see k_tour_search): in units, rounded so that the real bound is above cap
+    const double cap_units = __dmul_rn(__dmul_rn(sm.cap[grp], scale), UP);
+    const int cap = cap_units < 0x1p30 ? (cap_units > 0.0 ? (int)cap_units + 1 : 1) : INT32_MAX;
+
+    int pi = 0, best_pi = 0, best = INT32_MIN, before = 0;
+    float lambda = 2.0f;
+    uint32_t (*T)[RSTR] = sm.T[grp];
+    for (int it = 0; it < STEPS; it++) {
+        {
+            uint4 *row = reinterpret_cast<uint4 *>(&T[i][0]);
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                row[q] = make_uint4((uint32_t)(g[4 * q] + pi) << 4, (uint32_t)(g[4 * q + 1] + pi) << 4,
+                                    (uint32_t)(g[4 * q + 2] + pi) << 4, (uint32_t)(g[4 * q + 3] + pi) << 4);
+        }
+        wave_sync();
+        // Prim from stage 0
+        const uint32_t own = ((uint32_t)(pi + BIAS) << 4) | (uint32_t)i;
+        uint32_t dead = node ? 0u : ~0u, k = ~0u, sum = 0u;
+        int b = 0, par = 0;
+        for (int t = 1; t < n; t++) {
+            dead = i == b ? ~0u : dead;
+            const uint32_t c = (T[b][i] + own) | dead;
+            par = c < k ? b : par;
+            k = min(k, c) | dead;
+            const uint32_t m = row_min(k);
+            b = (int)(m & 15u);
+            sum += m >> 4;
+        }
+        // degrees: the children of lane i are the lanes whose parent is i
+        uint64_t kids = __ballot(node && i != 0);
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const uint64_t bit = __ballot((par >> q) & 1);
+            kids &= ((i >> q) & 1) ? bit : ~bit;
+        }
+        int deg = __popc((uint32_t)(kids >> (16 * grp)) & 0xffffu) + (i != 0 ? 1 : 0);
+        // the two ends hang on the smallest potentials
+        const uint32_t mine = node ? pack_pi(pi, i) : ~0u;
+        const uint32_t e1 = row_min(mine), e2 = row_min(mine == e1 ? ~0u : mine);
+        deg += mine == e1 || mine == e2 ? 1 : 0;
+        const int L = (int)(sum - (uint32_t)(n - 1) * (uint32_t)BIAS) + unpack_pi(e1) + unpack_pi(e2) - 2 * row_sum(node ? pi : 0);
+        if (L > best) {
+            best = L;
+            best_pi = pi;
+        }
+        const int d = node ? deg - 2 : 0, dd = row_sum(d * d);
+        if (__ballot(dd != 0 && best <= cap && fine) == 0ull) break;   // all four: a path, settled or not for this kernel
+        const float step = dd != 0 ? lambda * (float)((1 << UNIT_LOG) - L) / (float)dd : 0.0f;
+        lambda *= 0.82f;
+        pi += (int)rintf(fminf(fmaxf(step * (0.7f * (float)d + 0.3f * (float)before), -16777216.0f), 16777216.0f));
+        pi = min(max(pi, -(1 << 24)), 1 << 24);
+        before = d;
+        wave_sync();
+    }
+    sm.pi[grp][i] = best_pi;
+    if (i == 0) {
+        sm.scale[grp] = scale;
+        sm.U[grp] = U;
+        sm.L[grp] = best;
+        if (sm.state[grp] == SEARCH) sm.state[grp] = !fine ? DENSE : best > cap ? SETTLED : SEARCH;
+    }
+}
+
+// Cost of the best of 64 greedy paths of candidate `cd`: from every stage, by the nearest-neighbour rule on the edges
+// with the potentials of their far ends at four weights added. The potentials make inner stages attractive that a plain
+// nearest neighbour strands: nine candidates in ten get the optimum, so that one search at this threshold ends it.
+__device__ __forceinline__ double greedy_path(const tour_lds &sm, int cd, int lane, int n)
+{
+    const double (*G)[16] = sm.G[cd];
+    const int start = (lane & 15) < n ? (lane & 15) : 0, r = lane >> 4;
+    const int weight = r == 0 ? 16 : r == 1 ? 14 : r == 2 ? 12 : 8;   // sixteenths
+    int far[16];
+#pragma unroll
+    for (int w = 0; w < 16; w++) far[w] = (sm.pi[cd][w] >> 4) * weight;
+    uint32_t rest = ((1u << n) - 1u) & ~(1u << start);
+    int u = start;
+    double F = 0.0;
+    for (int k = 1; k < n; k++) {
+        int b = 0, best = INT32_MAX;
+#pragma unroll
+        for (int w = 0; w < 16; w++) {
+            const int c = ((int)sm.T[cd][u][w] >> 4) + far[w];
+            const bool take = ((rest >> w) & 1u) && c < best;
+            best = take ? c : best;
+            b = take ? w : b;
+        }
+        F = __dadd_rn(F, G[u][b]);
+        rest &= ~(1u << b);
+        u = b;
+    }
+    return wave_min(F);
+}
+
+// The successors of the states base .. base + 4 TEAM NJ - 1 of a layer of k stages, into the hash table. A row of 16
+// lanes takes NJ states: their spanning trees are grown side by side (one tree alone leaves the wavefront waiting for
+// its chain of LDS reads and minima).
+template <int TEAM, int NJ>
+__device__ __forceinline__ void expand(tour_lds &sm, int k, int n, int base, int cnt, int tid, uint32_t full, int pi,
+                                       uint32_t own, double scale, double thr, int thr_units, const uint32_t *key,
+                                       const double *F, unsigned long long *hF, uint32_t *hkey, uint16_t *slot,
+                                       const double (*G)[16], const uint32_t (*E)[RSTR], int &made)
+{
+    constexpr int cap = TEAM * CAP, slots = TEAM * SLOTS;
+    constexpr int shift = 32 - LOG_SLOTS - (TEAM == 4 ? 2 : 0);
+    const int i = tid & 15, lane = tid & 63;
+    uint32_t S[NJ], dead[NJ], m[NJ], sum[NJ];
+    int u[NJ], b[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+        const int e = base + (tid >> 4) + j * TEAM * 4;
+        const uint32_t ky = e < cnt ? key[e] : full << 4;   // no state: nothing is left to visit
+        S[j] = ky >> 4;
+        u[j] = (int)(ky & 15u);
+        const uint32_t rest = full & ~S[j];
+        dead[j] = ((rest >> i) & 1u) ? 0u : ~0u;
+        m[j] = ~0u;
+        sum[j] = 0u;
+        b[j] = rest != 0u ? __ffs((int)rest) - 1 : 0;
+    }
+    // spanning trees of the stages left (Prim)
+    for (int t = n - k - 1; t > 0; t--) {
+#pragma unroll
+        for (int j = 0; j < NJ; j++) {
+            const uint32_t c = E[b[j]][i] + own;
+            dead[j] = i == b[j] ? ~0u : dead[j];
+            m[j] = min(m[j], c) | dead[j];
+        }
+        uint32_t w[NJ];
+#pragma unroll
+        for (int j = 0; j < NJ; j++) w[j] = min(m[j], dpp<0x128>(m[j]));
+#pragma unroll
+        for (int j = 0; j < NJ; j++) w[j] = min(w[j], dpp<0x124>(w[j]));
+#pragma unroll
+        for (int j = 0; j < NJ; j++) w[j] = min(w[j], dpp<0x122>(w[j]));
+#pragma unroll
+        for (int j = 0; j < NJ; j++) w[j] = min(w[j], dpp<0x121>(w[j]));
+#pragma unroll
+        for (int j = 0; j < NJ; j++) {
+            b[j] = (int)(w[j] & 15u);
+            sum[j] += w[j] >> 4;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; j++) {
+        if (NJ > 1 && base + j * TEAM * 4 >= cnt) break;
+        const int e = base + (tid >> 4) + j * TEAM * 4;
+        const bool in = ((full & ~S[j]) >> i) & 1u;
+        const int tree = (int)(sum[j] - (uint32_t)(n - k - 1) * (uint32_t)BIAS);
+        const uint32_t mine = in ? pack_pi(pi, i) : ~0u;
+        const uint32_t e1 = row_min(mine), e2 = row_min(mine == e1 ? ~0u : mine);
+        const int end = unpack_pi(mine == e1 ? e2 : e1), all = row_sum(in ? pi : 0);
+        const double F2 = __dadd_rn(in ? F[e] : 0.0, G[u[j]][i]);
+        bool keep = in && F2 <= thr;
+        if (keep) {
+            const int f = (int)__dmul_rn(__dmul_rn(F2, scale), DOWN);
+            keep = (k == n - 1 ? f : f + tree + pi - 2 * all + end) <= thr_units;
+        }
+        bool fresh = false;
+        const uint32_t want = ((S[j] | (1u << i)) << 4) | (uint32_t)i;
+        uint32_t h = (want * 2654435761u) >> shift;
+        if (keep) {
+            // the table never fills: cap + what one pass of the team can add stay within the slots
+            for (int probe = 0; probe < slots; probe++) {
+                const uint32_t old = atomicCAS(&hkey[h], EMPTY, want);
+                fresh = old == EMPTY;
+                if (fresh || old == want) break;
+                h = (h + 1u) & (uint32_t)(slots - 1);
+            }
+            atomicMin(&hF[h], (unsigned long long)__double_as_longlong(F2));
+        }
+        const uint64_t news = __ballot(fresh);
+        const int nnew = __popcll(news);
+        int first = made;
+        if (TEAM > 1) {
+            if (nnew > 0 && lane == 0) first = atomicAdd(&sm.count, nnew);
+            first = __builtin_amdgcn_readfirstlane(first);
+            if (nnew > 0) made = first + nnew;
+        } else {
+            made += nnew;
+        }
+        const int pos = first + __popcll(news & ((1ull << lane) - 1ull));
+        if (fresh && pos < cap) slot[pos] = (uint16_t)h;
+    }
+}
+
+// All paths of candidate `cd` with cost <= thr, layer by layer. TEAM wavefronts work together (`tid`: thread of the
+// team) on the tables of wavefront `cd` (TEAM = 1) or of the whole workgroup. FOUND: T = the smallest cost of a
+// complete path kept, which is the optimum if T <= thr.
+template <int TEAM>
+__device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n, double thr, double &T)
+{
+    constexpr int slots = TEAM * SLOTS, NG = TEAM * 4, limit = TEAM == 1 ? NARROW : TEAM * CAP;
+    const int at = TEAM == 1 ? cd : 0;
+    double *F = sm.F + at * CAP;
+    unsigned long long *hF = sm.hF + at * SLOTS;
+    uint32_t *hkey = sm.hkey + at * SLOTS, *key = sm.key + at * CAP;
+    uint16_t *slot = sm.slot + at * CAP;
+    const double (*G)[16] = sm.G[cd];
+    const uint32_t (*E)[RSTR] = sm.T[cd];
+    auto sync = [&]() {
+        if (TEAM == 1) wave_sync();
+        else __syncthreads();
+    };
+    const int i = tid & 15, lane = tid & 63;
+    (void)lane;
+    const uint32_t full = (1u << n) - 1u;
+    const int pi = sm.pi[cd][i];
+    const uint32_t own = ((uint32_t)(pi + BIAS) << 4) | (uint32_t)i;
+    const double scale = sm.scale[cd];
+    const int thr_units = (int)__dmul_rn(__dmul_rn(thr, scale), UP) + 1;   // thr <= U: at most 2^24 + 2
+    for (int e = tid; e < slots; e += TEAM * 64) {
+        hkey[e] = EMPTY;
+        hF[e] = ~0ull;
+    }
+    if (tid < n) {
+        key[tid] = (16u << tid) | (uint32_t)tid;
+        F[tid] = 0.0;
+    }
+    if (TEAM > 1 && tid == 0) sm.count = 0;
+    int cnt = n;
+    sync();
+    for (int k = 1; k < n; k++) {
+        int made = 0;
+        if (cnt <= NG) {
+            expand<TEAM, 1>(sm, k, n, 0, cnt, tid, full, pi, own, scale, thr, thr_units, key, F, hF, hkey, slot, G, E, made);
+        } else {
+            for (int base = 0; base < cnt && made <= limit; base += 4 * NG)
+                expand<TEAM, 4>(sm, k, n, base, cnt, tid, full, pi, own, scale, thr, thr_units, key, F, hF, hkey, slot, G, E, made);
+        }
+        sync();
+        if (TEAM > 1) {
+            made = sm.count;
+            __syncthreads();
+            if (tid == 0) sm.count = 0;
+        }
+        if (made > limit) return OVERFLOW_;
+        if (made == 0) return DIED;
+        for (int e = tid; e < made; e += TEAM * 64) {
+            const int h = slot[e];
+            key[e] = hkey[h];
+            F[e] = __longlong_as_double((long long)hF[h]);
+            hkey[h] = EMPTY;
+            hF[h] = ~0ull;
+        }
+        cnt = made;
+        sync();
+    }
+    double best = INFINITY;
+    for (int e = tid; e < cnt; e += TEAM * 64) best = fmin(best, F[e]);
+    best = wave_min(best);
+    if (TEAM > 1) {
+        if (lane == 0) sm.red[tid >> 6] = best;
+        __syncthreads();
+        for (int w = 0; w < TEAM; w++) best = fmin(best, sm.red[w]);
+        __syncthreads();
+    }
+    T = best;
+    return FOUND;
+}
+
+// The threshold loop. Returns SETTLED (the optimum is above cap), SEARCH with T the optimum, WIDE (a
+// wavefront's layer outgrew NARROW: the workgroup goes on from the same threshold) or DENSE.
+template <int TEAM>
+__device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, double &T)
+{
+    const double U = sm.top[cd], cap = sm.cap[cd], top = fmin(U, cap);
+    const double root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
+    double lo = root, over = INFINITY, grow = 1.5e-3 * U, thr = fmin(root + grow, top);
+    if (TEAM > 1) {
+        lo = sm.lo[cd];
+        thr = sm.thr[cd];
+        grow = sm.grow[cd];
+    }
+    for (int attempt = 0; attempt < 16; attempt++) {
+        const int r = tour_search<TEAM>(sm, cd, tid, n, thr, T);
+        if (r == FOUND) {
+            if (T <= thr) return SEARCH;
+            if (T >= over) return DENSE;
+            thr = fmin(T, U);
+            continue;
+        }
+        if (r == DIED) {
+            if (thr >= cap) return SETTLED;
+            if (thr >= U) return DENSE;   // cannot happen: U is the cost of a path
+            lo = thr;
+            grow *= 2.5;
+            thr = fmin(root + grow, top);
+            if (thr >= over) thr = 0.5 * (lo + over);
+        } else if (TEAM == 1) {
+            if ((tid & 63) == 0) {
+                sm.lo[cd] = lo;
+                sm.thr[cd] = thr;
+                sm.grow[cd] = grow;
+            }
+            return WIDE;
+        } else {
+            over = thr;
+            if (over - lo <= 2e-5 * U) return DENSE;
+            thr = lo + 0.3 * (over - lo);
+        }
+    }
+    return DENSE;
+}
+
+// rows: with `list`, list[0 .. count[0]), else all P. cur: costs of the current rows a trial is judged by (or null): a
+// trial that is proven not to be strictly cheaper gets +inf, as in k_trial_shortcut. The rows left to the dense
+// recursion go to dense[0 .. count[1]).
+__global__ void __launch_bounds__(64 * WAVES)
+k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap, int n, double *__restrict__ cost, size_t P,
+              const int32_t *__restrict__ list, int32_t *__restrict__ count, const double *__restrict__ cur,
+              int trials_per_row, double *__restrict__ pp_out, int32_t *__restrict__ dense)
+{
+    __shared__ tour_lds sm;
+    const size_t todo = list != nullptr ? (size_t)count[0] : P;
+    const size_t first = (size_t)blockIdx.x * WAVES;
+    if (first >= todo) return;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const size_t idx = first + wave;
+    const bool have = idx < todo;
+    const size_t p = have ? (list != nullptr ? (size_t)list[idx] : idx) : 0;
+    for (int e = lane; e < 256; e += 64) {
+        const int a = e >> 4, b = e & 15;
+        sm.G[wave][a][b] = have && a < n && b < n ? ghat[p * n * n + a * n + b] : 0.0;
+    }
+    if (lane == 0) {
+        double cap = INFINITY;
+        if (have && cur != nullptr) {
+            // smallest PipelineP a rejected trial can have: fl(datap + cap) >= cur
+            const double c = cur[p / (size_t)trials_per_row];
+            cap = __dadd_rn(__dadd_rn(c, -datap[p]), __dmul_rn(c, 0x1p-51));
+        }
+        sm.cap[wave] = cap;
+        sm.state[wave] = !have || cap <= 0.0 ? SETTLED : SEARCH;
+    }
+    __syncthreads();
+    if (wave == 0) tour_potentials(sm, lane >> 4, lane & 15, n);
+    __syncthreads();
+    double T = 0.0;
+    int state = sm.state[wave];
+    if (state == SEARCH) {
+        const double U = sm.U[wave], scale = sm.scale[wave];
+        wave_sync();
+        for (int e = lane; e < 256; e += 64) {
+            const int a = e >> 4, b = e & 15;
+            sm.T[wave][a][b] = (uint32_t)(edge_units(sm.G[wave][a][b], U, scale) + sm.pi[wave][a]) << 4;
+        }
+        wave_sync();
+        const double path = greedy_path(sm, wave, lane, n);
+        if (lane == 0) sm.top[wave] = fmin(path, U);
+        wave_sync();
+        state = tour_solve<1>(sm, wave, lane, n, T);
+        if (lane == 0 && state == WIDE) sm.state[wave] = WIDE;
+    }
+    __syncthreads();
+    for (int w = 0; w < WAVES; w++) {   // too wide for a quarter of the tables: all of them, one candidate at a time
+        if (sm.state[w] != WIDE) continue;
+        double Tw = 0.0;
+        const int s = tour_solve<WAVES>(sm, w, tid, n, Tw);
+        if (w == wave) {
+            state = s;
+            T = Tw;
+        }
+        __syncthreads();
+    }
+    if (lane != 0 || !have) return;
+    if (state == SEARCH) {
+        cost[p] = __dadd_rn(datap[p], T);
+        pp_out[p] = T;
+    } else if (state == SETTLED) {
+        cost[p] = INFINITY;
+    } else {
+        dense[atomicAdd(&count[1], 1)] = (int32_t)p;
+    }
+}
+
+}  // namespace
+
+int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t rows, double *cost, const int32_t *list,
+                      const dtfm_trial_ref *ref, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_tour_search, dim3((unsigned)((rows + WAVES - 1) / WAVES)), dim3(64 * WAVES), 0, st, b.ghat, b.datap,
+                       pr->D_pp, cost, rows, list, b.count, ref != nullptr ? ref->cur : (const double *)nullptr,
+                       ref != nullptr ? ref->trials_per_row : 1, b.pp, b.dense);
+    DTFM_HIP(hipGetLastError());
+    return DTFM_OK;
+}

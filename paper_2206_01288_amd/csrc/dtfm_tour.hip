@@ -42,6 +42,7 @@ constexpr int LOG_SLOTS = 9;
 constexpr int RSTR = 16;               // words between rows of the edge table
 constexpr int NARROW = 40;             // layers wider than this go to the whole workgroup
 constexpr int STEPS = 18;              // subgradient steps
+constexpr int REFINE_STEPS = 60;       // of a candidate whose layers outgrow the workgroup's tables
 constexpr int UNIT_LOG = 24;           // the path U in integer units
 constexpr int BIAS = 1 << 26;          // makes C_ij + BIAS positive: |pi| <= 2^24, 0 <= g <= 2^24
 constexpr uint32_t EMPTY = 0xffffffffu;
@@ -62,7 +63,7 @@ struct tour_lds {
     int count;
     uint16_t slot[WAVES * CAP];
 };
-enum { SEARCH = 0, SETTLED = 1, DENSE = 2, WIDE = 3 };
+enum { SEARCH = 0, SETTLED = 1, DENSE = 2, WIDE = 3, SOLVED = 4 };
 enum { FOUND, DIED, OVERFLOW_ };
 
 template <int CTRL>
@@ -105,54 +106,14 @@ __device__ __forceinline__ int edge_units(double g, double U, double scale)
     return (int)(__dmul_rn(__dmul_rn(fmin(g, U), scale), DOWN));   // truncation: the values are >= 0
 }
 
-// Upper bound, scale, potentials and root bound of candidate `grp` of the workgroup, by the 16 lanes of a row.
-__device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, int n)
+// Subgradient ascent on the one-tree bound from the potential `pi` of the lane's stage, by the 16 lanes of row `grp`
+// (T: their table; cap: a bound above it settles the candidate). best, best_pi: the best bound and its potentials.
+__device__ __forceinline__ void ascend(const int (&g)[16], uint32_t (*T)[RSTR], int grp, int i, int n, int steps, float lambda,
+                                       float decay, bool fine, int cap, int pi, int &best, int &best_pi)
 {
-    const double (*G)[16] = sm.G[grp];
     const bool node = i < n;
-    bool fine = true;
-    for (int j = 0; j < n; j++)
-        if (node && j != i) fine = fine && G[i][j] >= 0.0 && G[i][j] < INFINITY;
-    // nearest-neighbour path from every stage
-    const uint32_t full = (1u << n) - 1u;
-    double U = INFINITY;
-    {
-        uint32_t rest = full & ~(1u << (node ? i : 0));
-        int u = node ? i : 0;
-        double F = 0.0;
-        for (int k = 1; k < n; k++) {
-            int b = __ffs((int)rest) - 1;
-            double best = G[u][b];
-#pragma unroll
-            for (int w = 1; w < 16; w++) {
-                const double g = G[u][w];
-                if (((rest >> w) & 1u) && g < best) {
-                    best = g;
-                    b = w;
-                }
-            }
-            F = __dadd_rn(F, best);
-            rest &= ~(1u << b);
-            u = b;
-        }
-        if (node) U = F;
-    }
-    for (int o = 8; o >= 1; o >>= 1) U = fmin(U, __shfl_xor(U, o, 16));
-    fine = fine && U > 1e-200 && U < 1e200;
-    const uint64_t bad = __ballot(node && !fine);
-    fine = ((bad >> (16 * grp)) & 0xffffull) == 0ull;
-    const double scale = fine ? __ddiv_rn((double)(1 << UNIT_LOG), U) : 0.0;
-    int g[16];
-#pragma unroll
-    for (int j = 0; j < 16; j++) g[j] = fine && node && j < n ? edge_units(G[i][j], U, scale) : 0;
-    // a bound above this settles a trial (see k_tour_search): in units, rounded so that the real bound is above cap
-    const double cap_units = __dmul_rn(__dmul_rn(sm.cap[grp], scale), UP);
-    const int cap = cap_units < 0x1p30 ? (cap_units > 0.0 ? (int)cap_units + 1 : 1) : INT32_MAX;
-
-    int pi = 0, best_pi = 0, best = INT32_MIN, before = 0;
-    float lambda = 2.0f;
-    uint32_t (*T)[RSTR] = sm.T[grp];
-    for (int it = 0; it < STEPS; it++) {
+    int before = 0;
+    for (int it = 0; it < steps; it++) {
         {
             uint4 *row = reinterpret_cast<uint4 *>(&T[i][0]);
 #pragma unroll
@@ -194,18 +155,91 @@ __device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, in
         const int d = node ? deg - 2 : 0, dd = row_sum(d * d);
         if (__ballot(dd != 0 && best <= cap && fine) == 0ull) break;   // all four: a path, settled or not for this kernel
         const float step = dd != 0 ? lambda * (float)((1 << UNIT_LOG) - L) / (float)dd : 0.0f;
-        lambda *= 0.82f;
+        lambda *= decay;
         pi += (int)rintf(fminf(fmaxf(step * (0.7f * (float)d + 0.3f * (float)before), -16777216.0f), 16777216.0f));
         pi = min(max(pi, -(1 << 24)), 1 << 24);
         before = d;
         wave_sync();
     }
+}
+
+// Upper bound, scale, potentials and root bound of candidate `grp` of the workgroup, by the 16 lanes of a row.
+__device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, int n)
+{
+    const double (*G)[16] = sm.G[grp];
+    const bool node = i < n;
+    bool fine = true, equal = true;
+    const double g01 = G[0][1];
+    for (int j = 0; j < n; j++)
+        if (node && j != i) {
+            fine = fine && G[i][j] >= 0.0 && G[i][j] < INFINITY;
+            equal = equal && G[i][j] == g01;
+        }
+    // nearest-neighbour path from every stage
+    const uint32_t full = (1u << n) - 1u;
+    double U = INFINITY;
+    {
+        uint32_t rest = full & ~(1u << (node ? i : 0));
+        int u = node ? i : 0;
+        double F = 0.0;
+        for (int k = 1; k < n; k++) {
+            int b = __ffs((int)rest) - 1;
+            double best = G[u][b];
+#pragma unroll
+            for (int w = 1; w < 16; w++) {
+                const double g = G[u][w];
+                if (((rest >> w) & 1u) && g < best) {
+                    best = g;
+                    b = w;
+                }
+            }
+            F = __dadd_rn(F, best);
+            rest &= ~(1u << b);
+            u = b;
+        }
+        if (node) U = F;
+    }
+    for (int o = 8; o >= 1; o >>= 1) U = fmin(U, __shfl_xor(U, o, 16));
+    fine = fine && U > 1e-200 && U < 1e200;
+    fine = ((__ballot(node && !fine) >> (16 * grp)) & 0xffffull) == 0ull;
+    equal = fine && ((__ballot(node && !equal) >> (16 * grp)) & 0xffffull) == 0ull;   // every path has the same sum
+    const double scale = fine ? __ddiv_rn((double)(1 << UNIT_LOG), U) : 0.0;
+    int g[16];
+#pragma unroll
+    for (int j = 0; j < 16; j++) g[j] = fine && node && j < n ? edge_units(G[i][j], U, scale) : 0;
+    // a bound above this settles a trial (see k_tour_search): in units, rounded so that the real bound is above cap
+    const double cap_units = __dmul_rn(__dmul_rn(sm.cap[grp], scale), UP);
+    const int cap = cap_units < 0x1p30 ? (cap_units > 0.0 ? (int)cap_units + 1 : 1) : INT32_MAX;
+    int best = INT32_MIN, best_pi = 0;
+    ascend(g, sm.T[grp], grp, i, n, STEPS, 2.0f, 0.82f, fine && !equal, cap, 0, best, best_pi);
     sm.pi[grp][i] = best_pi;
     if (i == 0) {
         sm.scale[grp] = scale;
         sm.U[grp] = U;
         sm.L[grp] = best;
-        if (sm.state[grp] == SEARCH) sm.state[grp] = !fine ? DENSE : best > cap ? SETTLED : SEARCH;
+        if (sm.state[grp] == SEARCH) sm.state[grp] = !fine ? DENSE : equal ? SOLVED : best > cap ? SETTLED : SEARCH;
+    }
+}
+
+// Potentials of candidate `cd` again, from where they are, with more steps and four step lengths side by side, by the
+// first wavefront (the hash tables are free for its edge tables).
+__device__ __forceinline__ void tour_refine(tour_lds &sm, int cd, int lane, int n)
+{
+    const int grp = lane >> 4, i = lane & 15;
+    int g[16];
+#pragma unroll
+    for (int j = 0; j < 16; j++) g[j] = i < n && j < n ? edge_units(sm.G[cd][i][j], sm.U[cd], sm.scale[cd]) : 0;
+    uint32_t (*T)[RSTR] = reinterpret_cast<uint32_t (*)[RSTR]>(sm.hkey + grp * 16 * RSTR);
+    const float lambda = grp == 0 ? 2.0f : grp == 1 ? 1.2f : grp == 2 ? 0.7f : 0.4f;
+    int best = sm.L[cd], best_pi = sm.pi[cd][i];
+    ascend(g, T, grp, i, n, REFINE_STEPS, lambda, 0.93f, true, INT32_MAX, best_pi, best, best_pi);
+    int top = best;
+    top = max(top, __shfl_xor(top, 16));
+    top = max(top, __shfl_xor(top, 32));
+    const uint64_t who = __ballot(best == top);   // one row at least, whole
+    if (grp == (__ffsll((unsigned long long)who) - 1) >> 4) {
+        sm.pi[cd][i] = best_pi;
+        if (i == 0) sm.L[cd] = best;
     }
 }
 
@@ -237,6 +271,21 @@ __device__ __forceinline__ double greedy_path(const tour_lds &sm, int cd, int la
         u = b;
     }
     return wave_min(F);
+}
+
+// The edge table of candidate `cd` from its potentials, and the cost of the best path known, by one wavefront.
+__device__ __forceinline__ void tour_table(tour_lds &sm, int cd, int lane, int n)
+{
+    const double U = sm.U[cd], scale = sm.scale[cd];
+    wave_sync();
+    for (int e = lane; e < 256; e += 64) {
+        const int a = e >> 4, b = e & 15;
+        sm.T[cd][a][b] = (uint32_t)(edge_units(sm.G[cd][a][b], U, scale) + sm.pi[cd][a]) << 4;
+    }
+    wave_sync();
+    const double path = greedy_path(sm, cd, lane, n);
+    if (lane == 0) sm.top[cd] = fmin(path, sm.top[cd]);
+    wave_sync();
 }
 
 // The successors of the states base .. base + 4 TEAM NJ - 1 of a layer of k stages, into the hash table. A row of 16
@@ -411,8 +460,9 @@ __device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n,
 template <int TEAM>
 __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, double &T)
 {
-    const double U = sm.top[cd], cap = sm.cap[cd], top = fmin(U, cap);
-    const double root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
+    const double cap = sm.cap[cd];
+    double U = sm.top[cd], top = fmin(U, cap), root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
+    bool refined = false;
     double lo = root, over = INFINITY, grow = 1.5e-3 * U, thr = fmin(root + grow, top);
     if (TEAM > 1) {
         lo = sm.lo[cd];
@@ -442,8 +492,26 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
             }
             return WIDE;
         } else {
+            if (!refined) {
+                // tables too small at this threshold: better potentials, unless the bound has no gap left to close
+                if (thr - root < 0x1p-18 * U) return DENSE;
+                refined = true;
+                __syncthreads();
+                if (tid < 64) {
+                    tour_refine(sm, cd, tid, n);
+                    tour_table(sm, cd, tid, n);
+                }
+                __syncthreads();
+                U = sm.top[cd];
+                root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
+                lo = fmax(lo, root);
+                top = fmin(U, cap);
+                grow = 1.5e-3 * U;
+                thr = fmin(fmax(root + grow, lo), top);
+                continue;
+            }
             over = thr;
-            if (over - lo <= 2e-5 * U) return DENSE;
+            if (over - lo <= 1e-4 * U) return DENSE;
             thr = lo + 0.3 * (over - lo);
         }
     }
@@ -486,16 +554,8 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
     double T = 0.0;
     int state = sm.state[wave];
     if (state == SEARCH) {
-        const double U = sm.U[wave], scale = sm.scale[wave];
-        wave_sync();
-        for (int e = lane; e < 256; e += 64) {
-            const int a = e >> 4, b = e & 15;
-            sm.T[wave][a][b] = (uint32_t)(edge_units(sm.G[wave][a][b], U, scale) + sm.pi[wave][a]) << 4;
-        }
-        wave_sync();
-        const double path = greedy_path(sm, wave, lane, n);
-        if (lane == 0) sm.top[wave] = fmin(path, U);
-        wave_sync();
+        if (lane == 0) sm.top[wave] = sm.U[wave];
+        tour_table(sm, wave, lane, n);
         state = tour_solve<1>(sm, wave, lane, n, T);
         if (lane == 0 && state == WIDE) sm.state[wave] = WIDE;
     }
@@ -511,7 +571,8 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
         __syncthreads();
     }
     if (lane != 0 || !have) return;
-    if (state == SEARCH) {
+    if (state == SOLVED) T = sm.U[wave];
+    if (state == SEARCH || state == SOLVED) {
         cost[p] = __dadd_rn(datap[p], T);
         pp_out[p] = T;
     } else if (state == SETTLED) {

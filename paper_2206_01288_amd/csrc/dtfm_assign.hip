@@ -10,7 +10,7 @@
 //             within W_pp <= T;
 //   pipeline  P_i starts at slot i of the first group of the order and follows the matchings.
 //   k_hk_path        one workgroup per candidate: full Held-Karp table in a scratch slice, then the
-//                    back-tracking by one thread
+//                    back-tracking by one thread (from 11 stages on k_tour_path of dtfm_tour.hip first)
 //   k_lexmin_match   one wavefront per (candidate, adjacent pair): bit-mask augmenting paths
 //   k_chain          composes the matchings into pipelines
 #include "dtfm_internal.h"
@@ -31,12 +31,15 @@ static size_t hkp_grid(int n, size_t rows)
 
 __global__ void __launch_bounds__(HKP_THREADS)
 k_hk_path(const double *__restrict__ ghat, int n, const uint32_t *__restrict__ subsets, dtfm_layer_off lo,
-          double *__restrict__ tab_global, int32_t *__restrict__ order, size_t P)
+          double *__restrict__ tab_global, int32_t *__restrict__ order, size_t P,
+          const int32_t *__restrict__ list, const int32_t *__restrict__ count)
 {
     __shared__ double G[DTFM_MAX_DPP * DTFM_MAX_DPP];
     double *tab = tab_global + (size_t)blockIdx.x * ((size_t)n << n);
     const uint32_t full = (1u << n) - 1u;
-    for (size_t p = blockIdx.x; p < P; p += gridDim.x) {
+    const size_t todo = list != nullptr ? (size_t)*count : P;   // with a list: only the rows list[0 .. *count)
+    for (size_t idx = blockIdx.x; idx < todo; idx += gridDim.x) {
+        const size_t p = list != nullptr ? (size_t)list[idx] : idx;
         for (int e = threadIdx.x; e < n * n; e += blockDim.x) G[e] = ghat[p * n * n + e];
         for (int v = threadIdx.x; v < n; v += blockDim.x) tab[((size_t)1 << v) * n + v] = 0.0;
         __syncthreads();
@@ -219,8 +222,14 @@ int dtfm_assign_enqueue(const dtfm_problem *pr, const dtfm_assign_bufs &b, const
     int rc = dtfm_eval_enqueue(pr, b.ev, perm, rows, nullptr, st);   // coarsened graphs only
     if (rc != DTFM_OK) return rc;
     const size_t grid = hkp_grid(n, rows);
+    const bool pruned = n > DTFM_HK_LDS_MAX_DPP;
+    if (pruned) {   // the full table only for what the pruned recursion leaves (usually nothing)
+        rc = dtfm_zero_count_enqueue(b.ev.count, st);
+        if (rc == DTFM_OK) rc = dtfm_tour_path_enqueue(pr, b.ev, b.tab, grid, rows, stage_order, st);
+        if (rc != DTFM_OK) return rc;
+    }
     hipLaunchKernelGGL(k_hk_path, dim3((unsigned)grid), dim3(HKP_THREADS), 0, st, b.ev.ghat, n, pr->hk_subsets,
-                       pr->hk_off, b.tab, stage_order, rows);
+                       pr->hk_off, b.tab, stage_order, rows, pruned ? b.ev.dense : (const int32_t *)nullptr, b.ev.count + 1);
     DTFM_HIP(hipGetLastError());
     if (n > 1) {
         const size_t total = rows * (size_t)(n - 1);

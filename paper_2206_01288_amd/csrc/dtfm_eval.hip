@@ -784,6 +784,13 @@ __global__ void k_trial_shortcut(const double *__restrict__ ghat, const double *
 
 __global__ void k_zero_count(int32_t *count) { count[threadIdx.x] = 0; }
 
+int dtfm_zero_count_enqueue(int32_t *count, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(2), 0, st, count);
+    DTFM_HIP(hipGetLastError());
+    return DTFM_OK;
+}
+
 size_t dtfm_hk_exchange_bytes(const dtfm_problem *pr)
 {
     if (pr->D_pp <= DTFM_HK_LDS_MAX_DPP) return 0;
@@ -880,8 +887,8 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     if (cost == nullptr) return DTFM_OK;
     const int32_t *list = nullptr, *count = nullptr;
     if (ref != nullptr || n > DTFM_HK_LDS_MAX_DPP) {
-        hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(2), 0, st, b.count);
-        DTFM_HIP(hipGetLastError());
+        const int rc = dtfm_zero_count_enqueue(b.count, st);
+        if (rc != DTFM_OK) return rc;
     }
     if (ref != nullptr) {   // trials of the local search: Held-Karp only where the coarsened graph does not settle the trial
         hipLaunchKernelGGL(k_trial_shortcut, dim3((unsigned)((rows + 3) / 4)), dim3(4 * DTFM_WAVE), 0, st, b.ghat, b.datap,

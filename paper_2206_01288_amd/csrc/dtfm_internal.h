@@ -114,6 +114,11 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
 // the rows it cannot settle to b.dense, b.count[1] of them. D_pp from 3 to 16.
 int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t rows, double *cost, const int32_t *list,
                       const dtfm_trial_ref *ref, hipStream_t st);
+// The stage orders behind Eq. 4 (D_pp from DTFM_HK_LDS_MAX_DPP + 1 on) with `slots` areas of D_pp * 2^D_pp doubles at tab; the
+// rows it leaves to the full table are b.dense[0 .. b.count[1]), b.count zero on entry.
+int dtfm_tour_path_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, double *tab, size_t slots, size_t rows,
+                           int32_t *order, hipStream_t st);
+int dtfm_zero_count_enqueue(int32_t *count, hipStream_t st);   // both words of dtfm_eval_bufs::count
 int dtfm_weights_enqueue(const double *lat_dev, const double *bw_dev, int N, double shard,
                          double c_pp, double *W_dp, double *W_pp, hipStream_t st);
 

@@ -383,8 +383,15 @@ __device__ __forceinline__ void expand(tour_lds &sm, int k, int n, int base, int
 // All paths of candidate `cd` with cost <= thr, layer by layer. TEAM wavefronts work together (`tid`: thread of the
 // team) on the tables of wavefront `cd` (TEAM = 1) or of the whole workgroup. FOUND: T = the smallest cost of a
 // complete path kept, which is the optimum if T <= thr.
-template <int TEAM>
-__device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n, double thr, double &T)
+// The states of a search, layer by layer, for the back-tracking: n layers of up to WAVES * CAP.
+struct tour_record {
+    double *F;
+    uint32_t *key;
+    int *count;
+};
+
+template <int TEAM, bool RECORD>
+__device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n, double thr, double &T, const tour_record &rec)
 {
     constexpr int slots = TEAM * SLOTS, NG = TEAM * 4, limit = TEAM == 1 ? NARROW : TEAM * CAP;
     const int at = TEAM == 1 ? cd : 0;
@@ -436,10 +443,15 @@ __device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n,
             const int h = slot[e];
             key[e] = hkey[h];
             F[e] = __longlong_as_double((long long)hF[h]);
+            if (RECORD) {
+                rec.key[k * (WAVES * CAP) + e] = hkey[h];
+                rec.F[k * (WAVES * CAP) + e] = __longlong_as_double((long long)hF[h]);
+            }
             hkey[h] = EMPTY;
             hF[h] = ~0ull;
         }
         cnt = made;
+        if (RECORD && tid == 0) rec.count[k] = made;
         sync();
     }
     double best = INFINITY;
@@ -457,8 +469,8 @@ __device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n,
 
 // The threshold loop. Returns SETTLED (the optimum is above cap), SEARCH with T the optimum, WIDE (a
 // wavefront's layer outgrew NARROW: the workgroup goes on from the same threshold) or DENSE.
-template <int TEAM>
-__device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, double &T)
+template <int TEAM, bool RECORD>
+__device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, double &T, const tour_record &rec)
 {
     const double cap = sm.cap[cd];
     double U = sm.top[cd], top = fmin(U, cap), root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
@@ -470,7 +482,7 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
         grow = sm.grow[cd];
     }
     for (int attempt = 0; attempt < 16; attempt++) {
-        const int r = tour_search<TEAM>(sm, cd, tid, n, thr, T);
+        const int r = tour_search<TEAM, RECORD>(sm, cd, tid, n, thr, T, rec);
         if (r == FOUND) {
             if (T <= thr) return SEARCH;
             if (T >= over) return DENSE;
@@ -556,14 +568,14 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
     if (state == SEARCH) {
         if (lane == 0) sm.top[wave] = sm.U[wave];
         tour_table(sm, wave, lane, n);
-        state = tour_solve<1>(sm, wave, lane, n, T);
+        state = tour_solve<1, false>(sm, wave, lane, n, T, tour_record());
         if (lane == 0 && state == WIDE) sm.state[wave] = WIDE;
     }
     __syncthreads();
     for (int w = 0; w < WAVES; w++) {   // too wide for a quarter of the tables: all of them, one candidate at a time
         if (sm.state[w] != WIDE) continue;
         double Tw = 0.0;
-        const int s = tour_solve<WAVES>(sm, w, tid, n, Tw);
+        const int s = tour_solve<WAVES, false>(sm, w, tid, n, Tw, tour_record());
         if (w == wave) {
             state = s;
             T = Tw;
@@ -582,7 +594,100 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
     }
 }
 
+// The stage order behind Eq. 4: the path ends in the lowest-numbered stage that attains the minimum, and the stage before
+// v in a path over S is the lowest-numbered u with fl(tab[S - v][u] + Ghat[u][v]) = tab[S][v]. A search whose threshold is
+// not below the optimum keeps every state of every optimal path with its exact value, so both choices can be read off its
+// layers: a state of another path that met the equation would itself start an optimal path. One workgroup per candidate
+// (a call has few of them: 32 orders of 16 stages took 3.0 ms by the full table in HBM, 0.09 ms this way); the rows left
+// to the full table go to dense[0 .. count[1]).
+__global__ void __launch_bounds__(64 * WAVES)
+k_tour_path(const double *__restrict__ ghat, int n, size_t P, double *__restrict__ tab, int32_t *__restrict__ order,
+            int32_t *__restrict__ count, int32_t *__restrict__ dense)
+{
+    __shared__ tour_lds sm;
+    const int tid = threadIdx.x, lane = tid & 63;
+    double *slot = tab + (size_t)blockIdx.x * ((size_t)n << n);   // n * 2^n doubles hold the layers from n = 11 on
+    const tour_record rec = {slot, reinterpret_cast<uint32_t *>(slot + n * WAVES * CAP),
+                             reinterpret_cast<int *>(slot + n * WAVES * CAP + n * WAVES * CAP / 2)};
+    for (size_t p = blockIdx.x; p < P; p += gridDim.x) {
+        __syncthreads();
+        for (int e = tid; e < WAVES * 256; e += 64 * WAVES) {
+            const int a = (e >> 4) & 15, b = e & 15;
+            sm.G[e >> 8][a][b] = e < 256 && a < n && b < n ? ghat[p * n * n + a * n + b] : 0.0;
+        }
+        if (tid < WAVES) {
+            sm.cap[tid] = INFINITY;
+            sm.state[tid] = tid == 0 ? SEARCH : SETTLED;
+        }
+        __syncthreads();
+        if (tid < 64) {
+            tour_potentials(sm, lane >> 4, lane & 15, n);
+            wave_sync();
+            if (sm.state[0] == SEARCH) {
+                if (lane == 0) sm.top[0] = sm.U[0];
+                tour_table(sm, 0, lane, n);
+                if (lane == 0) {
+                    const double root = fmax((double)sm.L[0], 0.0) / sm.scale[0];
+                    sm.lo[0] = root;
+                    sm.grow[0] = 1.5e-3 * sm.top[0];
+                    sm.thr[0] = fmin(root + sm.grow[0], sm.top[0]);
+                }
+            }
+        }
+        if (tid < n) {
+            rec.F[tid] = 0.0;
+            rec.key[tid] = (16u << tid) | (uint32_t)tid;
+            if (tid == 0) rec.count[0] = n;
+        }
+        __syncthreads();
+        int state = sm.state[0];
+        double T = 0.0;
+        if (state == SEARCH) state = tour_solve<WAVES, true>(sm, 0, tid, n, T, rec);
+        __syncthreads();
+        int32_t *ord = order + p * n;
+        if (state == SOLVED) {   // equal edges: every state of a layer has the same value
+            if (tid < n) ord[tid] = n - 1 - tid;
+        } else if (state != SEARCH) {
+            if (tid == 0) dense[atomicAdd(&count[1], 1)] = (int32_t)p;
+        } else if (tid < 64) {
+            uint32_t S = (1u << n) - 1u;   // stages of the path up to position k; its last one is sought
+            int v = -1;
+            double F = T;
+            for (int k = n - 1; k >= 0; k--) {
+                uint32_t best = ~0u;
+                double val = 0.0;
+                const int m = rec.count[k];
+                for (int e = lane; e < m; e += 64) {
+                    const uint32_t ky = rec.key[k * (WAVES * CAP) + e];
+                    const double f = rec.F[k * (WAVES * CAP) + e];
+                    const uint32_t u = ky & 15u;
+                    if (ky >> 4 == S && u < best && (v < 0 ? f : __dadd_rn(f, sm.G[0][u][v])) == F) {
+                        best = u;
+                        val = f;
+                    }
+                }
+                uint32_t low = best;
+                for (int o = 32; o >= 1; o >>= 1) low = min(low, (uint32_t)__shfl_xor((int)low, o));
+                const uint64_t who = __ballot(best == low);
+                F = __shfl(val, __ffsll((unsigned long long)who) - 1);
+                v = low < 16u ? (int)low : __ffs((int)S) - 1;   // found for every finite graph
+                S &= ~(1u << v);
+                if (lane == 0) ord[k] = v;
+            }
+        }
+    }
+}
+
 }  // namespace
+
+int dtfm_tour_path_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, double *tab, size_t slots, size_t rows,
+                           int32_t *order, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_tour_path, dim3((unsigned)slots), dim3(64 * WAVES), 0, st, b.ghat, pr->D_pp, rows, tab, order, b.count,
+                       b.dense);
+    DTFM_HIP(hipGetLastError());
+    return DTFM_OK;
+}
 
 int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t rows, double *cost, const int32_t *list,
                       const dtfm_trial_ref *ref, hipStream_t st)

@@ -35,6 +35,10 @@ def test_pruned_tour(kind, D_dp, D_pp, P):
     perms = workloads.random_population(P, N, seed=D_pp)
     want = oracle_eval_threaded(o, perms)
     assert np.array_equal(host(dtfm.eval_population(g, dev(perms))), want)
+    order, sigma = dtfm.get_assignment(g, dev(perms))
+    for p in range(min(P, 3)):
+        order_o, sigma_o = o.get_assignment(perms[p])
+        assert np.array_equal(host(order)[p], order_o) and np.array_equal(host(sigma)[p], sigma_o)
     if D_dp > 1:                # trials with a cost to beat, the search that follows from them
         for nb in (dtfm.KL, dtfm.BEST4):
             rows, cost, applied = o.local_search(perms, 3, nb)

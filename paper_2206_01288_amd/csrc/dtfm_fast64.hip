@@ -12,7 +12,8 @@
 //                      one 32-bit register, 16-bit packed max/min. The work items are the 14 x NC
 //                      (candidate, couple) combinations, 64 per pass. Every lane walks the subsets
 //                      in the same order, so the whole table lives in registers with compile-time
-//                      indices: no table traffic, no index arithmetic, 2 ALU ops per transition.
+//                      indices: no table traffic, no index arithmetic, 1.44 ALU ops per transition
+//                      (a maximum, and a minimum of three for every two).
 //   Held-Karp (Eq. 4)  lane = (candidate 0..7, stage v 0..7). The stages are taken as the group
 //                      Z_2^3: item (S, v) with S = v xor ({0} u D) belongs to class D (a subset of
 //                      {1..7}), and lane v holds the items (class D, v) of ALL classes, one register
@@ -104,8 +105,8 @@ __device__ __forceinline__ uint32_t match_couple(const wave_ctx &cx, const unsig
 
 // The same two matchings shared by a pair of neighbouring lanes: lane parity 0 matches rows 0..3 of each
 // block into every 4-column subset S, parity 1 rows 4..7; the optimum is the minimum over S of
-// max(first half into S, second half into the other four columns). 1,070 dependent-chain
-// instructions instead of 1,790: for wavefronts with at most 32 couples to match. Both lanes return
+// max(first half into S, second half into the other four columns). 900 dependent-chain
+// instructions instead of 1,470: for wavefronts with at most 32 couples to match. Both lanes return
 // the result.
 __device__ __forceinline__ uint32_t match_couple_halves(const wave_ctx &cx, const unsigned char *pb, const int (&j1)[2],
                                                         const int (&j2)[2])
@@ -119,14 +120,14 @@ __device__ __forceinline__ uint32_t match_couple_halves(const wave_ctx &cx, cons
         coldev[h] = *reinterpret_cast<const uint2 *>(pb + 8 * j2[h]);
     }
     uint32_t G[256];
-    match_rows<4, false>(cx.R, rowdev, coldev, G);
+    match_rows<4, true>(cx.R, rowdev, coldev, G);
     uint32_t best = 0;
 #pragma unroll
     for (int i = 0; i < BINOM8[4]; i++) {
         const int S = LAYER.s[4][i];
         const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)G[255 ^ S], DPP_XOR1, 0xF, 0xF, true);
-        const uint32_t m = pk_max(G[S], other);
-        best = i == 0 ? m : pk_min(best, m);
+        const uint32_t m = pk_max<true>(G[S], other);
+        best = i == 0 ? m : pk_min<true>(best, m);
     }
     return best;
 }
@@ -267,7 +268,7 @@ k_eval_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict__ rank
 // Population evaluation for populations so small that every SIMD has one group of four candidates and the launch
 // is as long as one wavefront's instruction stream: the group gets a PAIR of wavefronts (w and w + cw of the
 // workgroup, which share a SIMD). Both match: each takes two of the four candidates, two lanes per couple of stage
-// pairs (28 couples, 56 lanes, the programme of match_couple_halves, 1,070 instructions instead of 1,790), and the
+// pairs (28 couples, 56 lanes, the programme of match_couple_halves, 900 instructions instead of 1,470), and the
 // two streams fill each other's wait states. Then the first runs Held-Karp for all four candidates (64 lanes,
 // hk_registers<true>) while the second computes their DataP straight from the global W_dp (no LDS copy of it).
 // Workgroup barriers: after the table set-up, after the matching, before the final sum.

@@ -155,14 +155,27 @@ constexpr int LDS_TABLES = LDS_RANK_BYTES + LDS_RVAL_BYTES + LDS_WDP_BYTES;
 constexpr int WAVES_PER_BLOCK = 8;
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
+// Ranks are below 4096, so as bit patterns of halves they are finite, not negative and in the order of the integers.
+// Seen as halves (HALF) two minima take one instruction (v_pk_minimum3_f16, as fast as v_pk_min_u16; the packed 16-bit
+// integers have none such): the compiler forms it from pk_min(pk_min(a, b), c). Ranks below 1024 are subnormal halves,
+// which the kernels keep (the default mode).
+template <bool HALF>
 __device__ __forceinline__ uint32_t pk_max(uint32_t a, uint32_t b)
 {
+    if (HALF)
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_maximum(__builtin_bit_cast(f16x2, a),
+                                                                          __builtin_bit_cast(f16x2, b)));
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a),
                                                                   __builtin_bit_cast(u16x2, b)));
 }
+template <bool HALF>
 __device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b)
 {
+    if (HALF)
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_minimum(__builtin_bit_cast(f16x2, a),
+                                                                          __builtin_bit_cast(f16x2, b)));
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, a),
                                                                   __builtin_bit_cast(u16x2, b)));
 }
@@ -345,20 +358,16 @@ __device__ __forceinline__ double stage_datap(const double *Wdp, uint2 devs)
     return dp;
 }
 
-// always true, but not to the compiler: splits straight-line code into basic blocks
-__device__ __forceinline__ bool opaque_true()
-{
-    int t = 1;
-    asm volatile("" : "+s"(t));
-    return t != 0;
-}
-
 // The min-max subset programme of Eq. 3 for two blocks at once (low and high halves of every
 // register): after NROWS rows, G[S] for the column subsets S with NROWS elements is the bottleneck
 // optimum of matching rows 0 .. NROWS-1 into S. rowdev[h] / coldev[h]: the devices of the rows and of
 // the 8 columns of block h, one per byte. With NROWS = 8, G[255] is the optimum of the block; with
 // NROWS = 7, G[255 ^ (1 << c)] is the optimum of the 7 rows into all columns but c.
-template <int NROWS, bool SPLIT_ROWS>
+// HALF: 1016 maxima and 448 minima (two at a time) for eight rows, where integers take 1016 and 769. Measured: one
+// evaluation of 1,048,576 candidates 1341 -> 1212 us, of 4096 11.4 -> 10.5 us, a search of 20 generations 1853 -> 1766 us.
+// The exhaustive search stays with the integers: with halves its compilation spills more (40.9 against 44 ms for 20
+// rounds of 4096 allocations).
+template <int NROWS, bool HALF>
 __device__ __forceinline__ void match_rows(const uint16_t *R, const uint2 (&rowdev)[2], const uint2 (&coldev)[2],
                                            uint32_t (&G)[256])
 {
@@ -377,12 +386,6 @@ __device__ __forceinline__ void match_rows(const uint16_t *R, const uint2 (&rowd
     }
 #pragma unroll
     for (int r = 0; r < NROWS; r++) {
-        // With SPLIT_ROWS every row from the third on is a basic block of its own (a branch on a value
-        // the compiler cannot see, always taken): the instruction scheduler then cannot pile the gathers
-        // of all rows, with their LDS bank conflicts, in front of the programme; those of row r + 1 are
-        // issued with the arithmetic of row r and hidden behind it. It shortens a lone wavefront's pass
-        // by a few per cent; kernels that keep more state alive around the programme do better without.
-        if (SPLIT_ROWS && r >= 2 && !opaque_true()) continue;
         // row r of both blocks: w[c] = (rank of block-0 entry (r,c)) | (rank of block-1 entry) << 16
         uint32_t w[8];
 #pragma unroll
@@ -400,8 +403,8 @@ __device__ __forceinline__ void match_rows(const uint16_t *R, const uint2 (&rowd
 #pragma unroll
             for (int c = 0; c < 8; c++) {
                 if (!(S & (1 << c))) continue;
-                const uint32_t m = (r == 0) ? w[c] : pk_max(G[S ^ (1 << c)], w[c]);
-                acc = first ? m : pk_min(acc, m);
+                const uint32_t m = (r == 0) ? w[c] : pk_max<HALF>(G[S ^ (1 << c)], w[c]);
+                acc = first ? m : pk_min<HALF>(acc, m);
                 first = false;
             }
             G[S] = acc;

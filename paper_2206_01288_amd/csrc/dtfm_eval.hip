@@ -2,7 +2,7 @@
 //   k_weights     Sec. 2 symmetrisation + the per-link terms of Eqs. 2 and 3
 //   k_datap       Eq. 2 per stage and the max over stages (Sec. 3.2); for matrices beyond an XCD's L2
 //                 k_datap_sliced (by slice of devices) or k_positions + k_datap_rows + k_datap_reduce (by device)
-//   k_match       Eq. 3: bottleneck perfect matching of one stage pair per wavefront
+//   k_match       Eq. 3: bottleneck perfect matching of one stage pair per wavefront; k_match16: of four, when many and small
 //   k_held_karp   Eq. 4: open-loop TSP over the coarsened graph, exact, by subset dynamic
 //                 programming; adds the two parts (Eq. 1); k_held_karp_blocked from 11 stages on
 //   k_trial_shortcut   trials of the local search that the coarsened graph settles without Eq. 4
@@ -421,21 +421,9 @@ __device__ __forceinline__ uint32_t match_block(uint16_t *tile, uint32_t (&E)[16
     return result;
 }
 
-// One wavefront (= one workgroup) per (candidate, stage pair): the lane gathers its column of the block from the
-// table of codes, 2 bytes an entry (pad 0xffff outside the block), and keeps the block's LDS copy as s_E[r * 64 + c].
-template <int NB>  // number of 16-row blocks: D_dp <= 16 * NB
-__global__ void __launch_bounds__(DTFM_WAVE) __attribute__((amdgpu_waves_per_eu(5)))
-k_match(const uint16_t *__restrict__ Wcode, const uint32_t *__restrict__ Wrank, const double *__restrict__ rank_val, int shift0,
-        const int32_t *__restrict__ perm, int N, int D_dp, int D_pp,
-        double *__restrict__ ghat, int inc_j, int inc_jp)
+// Stage pair number t of a launch (j1 < j2).
+__device__ __forceinline__ void match_pair(int t, int D_pp, int inc_j, int inc_jp, int &j1, int &j2)
 {
-    constexpr int R = 16 * NB, RS = R - 16;
-    extern __shared__ uint16_t s_E[];   // R x 64 codes
-    const int lane = threadIdx.x;
-    const bool active = lane < D_dp;
-    const size_t p = blockIdx.x;   // candidate
-    const int t = (int)blockIdx.y; // stage pair
-    int j1, j2;
     if (inc_j < 0) {
         // t-th stage pair (j1 < j2) in lexicographic order
         int rem = t;
@@ -461,6 +449,24 @@ k_match(const uint16_t *__restrict__ Wcode, const uint32_t *__restrict__ Wrank, 
         j1 = a < k ? a : k;
         j2 = a < k ? k : a;
     }
+}
+
+// One wavefront (= one workgroup) per (candidate, stage pair): the lane gathers its column of the block from the
+// table of codes, 2 bytes an entry (pad 0xffff outside the block), and keeps the block's LDS copy as s_E[r * 64 + c].
+template <int NB>  // number of 16-row blocks: D_dp <= 16 * NB
+__global__ void __launch_bounds__(DTFM_WAVE) __attribute__((amdgpu_waves_per_eu(5)))
+k_match(const uint16_t *__restrict__ Wcode, const uint32_t *__restrict__ Wrank, const double *__restrict__ rank_val, int shift0,
+        const int32_t *__restrict__ perm, int N, int D_dp, int D_pp,
+        double *__restrict__ ghat, int inc_j, int inc_jp)
+{
+    constexpr int R = 16 * NB, RS = R - 16;
+    extern __shared__ uint16_t s_E[];   // R x 64 codes
+    const int lane = threadIdx.x;
+    const bool active = lane < D_dp;
+    const size_t p = blockIdx.x;   // candidate
+    const int t = (int)blockIdx.y; // stage pair
+    int j1, j2;
+    match_pair(t, D_pp, inc_j, inc_jp, j1, j2);
     const int32_t *row = perm + p * N;
     const int32_t *Ca = row + j1 * D_dp;   // wavefront-uniform: read through the scalar cache
     const uint32_t coldev = active ? (uint32_t)row[j2 * D_dp + lane] : 0u;
@@ -476,6 +482,144 @@ k_match(const uint16_t *__restrict__ Wcode, const uint32_t *__restrict__ Wrank, 
     });
     if (lane == 0) {
         const double v = result == 0xffffffffu ? INFINITY : rank_val[result];
+        double *G = ghat + p * D_pp * D_pp;
+        G[j1 * D_pp + j2] = v;
+        G[j2 * D_pp + j1] = v;
+    }
+}
+
+// Blocks of at most 16 rows, four to a wavefront: lane = 16 x candidate + column, one stage pair of four candidates. A
+// block of its own leaves 48 lanes of k_match idle in every gather and every step, and its scalar instructions serve one
+// search; here the state of a search (free columns, pending rows, the row matched to each column as 16 nibbles) is kept
+// by the 16 lanes of its block and all four advance together. The steps are those of match_block, with one difference
+// that does not change the threshold reached: a turn lets two reached columns join instead of all of them, so that the
+// four searches stay in step. Codes are ranks here (N <= 256: at most 32,641 distinct weights), one solve is exact.
+// Measured, a whole evaluation: 3001 candidates of 7 stages of 12: 107 -> 84 us; 2000 of 9 stages of 5: 82 -> 55 us; 4096 of
+// 16 stages of 16: 1055 -> 822 us, of 8: 754 -> 535 us. What bounds it: the vector instructions of a turn and the LDS reads
+// and exchanges behind one another in it.
+__device__ __forceinline__ uint32_t row16_min(uint32_t x)
+{
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));   // rotations inside 16 lanes
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));
+    x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xF, 0xF, true));
+    return min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xF, 0xF, true));
+}
+// lane r of every 16 to all of them (r known at compile time after unrolling)
+template <int r>
+__device__ __forceinline__ uint32_t row16_bcast(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + r, 0xF, 0xF, true);
+}
+template <int r>
+__device__ __forceinline__ void gather16(const uint16_t *__restrict__ Wcode, uint32_t rowbase, uint32_t coldev, bool active,
+                                         int D_dp, uint32_t (&E)[16])
+{
+    if constexpr (r < 16) {
+        const uint32_t v = Wcode[row16_bcast<r>(rowbase) + coldev];
+        E[r] = active && r < D_dp ? v : 0xffffu;
+        gather16<r + 1>(Wcode, rowbase, coldev, active, D_dp, E);
+    }
+}
+
+__global__ void __launch_bounds__(DTFM_WAVE) __attribute__((amdgpu_waves_per_eu(8)))
+k_match16(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_val, const int32_t *__restrict__ perm, int N,
+          int D_dp, int D_pp, double *__restrict__ ghat, size_t P, int inc_j, int inc_jp)
+{
+    __shared__ uint16_t s_E[16 * DTFM_WAVE];
+    const int lane = threadIdx.x, c = lane & 15, base = lane & 48;
+    const size_t p = (size_t)blockIdx.x * 4 + (size_t)(lane >> 4);
+    const bool have = p < P;
+    int j1, j2;
+    match_pair((int)blockIdx.y, D_pp, inc_j, inc_jp, j1, j2);
+    const bool active = have && c < D_dp;
+    const int32_t *row = perm + (have ? p : 0) * N;
+    const uint32_t rowbase = active ? (uint32_t)row[j1 * D_dp + c] * (uint32_t)N : 0u;
+    const uint32_t coldev = active ? (uint32_t)row[j2 * D_dp + c] : 0u;
+    uint32_t E[16];
+    gather16<0>(Wcode, rowbase, coldev, active, D_dp, E);
+    uint16_t *tile = s_E + lane;
+    uint32_t colmin = 0xffffu;
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        colmin = min(colmin, E[r]);
+        tile[r * DTFM_WAVE] = (uint16_t)E[r];
+    }
+    __builtin_amdgcn_wave_barrier();   // a lane reads only what it wrote itself
+    auto mask16 = [&](bool x) { return (uint32_t)(__ballot(x) >> base) & 0xffffu; };   // over the lanes of the block
+    uint32_t theta = ~row16_min(active ? ~colmin : 0xffffffffu);
+    uint32_t freecols = have ? (1u << D_dp) - 1u : 0u, pending = 0u;
+    uint64_t rows_of = 0ull;   // nibble q: the row matched to column q
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        if (r < D_dp) {
+            uint32_t m = mask16(E[r] <= theta);
+            if (__ballot(have && m == 0u) != 0ull) {
+                const uint32_t least = row16_min(E[r]);
+                theta = m == 0u ? least : theta;
+                m = mask16(E[r] <= theta);
+            }
+            m &= freecols;
+            const uint32_t q = (uint32_t)__ffs((int)m) - 1u;   // meaningless for m = 0
+            rows_of |= m != 0u ? (uint64_t)r << (4u * (q & 15u)) : 0ull;
+            pending |= have && m == 0u ? 1u << r : 0u;
+            freecols &= ~(m & (0u - m));
+        }
+    }
+    uint32_t thr = (theta << 7) | 127u, dist = 0u, parked = 0u;
+    int r0 = 0;
+    bool run = pending != 0u, failed = false;
+    auto begin = [&](bool start) {   // the next pending row of the blocks with `start`
+        r0 = start ? __ffs((int)pending) - 1 : r0;
+        const uint32_t d = ((uint32_t)tile[r0 * DTFM_WAVE] << 7) | DTFM_MATCH_ROOT;
+        dist = start ? d : dist;
+        pending &= start ? pending - 1u : ~0u;
+    };
+    begin(run);
+    // a turn parks a column or ends an insertion: 16 insertions of at most 17 turns
+    for (int turn = 0; turn < 16 * 18 && __ballot(run) != 0ull; turn++) {
+        uint32_t reach = mask16(run && dist - 1u < thr);   // unvisited (dist != 0) and within theta
+        if (__ballot(run && reach == 0u) != 0ull) {
+            // stuck: the smallest dist of an unvisited column
+            const uint32_t k = row16_min(dist - 1u);
+            const bool stuck = run && reach == 0u;
+            failed = failed || (stuck && k >= (0xffffu << 7) - 1u);
+            run = run && !failed;
+            thr = stuck && run ? (k + 1u) | 127u : thr;
+            reach = mask16(run && dist - 1u < thr);
+        }
+        const uint32_t hit = reach & freecols;
+        if (__ballot(hit != 0u) != 0ull) {
+            // flip the path: column q takes the row of its predecessor column; the first column takes r0
+            const uint32_t via = dist == 0u ? parked : dist & 127u;
+            bool go = hit != 0u;
+            uint32_t q = go ? (uint32_t)__ffs((int)hit) - 1u : 0u;
+            freecols &= ~(hit & (0u - hit));
+            for (int step = 0; step <= 16 && __ballot(go) != 0ull; step++) {   // a path has at most 16 columns
+                const uint32_t pc = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (base + (int)q), (int)via);
+                const uint32_t prow = pc == DTFM_MATCH_ROOT ? (uint32_t)r0 : (uint32_t)(rows_of >> (4u * (pc & 15u))) & 15u;
+                const uint64_t moved = (rows_of & ~(15ull << (4u * q))) | ((uint64_t)prow << (4u * q));
+                rows_of = go ? moved : rows_of;
+                go = go && pc != DTFM_MATCH_ROOT;
+                q = go ? pc & 15u : q;
+            }
+            run = run && !(hit != 0u && pending == 0u);
+            begin(run && hit != 0u);
+        }
+        // two reached columns join the search, and with them the rows matched to them
+        const bool grow = run && hit == 0u && reach != 0u;
+        const uint32_t c0 = grow ? (uint32_t)__ffs((int)reach) - 1u : 0u, left = reach & (reach - 1u);
+        const uint32_t c1 = grow && left != 0u ? (uint32_t)__ffs((int)left) - 1u : c0;   // none left: c0 once more
+        if (grow && ((uint32_t)c == c0 || (uint32_t)c == c1)) {
+            parked = dist & 127u;
+            dist = 0u;
+        }
+        const uint32_t m0 = (uint32_t)(rows_of >> (4u * c0)) & 15u, m1 = (uint32_t)(rows_of >> (4u * c1)) & 15u;
+        const uint32_t w0 = ((uint32_t)tile[m0 * DTFM_WAVE] << 7) | c0, w1 = ((uint32_t)tile[m1 * DTFM_WAVE] << 7) | c1;
+        dist = grow ? min(dist, min(w0, w1)) : dist;
+    }
+    theta = thr >> 7;
+    if (c == 0 && have) {
+        const double v = failed || run || theta < 2u ? INFINITY : rank_val[theta - 2u];
         double *G = ghat + p * D_pp * D_pp;
         G[j1 * D_pp + j2] = v;
         G[j2 * D_pp + j1] = v;
@@ -804,6 +948,12 @@ static bool datap_by_device(const dtfm_problem *pr)
     return (size_t)pr->N * pr->N * sizeof(double) > ((size_t)2 << 20) && pr->D_dp % 4 == 0 && pr->N % DTFM_DATAP_DPW == 0;
 }
 
+// Blocks of at most 16 rows go four to a wavefront (k_match16) when there are more of them than two rounds of k_match's
+// resident wavefronts (20 for each of 256 CUs). Below that a search of its own per wavefront ends earlier than the longest
+// of four: evaluations of 16 stages of 16, 8 / 32 / 64 / 128 candidates: 160 / 171 / 198 / 210 us with k_match, 170 / 177 /
+// 203 / 210 us with k_match16; 16 stages of 8, 32 / 128: 138 / 180 against 139 / 178 us; 4 stages of 2, 2000: 17 against 15.
+constexpr size_t MATCH16_MIN = 2 * 5120;
+
 dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t rows, size_t hk_grid_cap, bool lean)
 {
     dtfm_eval_bufs b;
@@ -876,11 +1026,16 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         const int nb = (pr->D_dp + 15) / 16;
         if (rows > 0x7fffffffu) return DTFM_ERR_ARG;
         if (match_pairs > 0) {
-        auto kern = nb <= 1 ? k_match<1> : nb == 2 ? k_match<2> : nb == 3 ? k_match<3> : k_match<4>;
-        // one wavefront per (candidate, stage pair)
-        hipLaunchKernelGGL(kern, dim3((unsigned)rows, (unsigned)match_pairs), dim3(DTFM_WAVE),
-                           (size_t)16 * nb * DTFM_WAVE * sizeof(uint16_t), st, pr->W_code, pr->W_rank, pr->rank_val, pr->rank_shift, perm, N, pr->D_dp, n,
-                           b.ghat, inc_j, inc_jp);
+        if (nb <= 1 && rows * (size_t)match_pairs > MATCH16_MIN) {
+            hipLaunchKernelGGL(k_match16, dim3((unsigned)((rows + 3) / 4), (unsigned)match_pairs), dim3(DTFM_WAVE), 0, st, pr->W_code,
+                               pr->rank_val, perm, N, pr->D_dp, n, b.ghat, rows, inc_j, inc_jp);
+        } else {
+            auto kern = nb <= 1 ? k_match<1> : nb == 2 ? k_match<2> : nb == 3 ? k_match<3> : k_match<4>;
+            // one wavefront per (candidate, stage pair)
+            hipLaunchKernelGGL(kern, dim3((unsigned)rows, (unsigned)match_pairs), dim3(DTFM_WAVE),
+                               (size_t)16 * nb * DTFM_WAVE * sizeof(uint16_t), st, pr->W_code, pr->W_rank, pr->rank_val,
+                               pr->rank_shift, perm, N, pr->D_dp, n, b.ghat, inc_j, inc_jp);
+        }
         DTFM_HIP(hipGetLastError());
         }
     }

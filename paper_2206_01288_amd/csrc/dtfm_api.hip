@@ -166,6 +166,7 @@ extern "C" int dtfm_create_problem(const double *latency, const double *bandwidt
         vals.erase(std::unique(vals.begin(), vals.end()), vals.end());
         // the matching kernel's first solve works on the table of 16-bit codes 2 + (rank >> shift) <= 0xfffe; the
         // table of ranks serves the entries inside the optimum's bucket when shift > 0
+        pr->weights = (int)vals.size();
         pr->rank_shift = 0;
         while (((vals.size() - 1) >> pr->rank_shift) + 2 > 0xfffe) pr->rank_shift++;
         std::vector<uint32_t> rk(w.size());

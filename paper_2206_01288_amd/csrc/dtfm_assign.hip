@@ -10,7 +10,7 @@
 //             within W_pp <= T;
 //   pipeline  P_i starts at slot i of the first group of the order and follows the matchings.
 //   k_hk_path        one workgroup per candidate: full Held-Karp table in a scratch slice, then the
-//                    back-tracking by one thread (from 11 stages on k_tour_path of dtfm_tour.hip first)
+//                    back-tracking by one thread (from 12 stages on k_tour_path of dtfm_tour.hip first)
 //   k_lexmin_match   one wavefront per (candidate, adjacent pair): bit-mask augmenting paths
 //   k_chain          composes the matchings into pipelines
 #include "dtfm_internal.h"
@@ -222,10 +222,12 @@ int dtfm_assign_enqueue(const dtfm_problem *pr, const dtfm_assign_bufs &b, const
     int rc = dtfm_eval_enqueue(pr, b.ev, perm, rows, nullptr, st);   // coarsened graphs only
     if (rc != DTFM_OK) return rc;
     const size_t grid = hkp_grid(n, rows);
-    const bool pruned = n > DTFM_HK_LDS_MAX_DPP;
-    if (pruned) {   // the full table only for what the pruned recursion leaves (usually nothing)
-        rc = dtfm_zero_count_enqueue(b.ev.count, st);
-        if (rc == DTFM_OK) rc = dtfm_tour_path_enqueue(pr, b.ev, b.tab, grid, rows, stage_order, st);
+    // From 12 stages on the full table only for what the pruned recursion leaves (usually nothing). Whole calls by the
+    // recursion and by the table, devices in regions, us: 12 stages of 4, 1 / 32 / 512 orders 76 / 104 / 134 and 132 / 139 / 260; 11
+    // stages of 4, 1 / 32 / 512: 70 / 97 / 154 and 75 / 81 / 153.
+    const bool pruned = n > 11;
+    if (pruned) {
+        rc = dtfm_tour_path_enqueue(pr, b.ev, b.tab, grid, rows, stage_order, st);
         if (rc != DTFM_OK) return rc;
     }
     hipLaunchKernelGGL(k_hk_path, dim3((unsigned)grid), dim3(HKP_THREADS), 0, st, b.ev.ghat, n, pr->hk_subsets,

@@ -47,10 +47,17 @@ int dtfm_weights_enqueue(const double *lat_dev, const double *bw_dev, int N, dou
 // a2/a3: one workgroup per candidate, one thread per position q (device d = perm[q], stage
 // j = q / D_dp, slot i = q % D_dp). The row sum runs over the stage's slots in order, skipping the
 // device's own slot, starting from +0.0; max over the devices of all stages is exact in any order.
-// Also zeroes the diagonal of the candidate's coarsened graph.
-__global__ void k_datap(const double *__restrict__ W_dp, const int32_t *__restrict__ perm, int N,
-                        int D_dp, int D_pp, double *__restrict__ datap, double *__restrict__ ghat)
+// Also zeroes the diagonal of the candidate's coarsened graph and, like every last kernel of DataP, the counters of
+// dtfm_eval_bufs for the kernels that follow.
+__device__ __forceinline__ void clear_counts(int32_t *count)
 {
+    if (blockIdx.x == 0 && threadIdx.x < 3) count[threadIdx.x] = 0;
+}
+
+__global__ void k_datap(const double *__restrict__ W_dp, const int32_t *__restrict__ perm, int N,
+                        int D_dp, int D_pp, double *__restrict__ datap, double *__restrict__ ghat, int32_t *__restrict__ count)
+{
+    clear_counts(count);
     extern __shared__ int32_t s_perm[];
     __shared__ double s_red[16];
     size_t p = blockIdx.x;
@@ -92,8 +99,9 @@ __global__ void k_datap(const double *__restrict__ W_dp, const int32_t *__restri
 #define DTFM_XCDS 8
 __global__ void k_datap_sliced(const double *__restrict__ W_dp, const int32_t *__restrict__ perm, int N,
                                int D_dp, int D_pp, size_t P, size_t stride, double *__restrict__ datap,
-                               double *__restrict__ ghat)
+                               double *__restrict__ ghat, int32_t *__restrict__ count)
 {
+    clear_counts(count);
     extern __shared__ int32_t s_all[];
     int32_t *s_perm = s_all, *s_list = s_all + N;   // the row; the positions of this slice
     __shared__ int s_count;
@@ -185,8 +193,10 @@ k_datap_rows(const double *__restrict__ W_dp, const int32_t *__restrict__ perm, 
 // max over a candidate's row sums (all weights are >= 0, so every row sum is >= +0.0); also zeroes the diagonal
 // of the candidate's coarsened graph
 __global__ void __launch_bounds__(256)
-k_datap_reduce(const double *__restrict__ rowsum, int N, int D_pp, double *__restrict__ datap, double *__restrict__ ghat)
+k_datap_reduce(const double *__restrict__ rowsum, int N, int D_pp, double *__restrict__ datap, double *__restrict__ ghat,
+               int32_t *__restrict__ count)
 {
+    clear_counts(count);
     __shared__ double s_red[4];
     const size_t p = blockIdx.x;
     double worst = 0.0;
@@ -926,15 +936,6 @@ __global__ void k_trial_shortcut(const double *__restrict__ ghat, const double *
     }
 }
 
-__global__ void k_zero_count(int32_t *count) { count[threadIdx.x] = 0; }
-
-int dtfm_zero_count_enqueue(int32_t *count, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_zero_count, dim3(1), dim3(2), 0, st, count);
-    DTFM_HIP(hipGetLastError());
-    return DTFM_OK;
-}
-
 size_t dtfm_hk_exchange_bytes(const dtfm_problem *pr)
 {
     if (pr->D_pp <= DTFM_HK_LDS_MAX_DPP) return 0;
@@ -976,7 +977,7 @@ dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t ro
     b.pp = ar.take<double>(rows);
     b.list = ar.take<int32_t>(rows);
     b.dense = lean || pr->D_pp <= DTFM_HK_LDS_MAX_DPP ? b.list : ar.take<int32_t>(rows);
-    b.count = ar.take<int32_t>(2);
+    b.count = ar.take<int32_t>(3);
     return b;
 }
 
@@ -1006,7 +1007,7 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         hipLaunchKernelGGL(k_datap_rows, dim3((unsigned)(N / DTFM_DATAP_DPW * DTFM_DATAP_SPLIT)), dim3(256),
                            (size_t)DTFM_DATAP_DPW * N * sizeof(double), st, pr->W_dp, perm, b.pos, N, pr->D_dp, rows, b.rowsum);
         DTFM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_datap_reduce, dim3((unsigned)rows), dim3(256), 0, st, b.rowsum, N, n, b.datap, b.ghat);
+        hipLaunchKernelGGL(k_datap_reduce, dim3((unsigned)rows), dim3(256), 0, st, b.rowsum, N, n, b.datap, b.ghat, b.count);
     } else if ((size_t)N * N * sizeof(double) > ((size_t)2 << 20) && N % DTFM_XCDS == 0) {
         // W_dp larger than half an XCD's L2: one slice of its rows per XCD
         hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, b.datap, rows);
@@ -1014,10 +1015,10 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         size_t per_slice = rows < 512 ? rows : 512;   // workgroups per slice; each strides over the candidates
         int slice_threads = ((N / DTFM_XCDS + DTFM_WAVE - 1) / DTFM_WAVE) * DTFM_WAVE;
         hipLaunchKernelGGL(k_datap_sliced, dim3((unsigned)(per_slice * DTFM_XCDS)), dim3(slice_threads),
-                           2 * N * sizeof(int32_t), st, pr->W_dp, perm, N, pr->D_dp, n, rows, per_slice, b.datap, b.ghat);
+                           2 * N * sizeof(int32_t), st, pr->W_dp, perm, N, pr->D_dp, n, rows, per_slice, b.datap, b.ghat, b.count);
     } else {
         hipLaunchKernelGGL(k_datap, dim3((unsigned)rows), dim3(threads), N * sizeof(int32_t), st, pr->W_dp,
-                           perm, N, pr->D_dp, n, b.datap, b.ghat);
+                           perm, N, pr->D_dp, n, b.datap, b.ghat, b.count);
     }
     DTFM_HIP(hipGetLastError());
     if (pr->npairs > 0) {
@@ -1041,10 +1042,6 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     }
     if (cost == nullptr) return DTFM_OK;
     const int32_t *list = nullptr, *count = nullptr;
-    if (ref != nullptr || n > DTFM_HK_LDS_MAX_DPP) {
-        const int rc = dtfm_zero_count_enqueue(b.count, st);
-        if (rc != DTFM_OK) return rc;
-    }
     if (ref != nullptr) {   // trials of the local search: Held-Karp only where the coarsened graph does not settle the trial
         hipLaunchKernelGGL(k_trial_shortcut, dim3((unsigned)((rows + 3) / 4)), dim3(4 * DTFM_WAVE), 0, st, b.ghat, b.datap,
                            n * n, ref->ghat_cur, ref->pp_cur, ref->cur, cost, b.pp, b.list, b.count, rows, ref->trials_per_row);
@@ -1061,9 +1058,13 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         hipLaunchKernelGGL(k_held_karp<true>, dim3((unsigned)rows), dim3(bt), lds, st, b.ghat, b.datap, n,
                            pr->hk_subsets, pr->hk_off, (double *)nullptr, cost, rows, list, count, b.pp);
     } else {
-        // the pruned recursion first; the dense one for what it left (usually nothing)
-        const int rc = dtfm_tour_enqueue(pr, b, rows, cost, list, ref, st);
-        if (rc != DTFM_OK) return rc;
+        // the pruned recursion first where it pays; the dense one for what it left
+        if (dtfm_tour_rule(pr, rows, b.hk_grid).worth(n, rows, 0)) {
+            const int rc = dtfm_tour_enqueue(pr, b, rows, cost, list, ref, st);
+            if (rc != DTFM_OK) return rc;
+            list = b.dense;
+            count = b.count + 1;
+        }
         size_t grid = b.hk_grid;
         constexpr int NL = DTFM_HK_BLOCK_LOW;
         // rows, Ghat, and the low parts in layer order with two more turns of entries behind them (read ahead, never used)
@@ -1071,8 +1072,8 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         auto kern = n <= 12 ? k_held_karp_blocked<NL, 6> : n <= 14 ? k_held_karp_blocked<NL, 7> : k_held_karp_blocked<NL, 8>;
         DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds));
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1 << NL), lds, st, b.ghat, b.datap, n, b.hk_tab, cost, rows, b.dense,
-                           b.count + 1, b.pp);
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(1 << NL), lds, st, b.ghat, b.datap, n, b.hk_tab, cost, rows, list, count,
+                           b.pp);
     }
     DTFM_HIP(hipGetLastError());
     return DTFM_OK;

@@ -43,6 +43,7 @@ struct dtfm_problem {
     uint16_t *W_code;       // device, N*N: 2 + (rank >> rank_shift), the codes of the matching kernel's first solve
     int rank_shift;         // smallest shift with which the codes stay below 0xffff
     double *rank_val;       // device: rank -> weight
+    int weights;            // different entries of W_pp
     dtfm_layer_off hk_off;
     char *scratch;          // device arena, grown on demand
     size_t scratch_bytes;
@@ -86,7 +87,38 @@ struct dtfm_eval_bufs {
     double *pp;      // rows: PipelineP-Cost (the Held-Karp value) of every row whose Held-Karp was run
     int32_t *list;   // rows: the rows whose Held-Karp is still to run (trial evaluations, see dtfm_trial_ref)
     int32_t *dense;  // rows: the rows the pruned recursion leaves to the dense one (lean: the buffer of `list`)
-    int32_t *count;  // 2: lengths of list and dense
+    int32_t *count;  // 3: lengths of list and dense, rows put on dense by the values of their edges; cleared with DataP
+};
+// Which rows of a launch from 11 stages on the pruned recursion of dtfm_tour.hip takes, by what the dense one needs for them:
+// a round for every hk_grid rows (18, 32, 68, 130, 255, 525 us at 11 to 16 stages).
+struct dtfm_tour_rule {
+    size_t hk_grid;   // workgroups of the dense recursion
+    int few;          // rows with 2 to `few` different edges go to the dense recursion, whose time a failed search would add to
+    bool split;       // they are counted and put there before the search
+    int work;         // states the joint searches of a workgroup may price, about 22 a microsecond
+    dtfm_tour_rule(const dtfm_problem *pr, size_t rows, size_t hk_grid) : hk_grid(hk_grid)
+    {
+        const int n = pr->D_pp;
+        const size_t rounds = rounds_of(rows);
+        // Of 16 rounds a failed search is a small part, and half the graphs of two or three values are solved (tied tables,
+        // 4096 rows of 16 stages of one device: 8.8 -> 1.9 ms; failing all, three latencies, 14 stages: 2.2 -> 2.4 ms).
+        few = rounds >= 16 ? (n >= 14 ? 1 : 6) : n - 4 < 40 - 2 * n ? n - 4 : 40 - 2 * n;
+        // A launch of 4 us, for networks whose optima, each about the largest of D_dp weights, may take few values (uniform
+        // in 1 .. 100: 71, 38, 15, 9 values among 120 edges at 1, 8, 32, 64 devices a stage).
+        split = rounds < 16 && rows > 8 && pr->weights < 16 * pr->D_dp;
+        work = ((n << n) >> (n < 14 ? 6 : 7)) * (int)(rounds < 8 ? 1 : rounds < 16 ? rounds / 4 : 4);
+    }
+    __host__ __device__ size_t rounds_of(size_t rows) const { return (rows + hk_grid - 1) / hk_grid; }
+    // Whether the rounds that a search of the other rows saves are worth its time: 60 us of the usual graphs against one
+    // round from 14 stages on, two if some rows go to the dense recursion anyway, and three, five and nine rounds at 13, 12
+    // and 11 stages. Evaluations with 4 devices a stage, independent links and regions, by search (by the dense recursion), us:
+    // 11 stages, 1024 rows 122, 182 (110), 2048: 137, 194 (200), 4096: 208, 255 (390); 12 stages, 512: 126, 125 (97), 1024:
+    // 138, 137 (175), 2048: 174, 169 (347); 13 stages, 512: 153, 274 (172), 768: 157, 280 (240), 2048: 206, 313 (643).
+    __host__ __device__ bool worth(int n, size_t rows, size_t few_rows) const
+    {
+        const size_t spare = n < 14 ? 16u >> (n - 10) : few_rows > 0 ? 1 : 0;
+        return rounds_of(rows) - rounds_of(few_rows) > spare;
+    }
 };
 // What a trial evaluation of the local search knows about the rows its trials were made from: with it, a trial
 // whose coarsened graph equals its current row's, or is nowhere below it while DataP + the current PipelineP
@@ -111,14 +143,13 @@ int dtfm_eval_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int
 int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int32_t *perm, size_t rows,
                           double *cost, int inc_j, int inc_jp, hipStream_t st, const dtfm_trial_ref *ref = nullptr);
 // Eq. 4 by pruned subset recursion (dtfm_tour.hip): cost and b.pp of the rows (with list: list[0 .. b.count[0])); appends
-// the rows it cannot settle to b.dense, b.count[1] of them. D_pp from 3 to 16.
+// the rows it cannot settle to b.dense, b.count[1] of them. D_pp from 11 to 16.
 int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t rows, double *cost, const int32_t *list,
                       const dtfm_trial_ref *ref, hipStream_t st);
-// The stage orders behind Eq. 4 (D_pp from DTFM_HK_LDS_MAX_DPP + 1 on) with `slots` areas of D_pp * 2^D_pp doubles at tab; the
+// The stage orders behind Eq. 4 (D_pp from 11 on) with `slots` areas of D_pp * 2^D_pp doubles at tab; the
 // rows it leaves to the full table are b.dense[0 .. b.count[1]), b.count zero on entry.
 int dtfm_tour_path_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, double *tab, size_t slots, size_t rows,
                            int32_t *order, hipStream_t st);
-int dtfm_zero_count_enqueue(int32_t *count, hipStream_t st);   // both words of dtfm_eval_bufs::count
 int dtfm_weights_enqueue(const double *lat_dev, const double *bw_dev, int N, double shard,
                          double c_pp, double *W_dp, double *W_pp, hipStream_t st);
 

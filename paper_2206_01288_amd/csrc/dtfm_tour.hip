@@ -19,16 +19,23 @@
 //              then kept, so T is the minimum. An attempt whose states die out proves T > thr; one that ends in
 //              T' > thr gives the upper bound T' for the next.
 // Sums along the path are fp64 in path order, exactly Held-Karp's; the result is the same number.
-// Measured, evaluation of 1024 allocations of 256 devices in 16 stages: 2.20 ms of k_held_karp_blocked became 0.17 ms;
-// 4096 allocations of 1024 devices: 8.4 ms became 0.26 ms.
+// Kernel times: 1024 allocations of 256 devices in 16 stages 0.24 ms (k_held_karp_blocked 2.2 ms), 4096 allocations of
+// 1024 devices in 16 stages 0.32 ms (8.4 ms).
 //
-// One workgroup of four wavefronts takes four candidates. The potentials of all four come from its first wavefront
-// (16 lanes a candidate, a lane per stage: the chain of dependent minima bounds this part, and one wavefront's
-// instructions serve four chains). Then every wavefront searches its own candidate: 16 lanes take a state, grow the
-// spanning tree of its rest (one minimum over 16 lanes and one LDS row per edge), price the successors, one per lane,
-// and put them into a hash table in LDS. A layer wider than a wavefront's share of the tables is repeated by the whole
-// workgroup on the joint tables; what does not fit there either, or is not finite, goes on a list for the dense
-// recursion (k_held_karp_blocked).
+// One workgroup of four wavefronts takes four candidates (a launch with few of them: two or one). The potentials of all
+// four come from its first wavefront (16 lanes a candidate, a lane per stage: the chain of dependent minima bounds this
+// part, and one wavefront's instructions serve four chains). Then every wavefront searches its own candidate: 16 lanes
+// take a state, grow the spanning tree of its rest (one minimum over 16 lanes and one LDS row per edge), price the
+// successors, one per lane, and put them into a hash table in LDS. A candidate with a layer of more than NARROW states is
+// searched again by the whole workgroup on the joint tables, and so is the only candidate of a workgroup from the start.
+// What does not fit there either, takes more than its share of the work (dtfm_tour_rule) or is not finite goes on a list
+// for the dense recursion (k_held_karp_blocked).
+//
+// What the dense recursion gets at once: a launch takes it one round for every 256 candidates (one workgroup a CU) of 18,
+// 32, 68, 130, 255 and 525 us at 11 to 16 stages, whatever the graph. A search takes 60 us where the graph has edges of
+// many values, up to 200 us where it has a dozen, and ends in overfull tables on graphs of a few values (on graphs of
+// region, cluster, independent and rounded networks of 1 to 64 devices a stage: 8 or more values at 16 stages: one
+// candidate in thirty; 7: one in three; 4 and 5: three in four), where its time is lost. dtfm_tour_enqueue has the rule.
 #include "dtfm_internal.h"
 
 #include <math.h>
@@ -37,29 +44,33 @@ namespace {
 
 constexpr int WAVES = 4;               // candidates (= wavefronts) per workgroup
 constexpr int CAP = 256;               // states per layer and wavefront
-constexpr int SLOTS = 512;             // hash slots per wavefront: CAP + one batch of 64 insertions stay below it
+constexpr int SLOTS = 512;             // hash slots per wavefront
 constexpr int LOG_SLOTS = 9;
 constexpr int RSTR = 16;               // words between rows of the edge table
 constexpr int NARROW = 40;             // layers wider than this go to the whole workgroup
+constexpr int BATCH = 16 * 15;         // new states of one pass of a wavefront: 16 states, at most 15 successors each
+// a pass is begun at no more than NARROW states (a wavefront alone) or WAVES * CAP (each wavefront of a workgroup)
+static_assert(NARROW + BATCH < SLOTS && WAVES * (CAP + BATCH) < WAVES * SLOTS, "a search needs a free slot");
 constexpr int STEPS = 18;              // subgradient steps
 constexpr int REFINE_STEPS = 60;       // of a candidate whose layers outgrow the workgroup's tables
 constexpr int UNIT_LOG = 24;           // the path U in integer units
 constexpr int BIAS = 1 << 26;          // makes C_ij + BIAS positive: |pi| <= 2^24, 0 <= g <= 2^24
 constexpr uint32_t EMPTY = 0xffffffffu;
+constexpr size_t SPREAD = 256;         // up to so many candidates have a workgroup and a CU each, up to twice as many share it
 constexpr double DOWN = 1.0 - 0x1p-50, UP = 1.0 + 0x1p-50;
 
 struct tour_lds {
     double G[WAVES][16][16];
     double F[WAVES * CAP];
     unsigned long long hF[WAVES * SLOTS];
-    uint32_t hkey[WAVES * SLOTS];
+    alignas(16) uint32_t hkey[WAVES * SLOTS];         // ascend() writes its edge tables 16 bytes at a time: here and T
     uint32_t key[WAVES * CAP];         // set << 4 | last stage
-    uint32_t T[WAVES][16][RSTR];       // (g_ij + pi_i) << 4
+    alignas(16) uint32_t T[WAVES][16][RSTR];          // (g_ij + pi_i) << 4
     int pi[WAVES][16];
     double scale[WAVES], U[WAVES], cap[WAVES], top[WAVES];
     double red[WAVES];
     double lo[WAVES], thr[WAVES], grow[WAVES];   // where a wavefront's own threshold loop stopped
-    int L[WAVES], state[WAVES];
+    int L[WAVES], state[WAVES], values[WAVES];   // values: see edge_values
     int count;
     uint16_t slot[WAVES * CAP];
 };
@@ -163,6 +174,39 @@ __device__ __forceinline__ void ascend(const int (&g)[16], uint32_t (*T)[RSTR], 
     }
 }
 
+__device__ __forceinline__ double lane_value(double x, int lane)   // lane: the same in all lanes
+{
+    const long long b = __double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)b, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// The number of different values among the edges of a graph (g(i, j): the edge), limit + 1 if there are more, by one
+// wavefront. The lanes hold the edges from stage i to stage i + k, k up to n / 2; a turn counts one value and strikes out
+// the edges that have it.
+template <typename Edge>
+__device__ __forceinline__ int edge_values(int lane, int n, int limit, Edge g)
+{
+    double own[2];
+    uint64_t left[2];
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        const int i = lane & 15, k = 4 * q + (lane >> 4) + 1, j = i + k < n ? i + k : i + k - n;
+        const bool edge = i < n && (2 * k < n || (2 * k == n && i < k));
+        own[q] = edge ? g(i, j) : 0.0;
+        left[q] = __ballot(edge);
+    }
+    int values = 0;
+    for (; values <= limit && (left[0] | left[1]) != 0ull; values++) {
+        const int q = left[0] != 0ull ? 0 : 1;
+        const double v = lane_value(q == 0 ? own[0] : own[1], __ffsll((unsigned long long)left[q]) - 1);
+        left[q] &= left[q] - 1ull;   // a NaN is not equal to itself
+        left[0] &= ~__ballot(own[0] == v);
+        left[1] &= ~__ballot(own[1] == v);
+    }
+    return values;
+}
+
 // Upper bound, scale, potentials and root bound of candidate `grp` of the workgroup, by the 16 lanes of a row.
 __device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, int n)
 {
@@ -211,7 +255,7 @@ __device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, in
     const double cap_units = __dmul_rn(__dmul_rn(sm.cap[grp], scale), UP);
     const int cap = cap_units < 0x1p30 ? (cap_units > 0.0 ? (int)cap_units + 1 : 1) : INT32_MAX;
     int best = INT32_MIN, best_pi = 0;
-    ascend(g, sm.T[grp], grp, i, n, STEPS, 2.0f, 0.82f, fine && !equal, cap, 0, best, best_pi);
+    ascend(g, sm.T[grp], grp, i, n, STEPS, 2.0f, 0.82f, fine && !equal && sm.state[grp] == SEARCH, cap, 0, best, best_pi);
     sm.pi[grp][i] = best_pi;
     if (i == 0) {
         sm.scale[grp] = scale;
@@ -356,7 +400,7 @@ __device__ __forceinline__ void expand(tour_lds &sm, int k, int n, int base, int
         const uint32_t want = ((S[j] | (1u << i)) << 4) | (uint32_t)i;
         uint32_t h = (want * 2654435761u) >> shift;
         if (keep) {
-            // the table never fills: cap + what one pass of the team can add stay within the slots
+            // the table never fills (see BATCH)
             for (int probe = 0; probe < slots; probe++) {
                 const uint32_t old = atomicCAS(&hkey[h], EMPTY, want);
                 fresh = old == EMPTY;
@@ -380,9 +424,6 @@ __device__ __forceinline__ void expand(tour_lds &sm, int k, int n, int base, int
     }
 }
 
-// All paths of candidate `cd` with cost <= thr, layer by layer. TEAM wavefronts work together (`tid`: thread of the
-// team) on the tables of wavefront `cd` (TEAM = 1) or of the whole workgroup. FOUND: T = the smallest cost of a
-// complete path kept, which is the optimum if T <= thr.
 // The states of a search, layer by layer, for the back-tracking: n layers of up to WAVES * CAP.
 struct tour_record {
     double *F;
@@ -390,10 +431,17 @@ struct tour_record {
     int *count;
 };
 
+// All paths of candidate `cd` with cost <= thr, layer by layer. TEAM wavefronts work together (`tid`: thread of the
+// team) on the tables of wavefront `cd` (TEAM = 1) or of the whole workgroup. FOUND: T = the smallest cost of a
+// complete path kept, which is the optimum if T <= thr. work: the states that may still be priced. Graphs of at most n / 2
+// values have layers of up to 560 states where the search succeeds (two cliques of eight stages) and outgrow any table
+// where it does not, so they are given up at 40 n; the stage orders, whose full table is dearer, are not.
 template <int TEAM, bool RECORD>
-__device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n, double thr, double &T, const tour_record &rec)
+__device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n, double thr, double &T, int &work,
+                                           const tour_record &rec)
 {
-    constexpr int slots = TEAM * SLOTS, NG = TEAM * 4, limit = TEAM == 1 ? NARROW : TEAM * CAP;
+    constexpr int slots = TEAM * SLOTS, NG = TEAM * 4;
+    const int limit = TEAM == 1 ? NARROW : !RECORD && sm.values[cd] <= n / 2 ? 40 * n : TEAM * CAP;
     const int at = TEAM == 1 ? cd : 0;
     double *F = sm.F + at * CAP;
     unsigned long long *hF = sm.hF + at * SLOTS;
@@ -437,7 +485,8 @@ __device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n,
             __syncthreads();
             if (tid == 0) sm.count = 0;
         }
-        if (made > limit) return OVERFLOW_;
+        work -= cnt;
+        if (made > limit || work < 0) return OVERFLOW_;
         if (made == 0) return DIED;
         for (int e = tid; e < made; e += TEAM * 64) {
             const int h = slot[e];
@@ -467,10 +516,19 @@ __device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n,
     return FOUND;
 }
 
+// Where the threshold loop of candidate `cd` starts when the workgroup runs all of it.
+__device__ __forceinline__ void first_threshold(tour_lds &sm, int cd)
+{
+    const double root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
+    sm.lo[cd] = root;
+    sm.grow[cd] = 1.5e-3 * sm.top[cd];
+    sm.thr[cd] = fmin(root + sm.grow[cd], fmin(sm.top[cd], sm.cap[cd]));
+}
+
 // The threshold loop. Returns SETTLED (the optimum is above cap), SEARCH with T the optimum, WIDE (a
 // wavefront's layer outgrew NARROW: the workgroup goes on from the same threshold) or DENSE.
 template <int TEAM, bool RECORD>
-__device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, double &T, const tour_record &rec)
+__device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, int &work, double &T, const tour_record &rec)
 {
     const double cap = sm.cap[cd];
     double U = sm.top[cd], top = fmin(U, cap), root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
@@ -482,7 +540,7 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
         grow = sm.grow[cd];
     }
     for (int attempt = 0; attempt < 16; attempt++) {
-        const int r = tour_search<TEAM, RECORD>(sm, cd, tid, n, thr, T, rec);
+        const int r = tour_search<TEAM, RECORD>(sm, cd, tid, n, thr, T, work, rec);
         if (r == FOUND) {
             if (T <= thr) return SEARCH;
             if (T >= over) return DENSE;
@@ -505,8 +563,9 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
             return WIDE;
         } else {
             if (!refined) {
-                // tables too small at this threshold: better potentials, unless the bound has no gap left to close
-                if (thr - root < 0x1p-18 * U) return DENSE;
+                // Tables too small at this threshold. The stage orders try better potentials, unless the graph has few
+                // values or the bound no gap left to close; Eq. 4 alone is cheaper by the dense recursion.
+                if (work < 0 || !RECORD || sm.values[cd] <= n / 2 || thr - root < 0x1p-18 * U) return DENSE;
                 refined = true;
                 __syncthreads();
                 if (tid < 64) {
@@ -522,6 +581,7 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
                 thr = fmin(fmax(root + grow, lo), top);
                 continue;
             }
+            if (work < 0) return DENSE;
             over = thr;
             if (over - lo <= 1e-4 * U) return DENSE;
             thr = lo + 0.3 * (over - lo);
@@ -536,15 +596,17 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
 __global__ void __launch_bounds__(64 * WAVES)
 k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap, int n, double *__restrict__ cost, size_t P,
               const int32_t *__restrict__ list, int32_t *__restrict__ count, const double *__restrict__ cur,
-              int trials_per_row, double *__restrict__ pp_out, int32_t *__restrict__ dense)
+              int trials_per_row, double *__restrict__ pp_out, int32_t *__restrict__ dense, dtfm_tour_rule rule)
 {
     __shared__ tour_lds sm;
     const size_t todo = list != nullptr ? (size_t)count[0] : P;
-    const size_t first = (size_t)blockIdx.x * WAVES;
+    const int per = todo <= SPREAD ? 1 : todo <= 2 * SPREAD ? 2 : WAVES;   // candidates of a workgroup
+    const size_t first = (size_t)blockIdx.x * per;
     if (first >= todo) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t idx = first + wave;
-    const bool have = idx < todo;
+    if (rule.split && (size_t)count[2] == todo) return;
+    const bool have = wave < per && idx < todo;
     const size_t p = have ? (list != nullptr ? (size_t)list[idx] : idx) : 0;
     for (int e = lane; e < 256; e += 64) {
         const int a = e >> 4, b = e & 15;
@@ -560,22 +622,39 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
         sm.cap[wave] = cap;
         sm.state[wave] = !have || cap <= 0.0 ? SETTLED : SEARCH;
     }
+    wave_sync();
+    const int values = edge_values(lane, n, max(rule.few, n / 2), [&](int i, int j) { return sm.G[wave][i][j]; });
+    const bool few = values > 1 && values <= rule.few;
+    if (lane == 0) {
+        sm.values[wave] = values;
+        if (sm.state[wave] == SEARCH && (few || !rule.worth(n, todo, (size_t)count[2]))) sm.state[wave] = DENSE;
+    }
     __syncthreads();
-    if (wave == 0) tour_potentials(sm, lane >> 4, lane & 15, n);
+    bool any = false;
+    for (int w = 0; w < WAVES; w++) any = any || sm.state[w] == SEARCH;
+    if (any && wave == 0) tour_potentials(sm, lane >> 4, lane & 15, n);
     __syncthreads();
     double T = 0.0;
     int state = sm.state[wave];
     if (state == SEARCH) {
         if (lane == 0) sm.top[wave] = sm.U[wave];
         tour_table(sm, wave, lane, n);
-        state = tour_solve<1, false>(sm, wave, lane, n, T, tour_record());
+        if (per == 1) {
+            if (lane == 0) first_threshold(sm, 0);
+            state = WIDE;
+        } else {
+            int work = INT32_MAX;
+            state = tour_solve<1, false>(sm, wave, lane, n, work, T, tour_record());
+            if (state == WIDE && n < 12) state = DENSE;   // 18 us there, 20 at the least here
+        }
         if (lane == 0 && state == WIDE) sm.state[wave] = WIDE;
     }
     __syncthreads();
+    int work = rule.work;
     for (int w = 0; w < WAVES; w++) {   // too wide for a quarter of the tables: all of them, one candidate at a time
         if (sm.state[w] != WIDE) continue;
         double Tw = 0.0;
-        const int s = tour_solve<WAVES, false>(sm, w, tid, n, Tw, tour_record());
+        const int s = work < 0 ? DENSE : tour_solve<WAVES, false>(sm, w, tid, n, work, Tw, tour_record());
         if (w == wave) {
             state = s;
             T = Tw;
@@ -589,7 +668,24 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
         pp_out[p] = T;
     } else if (state == SETTLED) {
         cost[p] = INFINITY;
-    } else {
+    } else if (!(rule.split && few)) {   // those are there already
+        dense[atomicAdd(&count[1], 1)] = (int32_t)p;
+    }
+}
+
+// Appends the rows whose graphs have 2 to rule.few values to dense and counts them in count[2], before the search: it
+// takes no row if the dense recursion needs as many rounds without them. One wavefront per row.
+__global__ void __launch_bounds__(64 * WAVES)
+k_tour_split(const double *__restrict__ ghat, int n, size_t P, const int32_t *__restrict__ list, int32_t *__restrict__ count,
+             int32_t *__restrict__ dense, dtfm_tour_rule rule)
+{
+    const int lane = threadIdx.x & 63;
+    const size_t idx = (size_t)blockIdx.x * WAVES + (threadIdx.x >> 6), todo = list != nullptr ? (size_t)count[0] : P;
+    if (idx >= todo) return;
+    const size_t p = list != nullptr ? (size_t)list[idx] : idx;
+    const int values = edge_values(lane, n, rule.few, [&](int i, int j) { return ghat[p * n * n + i * n + j]; });
+    if (lane == 0 && values > 1 && values <= rule.few) {
+        atomicAdd(&count[2], 1);
         dense[atomicAdd(&count[1], 1)] = (int32_t)p;
     }
 }
@@ -598,8 +694,8 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
 // v in a path over S is the lowest-numbered u with fl(tab[S - v][u] + Ghat[u][v]) = tab[S][v]. A search whose threshold is
 // not below the optimum keeps every state of every optimal path with its exact value, so both choices can be read off its
 // layers: a state of another path that met the equation would itself start an optimal path. One workgroup per candidate
-// (a call has few of them: 32 orders of 16 stages took 3.0 ms by the full table in HBM, 0.09 ms this way); the rows left
-// to the full table go to dense[0 .. count[1]).
+// (a call has few of them: 32 orders of 16 stages take 3.0 ms by the full table in HBM, 0.09 to 0.14 ms this way); the rows
+// left to the full table go to dense[0 .. count[1]).
 __global__ void __launch_bounds__(64 * WAVES)
 k_tour_path(const double *__restrict__ ghat, int n, size_t P, double *__restrict__ tab, int32_t *__restrict__ order,
             int32_t *__restrict__ count, int32_t *__restrict__ dense)
@@ -621,17 +717,16 @@ k_tour_path(const double *__restrict__ ghat, int n, size_t P, double *__restrict
         }
         __syncthreads();
         if (tid < 64) {
+            sm.values[0] = edge_values(lane, n, n / 2, [&](int i, int j) { return sm.G[0][i][j]; });
+            // the table of 12 stages takes 60 us, a search of such a graph up to 200
+            if (n == 12 && sm.values[0] > 1 && sm.values[0] <= n / 2) sm.state[0] = DENSE;
+            wave_sync();
             tour_potentials(sm, lane >> 4, lane & 15, n);
             wave_sync();
             if (sm.state[0] == SEARCH) {
                 if (lane == 0) sm.top[0] = sm.U[0];
                 tour_table(sm, 0, lane, n);
-                if (lane == 0) {
-                    const double root = fmax((double)sm.L[0], 0.0) / sm.scale[0];
-                    sm.lo[0] = root;
-                    sm.grow[0] = 1.5e-3 * sm.top[0];
-                    sm.thr[0] = fmin(root + sm.grow[0], sm.top[0]);
-                }
+                if (lane == 0) first_threshold(sm, 0);
             }
         }
         if (tid < n) {
@@ -642,7 +737,8 @@ k_tour_path(const double *__restrict__ ghat, int n, size_t P, double *__restrict
         __syncthreads();
         int state = sm.state[0];
         double T = 0.0;
-        if (state == SEARCH) state = tour_solve<WAVES, true>(sm, 0, tid, n, T, rec);
+        int work = min(max((n << n) >> 5, 1 << 12), 1 << 14);   // at most 0.7 ms
+        if (state == SEARCH) state = tour_solve<WAVES, true>(sm, 0, tid, n, work, T, rec);
         __syncthreads();
         int32_t *ord = order + p * n;
         if (state == SOLVED) {   // equal edges: every state of a layer has the same value
@@ -692,9 +788,18 @@ int dtfm_tour_path_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, doub
 int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t rows, double *cost, const int32_t *list,
                       const dtfm_trial_ref *ref, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_tour_search, dim3((unsigned)((rows + WAVES - 1) / WAVES)), dim3(64 * WAVES), 0, st, b.ghat, b.datap,
-                       pr->D_pp, cost, rows, list, b.count, ref != nullptr ? ref->cur : (const double *)nullptr,
-                       ref != nullptr ? ref->trials_per_row : 1, b.pp, b.dense);
+    // for any number of rows up to `rows` (with a list it is known on the device only)
+    const size_t packed = (rows + WAVES - 1) / WAVES, grid = rows < SPREAD ? rows : packed < SPREAD ? SPREAD : packed;
+    const dtfm_tour_rule rule(pr, rows, b.hk_grid);
+    const int n = pr->D_pp;
+    if (rule.split) {
+        hipLaunchKernelGGL(k_tour_split, dim3((unsigned)packed), dim3(64 * WAVES), 0, st, b.ghat, n, rows, list, b.count,
+                           b.dense, rule);
+        DTFM_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_tour_search, dim3((unsigned)grid), dim3(64 * WAVES), 0, st, b.ghat, b.datap,
+                       n, cost, rows, list, b.count, ref != nullptr ? ref->cur : (const double *)nullptr,
+                       ref != nullptr ? ref->trials_per_row : 1, b.pp, b.dense, rule);
     DTFM_HIP(hipGetLastError());
     return DTFM_OK;
 }

@@ -950,10 +950,15 @@ static bool datap_by_device(const dtfm_problem *pr)
 }
 
 // Blocks of at most 16 rows go four to a wavefront (k_match16) when there are more of them than two rounds of k_match's
-// resident wavefronts (20 for each of 256 CUs). Below that a search of its own per wavefront ends earlier than the longest
-// of four: evaluations of 16 stages of 16, 8 / 32 / 64 / 128 candidates: 160 / 171 / 198 / 210 us with k_match, 170 / 177 /
-// 203 / 210 us with k_match16; 16 stages of 8, 32 / 128: 138 / 180 against 139 / 178 us; 4 stages of 2, 2000: 17 against 15.
-constexpr size_t MATCH16_MIN = 2 * 5120;
+// resident wavefronts (20 for each of 256 CUs), and than five at 16 rows. Below that a search of its own per wavefront ends
+// earlier than the longest of four, the more so the longer the searches are. Evaluation time with k_match over that with
+// k_match16 at 10,300 / 14,000 / 20,500 / 24,000 / 33,000 blocks, devices in regions: 16 rows (3 stages) 0.86 / 0.83 / 0.94 / 0.98 /
+// 1.05, (8 stages) 0.95 / 0.96 / 1.04 / 1.02 / 1.09; 12 rows (7 stages) 0.96 / 0.97 / 1.07 / 1.09 / 1.17; 8 rows (5 stages) 0.98 /
+// 1.06 / 1.16 / 1.18 / 1.23; 2 rows 1.05 / 1.17 / 1.34 / 1.43 / 1.48.
+static bool four_blocks_a_wavefront(const dtfm_problem *pr, size_t blocks)
+{
+    return pr->D_dp <= 16 && blocks > (size_t)(pr->D_dp <= 6 ? 10240 : 1536 * pr->D_dp);
+}
 
 dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t rows, size_t hk_grid_cap, bool lean)
 {
@@ -1027,7 +1032,7 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         const int nb = (pr->D_dp + 15) / 16;
         if (rows > 0x7fffffffu) return DTFM_ERR_ARG;
         if (match_pairs > 0) {
-        if (nb <= 1 && rows * (size_t)match_pairs > MATCH16_MIN) {
+        if (four_blocks_a_wavefront(pr, rows * (size_t)match_pairs)) {
             hipLaunchKernelGGL(k_match16, dim3((unsigned)((rows + 3) / 4), (unsigned)match_pairs), dim3(DTFM_WAVE), 0, st, pr->W_code,
                                pr->rank_val, perm, N, pr->D_dp, n, b.ghat, rows, inc_j, inc_jp);
         } else {

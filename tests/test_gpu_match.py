@@ -1,8 +1,9 @@
-"""Matchings of blocks of at most 16 rows: four to a wavefront from some 10,000 blocks on, one to a wavefront below.
-Populations that leave the last wavefront with one, two and three candidates, all block sizes at the edges, weights with
+"""Matchings of blocks of at most 16 rows: four to a wavefront from 10,240 blocks on (1536 for each row from 7 rows on), one
+to a wavefront below. Populations that leave the last wavefront with one, two and three candidates, all block sizes at the edges, weights with
 many ties and without any, whole evaluations and the trials of the local search, against the oracle to the bit."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2206_01288_amd as dtfm
 import workloads
@@ -12,11 +13,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("ties", [0, 2, 40])
-@pytest.mark.parametrize("D_dp,D_pp,P", [(1, 4, 1709), (2, 3, 3415), (3, 9, 289), (7, 8, 367), (8, 5, 1027), (9, 12, 157),
-                                         (15, 6, 685), (16, 4, 1710), (16, 16, 87)])
+@pytest.mark.parametrize("D_dp,D_pp,P", [(1, 4, 1709), (2, 3, 3415), (3, 9, 289), (7, 8, 387), (8, 5, 1231), (9, 12, 213),
+                                         (15, 6, 1537), (16, 4, 4098), (16, 16, 207)])
 def test_four_blocks_to_a_wavefront(ties, D_dp, D_pp, P):
     N, pairs = D_dp * D_pp, D_pp * (D_pp - 1) // 2
-    assert P * pairs > 10240
+    assert P * pairs > max(10240, 1536 * D_dp)
     rng = np.random.default_rng(1000 * D_dp + D_pp + ties)
     lat = rng.uniform(1e-3, 0.1, (N, N)) if ties == 0 else rng.integers(1, ties + 1, (N, N)) * 0.01
     bw = 10.0 ** rng.uniform(7, 9, (N, N)) if ties == 0 else np.full((N, N), 1e9)
@@ -35,4 +36,53 @@ def test_four_blocks_to_a_wavefront(ties, D_dp, D_pp, P):
         rows_d = dev(perms)
         cost_d, _ = dtfm.local_search(g, rows_d, 2, dtfm.BEST4)
         assert np.array_equal(host(rows_d)[last], rows) and np.array_equal(host(cost_d)[last], want)
+    dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp,P", [(9, 12, 213), (16, 12, 373), (13, 16, 167), (16, 16, 207)])
+def test_four_blocks_to_a_wavefront_of_many_stages(D_dp, D_pp, P):
+    # every edge of the graphs themselves, and of trials that start from other graphs (2 D_pp - 3 blocks of a row; the
+    # graph of the accepted row carries them on)
+    N = D_dp * D_pp
+    rng = np.random.default_rng(D_dp)
+    lat, bw = rng.integers(1, 400, (N, N)) * 1e-4, np.full((N, N), 1e9)
+    lat, bw = np.triu(lat, 1) + np.triu(lat, 1).T, np.triu(bw, 1) + np.triu(bw, 1).T
+    np.fill_diagonal(bw, 1.0)
+    o, g = both(workloads.Workload("match", N, D_dp, D_pp, 1e7, 1e7, lat, bw, 0))
+    perms = workloads.random_population(P, N, seed=D_pp)
+    ghat, _ = dtfm.coarsened_graph(g, dev(perms))
+    ghat = host(ghat)
+    for p in np.r_[0:24, P - 24:P]:
+        assert np.array_equal(ghat[p], o.coarsen(perms[p])), p
+    many = np.concatenate([perms] * 6)
+    assert len(many) * (2 * D_pp - 3) > 1536 * D_dp
+    rows, want, _ = o.local_search(perms[-3:], 3, dtfm.KL)
+    rows_d = dev(many)
+    cost_d, _ = dtfm.local_search(g, rows_d, 3, dtfm.KL)
+    assert np.array_equal(host(rows_d)[-3:], rows) and np.array_equal(host(cost_d)[-3:], want)
+    dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp", [(12, 7), (16, 3)])
+@pytest.mark.parametrize("blocks", [10240, 1536 * 12, 1536 * 16])
+def test_no_jump_where_the_kernel_changes(D_dp, D_pp, blocks):
+    # one per cent more rows on the other side cost at most a tenth more
+    N, pairs = D_dp * D_pp, D_pp * (D_pp - 1) // 2
+    w = workloads.Workload("match", N, D_dp, D_pp, 1e8, 1e7, *workloads.network_regions(N // 4, 4, seed=1), 0)
+    g = dtfm.create_problem(w.latency, w.bandwidth, w.c_dp, w.c_pp, D_dp, D_pp)
+    below = blocks // pairs
+    perms = dev(workloads.random_population(below + below // 100 + 1, N, seed=2))
+    best = {}
+    for _ in range(8):
+        for P in (below, len(perms)):
+            rows, out = perms[:P], torch.empty(P, dtype=torch.float64, device="cuda")
+            dtfm.eval_population(g, rows, out)
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                dtfm.eval_population(g, rows, out)
+            b.record()
+            torch.cuda.synchronize()
+            best[P] = min(best.get(P, np.inf), a.elapsed_time(b))
+    assert best[len(perms)] <= 1.1 * best[below], best
     dtfm.destroy_problem(g)

@@ -88,7 +88,8 @@ __device__ __forceinline__ wave_ctx wave_setup(unsigned char *smem, const uint16
 }
 
 // a4 for one lane: the bottleneck matchings of the stage pairs (j1[0], j2[0]) and (j1[1], j2[1]) of the
-// candidate whose row is at pb, as two packed ranks.
+// candidate whose row is at pb, as two packed ranks. HALF: see match_rows.
+template <bool HALF>
 __device__ __forceinline__ uint32_t match_couple(const wave_ctx &cx, const unsigned char *pb, const int (&j1)[2],
                                                  const int (&j2)[2])
 {
@@ -99,7 +100,7 @@ __device__ __forceinline__ uint32_t match_couple(const wave_ctx &cx, const unsig
         coldev[h] = *reinterpret_cast<const uint2 *>(pb + 8 * j2[h]);   // devices of stage j2
     }
     uint32_t G[256];
-    match_rows<8, true>(cx.R, rowdev, coldev, G);
+    match_rows<8, HALF>(cx.R, rowdev, coldev, G);
     return G[255];
 }
 
@@ -189,7 +190,7 @@ __device__ __forceinline__ void eval_group(const wave_ctx &cx, double *__restric
         }
         uint32_t gfull;
         if (HALVES && halves) gfull = match_couple_halves(cx, wl + OFF_PB + mc * 64, j1, j2);
-        else gfull = match_couple(cx, wl + OFF_PB + mc * 64, j1, j2);
+        else gfull = match_couple<!INC || NC < 8>(cx, wl + OFF_PB + mc * 64, j1, j2);
         if (valid) {
             ghr16[mc * 28 + pair_index(j1[0], j2[0])] = (uint16_t)gfull;
             ghr16[mc * 28 + pair_index(j1[1], j2[1])] = (uint16_t)(gfull >> 16);

@@ -365,8 +365,10 @@ __device__ __forceinline__ double stage_datap(const double *Wdp, uint2 devs)
 // NROWS = 7, G[255 ^ (1 << c)] is the optimum of the 7 rows into all columns but c.
 // HALF: 1016 maxima and 448 minima (two at a time) for eight rows, where integers take 1016 and 769. Measured: one
 // evaluation of 1,048,576 candidates 1341 -> 1212 us, of 4096 11.4 -> 10.5 us, a search of 20 generations 1853 -> 1766 us.
-// The exhaustive search stays with the integers: with halves its compilation spills more (40.9 against 44 ms for 20
-// rounds of 4096 allocations).
+// Kernels that spill more registers with halves stay with the integers: the exhaustive search (20 rounds of 4096
+// allocations 40.9 against 44 ms) and the four-candidate search with 8 or 32 candidates a wavefront (56 spilled VGPRs
+// against 91 with 32; 8 rounds of 10,000 / 16,384 / 65,000 allocations 183 / 184 / 680 against 184 / 193 / 700 us with 8, 1,048,576: 10.22
+// against 10.23 ms with 32). With 4 candidates halves are faster (8,192 allocations 108 against 110 us).
 template <int NROWS, bool HALF>
 __device__ __forceinline__ void match_rows(const uint16_t *R, const uint2 (&rowdev)[2], const uint2 (&coldev)[2],
                                            uint32_t (&G)[256])

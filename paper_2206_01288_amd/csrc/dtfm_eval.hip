@@ -504,9 +504,9 @@ k_match(const uint16_t *__restrict__ Wcode, const uint32_t *__restrict__ Wrank, 
 // by the 16 lanes of its block and all four advance together. The steps are those of match_block, with one difference
 // that does not change the threshold reached: a turn lets two reached columns join instead of all of them, so that the
 // four searches stay in step. Codes are ranks here (N <= 256: at most 32,641 distinct weights), one solve is exact.
-// Measured, a whole evaluation: 3001 candidates of 7 stages of 12: 107 -> 84 us; 2000 of 9 stages of 5: 82 -> 55 us; 4096 of
-// 16 stages of 16: 1055 -> 822 us, of 8: 754 -> 535 us. What bounds it: the vector instructions of a turn and the LDS reads
-// and exchanges behind one another in it.
+// Measured, a whole evaluation: 3001 candidates of 7 stages of 12: 99.5 -> 77.9 us; 2000 of 9 stages of 5: 82 -> 55 us; 4096
+// of 16 stages of 16: 1055 -> 822 us, of 8: 754 -> 535 us. What bounds it: vector issue, 89 % of its slots on 16 stages of 16
+// (2,080 vector and 1,080 scalar instructions for four blocks).
 __device__ __forceinline__ uint32_t row16_min(uint32_t x)
 {
     x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));   // rotations inside 16 lanes

@@ -110,13 +110,14 @@ struct dtfm_tour_rule {
     }
     __host__ __device__ size_t rounds_of(size_t rows) const { return (rows + hk_grid - 1) / hk_grid; }
     // Whether the rounds that a search of the other rows saves are worth its time: 60 us of the usual graphs against one
-    // round from 14 stages on, two if some rows go to the dense recursion anyway, and three, five and nine rounds at 13, 12
-    // and 11 stages. Evaluations with 4 devices a stage, independent links and regions, by search (by the dense recursion), us:
+    // round from 14 stages on, and three, five and nine at 13, 12 and 11 stages. Where some rows go to the dense recursion
+    // anyway the others have not many more values and take up to 200 us: two rounds, three at 14 and five at 13 stages (768 rows of
+    // 14 stages of 16 devices, the paper's table, 520 us densely: 610 us with two rounds saved). Evaluations with 4 devices a stage, independent links and regions, by search (by the dense recursion), us:
     // 11 stages, 1024 rows 122, 182 (110), 2048: 137, 194 (200), 4096: 208, 255 (390); 12 stages, 512: 126, 125 (97), 1024:
     // 138, 137 (175), 2048: 174, 169 (347); 13 stages, 512: 153, 274 (172), 768: 157, 280 (240), 2048: 206, 313 (643).
     __host__ __device__ bool worth(int n, size_t rows, size_t few_rows) const
     {
-        const size_t spare = n < 14 ? 16u >> (n - 10) : few_rows > 0 ? 1 : 0;
+        const size_t spare = few_rows > 0 ? (n < 15 ? 32u >> (n - 10) : 1) : n < 14 ? 16u >> (n - 10) : 0;
         return rounds_of(rows) - rounds_of(few_rows) > spare;
     }
 };

@@ -263,7 +263,7 @@ def main():
                 "algorithmic_hbm_bytes_per_launch": (4 * N + 8) * P_big,
                 "kernel": "k_eval_fast64<32> (dtfm_eval_population)", "launch_candidates": P_big,
                 "launch_seconds": t_big, "launches_timed": 100, "ops_per_candidate": ops,
-                "frac_is": "ops of the chosen algorithms (DataP, subset-DP matching on packed 16-bit ranks, Held-Karp) "
+                "frac_is": "ops of the chosen algorithms (DataP, subset-DP matching on packed 16-bit ranks, two minima an operation, Held-Karp) "
                            "against the blended peak of that mix",
                 "algorithm_independent": {"ops_per_candidate": indep_ops, "achieved": indep_ops * P_big / t_big / 1e12,
                                           "peak": indep_peak, "unit": "Tops/s",

@@ -124,7 +124,7 @@ def test_config2_roofline_launch_size_sampled():
 
 
 def test_config4_full_population_every_row():
-    # the configured launch (1024 candidates, D_pp = 16: blocked Held-Karp, 16 x 16 matchings): every row against the oracle
+    # the configured launch (1024 candidates, D_pp = 16: pruned tours, 16 x 16 matchings): every row against the oracle
     w = workloads.config("C4")
     o, g = both(w)
     perms = workloads.random_population(1024, 256, seed=1)
@@ -138,7 +138,7 @@ def test_config4_full_population_every_row():
 
 
 def test_config5_population_every_row_of_256():
-    # 256 candidates of configuration 5 (64 x 64 matchings, sliced DataP, blocked Held-Karp): every row against the oracle
+    # 256 candidates of configuration 5 (64 x 64 matchings, DataP by device, pruned tours): every row against the oracle
     w = workloads.config("C5")
     o, g = both(w)
     perms = workloads.random_population(256, 1024, seed=1)
@@ -175,7 +175,7 @@ def test_odd_and_degenerate_shapes(D_dp, D_pp):
     N = D_dp * D_pp
     w = custom(N, D_dp, D_pp, seed=N + 1)
     o, g = both(w)
-    for P in (1, 67) + ((300,) if D_pp == 13 else ()):   # 300: more candidates than workgroups
+    for P in (1, 67) + ((300,) if D_pp == 13 else ()):   # 300: more candidates than workgroups of the blocked Held-Karp
         perms = workloads.random_population(P, N, seed=P)
         assert_costs_equal(host(dtfm.eval_population(g, dev(perms))), o.eval_population(perms))
 

@@ -20,7 +20,7 @@ def _problem(w):
 @pytest.mark.parametrize("name,shape,P1,P2", [
     ("C1", None, 300, 37),                    # general kernels, Held-Karp table in LDS
     ("custom", (36, 3, 12), 200, 9),          # blocked Held-Karp: exchange areas in the fixed scratch
-    ("C4", None, 160, 23),                    # D_pp = 16: few exchange areas, several candidates per workgroup
+    ("C4", None, 160, 23),                    # D_pp = 16: pruned tours; the few exchange areas: test_gpu_tour.py
     ("C5", None, 24, 5),                      # sliced DataP (zeroed scratch), 64 x 64 matchings
     ("C2", None, 5000, 100),                  # 64-device shape: no scratch at all
 ])

@@ -95,7 +95,7 @@ struct dtfm_tour_rule {
     size_t hk_grid;   // workgroups of the dense recursion
     int few;          // rows with 2 to `few` different edges go to the dense recursion, whose time a failed search would add to
     bool split;       // they are counted and put there before the search
-    int work;         // states the joint searches of a workgroup may price, about 22 a microsecond
+    int work;         // states the joint searches of a workgroup may price on graphs of at most 2 n values, about 22 a microsecond
     dtfm_tour_rule(const dtfm_problem *pr, size_t rows, size_t hk_grid) : hk_grid(hk_grid)
     {
         const int n = pr->D_pp;

@@ -181,9 +181,9 @@ __device__ __forceinline__ double lane_value(double x, int lane)   // lane: the 
     return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 
-// The number of different values among the edges of a graph (g(i, j): the edge), limit + 1 if there are more, by one
-// wavefront. The lanes hold the edges from stage i to stage i + k, k up to n / 2; a turn counts one value and strikes out
-// the edges that have it.
+// The number of different values among the edges of a graph (g(i, j): the edge), by one wavefront; beyond `limit` an
+// estimate, from the share of the edges that limit + 1 values take. The lanes hold the edges from stage i to stage i + k,
+// k up to n / 2; a turn counts one value and strikes out the edges that have it.
 template <typename Edge>
 __device__ __forceinline__ int edge_values(int lane, int n, int limit, Edge g)
 {
@@ -204,7 +204,8 @@ __device__ __forceinline__ int edge_values(int lane, int n, int limit, Edge g)
         left[0] &= ~__ballot(own[0] == v);
         left[1] &= ~__ballot(own[1] == v);
     }
-    return values;
+    const int edges = n * (n - 1) / 2, rest = __popcll(left[0]) + __popcll(left[1]);
+    return rest > 0 ? max(limit + 1, values * edges / (edges - rest)) : values;
 }
 
 // Upper bound, scale, potentials and root bound of candidate `grp` of the workgroup, by the 16 lanes of a row.
@@ -563,9 +564,11 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
             return WIDE;
         } else {
             if (!refined) {
-                // Tables too small at this threshold. The stage orders try better potentials, unless the graph has few
-                // values or the bound no gap left to close; Eq. 4 alone is cheaper by the dense recursion.
-                if (work < 0 || !RECORD || sm.values[cd] <= n / 2 || thr - root < 0x1p-18 * U) return DENSE;
+                // Tables too small at this threshold: better potentials, unless the graph has few values, the bound no gap
+                // left to close or the dense recursion takes less (up to 15 stages, where no order is asked for).
+                if (work < 0 || (!RECORD && n < 16) || sm.values[cd] <= (RECORD ? n / 2 : 2 * n) ||
+                    thr - root < 0x1p-18 * U)
+                    return DENSE;
                 refined = true;
                 __syncthreads();
                 if (tid < 64) {
@@ -654,7 +657,12 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
     for (int w = 0; w < WAVES; w++) {   // too wide for a quarter of the tables: all of them, one candidate at a time
         if (sm.state[w] != WIDE) continue;
         double Tw = 0.0;
-        const int s = work < 0 ? DENSE : tour_solve<WAVES, false>(sm, w, tid, n, work, Tw, tour_record());
+        // Graphs of more than 2 n values or so end well: one in some hundred takes long, none of those seen were left to the dense
+        // recursion, which would add its 525 us to a launch (1024 allocations of 1024 devices in regions: 1.46 and 1.97 ms).
+        const bool bounded = sm.values[w] <= 2 * n;
+        int budget = bounded ? work : INT32_MAX;
+        const int s = budget < 0 ? DENSE : tour_solve<WAVES, false>(sm, w, tid, n, budget, Tw, tour_record());
+        if (bounded) work = budget;
         if (w == wave) {
             state = s;
             T = Tw;

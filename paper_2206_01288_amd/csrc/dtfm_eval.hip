@@ -2,7 +2,8 @@
 //   k_weights     Sec. 2 symmetrisation + the per-link terms of Eqs. 2 and 3
 //   k_datap       Eq. 2 per stage and the max over stages (Sec. 3.2); for matrices beyond an XCD's L2
 //                 k_datap_sliced (by slice of devices) or k_positions + k_datap_rows + k_datap_reduce (by device)
-//   k_match       Eq. 3: bottleneck perfect matching of one stage pair per wavefront; k_match16: of four, when many and small
+//   k_match       Eq. 3, stages of at most 16 devices: bottleneck perfect matching of one stage pair per wavefront; k_match16: of
+//                 four, when there are many (larger stages: dtfm_match.hip)
 //   k_held_karp   Eq. 4: open-loop TSP over the coarsened graph, exact, by subset dynamic
 //                 programming; adds the two parts (Eq. 1); k_held_karp_blocked from 11 stages on
 //   k_trial_shortcut   trials of the local search that the coarsened graph settles without Eq. 4
@@ -237,16 +238,8 @@ __global__ void k_zero_f64(double *__restrict__ dst, size_t n)
 //
 // Lane c keeps its column of the block in registers for the steps whose row index is known at compile time
 // (1 and 2). For the search, where the row comes from a lane, the wavefront keeps the block in LDS,
-// s_E[r * 64 + c] (all lanes read one row: no bank conflicts); 8 KiB per wavefront, and the number of resident
-// wavefronts is what this latency-bound search lives on. Registers and LDS hold 16-bit codes, order-preserving
-// images of the ranks:
-//  - first solve: the entries are gathered from `Wcode`, 2 + (rank >> shift) with the `shift` that fits the
-//    problem's largest rank (0 up to 65,532 distinct weights), pad 0xffff: the result is the exact optimum when
-//    shift = 0, else the bucket of 2^shift ranks that holds it (a matching within a bucket exists iff one
-//    exists within the bucket's largest rank);
-//  - if the block holds more than one distinct rank of that bucket (looked up in `Wrank`, only by the lanes that
-//    hold an entry of the bucket), a second solve on 1 (ranks below the bucket: all "within"), 2 + rank - the
-//    bucket's first rank (inside), 0xffff (above: never needed) separates them.
+// s_E[r * 64 + c] (all lanes read one row: no bank conflicts). Registers and LDS hold codes, 2 + rank in 16 bits (N <= 256
+// here: at most 32,641 ranks), pad 0xffff.
 // dist carries, in its low 7 bits, the column whose matched row gave it (127: the inserted row), so relaxing is
 // one shift-OR and one unsigned minimum; a visited column parks that field in `parked` and holds dist = 0 from
 // then on, which no minimum changes. Lanes c >= D_dp hold the pad code and never take part.
@@ -279,15 +272,12 @@ __device__ __forceinline__ uint64_t dtfm_clear_bit(uint64_t m, int bit)
 
 #define DTFM_MATCH_ROOT 127u   // `via` field of a dist that comes from the inserted row itself
 
-// Steps 2 and 3 and the second solve for one block, by one wavefront. E: the lane's column as codes (pad 0xffff for the
-// rows and lanes outside the block); tile: room for the block's LDS copy, entry (row r, this lane) at tile[r * 64] (the
-// caller passes its lane's base). rank_of(r): the rank of the lane's entry in row r (looked up only inside the
-// optimum's bucket). Returns the optimum's rank, or 0xffffffff if a search fails (cannot happen for a finite block).
-template <int NB, typename RankOf>
-__device__ __forceinline__ uint32_t match_block(uint16_t *tile, uint32_t (&E)[16 * NB], int lane, bool active, int D_dp,
-                                                int shift0, RankOf rank_of)
+// All steps for one block, by one wavefront. E: the lane's column as codes (pad 0xffff for the rows and lanes outside the
+// block); tile: room for the block's LDS copy, entry (row r, this lane) at tile[r * 64] (the caller passes its lane's base).
+// Returns the optimum's rank, or 0xffffffff if a search fails (cannot happen for a finite block).
+__device__ __forceinline__ uint32_t match_block(uint16_t *tile, const uint32_t (&E)[16], int lane, bool active, int D_dp)
 {
-    constexpr int R = 16 * NB, RS = R - 16;   // rows below RS exist for every D_dp this instance is launched for
+    constexpr int R = 16;
     uint32_t colmin = 0xffffu;
 #pragma unroll
     for (int r = 0; r < R; r++) colmin = min(colmin, E[r]);
@@ -295,201 +285,116 @@ __device__ __forceinline__ uint32_t match_block(uint16_t *tile, uint32_t (&E)[16
     uint32_t theta = ~dtfm_wave_min_u32(active ? ~colmin : 0xffffffffu);   // the threshold, as a code
 
     const uint64_t allcols = D_dp >= 64 ? ~0ull : ((1ull << D_dp) - 1ull);
-    uint32_t base = 0u;              // second solve: first rank of the bucket
-    uint32_t result = 0xffffffffu;
-    for (int solve = 0; solve < 2; solve++) {
-        {
-            __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int r = 0; r < R; r++) tile[r * DTFM_WAVE] = (uint16_t)E[r];
-            __builtin_amdgcn_wave_barrier();   // one wavefront: its LDS accesses are executed in order
-        }
-        uint32_t thr = (theta << 7) | 127u;   // a key (code << 7 | via) is within theta iff key <= thr
+    for (int r = 0; r < R; r++) tile[r * DTFM_WAVE] = (uint16_t)E[r];
+    __builtin_amdgcn_wave_barrier();   // one wavefront: its LDS accesses are executed in order
+    uint32_t thr = (theta << 7) | 127u;   // a key (code << 7 | via) is within theta iff key <= thr
 
-        // step 2
-        uint64_t freecols = allcols, pending = 0ull;
-        int match_row = 0;   // row matched to this lane's column (meaningful when not free)
+    // step 2
+    uint64_t freecols = allcols, pending = 0ull;
+    int match_row = 0;   // row matched to this lane's column (meaningful when not free)
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            if (r < RS || r < D_dp) {
-                uint64_t m = __ballot(E[r] <= theta);
-                if (m == 0ull) {
-                    theta = dtfm_wave_min_u32(E[r]);
-                    thr = (theta << 7) | 127u;
-                    m = __ballot(E[r] <= theta);
-                }
-                m &= freecols;
-                if (m != 0ull) {
-                    const int c = dtfm_first_bit(m);
-                    freecols = dtfm_clear_bit(freecols, c);
-                    if (lane == c) match_row = r;
-                } else {
-                    pending |= 1ull << r;
-                }
+    for (int r = 0; r < R; r++) {
+        if (r < D_dp) {
+            uint64_t m = __ballot(E[r] <= theta);
+            if (m == 0ull) {
+                theta = dtfm_wave_min_u32(E[r]);
+                thr = (theta << 7) | 127u;
+                m = __ballot(E[r] <= theta);
+            }
+            m &= freecols;
+            if (m != 0ull) {
+                const int c = dtfm_first_bit(m);
+                freecols = dtfm_clear_bit(freecols, c);
+                if (lane == c) match_row = r;
+            } else {
+                pending |= 1ull << r;
             }
         }
+    }
 
-        // step 3
-        bool failed = false;
-        while (pending != 0ull) {
-            const int r0 = dtfm_first_bit(pending);
-            pending = dtfm_clear_bit(pending, r0);
-            uint32_t dist = ((uint32_t)tile[r0 * DTFM_WAVE] << 7) | DTFM_MATCH_ROOT;
-            uint32_t parked = 0u;
-            int cfin = -1;
-            uint64_t reach = __ballot(dist - 1u < thr);   // unvisited (dist != 0) and within theta
-            // every turn parks at least one column or ends the search: at most D_dp turns
-            for (int turn = 0; turn <= R; turn++) {
-                if (reach == 0ull) {
-                    // stuck: the smallest dist of an unvisited column; dist - 1 sends the visited ones (0) to the top
-                    const uint32_t k = dtfm_wave_min_u32(dist - 1u);
-                    if (k >= (0xffffu << 7) - 1u) break;   // no unvisited column with an entry of the block
-                    thr = (k + 1u) | 127u;
-                    reach = __ballot(dist - 1u < thr);
-                }
-                const uint64_t hit = reach & freecols;
-                if (hit != 0ull) {
-                    cfin = dtfm_first_bit(hit);
-                    break;
-                }
-                if (dist - 1u < thr) {
-                    parked = dist & 127u;
-                    dist = 0u;
-                }
-                do {   // the rows matched to the newly reached columns join the search, two per turn
-                    const int c0 = dtfm_first_bit(reach);
-                    reach = dtfm_clear_bit(reach, c0);
-                    const int c1 = max(dtfm_first_bit(reach), c0);   // none left: c0 once more
-                    reach = dtfm_clear_bit(reach, c1);
-                    const int m0 = __builtin_amdgcn_readlane(match_row, c0), m1 = __builtin_amdgcn_readlane(match_row, c1);
-                    const uint32_t w0 = ((uint32_t)tile[m0 * DTFM_WAVE] << 7) | (uint32_t)c0;
-                    const uint32_t w1 = ((uint32_t)tile[m1 * DTFM_WAVE] << 7) | (uint32_t)c1;
-                    dist = min(dist, min(w0, w1));
-                } while (reach != 0ull);
+    // step 3
+    bool failed = false;
+    while (pending != 0ull) {
+        const int r0 = dtfm_first_bit(pending);
+        pending = dtfm_clear_bit(pending, r0);
+        uint32_t dist = ((uint32_t)tile[r0 * DTFM_WAVE] << 7) | DTFM_MATCH_ROOT;
+        uint32_t parked = 0u;
+        int cfin = -1;
+        uint64_t reach = __ballot(dist - 1u < thr);   // unvisited (dist != 0) and within theta
+        // every turn parks at least one column or ends the search: at most D_dp turns
+        for (int turn = 0; turn <= R; turn++) {
+            if (reach == 0ull) {
+                // stuck: the smallest dist of an unvisited column; dist - 1 sends the visited ones (0) to the top
+                const uint32_t k = dtfm_wave_min_u32(dist - 1u);
+                if (k >= (0xffffu << 7) - 1u) break;   // no unvisited column with an entry of the block
+                thr = (k + 1u) | 127u;
                 reach = __ballot(dist - 1u < thr);
             }
-            if (cfin < 0) {
-                failed = true;
+            const uint64_t hit = reach & freecols;
+            if (hit != 0ull) {
+                cfin = dtfm_first_bit(hit);
                 break;
             }
-            // flip the path: column c takes the row of its predecessor column; the first column takes r0
-            const int via = (int)(dist == 0u ? parked : (dist & 127u));
-            int c = cfin;
-            for (int step = 0; step <= D_dp; step++) {  // a path has at most D_dp columns
-                const int pc = __builtin_amdgcn_readlane(via, c);
-                const int prow = __builtin_amdgcn_readlane(match_row, pc & 63);
-                if (lane == c) match_row = pc == (int)DTFM_MATCH_ROOT ? r0 : prow;
-                if (pc == (int)DTFM_MATCH_ROOT) break;
-                c = pc;
+            if (dist - 1u < thr) {
+                parked = dist & 127u;
+                dist = 0u;
             }
-            freecols = dtfm_clear_bit(freecols, cfin);
+            do {   // the rows matched to the newly reached columns join the search, two per turn
+                const int c0 = dtfm_first_bit(reach);
+                reach = dtfm_clear_bit(reach, c0);
+                const int c1 = max(dtfm_first_bit(reach), c0);   // none left: c0 once more
+                reach = dtfm_clear_bit(reach, c1);
+                const int m0 = __builtin_amdgcn_readlane(match_row, c0), m1 = __builtin_amdgcn_readlane(match_row, c1);
+                const uint32_t w0 = ((uint32_t)tile[m0 * DTFM_WAVE] << 7) | (uint32_t)c0;
+                const uint32_t w1 = ((uint32_t)tile[m1 * DTFM_WAVE] << 7) | (uint32_t)c1;
+                dist = min(dist, min(w0, w1));
+            } while (reach != 0ull);
+            reach = __ballot(dist - 1u < thr);
         }
-        theta = thr >> 7;   // >= 2: the first solve has no code below 2, the second no matching below its bucket
-        if (failed || theta < 2u) break;
-        if (solve > 0) {
-            result = base + theta - 2u;
+        if (cfin < 0) {
+            failed = true;
             break;
         }
-        if (shift0 == 0) {
-            result = theta - 2u;
-            break;
+        // flip the path: column c takes the row of its predecessor column; the first column takes r0
+        const int via = (int)(dist == 0u ? parked : (dist & 127u));
+        int c = cfin;
+        for (int step = 0; step <= D_dp; step++) {  // a path has at most D_dp columns
+            const int pc = __builtin_amdgcn_readlane(via, c);
+            const int prow = __builtin_amdgcn_readlane(match_row, pc & 63);
+            if (lane == c) match_row = pc == (int)DTFM_MATCH_ROOT ? r0 : prow;
+            if (pc == (int)DTFM_MATCH_ROOT) break;
+            c = pc;
         }
-        // The optimum lies in the bucket of 2^shift0 ranks with code theta. The block's entries with that code, as
-        // ranks (few: they are looked up one row at a time, and only by the lanes that hold one): if they are one
-        // rank, that is the optimum; else they are told apart by a second solve on 1 (below the bucket),
-        // 2 + rank - first rank of the bucket (inside), 0xffff (above it: never needed).
-        base = (theta - 2u) << shift0;
-        uint32_t lo = 0xffffffffu, hi = 0u;
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            const bool inside = E[r] == theta;
-            if (__ballot(inside) != 0ull) {   // wavefront-uniform
-                uint32_t code2 = E[r] < theta ? 1u : 0xffffu;
-                if (inside) {
-                    const uint32_t rk = rank_of(r);
-                    lo = min(lo, rk);
-                    hi = max(hi, rk);
-                    code2 = 2u + (rk - base);
-                }
-                E[r] = code2;
-            } else {
-                E[r] = E[r] < theta ? 1u : 0xffffu;
-            }
-        }
-        lo = dtfm_wave_min_u32(lo);
-        hi = ~dtfm_wave_min_u32(~hi);
-        if (lo == hi) {
-            result = lo;
-            break;
-        }
-        // theta of the second solve starts at the largest column minimum again
-        uint32_t cm = 0xffffu;
-#pragma unroll
-        for (int r = 0; r < R; r++) cm = min(cm, E[r]);
-        theta = ~dtfm_wave_min_u32(active ? ~cm : 0xffffffffu);
+        freecols = dtfm_clear_bit(freecols, cfin);
     }
-    return result;
-}
-
-// Stage pair number t of a launch (j1 < j2).
-__device__ __forceinline__ void match_pair(int t, int D_pp, int inc_j, int inc_jp, int &j1, int &j2)
-{
-    if (inc_j < 0) {
-        // t-th stage pair (j1 < j2) in lexicographic order
-        int rem = t;
-        j1 = 0;
-        while (rem >= D_pp - 1 - j1) {
-            rem -= D_pp - 1 - j1;
-            j1++;
-        }
-        j2 = j1 + 1 + rem;
-    } else {
-        // only the 2 D_pp - 3 pairs that contain stage inc_j or inc_jp (inc_j < inc_jp): (inc_j, k) for
-        // the D_pp - 1 stages k != inc_j, then (inc_jp, k) for the D_pp - 2 others
-        int a, k;
-        if (t < D_pp - 1) {
-            a = inc_j;
-            k = t + (t >= inc_j ? 1 : 0);
-        } else {
-            a = inc_jp;
-            k = t - (D_pp - 1);
-            k += k >= inc_j ? 1 : 0;
-            k += k >= inc_jp ? 1 : 0;
-        }
-        j1 = a < k ? a : k;
-        j2 = a < k ? k : a;
-    }
+    theta = thr >> 7;
+    return failed || theta < 2u ? 0xffffffffu : theta - 2u;
 }
 
 // One wavefront (= one workgroup) per (candidate, stage pair): the lane gathers its column of the block from the
 // table of codes, 2 bytes an entry (pad 0xffff outside the block), and keeps the block's LDS copy as s_E[r * 64 + c].
-template <int NB>  // number of 16-row blocks: D_dp <= 16 * NB
-__global__ void __launch_bounds__(DTFM_WAVE) __attribute__((amdgpu_waves_per_eu(5)))
-k_match(const uint16_t *__restrict__ Wcode, const uint32_t *__restrict__ Wrank, const double *__restrict__ rank_val, int shift0,
-        const int32_t *__restrict__ perm, int N, int D_dp, int D_pp,
-        double *__restrict__ ghat, int inc_j, int inc_jp)
+__global__ void __launch_bounds__(DTFM_WAVE)
+k_match(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_val, const int32_t *__restrict__ perm, int N, int D_dp,
+        int D_pp, double *__restrict__ ghat, int inc_j, int inc_jp)
 {
-    constexpr int R = 16 * NB, RS = R - 16;
-    extern __shared__ uint16_t s_E[];   // R x 64 codes
+    __shared__ uint16_t s_E[16 * DTFM_WAVE];
     const int lane = threadIdx.x;
     const bool active = lane < D_dp;
     const size_t p = blockIdx.x;   // candidate
-    const int t = (int)blockIdx.y; // stage pair
     int j1, j2;
-    match_pair(t, D_pp, inc_j, inc_jp, j1, j2);
+    dtfm_match_pair((int)blockIdx.y, D_pp, inc_j, inc_jp, j1, j2);
     const int32_t *row = perm + p * N;
     const int32_t *Ca = row + j1 * D_dp;   // wavefront-uniform: read through the scalar cache
     const uint32_t coldev = active ? (uint32_t)row[j2 * D_dp + lane] : 0u;
-    uint32_t E[R];
+    uint32_t E[16];
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const bool real = r < RS || r < D_dp;
-        const uint32_t v = Wcode[(uint32_t)Ca[real ? r : 0] * (uint32_t)N + coldev];
-        E[r] = (active && real) ? v : 0xffffu;
+    for (int r = 0; r < 16; r++) {
+        const uint32_t v = Wcode[(uint32_t)Ca[r < D_dp ? r : 0] * (uint32_t)N + coldev];
+        E[r] = (active && r < D_dp) ? v : 0xffffu;
     }
-    const uint32_t result = match_block<NB>(s_E + lane, E, lane, active, D_dp, shift0, [&](int r) {
-        return Wrank[(uint32_t)Ca[r] * (uint32_t)N + coldev];
-    });
+    const uint32_t result = match_block(s_E + lane, E, lane, active, D_dp);
     if (lane == 0) {
         const double v = result == 0xffffffffu ? INFINITY : rank_val[result];
         double *G = ghat + p * D_pp * D_pp;
@@ -540,7 +445,7 @@ k_match16(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_va
     const size_t p = (size_t)blockIdx.x * 4 + (size_t)(lane >> 4);
     const bool have = p < P;
     int j1, j2;
-    match_pair((int)blockIdx.y, D_pp, inc_j, inc_jp, j1, j2);
+    dtfm_match_pair((int)blockIdx.y, D_pp, inc_j, inc_jp, j1, j2);
     const bool active = have && c < D_dp;
     const int32_t *row = perm + (have ? p : 0) * N;
     const uint32_t rowbase = active ? (uint32_t)row[j1 * D_dp + c] * (uint32_t)N : 0u;
@@ -1029,18 +934,18 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     if (pr->npairs > 0) {
         // trial rows that differ from their current rows inside one stage only (inc_j = inc_jp) keep every edge
         const int match_pairs = inc_j >= 0 ? (inc_j == inc_jp ? 0 : 2 * n - 3) : pr->npairs;
-        const int nb = (pr->D_dp + 15) / 16;
         if (rows > 0x7fffffffu) return DTFM_ERR_ARG;
         if (match_pairs > 0) {
-        if (four_blocks_a_wavefront(pr, rows * (size_t)match_pairs)) {
+        if (pr->D_dp > 16) {
+            const int rc = dtfm_match_bits_enqueue(pr, perm, rows, match_pairs, b.ghat, inc_j, inc_jp, st);
+            if (rc != DTFM_OK) return rc;
+        } else if (four_blocks_a_wavefront(pr, rows * (size_t)match_pairs)) {
             hipLaunchKernelGGL(k_match16, dim3((unsigned)((rows + 3) / 4), (unsigned)match_pairs), dim3(DTFM_WAVE), 0, st, pr->W_code,
                                pr->rank_val, perm, N, pr->D_dp, n, b.ghat, rows, inc_j, inc_jp);
         } else {
-            auto kern = nb <= 1 ? k_match<1> : nb == 2 ? k_match<2> : nb == 3 ? k_match<3> : k_match<4>;
             // one wavefront per (candidate, stage pair)
-            hipLaunchKernelGGL(kern, dim3((unsigned)rows, (unsigned)match_pairs), dim3(DTFM_WAVE),
-                               (size_t)16 * nb * DTFM_WAVE * sizeof(uint16_t), st, pr->W_code, pr->W_rank, pr->rank_val,
-                               pr->rank_shift, perm, N, pr->D_dp, n, b.ghat, inc_j, inc_jp);
+            hipLaunchKernelGGL(k_match, dim3((unsigned)rows, (unsigned)match_pairs), dim3(DTFM_WAVE), 0, st, pr->W_code, pr->rank_val,
+                               perm, N, pr->D_dp, n, b.ghat, inc_j, inc_jp);
         }
         DTFM_HIP(hipGetLastError());
         }

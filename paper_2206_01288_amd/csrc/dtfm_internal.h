@@ -32,6 +32,14 @@ struct dtfm_layer_off {
     int off[DTFM_MAX_DPP + 2];  // off[k] = first index of the subsets of popcount k; off[n+1] = end
 };
 
+// Ranks of the pipeline weights in base 127 (dtfm_match.hip): entry (d, d') of digit q is code[(q * N + d) * N + d'].
+struct dtfm_digits {
+    uint8_t *code;     // device
+    double *first;     // device: the smallest weight of every leading digit, 128 with +inf behind the last; the allocation
+    int levels;        // digits of a rank
+    int top[3];        // largest value of each
+};
+
 struct dtfm_problem {
     int N, D_dp, D_pp, npairs;
     int device;
@@ -39,10 +47,10 @@ struct dtfm_problem {
     double *W_dp;           // device, N*N
     double *W_pp;           // device, N*N
     uint32_t *hk_subsets;   // device, 2^D_pp - 1 subsets ordered by (popcount, value)
-    uint32_t *W_rank;       // device, N*N: dense rank of W_pp[d][d'] among all entries (general shapes)
-    uint16_t *W_code;       // device, N*N: 2 + (rank >> rank_shift), the codes of the matching kernel's first solve
-    int rank_shift;         // smallest shift with which the codes stay below 0xffff
+    uint32_t *W_rank;       // device, N*N: dense rank of W_pp[d][d'] among all entries (stages of more than 16 devices)
+    uint16_t *W_code;       // device, N*N: 2 + rank (stages of at most 16 devices, N <= 256)
     double *rank_val;       // device: rank -> weight
+    dtfm_digits digits;     // stages of more than 16 devices
     int weights;            // different entries of W_pp
     dtfm_layer_off hk_off;
     char *scratch;          // device arena, grown on demand
@@ -143,6 +151,40 @@ int dtfm_eval_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int
 // inc_j < inc_jp (inc_j < 0: plain evaluation): only the edges of those two stages are matched again
 int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int32_t *perm, size_t rows,
                           double *cost, int inc_j, int inc_jp, hipStream_t st, const dtfm_trial_ref *ref = nullptr);
+// Eq. 3 for stages of more than 16 devices (dtfm_match.hip): the edges of all `pairs` stage pairs, or of those that contain
+// inc_j or inc_jp (inc_j >= 0: ghat holds the edges from before the swap), into ghat; prepare: the digit tables
+int dtfm_match_prepare(dtfm_problem *pr);
+int dtfm_match_bits_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t rows, int pairs, double *ghat, int inc_j, int inc_jp,
+                            hipStream_t st);
+// Stage pair number t of a launch (j1 < j2).
+__device__ __forceinline__ void dtfm_match_pair(int t, int D_pp, int inc_j, int inc_jp, int &j1, int &j2)
+{
+    if (inc_j < 0) {
+        // t-th stage pair (j1 < j2) in lexicographic order
+        int rem = t;
+        j1 = 0;
+        while (rem >= D_pp - 1 - j1) {
+            rem -= D_pp - 1 - j1;
+            j1++;
+        }
+        j2 = j1 + 1 + rem;
+    } else {
+        // only the 2 D_pp - 3 pairs that contain stage inc_j or inc_jp (inc_j < inc_jp): (inc_j, k) for
+        // the D_pp - 1 stages k != inc_j, then (inc_jp, k) for the D_pp - 2 others
+        int a, k;
+        if (t < D_pp - 1) {
+            a = inc_j;
+            k = t + (t >= inc_j ? 1 : 0);
+        } else {
+            a = inc_jp;
+            k = t - (D_pp - 1);
+            k += k >= inc_j ? 1 : 0;
+            k += k >= inc_jp ? 1 : 0;
+        }
+        j1 = a < k ? a : k;
+        j2 = a < k ? k : a;
+    }
+}
 // Eq. 4 by pruned subset recursion (dtfm_tour.hip): cost and b.pp of the rows (with list: list[0 .. b.count[0])); appends
 // the rows it cannot settle to b.dense, b.count[1] of them. D_pp from 11 to 16.
 int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t rows, double *cost, const int32_t *list,

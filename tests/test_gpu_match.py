@@ -86,3 +86,34 @@ def test_no_jump_where_the_kernel_changes(D_dp, D_pp, blocks):
             best[P] = min(best.get(P, np.inf), a.elapsed_time(b))
     assert best[len(perms)] <= 1.1 * best[below], best
     dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp,P", [(17, 3, 9), (31, 4, 40), (32, 3, 700), (33, 4, 9), (47, 3, 40), (63, 4, 3), (64, 4, 40),
+                                         (64, 2, 900)])
+@pytest.mark.parametrize("kind", ["equal", "few", "thousand", "all", "near"])
+def test_blocks_of_more_than_16_rows(kind, D_dp, D_pp, P):
+    # ranks of one digit (2 and 61 weights), two (1000) and three (16,130 and more); near: the blocks between two halves of
+    # the network hold weights of neighbouring ranks only, so that columns hold many entries of the optimum's leading digit
+    N = D_dp * D_pp
+    rng = np.random.default_rng(100 * D_dp + D_pp)
+    lat = {"equal": np.full((N, N), 0.01), "few": rng.integers(1, 62, (N, N)) * 1e-3,
+           "thousand": rng.integers(1, 1001, (N, N)) * 1e-4}.get(kind, rng.uniform(1e-3, 0.1, (N, N)))
+    if kind == "near":
+        far = (np.arange(N)[:, None] < N // 2) != (np.arange(N)[None, :] < N // 2)
+        lat = np.where(far, 0.05 + 1e-7 * rng.uniform(0.0, 1.0, (N, N)), lat)
+    lat = np.triu(lat, 1) + np.triu(lat, 1).T
+    bw = np.full((N, N), 1e9)
+    o, g = both(workloads.Workload("match", N, D_dp, D_pp, 1e7, 1e7, lat, bw, 0))
+    perms = workloads.random_population(P, N, seed=D_pp)
+    perms[0] = np.arange(N)              # stages that lie in one half each
+    perms[1] = np.arange(N)[::-1]
+    ghat = host(dtfm.coarsened_graph(g, dev(perms))[0])
+    some = np.r_[0:min(P, 6), max(P - 3, 0):P]
+    for p in some:
+        assert np.array_equal(ghat[p], o.coarsen(perms[p])), p
+    if D_pp > 2:                          # trials: the 2 D_pp - 3 blocks of a round's two stages
+        rows, want, _ = o.local_search(perms[some], 3, dtfm.KL)
+        rows_d = dev(perms)
+        cost_d, _ = dtfm.local_search(g, rows_d, 3, dtfm.KL)
+        assert np.array_equal(host(rows_d)[some], rows) and np.array_equal(host(cost_d)[some], want)
+    dtfm.destroy_problem(g)

@@ -379,8 +379,9 @@ __device__ __forceinline__ double wpp(const wave_ctx &cx, uint32_t a, uint32_t b
 
 // The round's proposal for every candidate slot (Sec. 3.4, "Improving Local Search Strategy"): the fastest
 // link inside stage j and inside stage jp of the current row, and of the four swaps of their end points
-// the one of largest Gain; its two positions (first < second) go to prop[2 c], prop[2 c + 1].
-template <int NC>
+// the one of largest Gain; its two positions (first < second) go to prop[2 c], prop[2 c + 1]. SHARED: one current row for
+// all slots, j and jp those of the lane's slot.
+template <int NC, bool SHARED = false>
 __device__ __forceinline__ void propose_gain4(const wave_ctx &cx, const unsigned char *pbcur, unsigned char *prop, int j,
                                               int jp)
 {
@@ -394,7 +395,7 @@ __device__ __forceinline__ void propose_gain4(const wave_ctx &cx, const unsigned
         // ---- proposal for candidate slot 4 * pass + lane / 16 by its 16 lanes: registers and
         // lane exchanges only, apart from the table gathers ----
         const int pslot = 4 * pass + (lane >> 4);
-        const unsigned char *pc = pbcur + pslot * 64;
+        const unsigned char *pc = pbcur + (SHARED ? 0 : pslot * 64);
         const uint2 cdev[2] = {*reinterpret_cast<const uint2 *>(pc + Cj), *reinterpret_cast<const uint2 *>(pc + Cjp)};
         int slot[2][2];
 #pragma unroll
@@ -653,6 +654,316 @@ k_ls_gain4_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_
     }
 }
 
+// ---- Launches of few allocations: one per workgroup, and the rounds of its local search several at a time
+// Most proposals are rejected, and a round after a rejected one starts from the same row. So the next eight rounds are
+// proposed and priced together, as eight trial rows of the current one, and the first that is cheaper is accepted; the rounds
+// behind it are proposed again from the new row. What each round compares is what it compares one at a time. A pass is as long as
+// one round alone (a wavefront prices four rows in the time of one): two wavefronts take four rounds each, a third the DataP of
+// the trial rows, and in the first pass a fourth prices the row itself. Half of the
+// rounds are accepted in a search from random rows: 4.5 passes for eight rounds. 200 generations of one offspring: 14.7 -> 7.65 ms.
+constexpr int AHEAD = 8;
+constexpr int SP_CUR = 0;                                // u8 [64]: current row
+constexpr int SP_PB = SP_CUR + 64;                       // u8 [AHEAD][64]: trial rows
+constexpr int SP_PROP = SP_PB + AHEAD * 64;              // u8 [AHEAD][2]: proposed positions
+constexpr int SP_GHR = SP_PROP + AHEAD * 2;              // u16 [AHEAD][28]: the trials' edges of the round's two stages
+constexpr int SP_GHRCUR = SP_GHR + AHEAD * 28 * 2;       // u16 [28]
+constexpr int SP_PP = (SP_GHRCUR + 28 * 2 + 7) / 8 * 8;  // double [AHEAD]
+constexpr int SP_DP = SP_PP + AHEAD * 8;                 // double [AHEAD]
+constexpr int SP_COST = SP_DP + AHEAD * 8;               // double: cost of the current row
+constexpr int SP_DPCUR = SP_COST + 8;                    // double: its DataP
+constexpr int SP_MK = SP_DPCUR + 8;
+constexpr int SP_BYTES = (SP_MK + mk_bytes(4) + 15) / 16 * 16;
+constexpr int SP_AT = LDS_TABLES + LDS_WDP_BYTES;
+constexpr int SP_THREADS = 256;
+constexpr int STEADY_MAX_P = 4096;                       // 40 KiB of costs and row numbers
+static_assert(SP_AT + SP_BYTES + STEADY_MAX_P * 10 + 64 <= 160 * 1024, "LDS budget of a CU");
+static_assert(SP_PB % 8 == 0 && SP_GHR % 4 == 0, "rows are read 8 bytes at a time");
+
+// DataP of the row at `row`, by the 8 lanes that share its slot
+__device__ __forceinline__ double row_datap(const wave_ctx &cx, const unsigned char *row)
+{
+    double dp = stage_datap(cx.Wdp, *reinterpret_cast<const uint2 *>(row + 8 * cx.hv));
+    dp = fmax(dp, dpp_move<DPP_XOR1>(dp));
+    dp = fmax(dp, dpp_move<DPP_XOR2>(dp));
+    return fmax(dp, dpp_move<DPP_HALF_MIRROR>(dp));
+}
+
+// Prices the row at SP_CUR and carries it through the rounds; the result stays at SP_CUR and SP_COST. applied: the row's moves,
+// or null. By the whole workgroup, the row visible to it; ends with a barrier.
+__device__ __forceinline__ void search_ahead(const wave_ctx &cx, unsigned char *sp, int moves, int64_t *applied)
+{
+    const int lane = cx.lane, wave = threadIdx.x >> 6;
+    unsigned char *cur = sp + SP_CUR, *pb = sp + SP_PB, *prop = sp + SP_PROP;
+    uint16_t *ghr = reinterpret_cast<uint16_t *>(sp + SP_GHR), *ghrcur = reinterpret_cast<uint16_t *>(sp + SP_GHRCUR);
+    double *pp = reinterpret_cast<double *>(sp + SP_PP), *dp = reinterpret_cast<double *>(sp + SP_DP);
+    double *cost = reinterpret_cast<double *>(sp + SP_COST), *dpcur = reinterpret_cast<double *>(sp + SP_DPCUR);
+    const int hc = (lane >> 3) & 3;
+    const bool relabel = lane >= 32;   // see hk_registers
+    const int v = relabel ? hk_swap01(cx.hv) : cx.hv;
+    int r = 0;
+    bool first = true;
+    do {
+        const int k = min(AHEAD, moves - r);   // rounds of this pass; zero only in the first
+        const bool trial = wave < 2 && 4 * wave < k;
+        if (trial) {
+            int j, jp;
+            pair8_decode(min(r + 4 * wave + (lane >> 4), moves - 1) % 28, j, jp);
+            propose_gain4<4, true>(cx, cur, prop + 8 * wave, j, jp);
+            WAVE_LDS_SYNC();
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const int s = 4 * wave + c, ta = prop[2 * s], tb = prop[2 * s + 1];
+                pb[s * 64 + lane] = cur[lane == ta ? tb : (lane == tb ? ta : lane)];
+            }
+        }
+        __syncthreads();
+        if (trial || (wave == 3 && first)) {
+            // lanes 2 t, 2 t + 1 share a couple of stage pairs: the 7 of the round's stages for each slot, or all 14 of the row
+            const int per = trial ? 7 : 14;
+            int t = lane >> 1;
+            const bool valid = t < 28 && !(lane & 1) && (trial || t < 14);
+            if (t >= 28) t = 27;   // idle lanes repeat the last item and write nothing
+            const int s = trial ? 4 * wave + t / per : 0, q = t % per;
+            int sj = 0, sjp = 0, j1[2], j2[2];
+            if (trial) pair8_decode(min(r + s, moves - 1) % 28, sj, sjp);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                if (trial) {
+                    // changed pair number e = 0..12: (sj, x) for the 7 stages x != sj, then (sjp, x) for the 6 others
+                    const int e = 2 * q + h < 12 ? 2 * q + h : 12;
+                    int a = sj, x = e + (e >= sj ? 1 : 0);
+                    if (e >= 7) {
+                        a = sjp;
+                        x = e - 7;
+                        x += x >= sj ? 1 : 0;
+                        x += x >= sjp ? 1 : 0;
+                    }
+                    j1[h] = a < x ? a : x;
+                    j2[h] = a < x ? x : a;
+                } else {
+                    pair8_decode(2 * q + h, j1[h], j2[h]);
+                }
+            }
+            const uint32_t g = match_couple_halves(cx, trial ? pb + s * 64 : cur, j1, j2);
+            if (valid) {
+                uint16_t *to = trial ? ghr + s * 28 : ghrcur;
+                to[pair_index(j1[0], j2[0])] = (uint16_t)g;
+                to[pair_index(j1[1], j2[1])] = (uint16_t)(g >> 16);
+            }
+        } else if (wave == 2) {
+            const double x = row_datap(cx, pb + (lane >> 3) * 64);   // rows of rounds beyond k: never looked at
+            if (cx.hv == 0) dp[lane >> 3] = x;
+            if (first) {
+                const double y = row_datap(cx, cur);
+                if (lane == 0) *dpcur = y;
+            }
+        }
+        __syncthreads();
+        if (trial || (wave == 3 && first)) {
+            const int s = 4 * wave + hc;
+            int sj = -1, sjp = -1;
+            if (trial) pair8_decode(min(r + s, moves - 1) % 28, sj, sjp);
+            double G[8];
+            G[0] = 0.0;
+#pragma unroll
+            for (int d = 1; d < 8; d++) {
+                const int u = v ^ (relabel ? hk_swap01(d) : d);
+                const int pi = pair_index(u < v ? u : v, u < v ? v : u);
+                const bool again = trial && (u == sj || u == sjp || v == sj || v == sjp);
+                G[d] = cx.rank_val[*(again ? ghr + s * 28 + pi : ghrcur + pi)];
+            }
+            const double x = hk_registers<true>(G, lane);
+            if (cx.hv == 0 && lane < 32) {
+                if (trial) pp[s] = x;
+                else if (lane == 0) *cost = __dadd_rn(*dpcur, x);
+            }
+        }
+        __syncthreads();
+        // the first round that is cheaper is accepted
+        const double now = *cost;
+        int take = k;
+        double best = 0.0;
+        for (int s = k - 1; s >= 0; s--) {
+            const double x = __dadd_rn(dp[s], pp[s]);
+            if (x < now) {
+                take = s;
+                best = x;
+            }
+        }
+        if (applied != nullptr && wave == 1 && lane < k && lane <= take) {
+            const long long ta = prop[2 * lane], tb = prop[2 * lane + 1];
+            applied[r + lane] = lane == take ? ta * NDEV - ta * (ta + 1) / 2 + (tb - ta - 1) : -1ll;
+        }
+        first = false;
+        __syncthreads();
+        if (take < k) {
+            if (wave == 0) {
+                int sj, sjp;
+                pair8_decode((r + take) % 28, sj, sjp);
+                cur[lane] = pb[take * 64 + lane];
+                int a, b;
+                pair8_decode(lane < 28 ? lane : 27, a, b);
+                if (lane < 28 && (a == sj || a == sjp || b == sj || b == sjp)) ghrcur[lane] = ghr[take * 28 + lane];
+                if (lane == 0) *cost = best;
+            }
+            __syncthreads();
+        }
+        r += take < k ? take + 1 : k;
+    } while (r < moves);
+}
+
+__device__ __forceinline__ wave_ctx ahead_setup(unsigned char *smem, const uint16_t *rank_tab, const double *rank_val,
+                                                const double *W_dp, const double *W_pp)
+{
+    wave_ctx cx;
+    cx.lane = threadIdx.x & 63;
+    cx.hv = cx.lane & 7;
+    cx.R = reinterpret_cast<const uint16_t *>(smem);
+    cx.rank_val = reinterpret_cast<const double *>(smem + LDS_RANK_BYTES);
+    cx.Wdp = reinterpret_cast<const double *>(smem + LDS_RANK_BYTES + LDS_RVAL_BYTES);
+    cx.Wpp = reinterpret_cast<const double *>(smem + LDS_TABLES);
+    cx.wl = smem + SP_AT;
+    stage_tables<true>(smem, rank_tab, rank_val, W_dp);
+#pragma unroll 8
+    for (int i = threadIdx.x; i < NDEV * NDEV / 2; i += blockDim.x)
+        reinterpret_cast<double2 *>(smem + LDS_TABLES)[i] = reinterpret_cast<const double2 *>(W_pp)[i];
+    return cx;
+}
+
+template <bool MAKE>
+__global__ void __launch_bounds__(SP_THREADS)
+k_ls_ahead_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_pp, const uint16_t *__restrict__ rank_tab,
+                  const double *__restrict__ rank_val, int32_t *__restrict__ perm, size_t P, int moves, double *__restrict__ cost,
+                  int64_t *__restrict__ applied, dtfm_offspring_src src)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char *sp = smem + SP_AT;
+    const size_t p = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    parent_rows par = {};
+    if (MAKE && wave == 0) par = load_parents4(src, p, P, lane);
+    const wave_ctx cx = ahead_setup(smem, rank_tab, rank_val, W_dp, W_pp);
+    if (wave == 0) {
+        if (MAKE) {   // four rows from p on, of which the first is this workgroup's
+            make_offspring4(cx, src, par, p, P, sp + SP_PB, sp + SP_MK);
+            sp[SP_CUR + lane] = sp[SP_PB + lane];
+        } else {
+            sp[SP_CUR + lane] = (unsigned char)perm[p * NDEV + lane];
+        }
+    }
+    __syncthreads();
+    search_ahead(cx, sp, moves, applied != nullptr ? applied + p * (size_t)moves : nullptr);
+    if (threadIdx.x < 64) perm[p * NDEV + lane] = sp[SP_CUR + lane];
+    if (threadIdx.x == 0) cost[p] = *reinterpret_cast<const double *>(sp + SP_COST);
+}
+
+// ---- Sec. 3.4's loop with one offspring a generation, `generations` of them in one launch of one workgroup
+// A generation's launches for the offspring, its search and two for the ranking wait for each other; here the costs in rank order and the
+// rows they belong to (order) stay in LDS, the offspring takes the row of the member that it displaces, and the rows are put in
+// order when the last generation is done. sorted: cost and order hold a state of an earlier launch; else they are the
+// costs of the rows as they lie, which generation src.g's parents are drawn from by position before they are ranked.
+__global__ void __launch_bounds__(SP_THREADS)
+k_steady_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_pp, const uint16_t *__restrict__ rank_tab,
+                const double *__restrict__ rank_val, int32_t *pop, double *__restrict__ cost, int32_t *__restrict__ order,
+                int sorted, int generations, int moves, double *__restrict__ trace, dtfm_offspring_src src)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char *sp = smem + SP_AT;
+    const int P = src.P, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double *key = reinterpret_cast<double *>(smem + SP_AT + SP_BYTES);
+    uint16_t *at = reinterpret_cast<uint16_t *>(key + P);
+    __shared__ int before;
+    const wave_ctx cx = ahead_setup(smem, rank_tab, rank_val, W_dp, W_pp);
+    for (int i = tid; i < P; i += SP_THREADS) {
+        key[i] = cost[i];
+        at[i] = (uint16_t)(sorted ? order[i] : i);
+    }
+    __syncthreads();
+    for (int g = 0; g < generations; g++, src.g++) {
+        if (wave == 0) {
+            const philox_out sel = philox4x32_10(0u, 0u, src.g, STREAM_SELECT, src.k0, src.k1);
+            const int32_t *par1 = pop + (size_t)at[randint(sel.w[0], (uint32_t)P)] * NDEV;
+            const int32_t *par2 = pop + (size_t)at[randint(sel.w[1], (uint32_t)P)] * NDEV;
+            parent_rows par;
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                par.d1[i] = par1[(lane & 15) + 16 * i];
+                par.d2[i] = par2[(lane & 15) + 16 * i];
+            }
+            make_offspring4(cx, src, par, 0, 1, sp + SP_PB, sp + SP_MK);
+            sp[SP_CUR + lane] = sp[SP_PB + lane];
+        }
+        __syncthreads();
+        search_ahead(cx, sp, moves, nullptr);
+        const double c = *reinterpret_cast<const double *>(sp + SP_COST);
+        constexpr int EACH = STEADY_MAX_P / SP_THREADS;
+        double kk[EACH];
+        int ka[EACH], kr[EACH];
+        if (!sorted) {   // rank under (cost, position)
+#pragma unroll
+            for (int e = 0; e < EACH; e++) {
+                const int i = tid + e * SP_THREADS;
+                kr[e] = 0;
+                if (i >= P) continue;
+                kk[e] = key[i];
+                for (int j = 0; j < P; j++) kr[e] += key[j] < kk[e] || (key[j] == kk[e] && j < i) ? 1 : 0;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < EACH; e++)
+                if (tid + e * SP_THREADS < P) {
+                    key[kr[e]] = kk[e];
+                    at[kr[e]] = (uint16_t)(tid + e * SP_THREADS);
+                }
+            sorted = 1;
+        }
+        if (tid == 0) before = 0;
+        __syncthreads();
+        // members with a cost up to the offspring's stay before it; the last one goes if there is another behind
+        int n = 0;
+        for (int i = tid; i < P; i += SP_THREADS) n += key[i] <= c ? 1 : 0;
+        if (n != 0) atomicAdd(&before, n);
+        __syncthreads();
+        const int pos = before;
+        if (pos < P) {
+            const int slot = at[P - 1];
+#pragma unroll
+            for (int e = 0; e < EACH; e++) {
+                const int i = tid + e * SP_THREADS;
+                if (i < pos || i >= P - 1) continue;
+                kk[e] = key[i];
+                ka[e] = at[i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < EACH; e++) {
+                const int i = tid + e * SP_THREADS;
+                if (i < pos || i >= P - 1) continue;
+                key[i + 1] = kk[e];
+                at[i + 1] = (uint16_t)ka[e];
+            }
+            if (tid < 64) pop[(size_t)slot * NDEV + lane] = sp[SP_CUR + lane];
+            if (tid == 0) {
+                key[pos] = c;
+                at[pos] = (uint16_t)slot;
+            }
+        }
+        __syncthreads();
+        if (tid == 0) trace[g] = key[0];
+    }
+    for (int i = tid; i < P; i += SP_THREADS) {
+        cost[i] = key[i];
+        order[i] = at[i];
+    }
+}
+
+// row i of `to` = row order[i] of `from` (order null: row i)
+__global__ void k_rows_in_order(const int32_t *__restrict__ from, const int32_t *__restrict__ order, int32_t *__restrict__ to)
+{
+    const size_t i = blockIdx.x, r = order != nullptr ? (size_t)order[i] : i;
+    to[i * NDEV + threadIdx.x] = from[r * NDEV + threadIdx.x];
+}
+
 // rank of every W_pp entry among all off-diagonal entries (number of strictly smaller ones): equal
 // weights get equal ranks, the order is preserved, and N*N <= 4096 values fit 16 bits. rank_val
 // maps a rank back to the weight.
@@ -706,6 +1017,12 @@ int dtfm_fast64_prepare(dtfm_problem *pr)
                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds_total(4, true)));
     DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ls_gain4_fast64<4, true>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, lds_total(4, true)));
+    DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ls_ahead_fast64<false>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, SP_AT + SP_BYTES));
+    DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ls_ahead_fast64<true>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, SP_AT + SP_BYTES));
+    DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_steady_fast64),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, SP_AT + SP_BYTES + STEADY_MAX_P * 10));
     int rc = dtfm_fast64_allpairs_prepare();
     if (rc != DTFM_OK) return rc;
     hipDeviceProp_t prop;
@@ -795,6 +1112,9 @@ int dtfm_fast64_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t rows
     return DTFM_OK;
 }
 
+// Eight rounds at a time, by a workgroup an allocation: as many as there are CUs (one workgroup fits a CU).
+static bool search_ahead_pays(const dtfm_problem *pr, size_t rows) { return rows <= (size_t)pr->f64_grid; }
+
 template <int NC>
 static void launch_ls(const dtfm_problem *pr, int32_t *perm, size_t rows, int moves, double *cost, int64_t *applied,
                       hipStream_t st)
@@ -817,6 +1137,12 @@ int dtfm_fast64_offspring_ls_gain4_enqueue(const dtfm_problem *pr, const dtfm_of
                                            size_t rows, int moves, double *cost, hipStream_t st)
 {
     if (!dtfm_fast64_ls_makes_offspring(pr, rows, moves)) return DTFM_ERR_ARG;
+    if (search_ahead_pays(pr, rows)) {
+        hipLaunchKernelGGL(k_ls_ahead_fast64<true>, dim3((unsigned)rows), dim3(SP_THREADS), SP_AT + SP_BYTES, st, pr->W_dp, pr->W_pp,
+                           pr->f64_rank, pr->f64_rank_val, perm, rows, moves, cost, (int64_t *)nullptr, src);
+        DTFM_HIP(hipGetLastError());
+        return DTFM_OK;
+    }
     size_t passes = (rows + 3) / 4;
     const int wpb = waves_per_block(pr, passes);
     size_t blocks = (passes + wpb - 1) / wpb;
@@ -839,11 +1165,41 @@ int dtfm_fast64_ls_gain4_enqueue(const dtfm_problem *pr, int32_t *perm, size_t r
         return dtfm_fast64_ls_gain4_enqueue(pr, perm + head * NDEV, rows - head, moves, cost + head,
                                             applied ? applied + head * (size_t)moves : nullptr, st);
     }
+    if (search_ahead_pays(pr, rows)) {
+        hipLaunchKernelGGL(k_ls_ahead_fast64<false>, dim3((unsigned)rows), dim3(SP_THREADS), SP_AT + SP_BYTES, st, pr->W_dp, pr->W_pp,
+                           pr->f64_rank, pr->f64_rank_val, perm, rows, moves, cost, applied, dtfm_offspring_src{});
+        DTFM_HIP(hipGetLastError());
+        return DTFM_OK;
+    }
     switch (group_size(pr, rows)) {
     case 32: launch_ls<32>(pr, perm, rows, moves, cost, applied, st); break;
     case 8: launch_ls<8>(pr, perm, rows, moves, cost, applied, st); break;
     default: launch_ls<4>(pr, perm, rows, moves, cost, applied, st); break;
     }
+    DTFM_HIP(hipGetLastError());
+    return DTFM_OK;
+}
+
+bool dtfm_fast64_steady(const dtfm_problem *pr, const dtfm_ga_params &prm)
+{
+    return pr->fast64 && prm.neighbourhood == DTFM_GAIN4 && prm.lambda == 1 && prm.P <= STEADY_MAX_P;
+}
+
+int dtfm_fast64_steady_enqueue(const dtfm_problem *pr, dtfm_offspring_src src, int generations, int moves, int32_t *population,
+                               double *cost, double *best_trace, int32_t *order, int32_t *rows, hipStream_t st)
+{
+    if (generations <= 0) return DTFM_OK;
+    constexpr int SPAN = 256;   // generations of a launch: some milliseconds
+    for (int g = 0; g < generations; g += SPAN) {
+        src.g = (uint32_t)g;
+        hipLaunchKernelGGL(k_steady_fast64, dim3(1), dim3(SP_THREADS), SP_AT + SP_BYTES + (size_t)src.P * 10, st, pr->W_dp, pr->W_pp,
+                           pr->f64_rank, pr->f64_rank_val, population, cost, order, g > 0 ? 1 : 0,
+                           generations - g < SPAN ? generations - g : SPAN, moves, best_trace + g, src);
+        DTFM_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_rows_in_order, dim3((unsigned)src.P), dim3(NDEV), 0, st, population, order, rows);
+    DTFM_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_rows_in_order, dim3((unsigned)src.P), dim3(NDEV), 0, st, rows, (const int32_t *)nullptr, population);
     DTFM_HIP(hipGetLastError());
     return DTFM_OK;
 }

@@ -232,6 +232,12 @@ bool dtfm_fast64_ls_makes_offspring(const dtfm_problem *pr, size_t rows, int mov
 int dtfm_fast64_offspring_ls_gain4_enqueue(const dtfm_problem *pr, const dtfm_offspring_src &src, int32_t *perm,
                                            size_t rows, int moves, double *cost, hipStream_t st);
 
+// The generation-wise search with one offspring a generation in a few launches (k_steady_fast64). order: P ints, rows: P * N
+// ints of scratch; the population is in place and its costs are in cost.
+bool dtfm_fast64_steady(const dtfm_problem *pr, const dtfm_ga_params &prm);
+int dtfm_fast64_steady_enqueue(const dtfm_problem *pr, dtfm_offspring_src src, int generations, int moves, int32_t *population,
+                               double *cost, double *best_trace, int32_t *order, int32_t *rows, hipStream_t st);
+
 // all `moves` >= 1 rounds of the ALL_PAIRS local search with incremental move evaluation in one launch
 // (dtfm_fast64_allpairs.hip); perm in/out, cost out, applied may be null
 int dtfm_fast64_allpairs_prepare();

@@ -893,6 +893,10 @@ int dtfm_ga_enqueue(const dtfm_problem *pr, const dtfm_ga_bufs &b, uint64_t seed
     }
     int rc = dtfm_eval_enqueue(pr, b.ls.ev, population, P, cost, st);
     if (rc != DTFM_OK) return rc;
+    if (dtfm_fast64_steady(pr, prm)) {
+        const dtfm_offspring_src src = {k0, k1, 0u, population, P, prm.m_x, prm.m_m};
+        return dtfm_fast64_steady_enqueue(pr, src, generations, prm.ls_moves, population, cost, best_trace, b.rank, b.next, st);
+    }
     const int nk = P + L;
     hipLaunchKernelGGL(k_fill_i32, dim3((nk + 255) / 256), dim3(256), 0, st, b.rank, 0, (size_t)nk);
     DTFM_HIP(hipGetLastError());

@@ -232,6 +232,43 @@ def test_evolve_config1():
     _evolve_parity(w, 4, 5, 9, lam=4, m_x=3, m_m=2, ls_moves=0)
 
 
+@pytest.mark.parametrize("name,P,moves", [("C2", 1, 1), ("C2", 2, 7), ("C2b", 3, 8), ("C2", 4, 9), ("C3h", 3, 16), ("C2b", 5, 31)])
+def test_gain4_rounds_ahead(name, P, moves):
+    # few rows: eight rounds are priced together; rounds that wrap around the 28 stage pairs and passes of all lengths
+    w = workloads.config(name)
+    _ls_parity(w, workloads.random_population(P, 64, seed=P), moves, dtfm.GAIN4)
+
+
+def test_gain4_rounds_ahead_up_to_a_workgroup_a_cu():
+    # 256 rows one to a workgroup, 257 four to a wavefront
+    w = workloads.config("C2")
+    perms = workloads.random_population(257, 64, seed=3)
+    rows = _ls_parity(w, perms, 10, dtfm.GAIN4)
+    _, g = both(w)
+    d = dev(perms[:256])
+    _, applied = dtfm.local_search(g, d, 10, dtfm.GAIN4, want_applied=True)
+    assert np.array_equal(host(applied), rows[:256])
+
+
+@pytest.mark.parametrize("name,P,generations,moves", [("C2", 1, 5, 8), ("C2", 2, 1, 0), ("C2b", 7, 259, 3), ("C2", 300, 12, 8),
+                                                      ("C3h", 33, 20, 9)])
+def test_evolve_one_offspring_a_generation(name, P, generations, moves):
+    # all generations in a launch (256 of them in the first); members of equal cost, the first ranking, a population of one
+    o, g = both(workloads.config(name))
+    ref = o.evolve(5, generations, P, lam=1, ls_moves=moves)
+    got = dtfm.evolve(g, 5, generations, P, lam=1, ls_moves=moves)
+    assert all(np.array_equal(host(a), b) for a, b in zip(got, ref))
+
+
+def test_evolve_one_offspring_above_and_below_the_population_in_lds():
+    o, g = both(workloads.config("C2b"))
+    for P in (4096, 4097):
+        start = workloads.random_population(P, 64, seed=1)
+        ref = o.evolve(9, 3, P, lam=1, ls_moves=2, population=start)
+        got = dtfm.evolve(g, 9, 3, P, lam=1, ls_moves=2, population=dev(start))
+        assert all(np.array_equal(host(a), b) for a, b in zip(got, ref)), P
+
+
 def test_evolve_steady_state_lambda_one():
     # the paper's loop: one offspring per generation, inserted iff better than the worst
     _evolve_parity(workloads.config("C1"), 11, 40, 7, lam=1, m_x=2, m_m=1, ls_moves=2, neighbourhood=dtfm.GAIN4)

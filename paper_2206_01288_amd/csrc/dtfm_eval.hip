@@ -812,14 +812,19 @@ k_held_karp_blocked(const double *__restrict__ ghat, const double *__restrict__ 
 // edge (fl(x + w) is), hence so is Eq. 4: a trial whose graph is nowhere below the current one has
 // PipelineP >= pp_cur, and if fl(DataP' + pp_cur) already reaches the current cost the trial cannot be strictly
 // cheaper: it is rejected, which is all the search needs of it (its cost is set to +inf). The other trials go on the
-// list for Held-Karp. One wavefront per trial; *count must be zero on entry.
-__global__ void k_trial_shortcut(const double *__restrict__ ghat, const double *__restrict__ datap, int nn,
+// list for Held-Karp. One wavefront per trial; *count must be zero on entry. Sixteen trials share a workgroup and one addition to
+// the counter: 4096 additions of their own waited for each other (4096 trials 41 -> 7.6 us).
+#define SHORTCUT_TRIALS 16
+__global__ void __launch_bounds__(SHORTCUT_TRIALS * DTFM_WAVE)
+k_trial_shortcut(const double *__restrict__ ghat, const double *__restrict__ datap, int nn,
                                  const double *__restrict__ ghat_cur, const double *__restrict__ pp_cur,
                                  const double *__restrict__ cur, double *__restrict__ cost, double *__restrict__ pp_out,
                                  int32_t *__restrict__ list, int32_t *__restrict__ count, size_t rows, int trials_per_row)
 {
-    const size_t p = (size_t)blockIdx.x * (blockDim.x / DTFM_WAVE) + threadIdx.x / DTFM_WAVE;
-    if (p >= rows) return;   // whole wavefront
+    __shared__ int s_open[SHORTCUT_TRIALS];
+    const int wave = (int)threadIdx.x / DTFM_WAVE;
+    const size_t p0 = (size_t)blockIdx.x * SHORTCUT_TRIALS;
+    const size_t p = min(p0 + (size_t)wave, rows - 1);   // behind the last: the last once more, listed by nobody
     const size_t c = p / (size_t)trials_per_row;   // the current row this trial was made from
     const int lane = threadIdx.x & (DTFM_WAVE - 1);
     bool differs = false, below = false;
@@ -829,16 +834,24 @@ __global__ void k_trial_shortcut(const double *__restrict__ ghat, const double *
         below |= a < b;
     }
     const bool any_differs = __ballot(differs) != 0ull, any_below = __ballot(below) != 0ull;
-    if (lane != 0) return;
     const double with_cur = __dadd_rn(datap[p], pp_cur[c]);
-    if (!any_differs) {
-        cost[p] = with_cur;
-        pp_out[p] = pp_cur[c];
-    } else if (!any_below && with_cur >= cur[c]) {
-        cost[p] = INFINITY;
-    } else {
-        list[atomicAdd(count, 1)] = (int32_t)p;
+    const bool rejected = !any_below && with_cur >= cur[c];
+    if (lane == 0) {
+        if (!any_differs) {
+            cost[p] = with_cur;
+            pp_out[p] = pp_cur[c];
+        } else if (rejected) {
+            cost[p] = INFINITY;
+        }
+        s_open[wave] = any_differs && !rejected && p0 + (size_t)wave < rows ? 1 : 0;
     }
+    __syncthreads();
+    if (wave != 0) return;
+    const bool open = lane < SHORTCUT_TRIALS && s_open[lane < SHORTCUT_TRIALS ? lane : 0] != 0;
+    const uint64_t all = __ballot(open);
+    int first = lane == 0 && all != 0ull ? atomicAdd(count, __popcll(all)) : 0;
+    first = __builtin_amdgcn_readfirstlane(first);
+    if (open) list[first + __popcll(all & ((1ull << lane) - 1ull))] = (int32_t)(p0 + (size_t)lane);
 }
 
 size_t dtfm_hk_exchange_bytes(const dtfm_problem *pr)
@@ -953,7 +966,7 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     if (cost == nullptr) return DTFM_OK;
     const int32_t *list = nullptr, *count = nullptr;
     if (ref != nullptr) {   // trials of the local search: Held-Karp only where the coarsened graph does not settle the trial
-        hipLaunchKernelGGL(k_trial_shortcut, dim3((unsigned)((rows + 3) / 4)), dim3(4 * DTFM_WAVE), 0, st, b.ghat, b.datap,
+        hipLaunchKernelGGL(k_trial_shortcut, dim3((unsigned)((rows + SHORTCUT_TRIALS - 1) / SHORTCUT_TRIALS)), dim3(SHORTCUT_TRIALS * DTFM_WAVE), 0, st, b.ghat, b.datap,
                            n * n, ref->ghat_cur, ref->pp_cur, ref->cur, cost, b.pp, b.list, b.count, rows, ref->trials_per_row);
         DTFM_HIP(hipGetLastError());
         list = b.list;

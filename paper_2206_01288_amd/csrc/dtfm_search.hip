@@ -154,10 +154,90 @@ __global__ void k_pick_apply(int32_t *__restrict__ perm, int N, long long M, siz
 // over slot pairs; the four end-point swaps ranked by the paper's Gain (sums over the pre-swap
 // sets in slot order from +0.0, divided by D_dp, four terms combined left to right), first
 // maximiser wins. Writes the swapped allocation and the two positions.
-__global__ void k_gain4_propose(const double *__restrict__ W_pp, const int32_t *__restrict__ perm,
+// The fastest link inside the stage of devices C[0 .. D): the first minimiser of W_pp over slot pairs, by one wavefront.
+__device__ __forceinline__ void fastest_link(const double *__restrict__ W_pp, const int32_t *C, int N, int D, int lane, int (&slot)[2],
+                                             double &link)
+{
+    const long long E = (long long)D * (D - 1) / 2;
+    double best = INFINITY;
+    long long be = E;
+    for (long long e = lane; e < E; e += DTFM_WAVE) {
+        int i, k;
+        pair_decode(D, e, i, k);
+        double w = W_pp[(size_t)C[i] * N + C[k]];
+        if (w < best) {
+            best = w;
+            be = e;
+        }
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        double ow = __shfl_xor(best, o);
+        long long oe = __shfl_xor(be, o);
+        if (ow < best || (ow == best && oe < be)) {
+            best = ow;
+            be = oe;
+        }
+    }
+    if (be >= E) be = 0;  // only on malformed (non-finite) weights
+    pair_decode(D, be, slot[0], slot[1]);
+    link = best;
+}
+
+// The same for stages of more than 16 devices, on the leading digits of the ranks: a byte a link instead of eight, sixteen
+// rows of 64 in flight, and the weights of the few links with the smallest digit alone. 4096 rows of 16 stages of 64: the
+// proposals of a round 231 -> 62 us, where each lane decoded its link's slots, read two devices and then a weight, one after another.
+__device__ __forceinline__ void fastest_link_digits(const uint8_t *__restrict__ code, const double *__restrict__ W_pp, const int32_t *C,
+                                                    int N, int D, int lane, int (&slot)[2], double &link)
+{
+    const uint32_t dev = min((uint32_t)C[lane < D ? lane : 0], (uint32_t)N - 1u), at = dev * (uint32_t)N;
+    uint32_t least = 255u;
+    uint64_t rows = 0ull;   // those that reach the lane's device with that digit
+#pragma unroll
+    for (int i0 = 0; i0 < 64; i0 += 16) {
+        if (i0 >= D) break;
+        uint32_t x[16];
+#pragma unroll
+        for (int q = 0; q < 16; q++) x[q] = code[(uint32_t)__builtin_amdgcn_readlane((int)at, i0 + q) + dev];
+#pragma unroll
+        for (int q = 0; q < 16; q++) {
+            const int i = i0 + q;
+            const uint32_t d = i < lane && lane < D ? x[q] : 255u;
+            rows = (d < least ? 0ull : rows) | (d <= least ? 1ull << i : 0ull);
+            least = min(least, d);
+        }
+    }
+    uint32_t all = least;
+    for (int o = 32; o >= 1; o >>= 1) all = min(all, (uint32_t)__shfl_xor((int)all, o));
+    if (least != all) rows = 0ull;
+    double best = INFINITY;
+    int be = 1 << 12;   // 64 i + k
+    while (rows != 0ull) {
+        const int i = __ffsll((unsigned long long)rows) - 1;
+        rows &= rows - 1ull;
+        const double w = W_pp[(size_t)min((uint32_t)C[i], (uint32_t)N - 1u) * N + dev];
+        if (w < best) {
+            best = w;
+            be = i * 64 + lane;
+        }
+    }
+    for (int o = 32; o >= 1; o >>= 1) {
+        const double ow = __shfl_xor(best, o);
+        const int oe = __shfl_xor(be, o);
+        if (ow < best || (ow == best && oe < be)) {
+            best = ow;
+            be = oe;
+        }
+    }
+    slot[0] = be < 1 << 12 ? be >> 6 : 0;
+    slot[1] = be < 1 << 12 ? be & 63 : 1;
+    link = best;
+}
+
+__global__ void k_gain4_propose(const double *__restrict__ W_pp, const uint8_t *__restrict__ code, const int32_t *__restrict__ perm,
                                 int N, int D_dp, int D_pp, int r, int32_t *__restrict__ tmp_perm,
                                 int32_t *__restrict__ move_ab)
 {
+    __shared__ double s_w[4][DTFM_MAX_DDP];
     const int lane = threadIdx.x;
     size_t p = blockIdx.x;
     int npairs = D_pp * (D_pp - 1) / 2;
@@ -167,40 +247,21 @@ __global__ void k_gain4_propose(const double *__restrict__ W_pp, const int32_t *
     const int32_t *Cs[2] = {row + j * D_dp, row + jp * D_dp};
     int slot[2][2];
     double link[2];
-    long long E = (long long)D_dp * (D_dp - 1) / 2;
     for (int s = 0; s < 2; s++) {
-        const int32_t *C = Cs[s];
-        double best = INFINITY;
-        long long be = E;
-        for (long long e = lane; e < E; e += DTFM_WAVE) {
-            int i, k;
-            pair_decode(D_dp, e, i, k);
-            double w = W_pp[(size_t)C[i] * N + C[k]];
-            if (w < best) {
-                best = w;
-                be = e;
-            }
-        }
-        for (int o = 32; o >= 1; o >>= 1) {
-            double ow = __shfl_xor(best, o);
-            long long oe = __shfl_xor(be, o);
-            if (ow < best || (ow == best && oe < be)) {
-                best = ow;
-                be = oe;
-            }
-        }
-        if (be >= E) be = 0;  // only on malformed (non-finite) weights
-        pair_decode(D_dp, be, slot[s][0], slot[s][1]);
-        link[s] = best;
+        if (code != nullptr) fastest_link_digits(code, W_pp, Cs[s], N, D_dp, lane, slot[s], link[s]);
+        else fastest_link(W_pp, Cs[s], N, D_dp, lane, slot[s], link[s]);
     }
-    // lanes 0,1: mean over C_j' of w[x][.] for x = d1, d2; lanes 2,3: mean over C_j of w[y][.]
+    // rows 0, 1: w[x][.] over C_j' for x = d1, d2; rows 2, 3: w[y][.] over C_j
+    for (int q = 0; q < 4; q++) {
+        const int s = q >> 1;                   // which stage the moving device is in
+        if (lane < D_dp) s_w[q][lane] = W_pp[(size_t)Cs[s][slot[s][q & 1]] * N + Cs[1 - s][lane]];
+    }
+    __syncthreads();
     double mean = 0.0;
     if (lane < 4) {
-        int s = lane >> 1;                      // which stage the moving device is in
-        int dev = Cs[s][slot[s][lane & 1]];
-        const int32_t *other = Cs[1 - s];
         double sum = 0.0;
-        for (int i = 0; i < D_dp; i++) sum = __dadd_rn(sum, W_pp[(size_t)dev * N + other[i]]);
+#pragma unroll 8
+        for (int i = 0; i < D_dp; i++) sum = __dadd_rn(sum, s_w[lane][i]);
         mean = __ddiv_rn(sum, (double)D_dp);
     }
     double mx[2] = {__shfl(mean, 0), __shfl(mean, 1)};
@@ -232,7 +293,7 @@ __global__ void k_gain4_propose(const double *__restrict__ W_pp, const int32_t *
 // BEST4 (the four candidates of the paper's neighbourhood judged by the cost): one wavefront per candidate writes
 // the four swapped allocations of round r, rows 4 p .. 4 p + 3 of tmp_perm in the order (d1,d1'), (d1,d2'), (d2,d1'),
 // (d2,d2'), and their positions. The fastest link of a stage as in k_gain4_propose.
-__global__ void k_best4_propose(const double *__restrict__ W_pp, const int32_t *__restrict__ perm,
+__global__ void k_best4_propose(const double *__restrict__ W_pp, const uint8_t *__restrict__ code, const int32_t *__restrict__ perm,
                                 int N, int D_dp, int D_pp, int r, int32_t *__restrict__ tmp_perm,
                                 int32_t *__restrict__ move_ab)
 {
@@ -244,30 +305,10 @@ __global__ void k_best4_propose(const double *__restrict__ W_pp, const int32_t *
     const int32_t *row = perm + p * N;
     const int32_t *Cs[2] = {row + j * D_dp, row + jp * D_dp};
     int slot[2][2];
-    long long E = (long long)D_dp * (D_dp - 1) / 2;
+    double link;
     for (int s = 0; s < 2; s++) {
-        const int32_t *C = Cs[s];
-        double best = INFINITY;
-        long long be = E;
-        for (long long e = lane; e < E; e += DTFM_WAVE) {
-            int i, k;
-            pair_decode(D_dp, e, i, k);
-            double w = W_pp[(size_t)C[i] * N + C[k]];
-            if (w < best) {
-                best = w;
-                be = e;
-            }
-        }
-        for (int o = 32; o >= 1; o >>= 1) {
-            double ow = __shfl_xor(best, o);
-            long long oe = __shfl_xor(be, o);
-            if (ow < best || (ow == best && oe < be)) {
-                best = ow;
-                be = oe;
-            }
-        }
-        if (be >= E) be = 0;  // only on malformed (non-finite) weights
-        pair_decode(D_dp, be, slot[s][0], slot[s][1]);
+        if (code != nullptr) fastest_link_digits(code, W_pp, Cs[s], N, D_dp, lane, slot[s], link);
+        else fastest_link(W_pp, Cs[s], N, D_dp, lane, slot[s], link);
     }
     for (int k = 0; k < 4; k++) {
         const int a = j * D_dp + slot[0][k >> 1], b = jp * D_dp + slot[1][k & 1];
@@ -609,9 +650,12 @@ int dtfm_ls_enqueue(const dtfm_problem *pr, const dtfm_ls_bufs &b, int32_t *perm
                     DTFM_HIP(hipGetLastError());
                 }
             }
-            hipLaunchKernelGGL(neighbourhood == DTFM_KL ? k_kl_propose : neighbourhood == DTFM_BEST4 ? k_best4_propose : k_gain4_propose,
-                               dim3((unsigned)P), dim3(DTFM_WAVE), 0, st, pr->W_pp, perm, N, pr->D_dp, pr->D_pp, r, b.tmp_perm,
-                               b.move_ab);
+            if (neighbourhood == DTFM_KL)
+                hipLaunchKernelGGL(k_kl_propose, dim3((unsigned)P), dim3(DTFM_WAVE), 0, st, pr->W_pp, perm, N, pr->D_dp, pr->D_pp, r,
+                                   b.tmp_perm, b.move_ab);
+            else
+                hipLaunchKernelGGL(neighbourhood == DTFM_BEST4 ? k_best4_propose : k_gain4_propose, dim3((unsigned)P), dim3(DTFM_WAVE), 0,
+                                   st, pr->W_pp, pr->digits.code, perm, N, pr->D_dp, pr->D_pp, r, b.tmp_perm, b.move_ab);
             DTFM_HIP(hipGetLastError());
             const dtfm_trial_ref ref = {b.ghat_cur, b.pp_cur, b.cur, tpr};
             rc = dtfm_eval_inc_enqueue(pr, b.ev, b.tmp_perm, T, b.tmp_cost, j, jp, st, inc ? &ref : nullptr);

@@ -547,51 +547,122 @@ k_match16(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_va
 // of equal size (list `subsets` ordered by popcount), one (S, v) item per thread, with a workgroup
 // barrier between layers. The table is in LDS when it fits, else in this workgroup's slice of an
 // HBM scratch area. One workgroup walks over candidates p = blockIdx.x, += gridDim.x.
-template <bool LDS_TABLE>
+// The layers of one candidate (tab and G in LDS), by `threads` threads, which sync() brings together; returns Eq. 4 in all of them.
+template <typename Sync>
+__device__ __forceinline__ double held_karp_layers(double *tab, const double *G, int n, const uint32_t *subsets,
+                                                   const dtfm_layer_off &lo, int tid, int threads, Sync sync)
+{
+    for (int v = tid; v < n; v += threads) tab[((size_t)1 << v) * n + v] = 0.0;
+    sync();
+    for (int k = 2; k <= n; k++) {
+        int first = lo.off[k], items = (lo.off[k + 1] - first) * k;
+        for (int it = tid; it < items; it += threads) {
+            int si = it / k, tv = it - si * k;
+            uint32_t S = subsets[first + si];
+            uint32_t m = S;
+            for (int z = 0; z < tv; z++) m &= m - 1;
+            int v = __ffs((int)m) - 1;
+            uint32_t rest = S ^ (1u << v);
+            const double *src = tab + (size_t)rest * n;
+            double best = INFINITY;
+            for (uint32_t r = rest; r; r &= r - 1) {
+                int u = __ffs((int)r) - 1;
+                best = fmin(best, __dadd_rn(src[u], G[u * n + v]));
+            }
+            tab[(size_t)S * n + v] = best;
+        }
+        sync();
+    }
+    double m = INFINITY;
+    for (int v = 0; v < n; v++) m = fmin(m, tab[(((size_t)1 << n) - 1) * n + v]);
+    return m;
+}
+
 __global__ void k_held_karp(const double *__restrict__ ghat, const double *__restrict__ datap, int n,
-                            const uint32_t *__restrict__ subsets, dtfm_layer_off lo,
-                            double *__restrict__ tab_global, double *__restrict__ cost, size_t P,
+                            const uint32_t *__restrict__ subsets, dtfm_layer_off lo, double *__restrict__ cost, size_t P,
                             const int32_t *__restrict__ list, const int32_t *__restrict__ count,
                             double *__restrict__ pp_out)
 {
     extern __shared__ double smem[];
     double *G = smem;
-    double *tab = LDS_TABLE ? smem + n * n : tab_global + (size_t)blockIdx.x * ((size_t)n << n);
-    const uint32_t full = (1u << n) - 1u;
+    double *tab = smem + n * n;
     // with a list: only the rows list[0 .. *count)
     const size_t todo = list != nullptr ? (size_t)*count : P;
     for (size_t idx = blockIdx.x; idx < todo; idx += gridDim.x) {
         const size_t p = list != nullptr ? (size_t)list[idx] : idx;
         for (int e = threadIdx.x; e < n * n; e += blockDim.x) G[e] = ghat[p * n * n + e];
-        for (int v = threadIdx.x; v < n; v += blockDim.x) tab[((size_t)1 << v) * n + v] = 0.0;
-        __syncthreads();
-        for (int k = 2; k <= n; k++) {
-            int first = lo.off[k], items = (lo.off[k + 1] - first) * k;
-            for (int it = threadIdx.x; it < items; it += blockDim.x) {
-                int si = it / k, tv = it - si * k;
-                uint32_t S = subsets[first + si];
-                uint32_t m = S;
-                for (int z = 0; z < tv; z++) m &= m - 1;
-                int v = __ffs((int)m) - 1;
-                uint32_t rest = S ^ (1u << v);
-                const double *src = tab + (size_t)rest * n;
-                double best = INFINITY;
-                for (uint32_t r = rest; r; r &= r - 1) {
-                    int u = __ffs((int)r) - 1;
-                    best = fmin(best, __dadd_rn(src[u], G[u * n + v]));
-                }
-                tab[(size_t)S * n + v] = best;
-            }
-            __syncthreads();
-        }
+        const double m = held_karp_layers(tab, G, n, subsets, lo, threadIdx.x, blockDim.x, [] { __syncthreads(); });
         if (threadIdx.x == 0) {
-            double m = INFINITY;
-            for (int v = 0; v < n; v++) m = fmin(m, tab[(size_t)full * n + v]);
             cost[p] = __dadd_rn(datap[p], m);
             if (pp_out != nullptr) pp_out[p] = m;
         }
         __syncthreads();
     }
+}
+
+// Eqs. 1-4 for a few candidates of at most 6 stages of at most 16 devices in one launch: DataP, matchings and Held-Karp are
+// three launches of 3 to 5 us that wait for each other, whatever they have to do. One workgroup per candidate, a wavefront per
+// stage pair. 64 candidates of 8 devices: 13.4 -> 8.3 us.
+#define SMALL_STAGES 6
+#define SMALL_WAVES 15
+__global__ void __launch_bounds__(SMALL_WAVES * DTFM_WAVE)
+k_eval_small(const double *__restrict__ W_dp, const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_val,
+             const int32_t *__restrict__ perm, int N, int D_dp, int n, const uint32_t *__restrict__ subsets, dtfm_layer_off lo,
+             double *__restrict__ cost, double *__restrict__ datap, double *__restrict__ ghat, double *__restrict__ pp)
+{
+    extern __shared__ double smem[];
+    __shared__ double s_red[SMALL_WAVES];
+    const int waves = (int)blockDim.x / DTFM_WAVE, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / DTFM_WAVE);
+    const int lane = (int)threadIdx.x & (DTFM_WAVE - 1);
+    double *G = smem, *tab = G + n * n;
+    uint16_t *tile = reinterpret_cast<uint16_t *>(tab + ((size_t)n << n)) + wave * 16 * DTFM_WAVE + lane;
+    int32_t *row = reinterpret_cast<int32_t *>(reinterpret_cast<uint16_t *>(tab + ((size_t)n << n)) + waves * 16 * DTFM_WAVE);
+    uint32_t *order = reinterpret_cast<uint32_t *>(row + N);   // the subsets: a layer does not wait for memory
+    const size_t p = blockIdx.x;
+    for (int q = threadIdx.x; q < N; q += blockDim.x) row[q] = perm[p * N + q];
+    for (int s = threadIdx.x; s < (1 << n) - 1; s += blockDim.x) order[s] = subsets[s];
+    for (int v = threadIdx.x; v < n; v += blockDim.x) G[v * n + v] = 0.0;
+    __syncthreads();
+    const bool active = lane < D_dp;
+    if (wave < n * (n - 1) / 2) {
+        int j1, j2;
+        dtfm_match_pair(wave, n, -1, -1, j1, j2);
+        const uint32_t coldev = active ? (uint32_t)row[j2 * D_dp + lane] : 0u;
+        uint32_t E[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const uint32_t v = Wcode[(uint32_t)row[j1 * D_dp + (r < D_dp ? r : 0)] * (uint32_t)N + coldev];
+            E[r] = (active && r < D_dp) ? v : 0xffffu;
+        }
+        const uint32_t result = match_block(tile, E, lane, active, D_dp);
+        if (lane == 0) G[j1 * n + j2] = G[j2 * n + j1] = result == 0xffffffffu ? INFINITY : rank_val[result];
+    }
+    double worst = 0.0;   // Eq. 2 as in k_datap
+    for (int q = threadIdx.x; q < N; q += blockDim.x) {
+        const int j = q / D_dp, i = q - j * D_dp;
+        const double *wr = W_dp + (size_t)row[q] * N;
+        const int32_t *C = row + j * D_dp;
+        double sum = 0.0;
+        for (int k = 0; k < D_dp; k++)
+            if (k != i) sum = __dadd_rn(sum, wr[C[k]]);
+        worst = fmax(worst, sum);
+    }
+    for (int o = 32; o >= 1; o >>= 1) worst = fmax(worst, __shfl_xor(worst, o));
+    if (lane == 0) s_red[wave] = worst;
+    __syncthreads();
+    for (int e = threadIdx.x; e < n * n; e += blockDim.x) ghat[p * n * n + e] = G[e];
+    if (wave != 0) return;   // Held-Karp of at most 6 stages is one wavefront's work
+    const double m = held_karp_layers(tab, G, n, order, lo, lane, DTFM_WAVE, [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    });
+    if (threadIdx.x != 0) return;
+    double d = s_red[0];
+    for (int w = 1; w < waves; w++) d = fmax(d, s_red[w]);
+    datap[p] = d;
+    pp[p] = m;
+    cost[p] = __dadd_rn(d, m);
 }
 
 // a5/a6 for D_pp above the LDS limit: the table is walked source-side, in blocks that live in LDS.
@@ -910,6 +981,15 @@ int dtfm_eval_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int
     return dtfm_eval_inc_enqueue(pr, b, perm, rows, cost, -1, -1, st);
 }
 
+// One launch (k_eval_small) where three take longer: up to 512 rows of 5 stages, 256 of 6. Whole evaluations in three launches
+// (in one), devices in regions, 64 / 256 / 512 / 1024 rows: 4 stages of 2 13.4 / 13.5 / 13.5 / 14.0 (8.3 / 8.2 / 8.4 / 12.1), 5 of 8
+// 16.7 / 17.7 / 19.0 / 24.9 (12.7 / 12.9 / 14.3 / 29.3), 6 of 16 23.6 / 26.7 / 32.3 / 44.0 (19.8 / 20.3 / 35.2 / 62.8), 7 of 12 23.4 /
+// 28.0 / 34.2 / 42.8 (24.8 / 27.0 / 43.1 / 79.2).
+bool dtfm_eval_in_one_launch(const dtfm_problem *pr, size_t rows)
+{
+    return !pr->fast64 && pr->D_dp <= 16 && pr->D_pp <= SMALL_STAGES && rows <= (pr->D_pp <= 5 ? 512u : 256u);
+}
+
 // As dtfm_eval_enqueue; with inc_j >= 0 (inc_j < inc_jp) b.ghat already holds the coarsened graphs of rows
 // that differ from `perm` only in stages inc_j and inc_jp: only the edges of those two stages are matched again.
 int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int32_t *perm, size_t rows,
@@ -920,6 +1000,15 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         return cost != nullptr ? dtfm_fast64_enqueue(pr, perm, rows, cost, nullptr, nullptr, st)
                                : dtfm_fast64_enqueue(pr, perm, rows, nullptr, b.ghat, b.datap, st);
     const int N = pr->N, n = pr->D_pp;
+    if (inc_j < 0 && cost != nullptr && dtfm_eval_in_one_launch(pr, rows)) {
+        const int waves = pr->npairs < 1 ? 1 : pr->npairs;
+        const size_t lds = ((size_t)n * n + ((size_t)n << n)) * sizeof(double) + (size_t)waves * 16 * DTFM_WAVE * sizeof(uint16_t) +
+                           (size_t)N * sizeof(int32_t) + (sizeof(uint32_t) << n);
+        hipLaunchKernelGGL(k_eval_small, dim3((unsigned)rows), dim3(waves * DTFM_WAVE), lds, st, pr->W_dp, pr->W_code, pr->rank_val,
+                           perm, N, pr->D_dp, n, pr->hk_subsets, pr->hk_off, cost, b.datap, b.ghat, b.pp);
+        DTFM_HIP(hipGetLastError());
+        return DTFM_OK;
+    }
     int threads = ((N + DTFM_WAVE - 1) / DTFM_WAVE) * DTFM_WAVE;
     if (threads > 1024) threads = 1024;
     if (b.pos != nullptr && rows >= 64 && (reinterpret_cast<uintptr_t>(perm) & 15u) == 0) {
@@ -976,10 +1065,10 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         size_t lds = ((size_t)n * n + ((size_t)n << n)) * sizeof(double);
         int bt = n <= 6 ? 64 : 256;
         if (lds > 48 * 1024)  // above the default dynamic-LDS limit: raise it for this kernel
-            DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_held_karp<true>),
+            DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_held_karp),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(k_held_karp<true>, dim3((unsigned)rows), dim3(bt), lds, st, b.ghat, b.datap, n,
-                           pr->hk_subsets, pr->hk_off, (double *)nullptr, cost, rows, list, count, b.pp);
+        hipLaunchKernelGGL(k_held_karp, dim3((unsigned)rows), dim3(bt), lds, st, b.ghat, b.datap, n,
+                           pr->hk_subsets, pr->hk_off, cost, rows, list, count, b.pp);
     } else {
         // the pruned recursion first where it pays; the dense one for what it left
         if (dtfm_tour_rule(pr, rows, b.hk_grid).worth(n, rows, 0)) {

@@ -147,6 +147,8 @@ size_t dtfm_hk_exchange_bytes(const dtfm_problem *pr);
 // enqueues a2..a6 for `rows` candidates; cost may be null (then only datap/ghat are produced)
 int dtfm_eval_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int32_t *perm,
                       size_t rows, double *cost, hipStream_t st);
+// whether that is one launch, which rows that differ from evaluated ones in two stages then take as well (no inc_j)
+bool dtfm_eval_in_one_launch(const dtfm_problem *pr, size_t rows);
 // the same when b.ghat already holds the coarsened graphs of rows that differ from `perm` only in stages
 // inc_j < inc_jp (inc_j < 0: plain evaluation): only the edges of those two stages are matched again
 int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const int32_t *perm, size_t rows,

@@ -625,9 +625,10 @@ int dtfm_ls_enqueue(const dtfm_problem *pr, const dtfm_ls_bufs &b, int32_t *perm
             // more stages the trial evaluation starts from the current rows' coarsened graphs and matches
             // again only the 2 D_pp - 3 edges of those two stages.
             const int n = pr->D_pp, nn = n * n;
-            const bool inc = n >= 3 && !pr->fast64;   // the 64-device shape prices rows with its own fused kernel
             const int tpr = neighbourhood == DTFM_BEST4 ? 4 : 1;   // trial rows per candidate
             const size_t T = P * (size_t)tpr;
+            // the 64-device shape prices rows with its own fused kernel, few rows of small shapes take one launch as well
+            const bool inc = n >= 3 && !pr->fast64 && !dtfm_eval_in_one_launch(pr, T);
             int j = -1, jp = -1;
             if (inc) {
                 int t = r % pr->npairs;   // the round's stage pair, lexicographic order

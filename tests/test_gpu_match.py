@@ -117,3 +117,26 @@ def test_blocks_of_more_than_16_rows(kind, D_dp, D_pp, P):
         cost_d, _ = dtfm.local_search(g, rows_d, 3, dtfm.KL)
         assert np.array_equal(host(rows_d)[some], rows) and np.array_equal(host(cost_d)[some], want)
     dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp", [(1, 1), (5, 1), (1, 2), (16, 2), (2, 4), (8, 5), (16, 5), (1, 6), (16, 6)])
+@pytest.mark.parametrize("ties", [0, 3])
+def test_small_evaluations_in_one_launch(ties, D_dp, D_pp):
+    # 512 rows of 5 stages and 256 of 6 in one launch, one more in three; searches whose rounds take one launch too
+    N, most = D_dp * D_pp, 512 if D_pp <= 5 else 256
+    rng = np.random.default_rng(D_dp + 100 * D_pp)
+    lat = rng.uniform(1e-3, 0.1, (N, N)) if ties == 0 else rng.integers(1, ties + 1, (N, N)) * 0.01
+    lat, bw = np.triu(lat, 1) + np.triu(lat, 1).T, np.full((N, N), 1e9)
+    o, g = both(workloads.Workload("small", N, D_dp, D_pp, 1e8, 1e7, lat, bw, 0))
+    perms = workloads.random_population(most + 1, N, seed=D_pp)
+    want = oracle_eval_threaded(o, perms)
+    for P in (1, 7, most, most + 1):
+        assert np.array_equal(host(dtfm.eval_population(g, dev(perms[:P]))), want[:P])
+    if D_dp > 1 and D_pp > 1:
+        for nb, P in ((dtfm.GAIN4, 9), (dtfm.KL, most), (dtfm.BEST4, most // 4), (dtfm.BEST4, most // 4 + 1), (dtfm.ALL_PAIRS, 2)):
+            moves = 1 if nb == dtfm.ALL_PAIRS else 3
+            rows, cost, _ = o.local_search(perms[:P], moves, nb)
+            rows_d = dev(perms[:P])
+            cost_d, _ = dtfm.local_search(g, rows_d, moves, nb)
+            assert np.array_equal(host(rows_d), rows) and np.array_equal(host(cost_d), cost)
+    dtfm.destroy_problem(g)

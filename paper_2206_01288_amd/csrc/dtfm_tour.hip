@@ -19,10 +19,10 @@
 //              then kept, so T is the minimum. An attempt whose states die out proves T > thr; one that ends in
 //              T' > thr gives the upper bound T' for the next.
 // Sums along the path are fp64 in path order, exactly Held-Karp's; the result is the same number.
-// Kernel times: 1024 allocations of 256 devices in 16 stages 0.24 ms (k_held_karp_blocked 2.2 ms), 4096 allocations of
+// Kernel times: 1024 allocations of 256 devices in 16 stages 0.16 ms (k_held_karp_blocked 2.2 ms), 4096 allocations of
 // 1024 devices in 16 stages 0.32 ms (8.4 ms).
 //
-// One workgroup of four wavefronts takes four candidates (a launch with few of them: two or one). The potentials of all
+// One workgroup of four wavefronts takes four candidates (a launch of up to 1024: one, dtfm_tour_enqueue). The potentials of all
 // four come from its first wavefront (16 lanes a candidate, a lane per stage: the chain of dependent minima bounds this
 // part, and one wavefront's instructions serve four chains). Then every wavefront searches its own candidate: 16 lanes
 // take a state, grow the spanning tree of its rest (one minimum over 16 lanes and one LDS row per edge), price the
@@ -43,7 +43,7 @@
 namespace {
 
 constexpr int WAVES = 4;               // candidates (= wavefronts) per workgroup
-constexpr int CAP = 256;               // states per layer and wavefront
+constexpr int CAP = 224;               // states per layer and wavefront (see tour_lds)
 constexpr int SLOTS = 512;             // hash slots per wavefront
 constexpr int LOG_SLOTS = 9;
 constexpr int RSTR = 16;               // words between rows of the edge table
@@ -52,6 +52,7 @@ constexpr int BATCH = 16 * 15;         // new states of one pass of a wavefront:
 // a pass is begun at no more than NARROW states (a wavefront alone) or WAVES * CAP (each wavefront of a workgroup)
 static_assert(NARROW + BATCH < SLOTS && WAVES * (CAP + BATCH) < WAVES * SLOTS, "a search needs a free slot");
 constexpr int STEPS = 18;              // subgradient steps
+constexpr int LONE_STEPS = 16;         // the same where four step lengths go side by side
 constexpr int REFINE_STEPS = 60;       // of a candidate whose layers outgrow the workgroup's tables
 constexpr int UNIT_LOG = 24;           // the path U in integer units
 constexpr int BIAS = 1 << 26;          // makes C_ij + BIAS positive: |pi| <= 2^24, 0 <= g <= 2^24
@@ -59,21 +60,24 @@ constexpr uint32_t EMPTY = 0xffffffffu;
 constexpr size_t SPREAD = 256;         // up to so many candidates have a workgroup and a CU each, up to twice as many share it
 constexpr double DOWN = 1.0 - 0x1p-50, UP = 1.0 + 0x1p-50;
 
+// PER: candidates of the workgroup. With one of them 40 KiB: four workgroups a CU.
+template <int PER>
 struct tour_lds {
-    double G[WAVES][16][16];
+    double G[PER][16][16];
     double F[WAVES * CAP];
     unsigned long long hF[WAVES * SLOTS];
     alignas(16) uint32_t hkey[WAVES * SLOTS];         // ascend() writes its edge tables 16 bytes at a time: here and T
     uint32_t key[WAVES * CAP];         // set << 4 | last stage
-    alignas(16) uint32_t T[WAVES][16][RSTR];          // (g_ij + pi_i) << 4
-    int pi[WAVES][16];
-    double scale[WAVES], U[WAVES], cap[WAVES], top[WAVES];
+    alignas(16) uint32_t T[PER][16][RSTR];            // (g_ij + pi_i) << 4
+    int pi[PER][16];
+    double scale[PER], U[PER], cap[PER], top[PER];
     double red[WAVES];
-    double lo[WAVES], thr[WAVES], grow[WAVES];   // where a wavefront's own threshold loop stopped
-    int L[WAVES], state[WAVES], values[WAVES];   // values: see edge_values
+    double lo[PER], thr[PER], grow[PER];   // where a wavefront's own threshold loop stopped
+    int L[PER], state[PER], values[PER];   // values: see edge_values
     int count;
     uint16_t slot[WAVES * CAP];
 };
+static_assert(sizeof(tour_lds<1>) <= 40960, "four workgroups a CU");
 enum { SEARCH = 0, SETTLED = 1, DENSE = 2, WIDE = 3, SOLVED = 4 };
 enum { FOUND, DIED, OVERFLOW_ };
 
@@ -208,10 +212,13 @@ __device__ __forceinline__ int edge_values(int lane, int n, int limit, Edge g)
     return rest > 0 ? max(limit + 1, values * edges / (edges - rest)) : values;
 }
 
-// Upper bound, scale, potentials and root bound of candidate `grp` of the workgroup, by the 16 lanes of a row.
-__device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, int n)
+// Upper bound, scale, potentials and root bound of candidate `grp` of the workgroup, by the 16 lanes of a row. The only candidate
+// of a workgroup has all four rows: each goes its own way up, and the best is kept.
+template <int PER>
+__device__ __forceinline__ void tour_potentials(tour_lds<PER> &sm, int grp, int i, int n)
 {
-    const double (*G)[16] = sm.G[grp];
+    const int cd = PER == 1 ? 0 : grp;
+    const double (*G)[16] = sm.G[cd];
     const bool node = i < n;
     bool fine = true, equal = true;
     const double g01 = G[0][1];
@@ -253,22 +260,35 @@ __device__ __forceinline__ void tour_potentials(tour_lds &sm, int grp, int i, in
 #pragma unroll
     for (int j = 0; j < 16; j++) g[j] = fine && node && j < n ? edge_units(G[i][j], U, scale) : 0;
     // a bound above this settles a trial (see k_tour_search): in units, rounded so that the real bound is above cap
-    const double cap_units = __dmul_rn(__dmul_rn(sm.cap[grp], scale), UP);
+    const double cap_units = __dmul_rn(__dmul_rn(sm.cap[cd], scale), UP);
     const int cap = cap_units < 0x1p30 ? (cap_units > 0.0 ? (int)cap_units + 1 : 1) : INT32_MAX;
     int best = INT32_MIN, best_pi = 0;
-    ascend(g, sm.T[grp], grp, i, n, STEPS, 2.0f, 0.82f, fine && !equal && sm.state[grp] == SEARCH, cap, 0, best, best_pi);
-    sm.pi[grp][i] = best_pi;
+    const bool go = fine && !equal && sm.state[cd] == SEARCH;
+    if constexpr (PER == 1) {   // the hash tables are free for the edge tables
+        uint32_t (*T)[RSTR] = reinterpret_cast<uint32_t (*)[RSTR]>(sm.hkey + grp * 16 * RSTR);
+        const float lambda = grp == 0 ? 2.0f : grp == 1 ? 1.0f : grp == 2 ? 3.0f : 1.5f;
+        const float decay = grp == 0 ? 0.80f : grp == 1 ? 0.87f : grp == 2 ? 0.73f : 0.79f;
+        ascend(g, T, grp, i, n, LONE_STEPS, lambda, decay, go, cap, 0, best, best_pi);
+        int top = max(best, __shfl_xor(best, 16));
+        top = max(top, __shfl_xor(top, 32));
+        const uint64_t who = __ballot(best == top);   // one row at least, whole
+        if (grp != (__ffsll((unsigned long long)who) - 1) >> 4) return;
+    } else {
+        ascend(g, sm.T[cd], grp, i, n, STEPS, 2.0f, 0.82f, go, cap, 0, best, best_pi);
+    }
+    sm.pi[cd][i] = best_pi;
     if (i == 0) {
-        sm.scale[grp] = scale;
-        sm.U[grp] = U;
-        sm.L[grp] = best;
-        if (sm.state[grp] == SEARCH) sm.state[grp] = !fine ? DENSE : equal ? SOLVED : best > cap ? SETTLED : SEARCH;
+        sm.scale[cd] = scale;
+        sm.U[cd] = U;
+        sm.L[cd] = best;
+        if (sm.state[cd] == SEARCH) sm.state[cd] = !fine ? DENSE : equal ? SOLVED : best > cap ? SETTLED : SEARCH;
     }
 }
 
 // Potentials of candidate `cd` again, from where they are, with more steps and four step lengths side by side, by the
 // first wavefront (the hash tables are free for its edge tables).
-__device__ __forceinline__ void tour_refine(tour_lds &sm, int cd, int lane, int n)
+template <int PER>
+__device__ __forceinline__ void tour_refine(tour_lds<PER> &sm, int cd, int lane, int n)
 {
     const int grp = lane >> 4, i = lane & 15;
     int g[16];
@@ -291,7 +311,8 @@ __device__ __forceinline__ void tour_refine(tour_lds &sm, int cd, int lane, int 
 // Cost of the best of 64 greedy paths of candidate `cd`: from every stage, by the nearest-neighbour rule on the edges
 // with the potentials of their far ends at four weights added. The potentials make inner stages attractive that a plain
 // nearest neighbour strands: nine candidates in ten get the optimum, so that one search at this threshold ends it.
-__device__ __forceinline__ double greedy_path(const tour_lds &sm, int cd, int lane, int n)
+template <int PER>
+__device__ __forceinline__ double greedy_path(const tour_lds<PER> &sm, int cd, int lane, int n)
 {
     const double (*G)[16] = sm.G[cd];
     const int start = (lane & 15) < n ? (lane & 15) : 0, r = lane >> 4;
@@ -319,7 +340,8 @@ __device__ __forceinline__ double greedy_path(const tour_lds &sm, int cd, int la
 }
 
 // The edge table of candidate `cd` from its potentials, and the cost of the best path known, by one wavefront.
-__device__ __forceinline__ void tour_table(tour_lds &sm, int cd, int lane, int n)
+template <int PER>
+__device__ __forceinline__ void tour_table(tour_lds<PER> &sm, int cd, int lane, int n)
 {
     const double U = sm.U[cd], scale = sm.scale[cd];
     wave_sync();
@@ -336,8 +358,8 @@ __device__ __forceinline__ void tour_table(tour_lds &sm, int cd, int lane, int n
 // The successors of the states base .. base + 4 TEAM NJ - 1 of a layer of k stages, into the hash table. A row of 16
 // lanes takes NJ states: their spanning trees are grown side by side (one tree alone leaves the wavefront waiting for
 // its chain of LDS reads and minima).
-template <int TEAM, int NJ>
-__device__ __forceinline__ void expand(tour_lds &sm, int k, int n, int base, int cnt, int tid, uint32_t full, int pi,
+template <int TEAM, int NJ, int PER>
+__device__ __forceinline__ void expand(tour_lds<PER> &sm, int k, int n, int base, int cnt, int tid, uint32_t full, int pi,
                                        uint32_t own, double scale, double thr, int thr_units, const uint32_t *key,
                                        const double *F, unsigned long long *hF, uint32_t *hkey, uint16_t *slot,
                                        const double (*G)[16], const uint32_t (*E)[RSTR], int &made)
@@ -437,8 +459,8 @@ struct tour_record {
 // complete path kept, which is the optimum if T <= thr. work: the states that may still be priced. Graphs of at most n / 2
 // values have layers of up to 560 states where the search succeeds (two cliques of eight stages) and outgrow any table
 // where it does not, so they are given up at 40 n; the stage orders, whose full table is dearer, are not.
-template <int TEAM, bool RECORD>
-__device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n, double thr, double &T, int &work,
+template <int TEAM, bool RECORD, int PER>
+__device__ __forceinline__ int tour_search(tour_lds<PER> &sm, int cd, int tid, int n, double thr, double &T, int &work,
                                            const tour_record &rec)
 {
     constexpr int slots = TEAM * SLOTS, NG = TEAM * 4;
@@ -518,7 +540,8 @@ __device__ __forceinline__ int tour_search(tour_lds &sm, int cd, int tid, int n,
 }
 
 // Where the threshold loop of candidate `cd` starts when the workgroup runs all of it.
-__device__ __forceinline__ void first_threshold(tour_lds &sm, int cd)
+template <int PER>
+__device__ __forceinline__ void first_threshold(tour_lds<PER> &sm, int cd)
 {
     const double root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
     sm.lo[cd] = root;
@@ -528,8 +551,8 @@ __device__ __forceinline__ void first_threshold(tour_lds &sm, int cd)
 
 // The threshold loop. Returns SETTLED (the optimum is above cap), SEARCH with T the optimum, WIDE (a
 // wavefront's layer outgrew NARROW: the workgroup goes on from the same threshold) or DENSE.
-template <int TEAM, bool RECORD>
-__device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, int &work, double &T, const tour_record &rec)
+template <int TEAM, bool RECORD, int PER>
+__device__ __forceinline__ int tour_solve(tour_lds<PER> &sm, int cd, int tid, int n, int &work, double &T, const tour_record &rec)
 {
     const double cap = sm.cap[cd];
     double U = sm.top[cd], top = fmin(U, cap), root = fmax((double)sm.L[cd], 0.0) / sm.scale[cd];
@@ -596,14 +619,15 @@ __device__ __forceinline__ int tour_solve(tour_lds &sm, int cd, int tid, int n, 
 // rows: with `list`, list[0 .. count[0]), else all P. cur: costs of the current rows a trial is judged by (or null): a
 // trial that is proven not to be strictly cheaper gets +inf, as in k_trial_shortcut. The rows left to the dense
 // recursion go to dense[0 .. count[1]).
+template <int PER>
 __global__ void __launch_bounds__(64 * WAVES)
 k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap, int n, double *__restrict__ cost, size_t P,
               const int32_t *__restrict__ list, int32_t *__restrict__ count, const double *__restrict__ cur,
               int trials_per_row, double *__restrict__ pp_out, int32_t *__restrict__ dense, dtfm_tour_rule rule)
 {
-    __shared__ tour_lds sm;
+    __shared__ tour_lds<PER> sm;
     const size_t todo = list != nullptr ? (size_t)count[0] : P;
-    const int per = todo <= SPREAD ? 1 : todo <= 2 * SPREAD ? 2 : WAVES;   // candidates of a workgroup
+    const int per = PER == 1 || todo <= SPREAD ? 1 : todo <= 2 * SPREAD ? 2 : WAVES;   // candidates of the workgroup
     const size_t first = (size_t)blockIdx.x * per;
     if (first >= todo) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -611,41 +635,45 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
     if (rule.split && (size_t)count[2] == todo) return;
     const bool have = wave < per && idx < todo;
     const size_t p = have ? (list != nullptr ? (size_t)list[idx] : idx) : 0;
-    for (int e = lane; e < 256; e += 64) {
-        const int a = e >> 4, b = e & 15;
-        sm.G[wave][a][b] = have && a < n && b < n ? ghat[p * n * n + a * n + b] : 0.0;
-    }
-    if (lane == 0) {
-        double cap = INFINITY;
-        if (have && cur != nullptr) {
-            // smallest PipelineP a rejected trial can have: fl(datap + cap) >= cur
-            const double c = cur[p / (size_t)trials_per_row];
-            cap = __dadd_rn(__dadd_rn(c, -datap[p]), __dmul_rn(c, 0x1p-51));
+    const bool few = [&]() {
+        if (wave >= PER) return false;
+        for (int e = lane; e < 256; e += 64) {
+            const int a = e >> 4, b = e & 15;
+            sm.G[wave][a][b] = have && a < n && b < n ? ghat[p * n * n + a * n + b] : 0.0;
         }
-        sm.cap[wave] = cap;
-        sm.state[wave] = !have || cap <= 0.0 ? SETTLED : SEARCH;
-    }
-    wave_sync();
-    const int values = edge_values(lane, n, max(rule.few, n / 2), [&](int i, int j) { return sm.G[wave][i][j]; });
-    const bool few = values > 1 && values <= rule.few;
-    if (lane == 0) {
-        sm.values[wave] = values;
-        if (sm.state[wave] == SEARCH && (few || !rule.worth(n, todo, (size_t)count[2]))) sm.state[wave] = DENSE;
-    }
+        if (lane == 0) {
+            double cap = INFINITY;
+            if (have && cur != nullptr) {
+                // smallest PipelineP a rejected trial can have: fl(datap + cap) >= cur
+                const double c = cur[p / (size_t)trials_per_row];
+                cap = __dadd_rn(__dadd_rn(c, -datap[p]), __dmul_rn(c, 0x1p-51));
+            }
+            sm.cap[wave] = cap;
+            sm.state[wave] = !have || cap <= 0.0 ? SETTLED : SEARCH;
+        }
+        wave_sync();
+        const int values = edge_values(lane, n, max(rule.few, n / 2), [&](int i, int j) { return sm.G[wave][i][j]; });
+        const bool f = values > 1 && values <= rule.few;
+        if (lane == 0) {
+            sm.values[wave] = values;
+            if (sm.state[wave] == SEARCH && (f || !rule.worth(n, todo, (size_t)count[2]))) sm.state[wave] = DENSE;
+        }
+        return f;
+    }();
     __syncthreads();
     bool any = false;
-    for (int w = 0; w < WAVES; w++) any = any || sm.state[w] == SEARCH;
+    for (int w = 0; w < PER; w++) any = any || sm.state[w] == SEARCH;
     if (any && wave == 0) tour_potentials(sm, lane >> 4, lane & 15, n);
     __syncthreads();
     double T = 0.0;
-    int state = sm.state[wave];
+    int state = wave < PER ? sm.state[wave] : SETTLED;
     if (state == SEARCH) {
         if (lane == 0) sm.top[wave] = sm.U[wave];
         tour_table(sm, wave, lane, n);
         if (per == 1) {
             if (lane == 0) first_threshold(sm, 0);
             state = WIDE;
-        } else {
+        } else if constexpr (PER > 1) {
             int work = INT32_MAX;
             state = tour_solve<1, false>(sm, wave, lane, n, work, T, tour_record());
             if (state == WIDE && n < 12) state = DENSE;   // 18 us there, 20 at the least here
@@ -654,7 +682,7 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
     }
     __syncthreads();
     int work = rule.work;
-    for (int w = 0; w < WAVES; w++) {   // too wide for a quarter of the tables: all of them, one candidate at a time
+    for (int w = 0; w < PER; w++) {   // too wide for a quarter of the tables: all of them, one candidate at a time
         if (sm.state[w] != WIDE) continue;
         double Tw = 0.0;
         // Graphs of more than 2 n values or so end well: one in some hundred takes long, none of those seen were left to the dense
@@ -708,20 +736,20 @@ __global__ void __launch_bounds__(64 * WAVES)
 k_tour_path(const double *__restrict__ ghat, int n, size_t P, double *__restrict__ tab, int32_t *__restrict__ order,
             int32_t *__restrict__ count, int32_t *__restrict__ dense)
 {
-    __shared__ tour_lds sm;
+    __shared__ tour_lds<1> sm;
     const int tid = threadIdx.x, lane = tid & 63;
     double *slot = tab + (size_t)blockIdx.x * ((size_t)n << n);   // n * 2^n doubles hold the layers from n = 11 on
     const tour_record rec = {slot, reinterpret_cast<uint32_t *>(slot + n * WAVES * CAP),
                              reinterpret_cast<int *>(slot + n * WAVES * CAP + n * WAVES * CAP / 2)};
     for (size_t p = blockIdx.x; p < P; p += gridDim.x) {
         __syncthreads();
-        for (int e = tid; e < WAVES * 256; e += 64 * WAVES) {
-            const int a = (e >> 4) & 15, b = e & 15;
-            sm.G[e >> 8][a][b] = e < 256 && a < n && b < n ? ghat[p * n * n + a * n + b] : 0.0;
+        {
+            const int a = tid >> 4, b = tid & 15;
+            sm.G[0][a][b] = a < n && b < n ? ghat[p * n * n + a * n + b] : 0.0;
         }
-        if (tid < WAVES) {
-            sm.cap[tid] = INFINITY;
-            sm.state[tid] = tid == 0 ? SEARCH : SETTLED;
+        if (tid == 0) {
+            sm.cap[0] = INFINITY;
+            sm.state[0] = SEARCH;
         }
         __syncthreads();
         if (tid < 64) {
@@ -805,7 +833,13 @@ int dtfm_tour_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, size_t ro
                            b.dense, rule);
         DTFM_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_tour_search, dim3((unsigned)grid), dim3(64 * WAVES), 0, st, b.ghat, b.datap,
+    // Up to four workgroups a CU: each candidate has one of its own from the start, so that a hard one has four wavefronts and
+    // waits for no other. Evaluations in regions, four candidates to a workgroup (one), 512 / 768 / 1024 rows: 16 stages of 16 287 /
+    // 350 / 382 (238 / 286 / 304) us, 2 249 / 271 / 274 (206 / 211 / 217), 14 of 2 141 / 169 / 173 (115 / 125 / 131); the graphs of single
+    // devices have no hard ones, 14 stages 74 / 77 / 80 (73 / 84 / 91).
+    const bool lone = rows <= (pr->D_dp == 1 ? 512u : 1024u);
+    hipLaunchKernelGGL(lone ? k_tour_search<1> : k_tour_search<WAVES>, dim3((unsigned)(lone ? rows : grid)),
+                       dim3(64 * WAVES), 0, st, b.ghat, b.datap,
                        n, cost, rows, list, b.count, ref != nullptr ? ref->cur : (const double *)nullptr,
                        ref != nullptr ? ref->trials_per_row : 1, b.pp, b.dense, rule);
     DTFM_HIP(hipGetLastError());

@@ -47,6 +47,12 @@ __device__ __forceinline__ int lane_first_bit(uint64_t m)   // per lane; m = 0: 
     asm("v_ffbl_b32 %0, %1" : "=v"(hi) : "v"((uint32_t)(m >> 32)));
     return (int)min(lo, hi | 32u);
 }
+__device__ __forceinline__ bool any_bit(uint64_t m)   // per lane, on 32-bit instructions: a 64-bit comparison takes longer than two
+{
+    uint32_t x;
+    asm("v_or_b32 %0, %1, %2" : "=v"(x) : "v"((uint32_t)m), "v"((uint32_t)(m >> 32)));
+    return x != 0u;
+}
 __device__ __forceinline__ bool in_lanes(uint64_t m)   // the lane's bit of a mask that is the same in all lanes
 {
     return __builtin_amdgcn_inverse_ballot_w64(m);
@@ -88,14 +94,16 @@ struct matching {
     int col_of, row_of;
 };
 
-// the path that ends in the free column c, back to the free row r0; from: the row that reached the lane's column
-__device__ __forceinline__ void augment(matching &m, int from, int c, int r0)
+// the path that ends in the free column c, back to the free row r0; from: the rows that reached the lane's column
+__device__ __forceinline__ void augment(matching &m, uint64_t from, int c, int r0)
 {
     m.freecols &= ~(1ull << c);
     m.freerows &= ~(1ull << r0);
     int r;
     do {   // to a column reached a turn earlier
-        r = __builtin_amdgcn_readlane(from, c);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)from, c);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(from >> 32), c);
+        r = first_bit((uint64_t)hi << 32 | lo);
         const int prev = __builtin_amdgcn_readlane(m.col_of, r);
         m.row_of = lane_write(r, c, m.row_of);
         m.col_of = lane_write(c, r, m.col_of);
@@ -109,14 +117,13 @@ __device__ __forceinline__ bool complete(matching &m, uint64_t adj)
     while (m.freerows != 0ull) {
         const int r0 = first_bit(m.freerows);
         const uint64_t col = 1ull << m.col_of;
-        uint64_t t = adj & (1ull << r0), cols = __ballot(t != 0ull), seen = 0ull, hit = cols & m.freecols;
-        int from = r0;
+        uint64_t t = adj & (1ull << r0), cols = __ballot(any_bit(t)), seen = 0ull, hit = cols & m.freecols, from = t;
         while (hit == 0ull && cols != 0ull) {   // a turn reaches a new column or ends the search
             seen |= cols;
-            const uint64_t rows = __ballot((col & cols) != 0ull) & ~m.freerows;
+            const uint64_t rows = __ballot(any_bit(col & cols)) & ~m.freerows;
             t = adj & rows;
-            cols = __ballot(t != 0ull) & ~seen;
-            from = in_lanes(cols) ? lane_first_bit(t) : from;
+            cols = __ballot(any_bit(t)) & ~seen;
+            from = in_lanes(cols) ? t : from;
             hit = cols & m.freecols;
         }
         if (hit == 0ull) return false;
@@ -128,8 +135,8 @@ __device__ __forceinline__ bool complete(matching &m, uint64_t adj)
 // takes the edges that the masks no longer hold out of the matching
 __device__ __forceinline__ void release(matching &m, uint64_t adj, uint64_t columns)
 {
-    const uint64_t lost = ~__ballot((adj >> m.row_of) & 1ull) & columns & ~m.freecols;
-    const uint64_t rows = __ballot((lost >> m.col_of) & 1ull) & ~m.freerows;
+    const uint64_t lost = ~__ballot(any_bit(adj & (1ull << m.row_of))) & columns & ~m.freecols;
+    const uint64_t rows = __ballot(any_bit(lost & (1ull << m.col_of))) & ~m.freerows;
     m.freecols |= lost;
     m.freerows |= rows;
 }
@@ -145,8 +152,8 @@ __device__ __forceinline__ void bids(matching &m, int lane, uint64_t adj, uint64
 #pragma unroll
     for (int round = 0; round < 4; round++) {
         const uint64_t open = adj & m.freerows, above = open & up;
-        const bool bid = open != 0ull && in_lanes(m.freecols);
-        const int r = lane_first_bit(above != 0ull ? above : open);
+        const bool bid = any_bit(open) && in_lanes(m.freecols);
+        const int r = lane_first_bit(any_bit(above) ? above : open);
         if (bid) slot[r] = (uint32_t)lane;
         lds_order();
         const bool won = bid && slot[r] == (uint32_t)lane;
@@ -269,14 +276,13 @@ k_match_bits(dtfm_digits dg, const uint32_t *__restrict__ Wrank, const double *_
             while (m.freerows != 0ull) {
                 const int r0 = first_bit(m.freerows);
                 const uint64_t col = 1ull << m.col_of;
-                uint64_t rows = 1ull << r0, reached = rows, seen = 0ull, hit;
-                int from = r0;
+                uint64_t rows = 1ull << r0, reached = rows, seen = 0ull, hit, from = 0ull;
                 do {   // a turn reaches a column, or admits an edge to one
-                    const uint64_t t = adj & rows, cols = __ballot(t != 0ull) & ~seen;
-                    from = in_lanes(cols) ? lane_first_bit(t) : from;
+                    const uint64_t t = adj & rows, cols = __ballot(any_bit(t)) & ~seen;
+                    from = in_lanes(cols) ? t : from;
                     hit = cols & m.freecols;
                     seen |= cols;
-                    rows = __ballot((col & cols) != 0ull) & ~m.freerows;
+                    rows = __ballot(any_bit(col & cols)) & ~m.freerows;
                     reached |= rows;
                     if (cols == 0ull) {
                         uint32_t k = ~0u;

@@ -10,7 +10,7 @@
 //     the columns of C_k except c (a 7-row subset programme, done once per round for every (j,k,i)),
 //     the new edge is min_c max(F[j][k][i][c], w[new device][C_k[c]]): 15 operations;
 //   * the edge (j,j'): a row and a column change; it is redone by the 8-row subset programme;
-//   * Held-Karp (Eq. 4) is rerun on the patched coarsened graph, eight swaps per pass.
+//   * Held-Karp (Eq. 4) is rerun on the patched coarsened graph, eight swaps per pass, of those that two bounds leave.
 // A swap inside a stage changes only the order of that stage's DataP sums.
 // The unchanged edges and the F tables are also where the round's own coarsened graph comes from
 // (replacing a row by itself), so a round costs 448 seven-row programmes, 1792 eight-row programmes
@@ -31,7 +31,11 @@ constexpr int AP_OFF_F = AP_OFF_EDGE + (128 + 1024) * 2;   // u16 [j][k][i][c]
 constexpr int AP_OFF_DPM = AP_OFF_F + 8 * 8 * 8 * 8 * 2;   // double [64]: DataP after swap mv
 constexpr int AP_OFF_DPB = AP_OFF_DPM + 64 * 8;            // double [8]: DataP of every stage of the current row
 constexpr int AP_OFF_LIST = AP_OFF_DPB + 64;               // u8 [64]: the swaps of the batch that can still win
-constexpr int AP_WAVE_BYTES = AP_OFF_LIST + 64;
+// The queue of swaps whose Held-Karp is to be run: an entry is the patched graph's 28 ranks (stage pairs in lexicographic order)
+// and the DataP after the swap, 64 bytes, two of them in each of the unused blocks F[1][1] .. F[7][7]; its positions in a list.
+constexpr int AP_QUEUE = 14;
+constexpr int AP_OFF_QKEY = AP_OFF_LIST + 64;              // u8 [AP_QUEUE][2]
+constexpr int AP_WAVE_BYTES = AP_OFF_QKEY + 32;
 constexpr int AP_LDS_TOTAL = LDS_TABLES + WAVES_PER_BLOCK * AP_WAVE_BYTES;
 static_assert(AP_OFF_F % 16 == 0 && AP_OFF_DPM % 8 == 0 && AP_WAVE_BYTES % 16 == 0, "alignment");
 static_assert(AP_LDS_TOTAL <= 160 * 1024, "LDS budget of a CU");
@@ -94,7 +98,7 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
     uint16_t *F = reinterpret_cast<uint16_t *>(wl + AP_OFF_F);
     double *dpm = reinterpret_cast<double *>(wl + AP_OFF_DPM);
     double *dpb = reinterpret_cast<double *>(wl + AP_OFF_DPB);
-    unsigned char *list = wl + AP_OFF_LIST;
+    unsigned char *list = wl + AP_OFF_LIST, *qkey = wl + AP_OFF_QKEY;
     const int hm = lane >> 3, hv = lane & 7;   // Held-Karp role: swap slot within the pass, stage
 
     const int wpb = blockDim.x >> 6;   // wavefronts per workgroup: WAVES_PER_BLOCK, fewer when there are few rows
@@ -157,10 +161,24 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
             }
             cur_cost = __dadd_rn(dp_base, pp_base);
             const bool prune = move_cost == nullptr;   // pricing every swap: nothing may be left out
-            // 28 batches (j < j') of 64 swaps; Held-Karp takes eight swaps per pass
+            // 28 batches (j < j') of 64 swaps, and an end that empties the queue
+            int head = 0, queued = 0;
 #pragma nounroll
-            for (int batch = 0; batch < 28; batch++) {
-                int j, jp;
+            for (int batch = 0; batch <= 28; batch++) {
+                int j = 0, jp = 1, cnt = 0;
+                double thr = INFINITY;
+                const int scr = (batch & 1) ? AP_EDGE_SCR_ODD : AP_EDGE_SCR;
+                // rank of edge (v, u) of the coarsened graph after swap mv: the (j,j') edge, an edge of j or j' with a
+                // row replaced, or an edge of the row's own graph
+                auto edge_index = [&](int mv, int v, int u) -> int {
+                    const bool vj = v == j, uj = u == j, vjp = v == jp, ujp = u == jp;
+                    int e = AP_EDGE_GBM + v * 8 + u;
+                    e = (vjp || ujp) ? AP_EDGE_REP + (64 + mv) * 8 + (vjp ? u : v) : e;
+                    e = (vj || uj) ? AP_EDGE_REP + mv * 8 + (vj ? u : v) : e;
+                    e = ((vj && ujp) || (vjp && uj)) ? scr + mv : e;
+                    return e;
+                };
+                if (batch < 28) {
                 pair8_decode(batch, j, jp);
                 const uint2 cj = *reinterpret_cast<const uint2 *>(cur + 8 * j), cjp = *reinterpret_cast<const uint2 *>(cur + 8 * jp);
                 const int i = lane >> 3, ip = lane & 7;            // this lane's swap mv = lane
@@ -194,17 +212,6 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                     if (k != j && k != jp) dp_swap = fmax(dp_swap, dpb[k]);
                 dpm[lane] = dp_swap;
                 WAVE_LDS_SYNC();
-                const int scr = (batch & 1) ? AP_EDGE_SCR_ODD : AP_EDGE_SCR;
-                // rank of edge (v, u) of the coarsened graph after swap mv: the (j,j') edge, an edge of j or j' with a
-                // row replaced, or an edge of the row's own graph
-                auto edge_index = [&](int mv, int v, int u) -> int {
-                    const bool vj = v == j, uj = u == j, vjp = v == jp, ujp = u == jp;
-                    int e = AP_EDGE_GBM + v * 8 + u;
-                    e = (vjp || ujp) ? AP_EDGE_REP + (64 + mv) * 8 + (vjp ? u : v) : e;
-                    e = (vj || uj) ? AP_EDGE_REP + mv * 8 + (vj ? u : v) : e;
-                    e = ((vj && ujp) || (vjp && uj)) ? scr + mv : e;
-                    return e;
-                };
                 // ---- which swaps can still win: a lower bound on the cost after the swap against the cheapest so far ----
                 // Half of each edge of a path over the 8 stages belongs to either end: a stage inside the path has two edges, at
                 // least its cheapest m_v and its second cheapest n_v, a stage at an end one, at least m_v. So Eq. 4 is at
@@ -214,9 +221,9 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                 // whose bound is strictly above the cheapest cost so far (or the row's own) can neither be applied nor
                 // tie with the winner, and is left out. 6 to 14 % of the swaps of random rows stay (by the m_v alone, each stage
                 // but the first entered by an edge of its own, 32 to 37 %; 1.5 to 2.7 % are cheaper than the threshold).
-                int cnt = 64;
+                cnt = 64;
                 if (prune) {
-                    double thr = bestc;
+                    thr = bestc;
 #pragma unroll
                     for (int o = 32; o >= 1; o >>= 1) thr = fmin(thr, __shfl_xor(thr, o));
                     thr = fmin(thr, cur_cost);
@@ -245,21 +252,81 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                     if (keep) list[rank] = (unsigned char)lane;
                     WAVE_LDS_SYNC();
                 }
-#pragma nounroll
-                for (int pass = 0; pass * 8 < cnt; pass++) {
+                }
+                // ---- the swaps left, eight at a time: priced by a minimum spanning tree, which a path is no cheaper than (the
+                // same roundings), and queued for Held-Karp if that bound leaves them too (a quarter of them), so that its passes are
+                // full: 1,900 instructions against 280 of a pass here. 4096 rows, 20 rounds: 27.8 -> 23.8 ms ----
+                int pass = 0;
+                for (;;) {
                     const int slot = pass * 8 + hm;
-                    const bool valid = slot < cnt;
-                    const int mv = prune ? list[valid ? slot : cnt - 1] : slot;
-                    double G[8];
-                    G[0] = 0.0;
+                    if (pass * 8 < cnt && queued + 8 <= AP_QUEUE) {
+                        const int mv = prune ? list[min(slot, cnt - 1)] : slot;
+                        uint32_t e[8];
 #pragma unroll
-                    for (int d = 1; d < 8; d++) G[d] = rank_val[edge[edge_index(mv, hv, hv ^ d)]];
-                    const double pp = hk_registers<false>(G, lane);
-                    const double total = __dadd_rn(dpm[mv], pp);
-                    const uint32_t a = 8 * j + (mv >> 3), b = 8 * jp + (mv & 7);
-                    if (valid) keep_best(bestc, bestk, total, 64 * a + b);
-                    if (move_cost != nullptr && hv == 0)
-                        move_cost[cand * (size_t)N_MOVES + (a * NDEV - a * (a + 1) / 2 + (b - a - 1))] = total;
+                        for (int d = 1; d < 8; d++) e[d] = edge[edge_index(mv, hv, hv ^ d)];
+                        bool keep = slot < cnt;
+                        if (prune) {
+                            double tree = 0.0;
+                            uint32_t key = hv == 0 ? ~0u : 0x7FFFFFFFu;   // rank of the cheapest edge to the tree, and the stage
+                            int b = 0;
+#pragma unroll
+                            for (int t = 0; t < 7; t++) {
+                                const int d = hv ^ b;   // 0: the stage that joined last
+                                const uint32_t x0 = (d & 1) ? e[1] : 0u, x1 = (d & 1) ? e[3] : e[2], x2 = (d & 1) ? e[5] : e[4],
+                                               x3 = (d & 1) ? e[7] : e[6];
+                                const uint32_t y0 = (d & 2) ? x1 : x0, y1 = (d & 2) ? x3 : x2, w = (d & 4) ? y1 : y0;
+                                key = d == 0 ? ~0u : key == ~0u ? ~0u : min(key, w << 3 | (uint32_t)hv);
+                                uint32_t k = key;
+                                k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_XOR1, 0xF, 0xF, true));
+                                k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_XOR2, 0xF, 0xF, true));
+                                k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_HALF_MIRROR, 0xF, 0xF, true));
+                                b = (int)(k & 7u);
+                                tree = __dadd_rn(tree, rank_val[k >> 3]);
+                            }
+                            keep = keep && !(__dadd_rn(dpm[mv], __dmul_rn(tree, 1.0 - 1e-12)) > thr);
+                        }
+                        const uint64_t kept = __ballot(keep && hv == 0);
+                        if (keep) {
+                            const int q = (head + queued + __popcll(kept & ((1ull << (lane & 56)) - 1ull))) % AP_QUEUE;
+                            uint16_t *entry = F + (1 + (q >> 1)) * 9 * 64 + (q & 1) * 32;
+#pragma unroll
+                            for (int d = 1; d < 8; d++) {   // either end writes the same
+                                const int u = hv ^ d;
+                                entry[pair_index(hv < u ? hv : u, hv < u ? u : hv)] = (uint16_t)e[d];
+                            }
+                            if (hv == 0) {
+                                *reinterpret_cast<double *>(entry + 28) = dpm[mv];
+                                qkey[2 * q] = (unsigned char)(8 * j + (mv >> 3));
+                                qkey[2 * q + 1] = (unsigned char)(8 * jp + (mv & 7));
+                            }
+                        }
+                        queued += __popcll(kept);
+                        pass++;
+                        WAVE_LDS_SYNC();
+                    } else if (queued + 8 > AP_QUEUE || (batch == 28 && queued > 0)) {
+                        const int now = min(queued, 8);
+                        const bool valid = hm < now;
+                        const int q = (head + min(hm, now - 1)) % AP_QUEUE;
+                        const uint16_t *entry = F + (1 + (q >> 1)) * 9 * 64 + (q & 1) * 32;
+                        double G[8];
+                        G[0] = 0.0;
+#pragma unroll
+                        for (int d = 1; d < 8; d++) {
+                            const int u = hv ^ d;
+                            G[d] = rank_val[entry[pair_index(hv < u ? hv : u, hv < u ? u : hv)]];
+                        }
+                        const double pp = hk_registers<false>(G, lane);
+                        const double total = __dadd_rn(*reinterpret_cast<const double *>(entry + 28), pp);
+                        const uint32_t a = qkey[2 * q], b = qkey[2 * q + 1];
+                        if (valid) keep_best(bestc, bestk, total, 64 * a + b);
+                        if (move_cost != nullptr && valid && hv == 0)
+                            move_cost[cand * (size_t)N_MOVES + (a * NDEV - a * (a + 1) / 2 + (b - a - 1))] = total;
+                        head = (head + now) % AP_QUEUE;
+                        queued -= now;
+                        WAVE_LDS_SYNC();
+                    } else {
+                        break;
+                    }
                 }
                 WAVE_LDS_SYNC();   // the next batch overwrites the slice
             }

@@ -379,9 +379,8 @@ __device__ __forceinline__ double wpp(const wave_ctx &cx, uint32_t a, uint32_t b
 
 // The round's proposal for every candidate slot (Sec. 3.4, "Improving Local Search Strategy"): the fastest
 // link inside stage j and inside stage jp of the current row, and of the four swaps of their end points
-// the one of largest Gain; its two positions (first < second) go to prop[2 c], prop[2 c + 1]. SHARED: one current row for
-// all slots, j and jp those of the lane's slot.
-template <int NC, bool SHARED = false>
+// the one of largest Gain; its two positions (first < second) go to prop[2 c], prop[2 c + 1].
+template <int NC>
 __device__ __forceinline__ void propose_gain4(const wave_ctx &cx, const unsigned char *pbcur, unsigned char *prop, int j,
                                               int jp)
 {
@@ -395,7 +394,7 @@ __device__ __forceinline__ void propose_gain4(const wave_ctx &cx, const unsigned
         // ---- proposal for candidate slot 4 * pass + lane / 16 by its 16 lanes: registers and
         // lane exchanges only, apart from the table gathers ----
         const int pslot = 4 * pass + (lane >> 4);
-        const unsigned char *pc = pbcur + (SHARED ? 0 : pslot * 64);
+        const unsigned char *pc = pbcur + pslot * 64;
         const uint2 cdev[2] = {*reinterpret_cast<const uint2 *>(pc + Cj), *reinterpret_cast<const uint2 *>(pc + Cjp)};
         int slot[2][2];
 #pragma unroll
@@ -654,27 +653,28 @@ k_ls_gain4_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_
     }
 }
 
-// ---- Launches of few allocations: one per workgroup, and the rounds of its local search several at a time
-// Most proposals are rejected, and a round after a rejected one starts from the same row. So the next eight rounds are
-// proposed and priced together, as eight trial rows of the current one, and the first that is cheaper is accepted; the rounds
-// behind it are proposed again from the new row. What each round compares is what it compares one at a time. A pass is as long as
-// one round alone (a wavefront prices four rows in the time of one): two wavefronts take four rounds each, a third the DataP of
-// the trial rows, and in the first pass a fourth prices the row itself. Half of the
-// rounds are accepted in a search from random rows: 4.5 passes for eight rounds. 200 generations of one offspring: 14.7 -> 7.65 ms.
-constexpr int AHEAD = 8;
+// ---- Launches of few allocations: one per workgroup, and four rounds of its local search at once
+// What a round starts from depends on which of the rounds before it were accepted, half of them in a search from random rows. So
+// all the ways that four rounds can go are priced together: trial i of 15 is the proposal of its round from the row that i stands
+// for, and has the trials 2 i (i rejected) and 2 i + 1 (accepted) of the next round behind it. Each round compares what it
+// compares one at a time. A wavefront prices four rows in the time of one: four wavefronts take the trials, two more their DataP,
+// and in the first pass another the row itself. 200 generations of one offspring: 14.7 ms a round at a time, 7.65 with the next
+// eight rounds from the same row at once (4.5 passes until the last is decided), 6.39 ms so;
+// eight rounds on 256 rows 67, 67 and 33 us.
+constexpr int DEEP = 4, TRIALS = 1 << DEEP;              // trial 0 stands for the current row
 constexpr int SP_CUR = 0;                                // u8 [64]: current row
-constexpr int SP_PB = SP_CUR + 64;                       // u8 [AHEAD][64]: trial rows
-constexpr int SP_PROP = SP_PB + AHEAD * 64;              // u8 [AHEAD][2]: proposed positions
-constexpr int SP_GHR = SP_PROP + AHEAD * 2;              // u16 [AHEAD][28]: the trials' edges of the round's two stages
-constexpr int SP_GHRCUR = SP_GHR + AHEAD * 28 * 2;       // u16 [28]
-constexpr int SP_PP = (SP_GHRCUR + 28 * 2 + 7) / 8 * 8;  // double [AHEAD]
-constexpr int SP_DP = SP_PP + AHEAD * 8;                 // double [AHEAD]
-constexpr int SP_COST = SP_DP + AHEAD * 8;               // double: cost of the current row
+constexpr int SP_PB = SP_CUR + 64;                       // u8 [TRIALS][64]: trial rows
+constexpr int SP_PROP = SP_PB + TRIALS * 64;             // u8 [TRIALS][2]: proposed positions
+constexpr int SP_GHR = SP_PROP + TRIALS * 2;             // u16 [TRIALS][28]: the trials' edges of their round's two stages, [0]: all of the row
+constexpr int SP_FROM = SP_GHR + TRIALS * 28 * 2;        // u16 [TRIALS][28]: where a trial has each edge, as an index into the former
+constexpr int SP_PP = (SP_FROM + TRIALS * 28 * 2 + 7) / 8 * 8;  // double [TRIALS]
+constexpr int SP_DP = SP_PP + TRIALS * 8;                // double [TRIALS]
+constexpr int SP_COST = SP_DP + TRIALS * 8;              // double: cost of the current row
 constexpr int SP_DPCUR = SP_COST + 8;                    // double: its DataP
 constexpr int SP_MK = SP_DPCUR + 8;
 constexpr int SP_BYTES = (SP_MK + mk_bytes(4) + 15) / 16 * 16;
 constexpr int SP_AT = LDS_TABLES + LDS_WDP_BYTES;
-constexpr int SP_THREADS = 256;
+constexpr int SP_THREADS = 512;
 constexpr int STEADY_MAX_P = 4096;                       // 40 KiB of costs and row numbers
 static_assert(SP_AT + SP_BYTES + STEADY_MAX_P * 10 + 64 <= 160 * 1024, "LDS budget of a CU");
 static_assert(SP_PB % 8 == 0 && SP_GHR % 4 == 0, "rows are read 8 bytes at a time");
@@ -688,55 +688,144 @@ __device__ __forceinline__ double row_datap(const wave_ctx &cx, const unsigned c
     return fmax(dp, dpp_move<DPP_HALF_MIRROR>(dp));
 }
 
+// the trial whose row trial i starts from: the last accepted one on the way to it (0: the current row)
+__device__ __forceinline__ int trial_base(int i) { return i >> __ffs(i); }
+__device__ __forceinline__ int trial_level(int i) { return 31 - __clz(i); }
+
+// propose_gain4 for one row by a whole wavefront, a lane per link of the two stages; the trial row goes to `to`
+__device__ __forceinline__ void propose_one(const wave_ctx &cx, const unsigned char *row, unsigned char *prop, unsigned char *to, int j,
+                                            int jp)
+{
+    const int lane = cx.lane, half = lane >> 5, e = min(lane & 31, 27);
+    const uint2 c0 = *reinterpret_cast<const uint2 *>(row + 8 * j), c1 = *reinterpret_cast<const uint2 *>(row + 8 * jp);
+    const uint2 own = half == 0 ? c0 : c1;
+    int i, k;
+    pair8_decode(e, i, k);
+    uint32_t key = (uint32_t)cx.R[byte_at(own, i) * RSTRIDE + byte_at(own, k)] << 8 | (uint32_t)e;
+    key = min(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x128, 0xF, 0xF, true));   // row_ror:8
+    key = min(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x124, 0xF, 0xF, true));
+    key = min(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x122, 0xF, 0xF, true));
+    key = min(key, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x121, 0xF, 0xF, true));
+    const int k0 = min(__builtin_amdgcn_readlane((int)key, 0), __builtin_amdgcn_readlane((int)key, 16)) & 0xFF;
+    const int k1 = min(__builtin_amdgcn_readlane((int)key, 32), __builtin_amdgcn_readlane((int)key, 48)) & 0xFF;
+    int slot[2][2];
+    pair8_decode(k0, slot[0][0], slot[0][1]);
+    pair8_decode(k1, slot[1][0], slot[1][1]);
+    // lanes 0, 1 of a quad: the mean over C_j' of w[x][.] for x = d1, d2; lanes 2, 3: the mean over C_j of w[y][.] for y = d1', d2'
+    const uint32_t x0 = byte_at(c0, slot[0][0]), x1 = byte_at(c0, slot[0][1]), y0 = byte_at(c1, slot[1][0]), y1 = byte_at(c1, slot[1][1]);
+    const uint32_t dv = (lane & 2) ? ((lane & 1) ? y1 : y0) : ((lane & 1) ? x1 : x0);
+    const uint2 other = (lane & 2) ? c0 : c1;
+    double w[8];
+#pragma unroll
+    for (int q = 0; q < 8; q++) w[q] = cx.Wpp[dv * NDEV + byte_of(other, q)];
+    const double link0 = cx.Wpp[x0 * NDEV + x1], link1 = cx.Wpp[y0 * NDEV + y1];
+    double sum = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; q++) sum = __dadd_rn(sum, w[q]);
+    const double mean = sum * 0.125;   // exact scaling, the same bits as the division
+    const double mx[2] = {dpp_move<0x00>(mean), dpp_move<0x55>(mean)}, my[2] = {dpp_move<0xAA>(mean), dpp_move<0xFF>(mean)};
+    double bestg = 0.0;
+    int bk = 0;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const double g = __dadd_rn(__dadd_rn(__dadd_rn(mx[q >> 1], -link0), my[q & 1]), -link1);
+        if (q == 0 || g > bestg) {
+            bestg = g;
+            bk = q;
+        }
+    }
+    const int a = 8 * j + slot[0][bk >> 1], b = 8 * jp + slot[1][bk & 1];
+    to[lane] = row[lane == a ? b : (lane == b ? a : lane)];
+    if (lane < 2) prop[lane] = (unsigned char)(lane == 0 ? a : b);
+}
+
 // Prices the row at SP_CUR and carries it through the rounds; the result stays at SP_CUR and SP_COST. applied: the row's moves,
 // or null. By the whole workgroup, the row visible to it; ends with a barrier.
-__device__ __forceinline__ void search_ahead(const wave_ctx &cx, unsigned char *sp, int moves, int64_t *applied)
+__device__ __forceinline__ void search_ahead(const wave_ctx &ctx, unsigned char *sp, int moves, int64_t *applied)
 {
-    const int lane = cx.lane, wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     unsigned char *cur = sp + SP_CUR, *pb = sp + SP_PB, *prop = sp + SP_PROP;
-    uint16_t *ghr = reinterpret_cast<uint16_t *>(sp + SP_GHR), *ghrcur = reinterpret_cast<uint16_t *>(sp + SP_GHRCUR);
+    uint16_t *ghr = reinterpret_cast<uint16_t *>(sp + SP_GHR), *from = reinterpret_cast<uint16_t *>(sp + SP_FROM);
     double *pp = reinterpret_cast<double *>(sp + SP_PP), *dp = reinterpret_cast<double *>(sp + SP_DP);
     double *cost = reinterpret_cast<double *>(sp + SP_COST), *dpcur = reinterpret_cast<double *>(sp + SP_DPCUR);
-    const int hc = (lane >> 3) & 3;
-    const bool relabel = lane >= 32;   // see hk_registers
-    const int v = relabel ? hk_swap01(cx.hv) : cx.hv;
+    const int ROW = 4;                 // the wavefront of the row itself
     int r = 0;
     bool first = true;
     do {
-        const int k = min(AHEAD, moves - r);   // rounds of this pass; zero only in the first
-        const bool trial = wave < 2 && 4 * wave < k;
-        if (trial) {
+        // what follows from the lane's number is worked out in each pass: kept from pass to pass it fills the registers
+        wave_ctx cx = ctx;
+        asm volatile("" : "+v"(cx.lane));
+        cx.hv = cx.lane & 7;
+        const int lane = cx.lane, hc = (lane >> 3) & 3;
+        const bool relabel = lane >= 32;   // see hk_registers
+        const int v = relabel ? hk_swap01(cx.hv) : cx.hv;
+        const int k = min(DEEP, moves - r), trials = 1 << k;   // rounds of this pass; none only in the first
+        auto stages = [&](int l, int &j, int &jp) { pair8_decode((r + l) % 28, j, jp); };
+        // the row of trial s, by a wavefront
+        auto propose = [&](int s) {
             int j, jp;
-            pair8_decode(min(r + 4 * wave + (lane >> 4), moves - 1) % 28, j, jp);
-            propose_gain4<4, true>(cx, cur, prop + 8 * wave, j, jp);
-            WAVE_LDS_SYNC();
+            stages(trial_level(s), j, jp);
+            const int b = trial_base(s);
+            propose_one(cx, b == 0 ? cur : pb + b * 64, prop + 2 * s, pb + s * 64, j, jp);
+        };
+        if (k > 0 && wave < 4) {
+            if (wave == 0) propose(1);
+        } else if (wave >= 4) {
+            // trial s has an edge from itself, or from the last trial on the way to it whose round had one of its stages, or
+            // from the current row
+            for (int t = 64 * (wave - 4) + lane; t < TRIALS * 28; t += 256) {
+                const int s = t / 28, e = t - 28 * s;
+                int a, b, x = s;
+                pair8_decode(e, a, b);
 #pragma unroll
-            for (int c = 0; c < 4; c++) {
-                const int s = 4 * wave + c, ta = prop[2 * s], tb = prop[2 * s + 1];
-                pb[s * 64 + lane] = cur[lane == ta ? tb : (lane == tb ? ta : lane)];
+                for (int step = 0; step < DEEP; step++) {
+                    int j, jp;
+                    stages(trial_level(max(x, 1)), j, jp);
+                    const bool here = x == 0 || a == j || a == jp || b == j || b == jp;
+                    x = here ? x : trial_base(x);
+                }
+                from[t] = (uint16_t)(x * 28 + e);
+            }
+        }
+        if (k > 1) {
+            __syncthreads();
+            if (wave < 2) propose(2 + wave);
+        }
+        if (k > 2) {
+            __syncthreads();
+            if (wave < 4) propose(4 + wave);
+        }
+        if (k > 3) {
+            __syncthreads();
+            if (wave < 4) {
+                propose(8 + wave);
+                propose(12 + wave);
             }
         }
         __syncthreads();
-        if (trial || (wave == 3 && first)) {
-            // lanes 2 t, 2 t + 1 share a couple of stage pairs: the 7 of the round's stages for each slot, or all 14 of the row
+        const bool trial = 4 * wave < trials && k > 0;   // of the first four wavefronts
+        if (trial || (wave == ROW && first)) {
+            // lanes 2 t, 2 t + 1 share a couple of stage pairs: the 7 of the round's stages for each trial, or all 14 of the row
             const int per = trial ? 7 : 14;
             int t = lane >> 1;
-            const bool valid = t < 28 && !(lane & 1) && (trial || t < 14);
+            const int s = trial ? max(4 * wave + min(t, 27) / per, 1) : 0;
+            const bool valid = t < 28 && !(lane & 1) && (trial ? 4 * wave + t / per > 0 : t < 14);
             if (t >= 28) t = 27;   // idle lanes repeat the last item and write nothing
-            const int s = trial ? 4 * wave + t / per : 0, q = t % per;
-            int sj = 0, sjp = 0, j1[2], j2[2];
-            if (trial) pair8_decode(min(r + s, moves - 1) % 28, sj, sjp);
+            const int q = t % per;
+            int j1[2], j2[2];
+            int a0, a1;
+            stages(trial_level(max(s, 1)), a0, a1);
 #pragma unroll
             for (int h = 0; h < 2; h++) {
                 if (trial) {
-                    // changed pair number e = 0..12: (sj, x) for the 7 stages x != sj, then (sjp, x) for the 6 others
+                    // changed pair number e = 0..12: (a0, x) for the 7 stages x != a0, then (a1, x) for the 6 others
                     const int e = 2 * q + h < 12 ? 2 * q + h : 12;
-                    int a = sj, x = e + (e >= sj ? 1 : 0);
+                    int a = a0, x = e + (e >= a0 ? 1 : 0);
                     if (e >= 7) {
-                        a = sjp;
+                        a = a1;
                         x = e - 7;
-                        x += x >= sj ? 1 : 0;
-                        x += x >= sjp ? 1 : 0;
+                        x += x >= a0 ? 1 : 0;
+                        x += x >= a1 ? 1 : 0;
                     }
                     j1[h] = a < x ? a : x;
                     j2[h] = a < x ? x : a;
@@ -746,31 +835,28 @@ __device__ __forceinline__ void search_ahead(const wave_ctx &cx, unsigned char *
             }
             const uint32_t g = match_couple_halves(cx, trial ? pb + s * 64 : cur, j1, j2);
             if (valid) {
-                uint16_t *to = trial ? ghr + s * 28 : ghrcur;
+                uint16_t *to = ghr + s * 28;
                 to[pair_index(j1[0], j2[0])] = (uint16_t)g;
                 to[pair_index(j1[1], j2[1])] = (uint16_t)(g >> 16);
             }
-        } else if (wave == 2) {
-            const double x = row_datap(cx, pb + (lane >> 3) * 64);   // rows of rounds beyond k: never looked at
-            if (cx.hv == 0) dp[lane >> 3] = x;
-            if (first) {
-                const double y = row_datap(cx, cur);
-                if (lane == 0) *dpcur = y;
+        } else if (wave == 5 || wave == 6) {
+            const int s = 8 * (wave - 5) + (lane >> 3);
+            if (8 * (wave - 5) < trials) {
+                const bool row = s == 0 || s >= trials;   // slot 0: the row itself
+                const double x = row_datap(cx, row ? cur : pb + s * 64);
+                if (cx.hv == 0 && !row) dp[s] = x;
+                if (lane == 0 && wave == 5 && first) *dpcur = x;
             }
         }
         __syncthreads();
-        if (trial || (wave == 3 && first)) {
-            const int s = 4 * wave + hc;
-            int sj = -1, sjp = -1;
-            if (trial) pair8_decode(min(r + s, moves - 1) % 28, sj, sjp);
+        if (trial || (wave == ROW && first)) {
+            const int s = trial ? max(4 * wave + hc, 1) : 0;
             double G[8];
             G[0] = 0.0;
 #pragma unroll
             for (int d = 1; d < 8; d++) {
                 const int u = v ^ (relabel ? hk_swap01(d) : d);
-                const int pi = pair_index(u < v ? u : v, u < v ? v : u);
-                const bool again = trial && (u == sj || u == sjp || v == sj || v == sjp);
-                G[d] = cx.rank_val[*(again ? ghr + s * 28 + pi : ghrcur + pi)];
+                G[d] = cx.rank_val[ghr[from[s * 28 + pair_index(u < v ? u : v, u < v ? v : u)]]];
             }
             const double x = hk_registers<true>(G, lane);
             if (cx.hv == 0 && lane < 32) {
@@ -779,36 +865,33 @@ __device__ __forceinline__ void search_ahead(const wave_ctx &cx, unsigned char *
             }
         }
         __syncthreads();
-        // the first round that is cheaper is accepted
-        const double now = *cost;
-        int take = k;
-        double best = 0.0;
-        for (int s = k - 1; s >= 0; s--) {
-            const double x = __dadd_rn(dp[s], pp[s]);
-            if (x < now) {
-                take = s;
-                best = x;
+        // the way that the rounds go
+        const double start = *cost;
+        double now = start;
+        int at = 1, base = 0;
+        for (int l = 0; l < k; l++) {
+            const double x = __dadd_rn(dp[at], pp[at]);
+            const bool take = x < now;
+            if (applied != nullptr && threadIdx.x == 0) {
+                const long long ta = prop[2 * at], tb = prop[2 * at + 1];
+                applied[r + l] = take ? ta * NDEV - ta * (ta + 1) / 2 + (tb - ta - 1) : -1ll;
             }
-        }
-        if (applied != nullptr && wave == 1 && lane < k && lane <= take) {
-            const long long ta = prop[2 * lane], tb = prop[2 * lane + 1];
-            applied[r + lane] = lane == take ? ta * NDEV - ta * (ta + 1) / 2 + (tb - ta - 1) : -1ll;
+            now = take ? x : now;
+            base = take ? at : base;
+            at = 2 * at + (take ? 1 : 0);
         }
         first = false;
         __syncthreads();
-        if (take < k) {
+        if (base != 0) {
             if (wave == 0) {
-                int sj, sjp;
-                pair8_decode((r + take) % 28, sj, sjp);
-                cur[lane] = pb[take * 64 + lane];
-                int a, b;
-                pair8_decode(lane < 28 ? lane : 27, a, b);
-                if (lane < 28 && (a == sj || a == sjp || b == sj || b == sjp)) ghrcur[lane] = ghr[take * 28 + lane];
-                if (lane == 0) *cost = best;
+                const uint16_t e = ghr[from[base * 28 + min(lane, 27)]];
+                cur[lane] = pb[base * 64 + lane];
+                if (lane < 28) ghr[lane] = e;
+                if (lane == 0) *cost = now;
             }
             __syncthreads();
         }
-        r += take < k ? take + 1 : k;
+        r += k;
     } while (r < moves);
 }
 
@@ -1112,7 +1195,7 @@ int dtfm_fast64_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t rows
     return DTFM_OK;
 }
 
-// Eight rounds at a time, by a workgroup an allocation: as many as there are CUs (one workgroup fits a CU).
+// Four rounds at a time, by a workgroup an allocation: as many as there are CUs (one workgroup fits a CU).
 static bool search_ahead_pays(const dtfm_problem *pr, size_t rows) { return rows <= (size_t)pr->f64_grid; }
 
 template <int NC>

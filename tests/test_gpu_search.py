@@ -232,9 +232,9 @@ def test_evolve_config1():
     _evolve_parity(w, 4, 5, 9, lam=4, m_x=3, m_m=2, ls_moves=0)
 
 
-@pytest.mark.parametrize("name,P,moves", [("C2", 1, 1), ("C2", 2, 7), ("C2b", 3, 8), ("C2", 4, 9), ("C3h", 3, 16), ("C2b", 5, 31)])
+@pytest.mark.parametrize("name,P,moves", [("C2", 1, 1), ("C2", 2, 2), ("C2", 2, 7), ("C2b", 3, 8), ("C2", 4, 9), ("C3h", 3, 16), ("C2b", 5, 31)])
 def test_gain4_rounds_ahead(name, P, moves):
-    # few rows: eight rounds are priced together; rounds that wrap around the 28 stage pairs and passes of all lengths
+    # few rows: four rounds are priced together; rounds that wrap around the 28 stage pairs and passes of all lengths
     w = workloads.config(name)
     _ls_parity(w, workloads.random_population(P, 64, seed=P), moves, dtfm.GAIN4)
 

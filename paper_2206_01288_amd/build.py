@@ -30,7 +30,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 # default scheduler orders them for low register pressure, which leaves every packed 16-bit result
 # one wait state away from its consumer. The ILP-first strategy interleaves the independent chains.
 _ILP = ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
-FILE_FLAGS = {"dtfm_fast64.hip": _ILP, "dtfm_fast64_allpairs.hip": _ILP}
+FILE_FLAGS = {"dtfm_fast64.hip": _ILP, "dtfm_fast64_allpairs.hip": _ILP,
+              "dtfm_match_lanes.hip": _ILP}
 
 
 def sources():

@@ -2,8 +2,8 @@
 //   k_weights     Sec. 2 symmetrisation + the per-link terms of Eqs. 2 and 3
 //   k_datap       Eq. 2 per stage and the max over stages (Sec. 3.2); for matrices beyond an XCD's L2
 //                 k_datap_sliced (by slice of devices) or k_positions + k_datap_rows + k_datap_reduce (by device)
-//   k_match       Eq. 3, stages of at most 16 devices: bottleneck perfect matching of one stage pair per wavefront; k_match16: of
-//                 four, when there are many (larger stages: dtfm_match.hip)
+//   k_match       Eq. 3, stages of 9 to 16 devices: bottleneck perfect matching of one stage pair per wavefront; k_match16: of
+//                 four, when there are many (smaller stages: dtfm_match_lanes.hip, larger ones: dtfm_match.hip)
 //   k_held_karp   Eq. 4: open-loop TSP over the coarsened graph, exact, by subset dynamic
 //                 programming; adds the two parts (Eq. 1); k_held_karp_blocked from 11 stages on
 //   k_trial_shortcut   trials of the local search that the coarsened graph settles without Eq. 4
@@ -409,8 +409,8 @@ k_match(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_val,
 // by the 16 lanes of its block and all four advance together. The steps are those of match_block, with one difference
 // that does not change the threshold reached: a turn lets two reached columns join instead of all of them, so that the
 // four searches stay in step. Codes are ranks here (N <= 256: at most 32,641 distinct weights), one solve is exact.
-// Measured, a whole evaluation: 3001 candidates of 7 stages of 12: 99.5 -> 77.9 us; 2000 of 9 stages of 5: 82 -> 55 us; 4096
-// of 16 stages of 16: 1055 -> 822 us, of 8: 754 -> 535 us. What bounds it: vector issue, 89 % of its slots on 16 stages of 16
+// Measured, a whole evaluation: 3001 candidates of 7 stages of 12: 99.5 -> 77.9 us; 4096 of 16 stages of 16: 1055 -> 822 us.
+// What bounds it: vector issue, 89 % of its slots on 16 stages of 16
 // (2,080 vector and 1,080 scalar instructions for four blocks).
 __device__ __forceinline__ uint32_t row16_min(uint32_t x)
 {
@@ -938,15 +938,15 @@ static bool datap_by_device(const dtfm_problem *pr)
     return (size_t)pr->N * pr->N * sizeof(double) > ((size_t)2 << 20) && pr->D_dp % 4 == 0 && pr->N % DTFM_DATAP_DPW == 0;
 }
 
-// Blocks of at most 16 rows go four to a wavefront (k_match16) when there are more of them than two rounds of k_match's
-// resident wavefronts (20 for each of 256 CUs), and than five at 16 rows. Below that a search of its own per wavefront ends
-// earlier than the longest of four, the more so the longer the searches are. Evaluation time with k_match over that with
-// k_match16 at 10,300 / 14,000 / 20,500 / 24,000 / 33,000 blocks, devices in regions: 16 rows (3 stages) 0.86 / 0.83 / 0.94 / 0.98 /
-// 1.05, (8 stages) 0.95 / 0.96 / 1.04 / 1.02 / 1.09; 12 rows (7 stages) 0.96 / 0.97 / 1.07 / 1.09 / 1.17; 8 rows (5 stages) 0.98 /
-// 1.06 / 1.16 / 1.18 / 1.23; 2 rows 1.05 / 1.17 / 1.34 / 1.43 / 1.48.
+// Blocks of 9 to 16 rows go four to a wavefront (k_match16) when there are more of them than 1536 for each row: below that a
+// search of its own per wavefront ends earlier than the longest of four, the more so the longer the searches are. Evaluation time
+// with k_match over that with k_match16 at 10,300 / 14,000 / 20,500 / 24,000 / 33,000 blocks, devices in regions: 16 rows (3 stages)
+// 0.86 / 0.83 / 0.94 / 0.98 / 1.05, (8 stages) 0.95 / 0.96 / 1.04 / 1.02 / 1.09; 12 rows (7 stages) 0.96 / 0.97 / 1.07 / 1.09 / 1.17.
+// Blocks of at most 8 rows go to k_match_lanes, one launch's time whatever their number (20 rows of 9 stages of 5 20.6 us by k_match,
+// 18.2; of 16 stages of 8 104.5 and 105.8).
 static bool four_blocks_a_wavefront(const dtfm_problem *pr, size_t blocks)
 {
-    return pr->D_dp <= 16 && blocks > (size_t)(pr->D_dp <= 6 ? 10240 : 1536 * pr->D_dp);
+    return blocks > (size_t)1536 * pr->D_dp;
 }
 
 dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t rows, size_t hk_grid_cap, bool lean)
@@ -1040,6 +1040,9 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         if (match_pairs > 0) {
         if (pr->D_dp > 16) {
             const int rc = dtfm_match_bits_enqueue(pr, perm, rows, match_pairs, b.ghat, inc_j, inc_jp, st);
+            if (rc != DTFM_OK) return rc;
+        } else if (pr->D_dp <= 8) {
+            const int rc = dtfm_match_lanes_enqueue(pr, perm, rows, match_pairs, b.ghat, inc_j, inc_jp, st);
             if (rc != DTFM_OK) return rc;
         } else if (four_blocks_a_wavefront(pr, rows * (size_t)match_pairs)) {
             hipLaunchKernelGGL(k_match16, dim3((unsigned)((rows + 3) / 4), (unsigned)match_pairs), dim3(DTFM_WAVE), 0, st, pr->W_code,

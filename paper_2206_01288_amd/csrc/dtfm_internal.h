@@ -158,6 +158,9 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
 int dtfm_match_prepare(dtfm_problem *pr);
 int dtfm_match_bits_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t rows, int pairs, double *ghat, int inc_j, int inc_jp,
                             hipStream_t st);
+// The same for stages of at most 8 devices (dtfm_match_lanes.hip)
+int dtfm_match_lanes_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t rows, int pairs, double *ghat, int inc_j, int inc_jp,
+                             hipStream_t st);
 // Stage pair number t of a launch (j1 < j2).
 __device__ __forceinline__ void dtfm_match_pair(int t, int D_pp, int inc_j, int inc_jp, int &j1, int &j2)
 {

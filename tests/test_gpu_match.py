@@ -1,5 +1,5 @@
-"""Matchings of blocks of at most 16 rows: four to a wavefront from 10,240 blocks on (1536 for each row from 7 rows on), one
-to a wavefront below. Populations that leave the last wavefront with one, two and three candidates, all block sizes at the edges, weights with
+"""Matchings of blocks of 9 to 16 rows: four to a wavefront from 1536 blocks for each row on, one to a wavefront below; of at most
+8 rows a lane for two; of more on bit masks. Populations that leave the last wavefront with one, two and three candidates, all block sizes at the edges, weights with
 many ties and without any, whole evaluations and the trials of the local search, against the oracle to the bit."""
 import numpy as np
 import pytest
@@ -139,4 +139,26 @@ def test_small_evaluations_in_one_launch(ties, D_dp, D_pp):
             rows_d = dev(perms[:P])
             cost_d, _ = dtfm.local_search(g, rows_d, moves, nb)
             assert np.array_equal(host(rows_d), rows) and np.array_equal(host(cost_d), cost)
+    dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp,P", [(1, 7, 1), (2, 7, 3), (3, 7, 171), (4, 8, 2), (5, 11, 40), (6, 9, 700), (7, 8, 5), (8, 7, 90),
+                                         (8, 16, 6)])
+@pytest.mark.parametrize("ties", [0, 3])
+def test_two_blocks_to_a_lane(ties, D_dp, D_pp, P):
+    # odd and even numbers of stage pairs (the odd one out is matched twice) and of trial pairs; 16 x 8: codes up to 8130
+    N = D_dp * D_pp
+    rng = np.random.default_rng(D_dp + 100 * D_pp)
+    lat = rng.uniform(1e-3, 0.1, (N, N)) if ties == 0 else rng.integers(1, ties + 1, (N, N)) * 0.01
+    lat, bw = np.triu(lat, 1) + np.triu(lat, 1).T, np.full((N, N), 1e9)
+    o, g = both(workloads.Workload("lanes", N, D_dp, D_pp, 1e8, 1e7, lat, bw, 0))
+    perms = workloads.random_population(P, N, seed=D_pp)
+    ghat = host(dtfm.coarsened_graph(g, dev(perms))[0])
+    some = np.r_[0:min(P, 6), max(P - 3, 0):P]
+    for p in some:
+        assert np.array_equal(ghat[p], o.coarsen(perms[p])), p
+    rows, want, _ = o.local_search(perms[some], 2, dtfm.KL)
+    rows_d = dev(perms)
+    cost_d, _ = dtfm.local_search(g, rows_d, 2, dtfm.KL)
+    assert np.array_equal(host(rows_d)[some], rows) and np.array_equal(host(cost_d)[some], want)
     dtfm.destroy_problem(g)

@@ -628,10 +628,11 @@ k_tour_search(const double *__restrict__ ghat, const double *__restrict__ datap,
     __shared__ tour_lds<PER> sm;
     const size_t todo = list != nullptr ? (size_t)count[0] : P;
     const int per = PER == 1 || todo <= SPREAD ? 1 : todo <= 2 * SPREAD ? 2 : WAVES;   // candidates of the workgroup
-    const size_t first = (size_t)blockIdx.x * per;
-    if (first >= todo) return;
+    // its candidates lie apart in the launch: neighbours are often trials of one row, and hard together
+    const size_t groups = (todo + per - 1) / per;
+    if (blockIdx.x >= groups) return;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const size_t idx = first + wave;
+    const size_t idx = (size_t)blockIdx.x + (size_t)wave * groups;
     if (rule.split && (size_t)count[2] == todo) return;
     const bool have = wave < per && idx < todo;
     const size_t p = have ? (list != nullptr ? (size_t)list[idx] : idx) : 0;

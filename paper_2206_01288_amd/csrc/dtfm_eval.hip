@@ -142,7 +142,7 @@ __global__ void k_datap_sliced(const double *__restrict__ W_dp, const int32_t *_
     }
 }
 
-// Eq. 2 by device, for the same large matrices as k_datap_sliced, when a stage is a whole number of 16-byte pieces of
+// Eq. 2 by device (datap_by_device), when a stage is a whole number of 16-byte pieces of
 // the row (D_dp a multiple of 4, rows 16-byte aligned). A gather of W_dp from L2 moves a cache sector per 8 bytes
 // used; here every workgroup keeps DTFM_DATAP_DPW rows of W_dp in LDS and sums, for each candidate of its share,
 // the row sums of those devices: the device's position comes from the inverse of the row (k_positions), the
@@ -932,10 +932,16 @@ size_t dtfm_hk_exchange_bytes(const dtfm_problem *pr)
     return ((nh << nh) << DTFM_HK_BLOCK_LOW) * sizeof(double);
 }
 
-// DataP by device (k_datap_rows) pays when W_dp is too large for an XCD's L2; it needs D_dp a multiple of 4
-static bool datap_by_device(const dtfm_problem *pr)
+// DataP by device (k_datap_rows) needs D_dp a multiple of 4. It pays when W_dp is too large for an XCD's L2, when a stage has so
+// many devices that the gathers of k_datap are its time, and in larger launches where three launches do not matter. Whole
+// evaluations by candidate (by device), 64 / 512 / 3000 rows: 4 stages of 32 26.4 / 31.2 / 92.9 (26.1 / 31.0 / 76.4) us, 2 of 64 32.7 / 40.9 /
+// 111.8 (27.6 / 34.1 / 63.9), 8 of 64 54.6 / 141 / 711 (47.0 / 92.4 / 397); 1024 / 3000 rows: 16 of 16 305 / 659 (299 / 634), 10 of 16 141 /
+// 369 (140 / 362), 7 of 16 55 / 101 (57 / 102), 5 of 20 44 / 90 (47 / 93), 9 of 8 25.5 / 48.6 (31.3 / 61.0).
+static bool datap_by_device(const dtfm_problem *pr, size_t rows)
 {
-    return (size_t)pr->N * pr->N * sizeof(double) > ((size_t)2 << 20) && pr->D_dp % 4 == 0 && pr->N % DTFM_DATAP_DPW == 0;
+    if (pr->D_dp % 4 != 0 || pr->N % DTFM_DATAP_DPW != 0 || rows < 64) return false;
+    return (size_t)pr->N * pr->N * sizeof(double) > ((size_t)2 << 20) || pr->D_dp >= 32 ||
+           (pr->D_dp >= 16 && pr->N >= 160 && rows >= 1024);
 }
 
 // Blocks of 9 to 16 rows go four to a wavefront (k_match16) when there are more of them than 1536 for each row: below that a
@@ -955,7 +961,7 @@ dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t ro
     size_t n = pr->D_pp;
     b.pos = nullptr;
     b.rowsum = nullptr;
-    if (!lean && datap_by_device(pr)) {
+    if (!lean && datap_by_device(pr, rows)) {
         b.pos = ar.take<int32_t>(rows * pr->N);
         b.rowsum = ar.take<double>(rows * pr->N);
     }
@@ -1011,8 +1017,8 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     }
     int threads = ((N + DTFM_WAVE - 1) / DTFM_WAVE) * DTFM_WAVE;
     if (threads > 1024) threads = 1024;
-    if (b.pos != nullptr && rows >= 64 && (reinterpret_cast<uintptr_t>(perm) & 15u) == 0) {
-        // W_dp larger than half an XCD's L2 and stages made of 16-byte pieces: rows of W_dp in LDS, by device
+    if (b.pos != nullptr && datap_by_device(pr, rows) && (reinterpret_cast<uintptr_t>(perm) & 15u) == 0) {
+        // rows of W_dp in LDS, by device
         const size_t total = rows * (size_t)N;
         hipLaunchKernelGGL(k_positions, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, perm, N, total, b.pos);
         DTFM_HIP(hipGetLastError());

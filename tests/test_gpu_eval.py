@@ -318,3 +318,24 @@ def test_reserve_keeps_hot_calls_from_growing_the_arena():
     with pytest.raises(dtfm.DtfmError):
         dtfm.reserve(g, -1)
     dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp,rows", [(32, 2, 64), (64, 2, 65), (32, 4, 70), (16, 10, 1024), (20, 8, 1027)])
+def test_datap_by_device_and_by_candidate(D_dp, D_pp, rows):
+    # the first size by device, and rows one short of it, or from an address in the middle of 16 bytes, by candidate
+    N = D_dp * D_pp
+    rng = np.random.default_rng(N)
+    lat, bw = rng.uniform(1e-3, 0.1, (N, N)), 10.0 ** rng.uniform(7, 9, (N, N))
+    lat, bw = np.triu(lat, 1) + np.triu(lat, 1).T, np.triu(bw, 1) + np.triu(bw, 1).T
+    np.fill_diagonal(bw, 1.0)
+    o, g = both(workloads.Workload("datap", N, D_dp, D_pp, 1e8, 1e7, lat, bw, 0))
+    perms = workloads.random_population(rows, N, seed=D_pp)
+    cost = host(dtfm.eval_population(g, dev(perms)))
+    some = np.r_[0:8, rows - 8:rows]
+    assert np.array_equal(cost[some], o.eval_population(perms[some]))
+    least = 1024 if D_dp < 32 else 64
+    assert np.array_equal(host(dtfm.eval_population(g, dev(perms[:least - 1]))), cost[:least - 1])
+    odd = torch.empty(rows * N + 1, dtype=torch.int32, device="cuda")
+    odd[1:] = dev(perms).reshape(-1)
+    assert np.array_equal(host(dtfm.eval_population(g, odd[1:].view(rows, N))), cost)
+    dtfm.destroy_problem(g)

@@ -174,6 +174,18 @@ def test_gain4_odd_shapes(D_dp, D_pp):
     _ls_parity(custom(N, D_dp, D_pp, seed=N), workloads.random_population(20, N, seed=4), 12, dtfm.GAIN4)
 
 
+@pytest.mark.parametrize("neighbourhood", [dtfm.GAIN4, dtfm.BEST4])
+@pytest.mark.parametrize("values", [1, 3, 2000])
+@pytest.mark.parametrize("D_dp,D_pp", [(17, 3), (31, 2), (32, 3), (33, 2), (48, 3), (49, 2), (63, 3), (64, 2)])
+def test_proposals_of_stages_of_more_than_16_devices(D_dp, D_pp, values, neighbourhood):
+    # the fastest link of a stage by digits: every link ties (1), many do (3), ranks of two digits whose leading one ties (2000)
+    N = D_dp * D_pp
+    lat = np.random.default_rng(N + values).integers(1, values + 1, (N, N)) * 1e-4
+    lat = np.triu(lat, 1) + np.triu(lat, 1).T
+    w = workloads.Workload("links", N, D_dp, D_pp, 1e7, 1e7, lat, np.full((N, N), 1e9), 0)
+    _ls_parity(w, workloads.random_population(3, N, seed=D_dp), 4, neighbourhood)
+
+
 @pytest.mark.parametrize("name,P,rounds", [("C1", 40, 14), ("C2", 64, 30), ("C2b", 24, 30), ("C3h", 8, 5)])
 def test_kl_neighbourhood_parity(name, P, rounds):
     w = workloads.config(name)

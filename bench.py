@@ -301,6 +301,7 @@ def main():
             t_front = time_eval(pg, perms, 5, 2, fn=lambda: dtfm.coarsened_graph(pg, perms, out=(gh, dpv)))
             og = algorithmic_ops(wg.N, wg.D_dp, wg.D_pp)
             t_hk = max(t_eval - t_front, 1e-9)
+            gather_peak = 256 * (2.30 if wg.D_dp > 16 else 1.74) * 2.4e9
             general[name] = {"population": Pg, "seconds_eval_population": t_eval,
                              "seconds_datap_and_matching": t_front, "seconds_tour": t_hk,
                              "candidates_per_s": Pg / t_eval,
@@ -308,12 +309,12 @@ def main():
                              "tour": {"candidates_per_s": Pg / t_hk},
                              "datap_and_matching": {"block_entries_per_s": og["matching_compulsory_ops"] * Pg / t_front,
                                                     "datap_adds_per_s": wg.N * (wg.D_dp - 1) * Pg / t_front,
-                                                    # every block entry is one lane of a gather from the table of codes;
-                                                    # bare gathers of 64 random 2-byte columns of a table row run at 1.74
+                                                    # every block entry is one lane of a gather from the table of digits
+                                                    # (bytes, stages of more than 16 devices) or of codes (2 bytes);
+                                                    # bare gathers of 64 random columns of a table row run at 2.30 and 1.74
                                                     # lanes per cycle and CU (profiles/gather_rate_gfx950.md)
-                                                    "gather_lanes_peak_per_s": 256 * 1.74 * 2.4e9,
-                                                    "frac_of_gather_rate": og["matching_compulsory_ops"] * Pg / t_front
-                                                                           / (256 * 1.74 * 2.4e9)},
+                                                    "gather_lanes_peak_per_s": gather_peak,
+                                                    "frac_of_gather_rate": og["matching_compulsory_ops"] * Pg / t_front / gather_peak},
                              "timing": "HIP events over 5 launches each of dtfm_eval_population and of dtfm_coarsened_graph "
                                        "(DataP + matching only); the tour = the difference"}
             dtfm.destroy_problem(pg)

@@ -1,7 +1,7 @@
-// Gather-rate microbenchmark for gfx950: how fast a CU serves the gathers of the general matching kernel. Every
-// wavefront reads ROWS rows of a block the way k_match does: row r of the table (wavefront-uniform, as if it were the
-// device of the block's row r) at 64 per-lane columns (the devices of the block's columns), entries of 2 or 4
-// bytes, table of 1024 x 1024 entries; the columns are random, sorted, or the 64 consecutive ones. The sum of what
+// Gather-rate microbenchmark for gfx950: how fast a CU serves the gathers of the general matching kernels. Every
+// wavefront reads ROWS rows of a block the way k_match_bits and k_match do: row r of the table (wavefront-uniform, as if it were the
+// device of the block's row r) at 64 per-lane columns (the devices of the block's columns), entries of 1, 2
+// or 4 bytes, table of 1024 x 1024 entries; the columns are random, sorted, or the 64 consecutive ones. The sum of what
 // was read is stored so that nothing is optimised away. Prints the time per launch and the cycles (at 2.4 GHz) a
 // CU spends per 64-lane gather.
 // Built and run by `python -m paper_2206_01288_amd.microbench`; its output backs the gather rate quoted in the
@@ -58,14 +58,17 @@ static int cmp_i32(const void *a, const void *b) { return *(const int32_t *)a - 
 int main()
 {
     const int waves = 4096 * 120;   // the blocks of one evaluation of 4096 candidates with 16 stages
+    uint8_t *t8;
     uint16_t *t16;
     uint32_t *t32, *out;
     int32_t *rows, *cols[3];
+    hipMalloc(&t8, (size_t)N * N);
     hipMalloc(&t16, (size_t)N * N * 2);
     hipMalloc(&t32, (size_t)N * N * 4);
     hipMalloc(&out, (size_t)waves * 64 * 4);
     hipMalloc(&rows, (size_t)waves * ROWS * 4);
     for (int i = 0; i < 3; i++) hipMalloc(&cols[i], (size_t)waves * 64 * 4);
+    hipMemset(t8, 1, (size_t)N * N);
     hipMemset(t16, 1, (size_t)N * N * 2);
     hipMemset(t32, 1, (size_t)N * N * 4);
     int32_t *h = (int32_t *)malloc((size_t)waves * 64 * 4);
@@ -84,6 +87,7 @@ int main()
     hipMemcpy(cols[2], h, (size_t)waves * 64 * 4, hipMemcpyHostToDevice);
     const char *order[3] = {"random", "sorted", "contiguous"};
     for (int i = 0; i < 3; i++) {
+        run<uint8_t>("u8", order[i], t8, rows, cols[i], out, waves);
         run<uint16_t>("u16", order[i], t16, rows, cols[i], out, waves);
         run<uint32_t>("u32", order[i], t32, rows, cols[i], out, waves);
     }

@@ -233,6 +233,7 @@ __device__ __forceinline__ void fastest_link_digits(const uint8_t *__restrict__ 
     link = best;
 }
 
+template <bool DIGITS>
 __global__ void k_gain4_propose(const double *__restrict__ W_pp, const uint8_t *__restrict__ code, const int32_t *__restrict__ perm,
                                 int N, int D_dp, int D_pp, int r, int32_t *__restrict__ tmp_perm,
                                 int32_t *__restrict__ move_ab)
@@ -248,7 +249,7 @@ __global__ void k_gain4_propose(const double *__restrict__ W_pp, const uint8_t *
     int slot[2][2];
     double link[2];
     for (int s = 0; s < 2; s++) {
-        if (code != nullptr) fastest_link_digits(code, W_pp, Cs[s], N, D_dp, lane, slot[s], link[s]);
+        if constexpr (DIGITS) fastest_link_digits(code, W_pp, Cs[s], N, D_dp, lane, slot[s], link[s]);
         else fastest_link(W_pp, Cs[s], N, D_dp, lane, slot[s], link[s]);
     }
     // rows 0, 1: w[x][.] over C_j' for x = d1, d2; rows 2, 3: w[y][.] over C_j
@@ -293,6 +294,7 @@ __global__ void k_gain4_propose(const double *__restrict__ W_pp, const uint8_t *
 // BEST4 (the four candidates of the paper's neighbourhood judged by the cost): one wavefront per candidate writes
 // the four swapped allocations of round r, rows 4 p .. 4 p + 3 of tmp_perm in the order (d1,d1'), (d1,d2'), (d2,d1'),
 // (d2,d2'), and their positions. The fastest link of a stage as in k_gain4_propose.
+template <bool DIGITS>
 __global__ void k_best4_propose(const double *__restrict__ W_pp, const uint8_t *__restrict__ code, const int32_t *__restrict__ perm,
                                 int N, int D_dp, int D_pp, int r, int32_t *__restrict__ tmp_perm,
                                 int32_t *__restrict__ move_ab)
@@ -307,7 +309,7 @@ __global__ void k_best4_propose(const double *__restrict__ W_pp, const uint8_t *
     int slot[2][2];
     double link;
     for (int s = 0; s < 2; s++) {
-        if (code != nullptr) fastest_link_digits(code, W_pp, Cs[s], N, D_dp, lane, slot[s], link);
+        if constexpr (DIGITS) fastest_link_digits(code, W_pp, Cs[s], N, D_dp, lane, slot[s], link);
         else fastest_link(W_pp, Cs[s], N, D_dp, lane, slot[s], link);
     }
     for (int k = 0; k < 4; k++) {
@@ -651,12 +653,18 @@ int dtfm_ls_enqueue(const dtfm_problem *pr, const dtfm_ls_bufs &b, int32_t *perm
                     DTFM_HIP(hipGetLastError());
                 }
             }
-            if (neighbourhood == DTFM_KL)
+            if (neighbourhood == DTFM_KL) {
                 hipLaunchKernelGGL(k_kl_propose, dim3((unsigned)P), dim3(DTFM_WAVE), 0, st, pr->W_pp, perm, N, pr->D_dp, pr->D_pp, r,
                                    b.tmp_perm, b.move_ab);
-            else
-                hipLaunchKernelGGL(neighbourhood == DTFM_BEST4 ? k_best4_propose : k_gain4_propose, dim3((unsigned)P), dim3(DTFM_WAVE), 0,
-                                   st, pr->W_pp, pr->digits.code, perm, N, pr->D_dp, pr->D_pp, r, b.tmp_perm, b.move_ab);
+            } else {
+                // by digits for stages of more than 16 devices; kernels of their own, since one that holds both ways starts later (68 rows
+                // of 64 devices, best of four: 6.6 us a launch against 7.5)
+                const bool digits = pr->digits.code != nullptr;
+                auto propose = neighbourhood == DTFM_BEST4 ? (digits ? k_best4_propose<true> : k_best4_propose<false>)
+                                                           : (digits ? k_gain4_propose<true> : k_gain4_propose<false>);
+                hipLaunchKernelGGL(propose, dim3((unsigned)P), dim3(DTFM_WAVE), 0, st, pr->W_pp, pr->digits.code, perm, N, pr->D_dp,
+                                   pr->D_pp, r, b.tmp_perm, b.move_ab);
+            }
             DTFM_HIP(hipGetLastError());
             const dtfm_trial_ref ref = {b.ghat_cur, b.pp_cur, b.cur, tpr};
             rc = dtfm_eval_inc_enqueue(pr, b.ev, b.tmp_perm, T, b.tmp_cost, j, jp, st, inc ? &ref : nullptr);

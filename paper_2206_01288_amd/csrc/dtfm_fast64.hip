@@ -691,6 +691,23 @@ __device__ __forceinline__ double row_datap(const wave_ctx &cx, const unsigned c
 // the trial whose row trial i starts from: the last accepted one on the way to it (0: the current row)
 __device__ __forceinline__ int trial_base(int i) { return i >> __ffs(i); }
 __device__ __forceinline__ int trial_level(int i) { return 31 - __clz(i); }
+// The trial that wavefront `wave` prices in the place `at` of its four. A place for which the pass has no trial repeats one that it
+// has: the rows of the others may never have been written, and bytes that name no device lead out of the tables.
+__host__ __device__ constexpr int priced_trial(int wave, int at, int trials)
+{
+    const int s = 4 * wave + at;
+    return s < 1 ? 1 : s < trials ? s : trials - 1;
+}
+constexpr bool priced_trials_are_proposed()
+{
+    for (int k = 1; k <= DEEP; k++)   // a pass of k rounds proposes the trials 1 to 2^k - 1
+        for (int s = 0; s < (((1 << k) + 3) & ~3); s++) {
+            const int at = priced_trial(s / 4, s % 4, 1 << k);
+            if (at < 1 || at >= 1 << k || (s >= 1 && s < 1 << k && at != s)) return false;
+        }
+    return true;
+}
+static_assert(priced_trials_are_proposed(), "every trial has its place, and no place has another's row");
 
 // propose_gain4 for one row by a whole wavefront, a lane per link of the two stages; the trial row goes to `to`
 __device__ __forceinline__ void propose_one(const wave_ctx &cx, const unsigned char *row, unsigned char *prop, unsigned char *to, int j,
@@ -808,8 +825,8 @@ __device__ __forceinline__ void search_ahead(const wave_ctx &ctx, unsigned char 
             // lanes 2 t, 2 t + 1 share a couple of stage pairs: the 7 of the round's stages for each trial, or all 14 of the row
             const int per = trial ? 7 : 14;
             int t = lane >> 1;
-            const int s = trial ? max(4 * wave + min(t, 27) / per, 1) : 0;
-            const bool valid = t < 28 && !(lane & 1) && (trial ? 4 * wave + t / per > 0 : t < 14);
+            const int s = trial ? priced_trial(wave, min(t, 27) / per, trials) : 0;
+            const bool valid = t < 28 && !(lane & 1) && (trial ? 4 * wave + t / per == s : t < 14);
             if (t >= 28) t = 27;   // idle lanes repeat the last item and write nothing
             const int q = t % per;
             int j1[2], j2[2];
@@ -850,7 +867,7 @@ __device__ __forceinline__ void search_ahead(const wave_ctx &ctx, unsigned char 
         }
         __syncthreads();
         if (trial || (wave == ROW && first)) {
-            const int s = trial ? max(4 * wave + hc, 1) : 0;
+            const int s = trial ? priced_trial(wave, hc, trials) : 0;
             double G[8];
             G[0] = 0.0;
 #pragma unroll

@@ -251,6 +251,16 @@ def test_gain4_rounds_ahead(name, P, moves):
     _ls_parity(w, workloads.random_population(P, 64, seed=P), moves, dtfm.GAIN4)
 
 
+@pytest.mark.parametrize("P", [1, 5, 256])
+def test_gain4_one_round_of_few_rows(P):
+    # two of the four places of a wavefront have no trial: they repeat one, and write nothing of their own
+    w = workloads.config("C2")
+    _ls_parity(w, workloads.random_population(P, 64, seed=P), 1, dtfm.GAIN4)
+    o, g = both(w)
+    ref = o.evolve(3, 3, P, lam=P, ls_moves=1)
+    assert all(np.array_equal(host(a), b) for a, b in zip(dtfm.evolve(g, 3, 3, P, lam=P, ls_moves=1), ref))
+
+
 def test_gain4_rounds_ahead_up_to_a_workgroup_a_cu():
     # 256 rows one to a workgroup, 257 four to a wavefront
     w = workloads.config("C2")

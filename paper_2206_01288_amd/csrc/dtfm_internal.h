@@ -38,6 +38,7 @@ struct dtfm_digits {
     double *first;     // device: the smallest weight of every leading digit, 128 with +inf behind the last; the allocation
     int levels;        // digits of a rank
     int top[3];        // largest value of each
+    int usual;         // leading digit that the optimum of a block usually has
 };
 
 struct dtfm_problem {

@@ -3,15 +3,19 @@
 // The optimum of a block (the rows: devices of one stage, the columns: of another) is one of its entries and depends on
 // their order only, so the ranks of the weights stand for them. Written in base 127 a rank has one to three digits; each
 // digit of every entry is a byte of a table of its own (code). A wavefront takes a block, lane = column:
-//   digits     the lane gathers the leading digits of its column, a byte an entry (64 rows: 16 registers), and the optimum's
-//              digit T is sought: the smallest one within which a perfect matching exists.
-//   masks      one subtraction compares four bytes with a threshold, so the rows that the column reaches within it are a
-//              64-bit mask a lane after 48 instructions. An alternating-path search then takes a handful of instructions a
+//   digits     the lane gathers the leading digits of its column, a byte an entry (24, 32, 48 or 64 rows: 8 or 16 registers),
+//              and the optimum's digit T is sought: the smallest one within which a perfect matching exists.
+//   masks      one subtraction compares four bytes with a threshold, so the rows that the column reaches within it are a mask
+//              a lane of 32 or 64 bits after 24 or 48 instructions. An alternating-path search then takes a handful of instructions a
 //              level, whatever the number of rows in it: the columns reached are the lanes whose mask meets the set of rows
 //              (one ballot), the rows matched to them the lanes whose column is among those (another).
-//   thresholds start at the digit of the wavefront's last block (or of the edge that a trial changes) and go up after a
-//              failed search, down after a success, in growing steps until both bounds are known. A matching stays valid
-//              when the threshold rises, and loses the edges above it when it falls, so a step repairs a few rows.
+//   thresholds start at the digit of the wavefront's last block (or of the edge that a trial changes; the first block: at
+//              the usual digit of the problem's blocks, dtfm_match_prepare) and go up after a failed search, down after a
+//              success, in growing steps until both bounds are known. A matching stays valid when the threshold rises, and loses
+//              the edges above it when it falls, so a step repairs a few rows; where a step down leaves more than a few of
+//              them free, they bid again before they are searched for one by one. Networks whose links are all of their own have
+//              their optimum at a small digit: with a first threshold of 31 and no second bids 1000 allocations of 8 stages of
+//              64 took 217 us (the searches by smallest entries before this kernel 183), now 126; of 8 of 33 128 (76), now 88.
 //   ranks      the entries with digit T (some 33 of 4096 on 1024 devices) are told apart by their ranks: a lane lists those of
 //              its column, and the rows that the matching below T leaves free are inserted by searches that, when stuck,
 //              admit the smallest listed entry from a reached row to a column not yet reached. Reached rows own one column
@@ -26,12 +30,17 @@
 
 #include <math.h>
 
+#include <algorithm>
+#include <type_traits>
+#include <vector>
+
 // x with lane `lane` set to value
 __device__ int lane_write(int value, int lane, int x) __asm("llvm.amdgcn.writelane.i32");
 
 namespace {
 
 constexpr int LIST = 6;        // entries of a column that are told apart by their ranks
+constexpr int BIDS = 5;        // as many free rows are matched by searches of their own, more by rounds of bids first
 constexpr int WAVES = 4;       // wavefronts of a workgroup (launches of few blocks: one); they share nothing
 
 __device__ __forceinline__ int first_bit(uint64_t m)   // scalar; -1: empty
@@ -40,13 +49,26 @@ __device__ __forceinline__ int first_bit(uint64_t m)   // scalar; -1: empty
     asm("s_ff1_i32_b64 %0, %1" : "=s"(c) : "s"(m));
     return c;
 }
-__device__ __forceinline__ int lane_first_bit(uint64_t m)   // per lane; m = 0: -1
+__device__ __forceinline__ int first_bit(uint32_t m)
+{
+    int c;
+    asm("s_ff1_i32_b32 %0, %1" : "=s"(c) : "s"(m));
+    return c;
+}
+__device__ __forceinline__ int lane_first_bit(uint32_t m)   // per lane; m = 0: -1
+{
+    int c;
+    asm("v_ffbl_b32 %0, %1" : "=v"(c) : "v"(m));
+    return c;
+}
+__device__ __forceinline__ int lane_first_bit(uint64_t m)
 {
     uint32_t lo, hi;
     asm("v_ffbl_b32 %0, %1" : "=v"(lo) : "v"((uint32_t)m));   // ~0 for 0
     asm("v_ffbl_b32 %0, %1" : "=v"(hi) : "v"((uint32_t)(m >> 32)));
     return (int)min(lo, hi | 32u);
 }
+__device__ __forceinline__ bool any_bit(uint32_t m) { return m != 0u; }
 __device__ __forceinline__ bool any_bit(uint64_t m)   // per lane, on 32-bit instructions: a 64-bit comparison takes longer than two
 {
     uint32_t x;
@@ -74,18 +96,26 @@ __device__ __forceinline__ void lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Rows whose byte is at most t (t from -1; bytes at most 127): bit 8 k + i for byte k of E[i], 32 + 8 k + i of E[8 + i].
+// A lane's set of rows of a block.
 template <int R>
-__device__ __forceinline__ uint64_t within(const uint32_t (&E)[R / 4], int t)
+using rowset = std::conditional_t<R <= 32, uint32_t, uint64_t>;
+
+// Registers of a lane's column of R rows: row 8 k + i is byte k of the i-th, row 32 + 8 k + i of the (8 + i)-th.
+template <int R>
+constexpr int regs = R <= 32 ? 8 : 16;
+
+// Rows whose byte is at most t (t from -1; bytes at most 127), as bits; those from R on have any value.
+template <int R>
+__device__ __forceinline__ rowset<R> within(const uint32_t (&E)[regs<R>], int t)
 {
     const uint32_t top = (uint32_t)(0x80 + t) * 0x01010101u;   // a byte's difference keeps its bit 7 iff the byte is <= t
     uint32_t lo = 0u, hi = 0u;
 #pragma unroll
     for (int i = 0; i < 8; i++) lo = (lo >> 1) | ((top - E[i]) & 0x80808080u);
-    if constexpr (R == 64)
+    if constexpr (R > 32)
 #pragma unroll
         for (int i = 0; i < 8; i++) hi = (hi >> 1) | ((top - E[8 + i]) & 0x80808080u);
-    return (uint64_t)hi << 32 | lo;
+    return (rowset<R>)((uint64_t)hi << 32 | lo);
 }
 
 // A matching of the block: free rows and columns as masks, lane b holds the column of row b and the row of column b.
@@ -95,15 +125,20 @@ struct matching {
 };
 
 // the path that ends in the free column c, back to the free row r0; from: the rows that reached the lane's column
-__device__ __forceinline__ void augment(matching &m, uint64_t from, int c, int r0)
+template <typename M>
+__device__ __forceinline__ void augment(matching &m, M from, int c, int r0)
 {
     m.freecols &= ~(1ull << c);
     m.freerows &= ~(1ull << r0);
     int r;
     do {   // to a column reached a turn earlier
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)from, c);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(from >> 32), c);
-        r = first_bit((uint64_t)hi << 32 | lo);
+        if constexpr (sizeof(M) == 4) {
+            r = first_bit(lo);
+        } else {
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(from >> 32), c);
+            r = first_bit((uint64_t)hi << 32 | lo);
+        }
         const int prev = __builtin_amdgcn_readlane(m.col_of, r);
         m.row_of = lane_write(r, c, m.row_of);
         m.col_of = lane_write(c, r, m.col_of);
@@ -112,16 +147,18 @@ __device__ __forceinline__ void augment(matching &m, uint64_t from, int c, int r
 }
 
 // Matches every free row within the masks; false: no perfect matching (the free rows left stay free).
-__device__ __forceinline__ bool complete(matching &m, uint64_t adj)
+template <typename M>
+__device__ __forceinline__ bool complete(matching &m, M adj)
 {
     while (m.freerows != 0ull) {
         const int r0 = first_bit(m.freerows);
-        const uint64_t col = 1ull << m.col_of;
-        uint64_t t = adj & (1ull << r0), cols = __ballot(any_bit(t)), seen = 0ull, hit = cols & m.freecols, from = t;
+        const M col = (M)1 << m.col_of;
+        M t = adj & ((M)1 << r0), from = t;
+        uint64_t cols = __ballot(any_bit(t)), seen = 0ull, hit = cols & m.freecols;
         while (hit == 0ull && cols != 0ull) {   // a turn reaches a new column or ends the search
             seen |= cols;
-            const uint64_t rows = __ballot(any_bit(col & cols)) & ~m.freerows;
-            t = adj & rows;
+            const uint64_t rows = __ballot(any_bit((M)(col & (M)cols))) & ~m.freerows;
+            t = adj & (M)rows;
             cols = __ballot(any_bit(t)) & ~seen;
             from = in_lanes(cols) ? t : from;
             hit = cols & m.freecols;
@@ -133,10 +170,11 @@ __device__ __forceinline__ bool complete(matching &m, uint64_t adj)
 }
 
 // takes the edges that the masks no longer hold out of the matching
-__device__ __forceinline__ void release(matching &m, uint64_t adj, uint64_t columns)
+template <typename M>
+__device__ __forceinline__ void release(matching &m, M adj, uint64_t columns)
 {
-    const uint64_t lost = ~__ballot(any_bit(adj & (1ull << m.row_of))) & columns & ~m.freecols;
-    const uint64_t rows = __ballot(any_bit(lost & (1ull << m.col_of))) & ~m.freerows;
+    const uint64_t lost = ~__ballot(any_bit((M)(adj & ((M)1 << m.row_of)))) & columns & ~m.freecols;
+    const uint64_t rows = __ballot(any_bit((M)((M)lost & ((M)1 << m.col_of)))) & columns & ~m.freerows;
     m.freecols |= lost;
     m.freerows |= rows;
 }
@@ -144,14 +182,15 @@ __device__ __forceinline__ void release(matching &m, uint64_t adj, uint64_t colu
 // Rounds in which every free column bids for a row it reaches, and the last bid in LDS wins it. The columns look upwards
 // from their own number: bids for the lowest rows alone would meet.
 template <int R>
-__device__ __forceinline__ void bids(matching &m, int lane, uint64_t adj, uint64_t rows, uint32_t *slot)
+__device__ __forceinline__ void bids(matching &m, int lane, rowset<R> adj, uint64_t rows, uint32_t *slot)
 {
-    const uint64_t up = ~0ull << (lane & (R - 1));
-    slot[lane] = ~0u;
+    using M = rowset<R>;
+    const M up = (M)~0ull << (lane & (R <= 32 ? 31 : 63));
+    slot[lane] = in_lanes(rows & ~m.freerows) ? (uint32_t)m.col_of : ~0u;
     lds_order();
 #pragma unroll
     for (int round = 0; round < 4; round++) {
-        const uint64_t open = adj & m.freerows, above = open & up;
+        const M open = adj & (M)m.freerows, above = open & up;
         const bool bid = any_bit(open) && in_lanes(m.freecols);
         const int r = lane_first_bit(any_bit(above) ? above : open);
         if (bid) slot[r] = (uint32_t)lane;
@@ -161,11 +200,11 @@ __device__ __forceinline__ void bids(matching &m, int lane, uint64_t adj, uint64
         m.freecols &= ~__ballot(won);
         m.freerows = rows & ~__ballot(slot[lane] != ~0u);
     }
-    m.col_of = (int)slot[lane] & 63;
+    m.col_of = (int)slot[lane] & (R <= 32 ? 31 : 63);
 }
 
 // One wavefront after another takes the blocks of stage pair (wavefront mod pairs) of every `chunks`-th candidate.
-// R: rows of the masks (32 or 64), at least D_dp.
+// R: rows that are gathered (24, 32, 48 or 64), at least D_dp.
 template <int R>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(7)))
 k_match_bits(dtfm_digits dg, const uint32_t *__restrict__ Wrank, const double *__restrict__ rank_val,
@@ -183,14 +222,15 @@ k_match_bits(dtfm_digits dg, const uint32_t *__restrict__ Wrank, const double *_
     uint32_t *slot = slots[wave];
     const uint64_t all = D_dp >= 64 ? ~0ull : (1ull << D_dp) - 1ull;
     const bool active = lane < D_dp;
-    const uint64_t mine = active ? all : 0ull;
+    using M = rowset<R>;
+    const M mine = active ? (M)all : 0;
     const uint32_t last = (uint32_t)N - 1u;
     double first[2];   // the smallest weight of digits lane and lane + 64
     if (inc_j >= 0) {
         first[0] = dg.first[lane];
         first[1] = dg.first[64 + lane];
     }
-    int guess = dg.top[0] / 4;
+    int guess = dg.usual;
     for (int p = chunk; p < P; p += chunks) {
         const int32_t *row = perm + (size_t)p * N, *Ca = row + j1 * D_dp;
         double *G = ghat + (size_t)p * D_pp * D_pp;
@@ -200,15 +240,16 @@ k_match_bits(dtfm_digits dg, const uint32_t *__restrict__ Wrank, const double *_
             guess = max(__popcll(__ballot(first[0] <= v)) + __popcll(__ballot(first[1] <= v)) - 1, 0);
         }
         const uint32_t rowdev = active ? min((uint32_t)Ca[lane], last) : 0u, rowat = rowdev * (uint32_t)N;
-        uint32_t E[R / 4];
+        uint32_t E[regs<R>];
         auto gather = [&](int level) {
             const auto W = __builtin_amdgcn_make_buffer_rsrc(dg.code + (size_t)level * N * N, 0, N * N, 0x00027000);
 #pragma unroll
-            for (int h = 0; h < R / 32; h++) {   // 32 rows in flight
+            for (int h = 0; 32 * h < R; h++) {   // at most 32 rows in flight
                 uint32_t x[32];
 #pragma unroll
                 for (int b = 0; b < 32; b++)
-                    x[b] = __builtin_amdgcn_raw_buffer_load_b8(W, (int)coldev, __builtin_amdgcn_readlane((int)rowat, 32 * h + b), 0);
+                    x[b] = 32 * h + b < R ? __builtin_amdgcn_raw_buffer_load_b8(W, (int)coldev, __builtin_amdgcn_readlane((int)rowat, 32 * h + b), 0)
+                                          : 0u;
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int i = 0; i < 8; i++) E[8 * h + i] = (x[i] | x[8 + i] << 8) | (x[16 + i] | x[24 + i] << 8) << 16;
@@ -217,21 +258,19 @@ k_match_bits(dtfm_digits dg, const uint32_t *__restrict__ Wrank, const double *_
         };
         gather(0);
         matching m = {all, all, 0, 0};
-        uint64_t low = 0ull, eq = mine;
+        M low = 0, eq = mine;
         uint32_t result = ~0u;
-        bool begun = false;
         for (int level = 0; level < dg.levels; level++) {
             // a matching exists within digit hi, and none within digit lo
             int lo = -1, hi = dg.top[level], t = level == 0 ? guess : hi >> 1, step = 1;
             bool above = level != 0, below = level != 0;   // the bounds are close: halve what lies between
-            uint64_t upto = low | eq, under = low;         // the masks within hi and lo
+            M upto = low | eq, under = low;                // the masks within hi and lo
             bool fell = false;                             // the matching may hold edges above lo
             while (hi - lo > 1) {
                 t = min(max(t, lo + 1), hi - 1);
-                const uint64_t adj = low | (eq & within<R>(E, t));
-                if (!begun) bids<R>(m, lane, adj, all, slot);
-                else if (fell) release(m, adj, all);
-                begun = true;
+                const M adj = low | (eq & within<R>(E, t));
+                if (fell) release(m, adj, all);
+                if (__popcll(m.freerows) > BIDS) bids<R>(m, lane, adj, all, slot);
                 fell = complete(m, adj);
                 if (fell) {
                     hi = t;
@@ -251,48 +290,50 @@ k_match_bits(dtfm_digits dg, const uint32_t *__restrict__ Wrank, const double *_
             eq = upto & ~low;
             if (level == 0) guess = hi;
             if (level + 1 == dg.levels) {   // all of one rank
-                const uint64_t who = __ballot(eq != 0ull);
-                const int r = eq != 0ull ? lane_first_bit(eq) : 0;
+                const uint64_t who = __ballot(any_bit(eq));
+                const int r = any_bit(eq) ? lane_first_bit(eq) : 0;
                 const uint32_t d = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * r, (int)rowdev);
-                const uint32_t k = eq != 0ull ? Wrank[d * (uint32_t)N + coldev] : 0u;
+                const uint32_t k = any_bit(eq) ? Wrank[d * (uint32_t)N + coldev] : 0u;
                 result = (uint32_t)__builtin_amdgcn_readlane((int)k, max(first_bit(who), 0));
                 break;
             }
-            if (__ballot(__popcll(eq) > LIST) != 0ull) {
+            if (__ballot((R <= 32 ? __popc((uint32_t)eq) : __popcll(eq)) > LIST) != 0ull) {
                 gather(level + 1);
                 continue;
             }
             uint32_t key[LIST];   // rank and row
 #pragma unroll
             for (int q = 0; q < LIST; q++) {
-                const bool has = eq != 0ull;
+                const bool has = any_bit(eq);
                 const int r = has ? lane_first_bit(eq) : 0;
                 const uint32_t d = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * r, (int)rowdev);
                 key[q] = has ? Wrank[d * (uint32_t)N + coldev] << 6 | (uint32_t)r : ~0u;
-                eq &= eq - 1ull;
+                eq &= eq - 1;
             }
             uint32_t rank = 0u;
-            uint64_t adj = low;
+            M adj = low;
             while (m.freerows != 0ull) {
                 const int r0 = first_bit(m.freerows);
-                const uint64_t col = 1ull << m.col_of;
-                uint64_t rows = 1ull << r0, reached = rows, seen = 0ull, hit, from = 0ull;
+                const M col = (M)1 << m.col_of;
+                M from = 0;
+                uint64_t rows = 1ull << r0, reached = rows, seen = 0ull, hit;
                 do {   // a turn reaches a column, or admits an edge to one
-                    const uint64_t t = adj & rows, cols = __ballot(any_bit(t)) & ~seen;
+                    const M t = adj & (M)rows;
+                    const uint64_t cols = __ballot(any_bit(t)) & ~seen;
                     from = in_lanes(cols) ? t : from;
                     hit = cols & m.freecols;
                     seen |= cols;
-                    rows = __ballot(any_bit(col & cols)) & ~m.freerows;
+                    rows = __ballot(any_bit((M)(col & (M)cols))) & ~m.freerows;
                     reached |= rows;
                     if (cols == 0ull) {
                         uint32_t k = ~0u;
 #pragma unroll
-                        for (int q = 0; q < LIST; q++) k = min(k, ((reached >> (key[q] & 63u)) & 1ull) != 0ull ? key[q] : ~0u);
+                        for (int q = 0; q < LIST; q++) k = min(k, (((M)reached >> (key[q] & (R <= 32 ? 31u : 63u))) & 1) != 0 ? key[q] : ~0u);
                         k = in_lanes(seen) ? ~0u : k;
                         const uint32_t least = wave_min(k) >> 6;
                         if (least == ~0u >> 6) break;   // cannot happen: a matching exists within hi
                         rank = max(rank, least);
-                        adj |= k >> 6 == least ? 1ull << (k & 63u) : 0ull;
+                        adj |= k >> 6 == least ? (M)1 << (k & (R <= 32 ? 31u : 63u)) : (M)0;
                         rows = reached;
                     }
                 } while (hit == 0ull);
@@ -331,6 +372,43 @@ __global__ void k_digit_first(const double *__restrict__ rank_val, int ranks, in
 
 }  // namespace
 
+// The digit that the searches begin at: the usual one of the blocks of a random allocation (D_pp (D_pp - 1) / 2 of them).
+static int dtfm_match_usual(dtfm_problem *pr)
+{
+    const int N = pr->N, n = pr->D_pp;
+    if (pr->npairs < 1) {
+        DTFM_HIP(hipDeviceSynchronize());
+        return DTFM_OK;
+    }
+    std::vector<int32_t> row(N);
+    uint32_t x = 1u;
+    for (int q = 0; q < N; q++) {
+        x = x * 1664525u + 1013904223u;
+        const int at = (int)(((uint64_t)x * (uint64_t)(q + 1)) >> 32);
+        row[q] = row[at];
+        row[at] = q;
+    }
+    std::vector<double> first(128), graph((size_t)n * n), edges;
+    char *mem = nullptr;
+    DTFM_HIP(hipMalloc((void **)&mem, graph.size() * sizeof(double) + row.size() * sizeof(int32_t)));
+    double *ghat = reinterpret_cast<double *>(mem);
+    int32_t *perm = reinterpret_cast<int32_t *>(mem + graph.size() * sizeof(double));
+    int rc = DTFM_OK;
+    hipError_t e = hipMemcpy(perm, row.data(), row.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) rc = dtfm_match_bits_enqueue(pr, perm, 1, pr->npairs, ghat, -1, -1, (hipStream_t) nullptr);
+    if (e == hipSuccess && rc == DTFM_OK) e = hipMemcpy(graph.data(), ghat, graph.size() * sizeof(double), hipMemcpyDeviceToHost);
+    if (e == hipSuccess && rc == DTFM_OK) e = hipMemcpy(first.data(), pr->digits.first, 128 * sizeof(double), hipMemcpyDeviceToHost);
+    (void)hipFree(mem);
+    if (rc != DTFM_OK) return rc;
+    DTFM_HIP(e);
+    for (int a = 0; a < n; a++)
+        for (int b = a + 1; b < n; b++) edges.push_back(graph[a * n + b]);
+    std::nth_element(edges.begin(), edges.begin() + edges.size() / 2, edges.end());
+    const double usual = edges[edges.size() / 2];
+    pr->digits.usual = (int)std::max<ptrdiff_t>(std::upper_bound(first.begin(), first.end(), usual) - first.begin() - 1, 0);
+    return DTFM_OK;
+}
+
 // W_rank and rank_val are there
 int dtfm_match_prepare(dtfm_problem *pr)
 {
@@ -352,8 +430,8 @@ int dtfm_match_prepare(dtfm_problem *pr)
     DTFM_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_digit_first, dim3(1), dim3(128), 0, (hipStream_t) nullptr, pr->rank_val, ranks, w1, dg.first);
     DTFM_HIP(hipGetLastError());
-    DTFM_HIP(hipDeviceSynchronize());
-    return DTFM_OK;
+    dg.usual = dg.top[0] / 4;
+    return dtfm_match_usual(pr);
 }
 
 int dtfm_match_bits_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t rows, int pairs, double *ghat, int inc_j, int inc_jp,
@@ -362,7 +440,8 @@ int dtfm_match_bits_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t 
     // twice the wavefronts that the chip holds, each with as many candidates of one stage pair as that takes
     const size_t share = ((size_t)2 * 256 * 32 + pairs - 1) / pairs, chunks = rows < share ? rows : share;
     const unsigned waves = (unsigned)(chunks * pairs), w = waves <= 2048u ? 1u : WAVES;
-    hipLaunchKernelGGL(pr->D_dp <= 32 ? k_match_bits<32> : k_match_bits<64>, dim3((waves + w - 1) / w), dim3(64 * w), 0, st, pr->digits,
+    auto kern = pr->D_dp <= 24 ? k_match_bits<24> : pr->D_dp <= 32 ? k_match_bits<32> : pr->D_dp <= 48 ? k_match_bits<48> : k_match_bits<64>;
+    hipLaunchKernelGGL(kern, dim3((waves + w - 1) / w), dim3(64 * w), 0, st, pr->digits,
                        pr->W_rank, pr->rank_val, perm, pr->N, pr->D_dp, pr->D_pp, ghat, (int)rows, inc_j, inc_jp, pairs, (int)chunks);
     DTFM_HIP(hipGetLastError());
     return DTFM_OK;

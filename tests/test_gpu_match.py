@@ -162,3 +162,30 @@ def test_two_blocks_to_a_lane(ties, D_dp, D_pp, P):
     cost_d, _ = dtfm.local_search(g, rows_d, 2, dtfm.KL)
     assert np.array_equal(host(rows_d)[some], rows) and np.array_equal(host(cost_d)[some], want)
     dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp", [48, 64])
+def test_links_of_their_own_take_no_longer(D_dp):
+    # every link of its own: optima of small digits, which a descent from a larger one reaches by losing most of the matching
+    N, P = 8 * D_dp, 1000
+    rng = np.random.default_rng(D_dp)
+    best = {}
+    perms = dev(workloads.random_population(P, N, seed=1))
+    for kind in ("own", "regions"):
+        lat = rng.uniform(1e-3, 0.1, (N, N))
+        if kind == "regions":
+            of = np.arange(N) * 8 // N
+            lat = rng.uniform(0.02, 0.25, (8, 8))[np.ix_(of, of)] * rng.uniform(0.95, 1.05, (N, N))
+        lat = np.triu(lat, 1) + np.triu(lat, 1).T
+        g = dtfm.create_problem(lat, np.full((N, N), 1e9), 1e7, 1e7, D_dp, 8)
+        out = dtfm.coarsened_graph(g, perms)
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                dtfm.coarsened_graph(g, perms, out=out)
+            b.record()
+            b.synchronize()
+            best[kind] = min(best.get(kind, np.inf), a.elapsed_time(b))
+        dtfm.destroy_problem(g)
+    assert best["own"] <= 1.25 * best["regions"], best

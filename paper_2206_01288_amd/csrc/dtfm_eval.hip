@@ -149,7 +149,8 @@ __global__ void k_datap_sliced(const double *__restrict__ W_dp, const int32_t *_
 // members of its stage are read as contiguous 16-byte pieces, and the entries come from LDS. The sum runs over
 // the stage's slots in order from +0.0; the device's own slot adds W_dp[d][d] = +0.0, which leaves the (non-
 // negative) sum as it is, so the bits are those of the sum that skips it. Row sums go to rowsum[p][position];
-// k_datap_reduce takes the maximum per candidate.
+// k_datap_reduce takes the maximum per candidate, and sums a row that repeats a device, whose inverse does not
+// exist, by position.
 #define DTFM_DATAP_DPW 4
 #define DTFM_DATAP_SPLIT 4   // workgroups that share a group of devices; each takes every SPLIT-th pass of candidates
 
@@ -192,16 +193,34 @@ k_datap_rows(const double *__restrict__ W_dp, const int32_t *__restrict__ perm, 
 }
 
 // max over a candidate's row sums (all weights are >= 0, so every row sum is >= +0.0); also zeroes the diagonal
-// of the candidate's coarsened graph
+// of the candidate's coarsened graph. The positions of a row are those of its devices unless one is repeated.
 __global__ void __launch_bounds__(256)
-k_datap_reduce(const double *__restrict__ rowsum, int N, int D_pp, double *__restrict__ datap, double *__restrict__ ghat,
+k_datap_reduce(const double *__restrict__ W_dp, const int32_t *__restrict__ perm, const int32_t *__restrict__ pos,
+               const double *__restrict__ rowsum, int N, int D_dp, int D_pp, double *__restrict__ datap, double *__restrict__ ghat,
                int32_t *__restrict__ count)
 {
     clear_counts(count);
     __shared__ double s_red[4];
     const size_t p = blockIdx.x;
+    const int32_t *row = perm + p * N;
+    const uint32_t last = (uint32_t)N - 1u;
     double worst = 0.0;
-    for (int q = threadIdx.x; q < N; q += blockDim.x) worst = fmax(worst, rowsum[p * N + q]);
+    bool repeats = false;
+    for (int q = threadIdx.x; q < N; q += blockDim.x) {
+        worst = fmax(worst, rowsum[p * N + q]);
+        repeats |= pos[p * N + min((uint32_t)row[q], last)] != q;
+    }
+    if (__syncthreads_or(repeats)) {
+        worst = 0.0;
+        for (int q = threadIdx.x; q < N; q += blockDim.x) {
+            const int j = q / D_dp, i = q - j * D_dp;
+            const double *wr = W_dp + (size_t)min((uint32_t)row[q], last) * N;
+            double sum = 0.0;
+            for (int k = 0; k < D_dp; k++)
+                if (k != i) sum = __dadd_rn(sum, wr[min((uint32_t)row[j * D_dp + k], last)]);
+            worst = fmax(worst, sum);
+        }
+    }
     if (ghat != nullptr)
         for (int j = threadIdx.x; j < D_pp; j += blockDim.x) ghat[(p * D_pp + j) * D_pp + j] = 0.0;
     for (int o = 32; o >= 1; o >>= 1) worst = fmax(worst, __shfl_xor(worst, o));
@@ -1032,7 +1051,8 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         hipLaunchKernelGGL(k_datap_rows, dim3((unsigned)(N / DTFM_DATAP_DPW * DTFM_DATAP_SPLIT)), dim3(256),
                            (size_t)DTFM_DATAP_DPW * N * sizeof(double), st, pr->W_dp, perm, b.pos, N, pr->D_dp, rows, b.rowsum);
         DTFM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_datap_reduce, dim3((unsigned)rows), dim3(256), 0, st, b.rowsum, N, n, b.datap, b.ghat, b.count);
+        hipLaunchKernelGGL(k_datap_reduce, dim3((unsigned)rows), dim3(256), 0, st, pr->W_dp, perm, b.pos, b.rowsum, N, pr->D_dp, n,
+                           b.datap, b.ghat, b.count);
     } else if ((size_t)N * N * sizeof(double) > ((size_t)2 << 20) && N % DTFM_XCDS == 0) {
         // W_dp larger than half an XCD's L2: one slice of its rows per XCD
         hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, b.datap, rows);

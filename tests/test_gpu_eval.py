@@ -339,3 +339,33 @@ def test_datap_by_device_and_by_candidate(D_dp, D_pp, rows):
     odd[1:] = dev(perms).reshape(-1)
     assert np.array_equal(host(dtfm.eval_population(g, odd[1:].view(rows, N))), cost)
     dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp,rows", [(32, 4, 70), (20, 8, 1025), (64, 16, 65)])
+def test_datap_of_rows_that_repeat_a_device(D_dp, D_pp, rows):
+    # rows are not checked: Eq. 2 over the listed devices, whatever the launch's size, the row's neighbours or earlier calls
+    N = D_dp * D_pp
+    w = custom(N, D_dp, D_pp, seed=5)
+    _, g = both(w)
+    perms = workloads.random_population(rows, N, seed=6)
+    dtfm.eval_population(g, dev(perms))                      # leaves positions and sums of other rows behind
+    bad = np.array([0, 3, rows - 1])
+    perms[0, 1] = perms[0, 0]                                # inside a stage
+    perms[3, N - 1] = perms[3, 0]                            # across stages
+    perms[rows - 1] = perms[rows - 1, 2]                     # one device everywhere
+    _, datap = dtfm.coarsened_graph(g, dev(perms))
+    W_dp, _ = dtfm.get_weights(g)
+    want = []
+    for row in perms[bad]:
+        worst = 0.0
+        for q in range(N):
+            C, total = row[q // D_dp * D_dp:][:D_dp], 0.0
+            for k in range(D_dp):
+                if k != q % D_dp:
+                    total += W_dp[row[q], C[k]]
+            worst = max(worst, total)
+        want.append(worst)
+    assert np.array_equal(host(datap)[bad], want)
+    few = host(dtfm.eval_population(g, dev(perms[bad])))     # by candidate
+    assert np.array_equal(host(dtfm.eval_population(g, dev(perms)))[bad], few)
+    dtfm.destroy_problem(g)

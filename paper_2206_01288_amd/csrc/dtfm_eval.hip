@@ -970,6 +970,15 @@ static bool datap_by_device(const dtfm_problem *pr, size_t rows)
            (pr->D_dp >= 16 && pr->N >= 160 && rows >= 1024);
 }
 
+// Positions and row sums are 12 N bytes a row, three times the population itself, and needed for one launch at a time: they
+// are kept for a slice of the rows, 128 MiB of them (1,048,576 rows of 512 devices took 6.4 GB). Three launches a slice are
+// some 10 us against 350 us of sums.
+static size_t datap_slice(const dtfm_problem *pr, size_t rows)
+{
+    const size_t most = ((size_t)128 << 20) / ((size_t)pr->N * (sizeof(int32_t) + sizeof(double)));
+    return rows < most ? rows : most;
+}
+
 // Blocks of 9 to 16 rows go four to a wavefront (k_match16) when there are more of them than 1536 for each row: below that a
 // search of its own per wavefront ends earlier than the longest of four, the more so the longer the searches are. Evaluation time
 // with k_match over that with k_match16 at 10,300 / 14,000 / 20,500 / 24,000 / 33,000 blocks, devices in regions: 16 rows (3 stages)
@@ -988,8 +997,8 @@ dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t ro
     b.pos = nullptr;
     b.rowsum = nullptr;
     if (!lean && datap_by_device(pr, rows)) {
-        b.pos = ar.take<int32_t>(rows * pr->N);
-        b.rowsum = ar.take<double>(rows * pr->N);
+        b.pos = ar.take<int32_t>(datap_slice(pr, rows) * pr->N);
+        b.rowsum = ar.take<double>(datap_slice(pr, rows) * pr->N);
     }
     b.datap = ar.take<double>(rows);
     b.ghat = ar.take<double>(rows * n * n);
@@ -1045,14 +1054,19 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     if (threads > 1024) threads = 1024;
     if (b.pos != nullptr && datap_by_device(pr, rows) && (reinterpret_cast<uintptr_t>(perm) & 15u) == 0) {
         // rows of W_dp in LDS, by device
-        const size_t total = rows * (size_t)N;
-        hipLaunchKernelGGL(k_positions, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, perm, N, total, b.pos);
-        DTFM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_datap_rows, dim3((unsigned)(N / DTFM_DATAP_DPW * DTFM_DATAP_SPLIT)), dim3(256),
-                           (size_t)DTFM_DATAP_DPW * N * sizeof(double), st, pr->W_dp, perm, b.pos, N, pr->D_dp, rows, b.rowsum);
-        DTFM_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_datap_reduce, dim3((unsigned)rows), dim3(256), 0, st, pr->W_dp, perm, b.pos, b.rowsum, N, pr->D_dp, n,
-                           b.datap, b.ghat, b.count);
+        const size_t slice = datap_slice(pr, rows);
+        for (size_t p0 = 0; p0 < rows; p0 += slice) {
+            const size_t cp = rows - p0 < slice ? rows - p0 : slice, total = cp * (size_t)N;
+            const int32_t *part = perm + p0 * N;
+            hipLaunchKernelGGL(k_positions, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, part, N, total, b.pos);
+            DTFM_HIP(hipGetLastError());
+            hipLaunchKernelGGL(k_datap_rows, dim3((unsigned)(N / DTFM_DATAP_DPW * DTFM_DATAP_SPLIT)), dim3(256),
+                               (size_t)DTFM_DATAP_DPW * N * sizeof(double), st, pr->W_dp, part, b.pos, N, pr->D_dp, cp, b.rowsum);
+            DTFM_HIP(hipGetLastError());
+            hipLaunchKernelGGL(k_datap_reduce, dim3((unsigned)cp), dim3(256), 0, st, pr->W_dp, part, b.pos, b.rowsum, N, pr->D_dp, n,
+                               b.datap + p0, b.ghat + p0 * n * n, b.count);
+            DTFM_HIP(hipGetLastError());
+        }
     } else if ((size_t)N * N * sizeof(double) > ((size_t)2 << 20) && N % DTFM_XCDS == 0) {
         // W_dp larger than half an XCD's L2: one slice of its rows per XCD
         hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, b.datap, rows);

@@ -369,3 +369,25 @@ def test_datap_of_rows_that_repeat_a_device(D_dp, D_pp, rows):
     few = host(dtfm.eval_population(g, dev(perms[bad])))     # by candidate
     assert np.array_equal(host(dtfm.eval_population(g, dev(perms)))[bad], few)
     dtfm.destroy_problem(g)
+
+
+def test_datap_by_device_in_slices_of_bounded_scratch():
+    # 12 N bytes a row are kept for 128 MiB of rows at a time (87,381 of 128 devices), whatever the population
+    D_dp, D_pp, P = 32, 4, 262_150
+    N = D_dp * D_pp
+    _, g = both(custom(N, D_dp, D_pp, seed=8))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    perm = torch.rand((P, N), generator=gen, device="cuda").argsort(dim=1).to(torch.int32)
+    cost = torch.empty(P, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    dtfm.eval_population(g, perm, cost)
+    torch.cuda.synchronize()
+    others = P * (8 + 8 * D_pp * D_pp + 8 + 4)               # DataP, graphs, tours, list
+    assert before - torch.cuda.mem_get_info()[0] <= 1.125 * (others + (128 << 20)) + (4 << 20)
+    edge = (128 << 20) // (12 * N)
+    for at in (0, edge - 20, 2 * edge - 20, 3 * edge - 20, P - 40):
+        some = perm[at:at + 40].clone()                      # by candidate
+        assert torch.equal(dtfm.eval_population(g, some), cost[at:at + 40]), at
+    dtfm.destroy_problem(g)

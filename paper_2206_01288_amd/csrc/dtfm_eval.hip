@@ -959,20 +959,24 @@ size_t dtfm_hk_exchange_bytes(const dtfm_problem *pr)
 }
 
 // DataP by device (k_datap_rows) needs D_dp a multiple of 4. It pays when W_dp is too large for an XCD's L2, when a stage has so
-// many devices that the gathers of k_datap are its time, and in larger launches where three launches do not matter. Whole
-// evaluations by candidate (by device), 64 / 512 / 3000 rows: 4 stages of 32 26.4 / 31.2 / 92.9 (26.1 / 31.0 / 76.4) us, 2 of 64 32.7 / 40.9 /
-// 111.8 (27.6 / 34.1 / 63.9), 8 of 64 54.6 / 141 / 711 (47.0 / 92.4 / 397); 1024 / 3000 rows: 16 of 16 305 / 659 (299 / 634), 10 of 16 141 /
-// 369 (140 / 362), 7 of 16 55 / 101 (57 / 102), 5 of 20 44 / 90 (47 / 93), 9 of 8 25.5 / 48.6 (31.3 / 61.0).
+// many devices that the gathers of k_datap are its time and there are devices enough to fill the chip (a workgroup for each),
+// and in larger launches where three launches do not matter. Whole evaluations by candidate (by device), 64 / 512 / 3000 rows: 4
+// stages of 32 26.4 / 31.2 / 92.9 (26.1 / 31.0 / 76.4) us, 2 of 64 32.7 / 40.9 / 111.8 (27.6 / 34.1 / 63.9), 8 of 64 54.6 / 141 / 711 (47.0 /
+// 92.4 / 397); 64 / 3000 / 40,000 rows: 1 of 32 14.6 / 14.2 / 91 (19.6 / 22.4 / 190), 1 of 64 15.6 / 27.3 / 279 (19.4 / 31.8 / 338), 2 of 32
+// 24.2 / 36.6 / 252 (24.1 / 43.6 / 325), 2 of 40 26.7 / 50.1 / 401 (25.6 / 53.2 / 413), 3 of 32 25.2 / 60.8 / 555 (24.5 / 57.6 / 490), 2 of 48
+// 28.1 / 65.4 / 562 (25.3 / 55.0 / 425); 1024 / 3000 rows: 16 of 16 305 / 659 (299 / 634), 10 of 16 141 / 369 (140 / 362), 7 of 16 55 / 101 (57 /
+// 102), 5 of 20 44 / 90 (47 / 93), 9 of 8 25.5 / 48.6 (31.3 / 61.0).
 static bool datap_by_device(const dtfm_problem *pr, size_t rows)
 {
     if (pr->D_dp % 4 != 0 || pr->N % DTFM_DATAP_DPW != 0 || rows < 64) return false;
-    return (size_t)pr->N * pr->N * sizeof(double) > ((size_t)2 << 20) || pr->D_dp >= 32 ||
+    return (size_t)pr->N * pr->N * sizeof(double) > ((size_t)2 << 20) || (pr->D_dp >= 32 && pr->N >= 96) ||
            (pr->D_dp >= 16 && pr->N >= 160 && rows >= 1024);
 }
 
 // Positions and row sums are 12 N bytes a row, three times the population itself, and needed for one launch at a time: they
-// are kept for a slice of the rows, 128 MiB of them (1,048,576 rows of 512 devices took 6.4 GB). Three launches a slice are
-// some 10 us against 350 us of sums.
+// are kept for a slice of the rows, 128 MiB of them (1,048,576 rows of 512 devices took 6.4 GB). The three launches
+// of a slice take 420 us (10,922 rows of 1024 devices), and the positions are still cached when they are read: 40,000 such rows 2.03 ms
+// in one slice, 1.92 so.
 static size_t datap_slice(const dtfm_problem *pr, size_t rows)
 {
     const size_t most = ((size_t)128 << 20) / ((size_t)pr->N * (sizeof(int32_t) + sizeof(double)));

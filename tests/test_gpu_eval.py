@@ -391,3 +391,27 @@ def test_datap_by_device_in_slices_of_bounded_scratch():
         some = perm[at:at + 40].clone()                      # by candidate
         assert torch.equal(dtfm.eval_population(g, some), cost[at:at + 40]), at
     dtfm.destroy_problem(g)
+
+
+@pytest.mark.parametrize("D_dp,D_pp", [(32, 1), (64, 1), (32, 2), (48, 2), (32, 3), (64, 4), (20, 8)])
+@pytest.mark.parametrize("rows", [64, 20000])
+def test_datap_goes_the_faster_way(D_dp, D_pp, rows):
+    # rows at an address that is no multiple of 16 always go by candidate: the others must not take longer
+    N = D_dp * D_pp
+    _, g = both(custom(N, D_dp, D_pp, seed=9))
+    perms = workloads.random_population(rows, N, seed=9)
+    buf = torch.empty(rows * N + 1, dtype=torch.int32, device="cuda")
+    buf[1:] = dev(perms).reshape(-1)
+    best = {}
+    for name, perm in (("any", dev(perms)), ("by candidate", buf[1:].view(rows, N))):
+        out = dtfm.coarsened_graph(g, perm)
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                dtfm.coarsened_graph(g, perm, out=out)
+            b.record()
+            b.synchronize()
+            best[name] = min(best.get(name, np.inf), a.elapsed_time(b) / 20)
+    assert best["any"] <= 1.1 * best["by candidate"] + 0.002, best
+    dtfm.destroy_problem(g)

@@ -28,6 +28,8 @@
 #include "dtfm_fast64_device.h"
 #include "dtfm_philox.h"
 
+#include <algorithm>
+
 namespace {
 
 // ---- LDS layout: tables shared by the workgroup, then one slice per wavefront ----
@@ -676,6 +678,7 @@ constexpr int SP_BYTES = (SP_MK + mk_bytes(4) + 15) / 16 * 16;
 constexpr int SP_AT = LDS_TABLES + LDS_WDP_BYTES;
 constexpr int SP_THREADS = 512;
 constexpr int STEADY_MAX_P = 4096;                       // 40 KiB of costs and row numbers
+constexpr int STEADY_RANKS = 192;                        // more rows are ranked by a launch of their own
 static_assert(SP_AT + SP_BYTES + STEADY_MAX_P * 10 + 64 <= 160 * 1024, "LDS budget of a CU");
 static_assert(SP_PB % 8 == 0 && SP_GHR % 4 == 0, "rows are read 8 bytes at a time");
 
@@ -960,12 +963,14 @@ k_ls_ahead_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_
 // ---- Sec. 3.4's loop with one offspring a generation, `generations` of them in one launch of one workgroup
 // A generation's launches for the offspring, its search and two for the ranking wait for each other; here the costs in rank order and the
 // rows they belong to (order) stay in LDS, the offspring takes the row of the member that it displaces, and the rows are put in
-// order when the last generation is done. sorted: cost and order hold a state of an earlier launch; else they are the
-// costs of the rows as they lie, which generation src.g's parents are drawn from by position before they are ranked.
+// order when the last generation is done. state: cost and order are those that an earlier launch left (SORTED), or the costs of
+// the rows as they lie, which generation src.g's parents are drawn from by position before they are ranked: with order their
+// ranks (RANKED), or by the workgroup itself (UNRANKED), which takes P comparisons of each of its threads for every SP_THREADS rows.
+enum { UNRANKED, RANKED, SORTED };
 __global__ void __launch_bounds__(SP_THREADS)
 k_steady_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_pp, const uint16_t *__restrict__ rank_tab,
                 const double *__restrict__ rank_val, int32_t *pop, double *__restrict__ cost, int32_t *__restrict__ order,
-                int sorted, int generations, int moves, double *__restrict__ trace, dtfm_offspring_src src)
+                int state, int generations, int moves, double *__restrict__ trace, dtfm_offspring_src src)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *sp = smem + SP_AT;
@@ -976,7 +981,7 @@ k_steady_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_pp
     const wave_ctx cx = ahead_setup(smem, rank_tab, rank_val, W_dp, W_pp);
     for (int i = tid; i < P; i += SP_THREADS) {
         key[i] = cost[i];
-        at[i] = (uint16_t)(sorted ? order[i] : i);
+        at[i] = (uint16_t)(state == SORTED ? order[i] : i);
     }
     __syncthreads();
     for (int g = 0; g < generations; g++, src.g++) {
@@ -999,14 +1004,16 @@ k_steady_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_pp
         constexpr int EACH = STEADY_MAX_P / SP_THREADS;
         double kk[EACH];
         int ka[EACH], kr[EACH];
-        if (!sorted) {   // rank under (cost, position)
+        if (state != SORTED) {   // rank under (cost, position)
 #pragma unroll
             for (int e = 0; e < EACH; e++) {
                 const int i = tid + e * SP_THREADS;
                 kr[e] = 0;
                 if (i >= P) continue;
                 kk[e] = key[i];
-                for (int j = 0; j < P; j++) kr[e] += key[j] < kk[e] || (key[j] == kk[e] && j < i) ? 1 : 0;
+                if (state == RANKED) kr[e] = order[i];
+                else
+                    for (int j = 0; j < P; j++) kr[e] += key[j] < kk[e] || (key[j] == kk[e] && j < i) ? 1 : 0;
             }
             __syncthreads();
 #pragma unroll
@@ -1015,7 +1022,7 @@ k_steady_fast64(const double *__restrict__ W_dp, const double *__restrict__ W_pp
                     key[kr[e]] = kk[e];
                     at[kr[e]] = (uint16_t)(tid + e * SP_THREADS);
                 }
-            sorted = 1;
+            state = SORTED;
         }
         if (tid == 0) before = 0;
         __syncthreads();
@@ -1280,21 +1287,29 @@ int dtfm_fast64_ls_gain4_enqueue(const dtfm_problem *pr, int32_t *perm, size_t r
     return DTFM_OK;
 }
 
-bool dtfm_fast64_steady(const dtfm_problem *pr, const dtfm_ga_params &prm)
+// Up to STEADY_RANKS rows the workgroup ranks them itself, above a launch over the whole chip does (all pairs of 4096 rows take one
+// workgroup 1 ms): 1 generation without a local search 40.4 and 43.1 us at 128 rows, 43.9 and 43.1 at 256, 102 and 45 at 1024, 1073 and 55
+// at 4096. Above that line a single generation has nothing to keep on the chip: 43.1 us at 1024 and 49.9 at 4096 by the
+// launches of a generation (2 generations 58.2 and 60.5, 68.4 and 67.3).
+bool dtfm_fast64_steady(const dtfm_problem *pr, const dtfm_ga_params &prm, int generations)
 {
-    return pr->fast64 && prm.neighbourhood == DTFM_GAIN4 && prm.lambda == 1 && prm.P <= STEADY_MAX_P;
+    return pr->fast64 && prm.neighbourhood == DTFM_GAIN4 && prm.lambda == 1 && prm.P <= STEADY_MAX_P &&
+           (generations > 1 || prm.P <= STEADY_RANKS);
 }
+
+bool dtfm_fast64_steady_wants_ranks(int P) { return P > STEADY_RANKS; }
 
 int dtfm_fast64_steady_enqueue(const dtfm_problem *pr, dtfm_offspring_src src, int generations, int moves, int32_t *population,
                                double *cost, double *best_trace, int32_t *order, int32_t *rows, hipStream_t st)
 {
     if (generations <= 0) return DTFM_OK;
-    constexpr int SPAN = 256;   // generations of a launch: some milliseconds
-    for (int g = 0; g < generations; g += SPAN) {
+    constexpr int span = 256;   // generations of a launch: some milliseconds
+    for (int g = 0; g < generations; g += span) {
         src.g = (uint32_t)g;
         hipLaunchKernelGGL(k_steady_fast64, dim3(1), dim3(SP_THREADS), SP_AT + SP_BYTES + (size_t)src.P * 10, st, pr->W_dp, pr->W_pp,
-                           pr->f64_rank, pr->f64_rank_val, population, cost, order, g > 0 ? 1 : 0,
-                           generations - g < SPAN ? generations - g : SPAN, moves, best_trace + g, src);
+                           pr->f64_rank, pr->f64_rank_val, population, cost, order,
+                           g > 0 ? SORTED : dtfm_fast64_steady_wants_ranks(src.P) ? RANKED : UNRANKED,
+                           std::min(generations - g, span), moves, best_trace + g, src);
         DTFM_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_rows_in_order, dim3((unsigned)src.P), dim3(NDEV), 0, st, population, order, rows);

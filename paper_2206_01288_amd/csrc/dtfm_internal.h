@@ -238,9 +238,11 @@ bool dtfm_fast64_ls_makes_offspring(const dtfm_problem *pr, size_t rows, int mov
 int dtfm_fast64_offspring_ls_gain4_enqueue(const dtfm_problem *pr, const dtfm_offspring_src &src, int32_t *perm,
                                            size_t rows, int moves, double *cost, hipStream_t st);
 
-// The generation-wise search with one offspring a generation in a few launches (k_steady_fast64). order: P ints, rows: P * N
-// ints of scratch; the population is in place and its costs are in cost.
-bool dtfm_fast64_steady(const dtfm_problem *pr, const dtfm_ga_params &prm);
+// The generation-wise search with one offspring a generation in a few launches (k_steady_fast64). order: P ints (in: the ranks
+// of the rows under (cost, position) if it wants them), rows: P * N ints of scratch; the population is in place and its costs are
+// in cost.
+bool dtfm_fast64_steady(const dtfm_problem *pr, const dtfm_ga_params &prm, int generations);
+bool dtfm_fast64_steady_wants_ranks(int P);
 int dtfm_fast64_steady_enqueue(const dtfm_problem *pr, dtfm_offspring_src src, int generations, int moves, int32_t *population,
                                double *cost, double *best_trace, int32_t *order, int32_t *rows, hipStream_t st);
 

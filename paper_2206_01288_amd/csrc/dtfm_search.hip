@@ -946,7 +946,22 @@ int dtfm_ga_enqueue(const dtfm_problem *pr, const dtfm_ga_bufs &b, uint64_t seed
     }
     int rc = dtfm_eval_enqueue(pr, b.ls.ev, population, P, cost, st);
     if (rc != DTFM_OK) return rc;
-    if (dtfm_fast64_steady(pr, prm)) {
+    auto rank = [&](const double *parents, const double *offspring, int members, int sorted) -> int {   // ranks added to b.rank
+        const int n = P + members;
+        int chunk = DTFM_RANK_CHUNK;   // longer chunks when the grid's second dimension would not hold the short ones
+        while ((n + chunk - 1) / chunk > 65535) chunk *= 2;
+        hipLaunchKernelGGL(k_rank_count, dim3((n + 255) / 256, (n + chunk - 1) / chunk), dim3(256), 0, st, parents, offspring, P,
+                           members, sorted, chunk, b.rank);
+        DTFM_HIP(hipGetLastError());
+        return DTFM_OK;
+    };
+    if (dtfm_fast64_steady(pr, prm, generations)) {
+        if (dtfm_fast64_steady_wants_ranks(P)) {
+            hipLaunchKernelGGL(k_fill_i32, dim3((P + 255) / 256), dim3(256), 0, st, b.rank, 0, (size_t)P);
+            DTFM_HIP(hipGetLastError());
+            rc = rank(cost, b.off_cost, 0, 0);
+            if (rc != DTFM_OK) return rc;
+        }
         const dtfm_offspring_src src = {k0, k1, 0u, population, P, prm.m_x, prm.m_m};
         return dtfm_fast64_steady_enqueue(pr, src, generations, prm.ls_moves, population, cost, best_trace, b.rank, b.next, st);
     }
@@ -969,11 +984,8 @@ int dtfm_ga_enqueue(const dtfm_problem *pr, const dtfm_ga_bufs &b, uint64_t seed
             rc = dtfm_ls_enqueue(pr, b.ls, b.off, L, prm.ls_moves, prm.neighbourhood, b.off_cost, nullptr, st);
             if (rc != DTFM_OK) return rc;
         }
-        int chunk = DTFM_RANK_CHUNK;   // longer chunks when the grid's second dimension would not hold the short ones
-        while ((nk + chunk - 1) / chunk > 65535) chunk *= 2;
-        hipLaunchKernelGGL(k_rank_count, dim3((nk + 255) / 256, (nk + chunk - 1) / chunk), dim3(256), 0,
-                           st, cost_cur, b.off_cost, P, L, g > 0 ? 1 : 0, chunk, b.rank);
-        DTFM_HIP(hipGetLastError());
+        rc = rank(cost_cur, b.off_cost, L, g > 0 ? 1 : 0);
+        if (rc != DTFM_OK) return rc;
         hipLaunchKernelGGL(k_rank_place, dim3(nk), dim3(DTFM_WAVE), 0, st, pop_cur, b.off, cost_cur, b.off_cost, P, L, N,
                            b.rank, pop_next, cost_next, best_trace + g);
         DTFM_HIP(hipGetLastError());

@@ -291,6 +291,36 @@ def test_evolve_one_offspring_above_and_below_the_population_in_lds():
         assert all(np.array_equal(host(a), b) for a, b in zip(got, ref)), P
 
 
+@pytest.mark.parametrize("P", [192, 193, 1500, 4096])
+@pytest.mark.parametrize("generations", [1, 2, 5])
+def test_evolve_one_offspring_first_ranking(P, generations):
+    # ranked by the workgroup up to 192 rows, by a launch of its own above; homogeneous network: all costs tie
+    o, g = both(workloads.config("C3h"))
+    start = workloads.random_population(P, 64, seed=2)
+    ref = o.evolve(4, generations, P, lam=1, ls_moves=1, population=start)
+    got = dtfm.evolve(g, 4, generations, P, lam=1, ls_moves=1, population=dev(start))
+    assert all(np.array_equal(host(a), b) for a, b in zip(got, ref))
+
+
+@pytest.mark.parametrize("P,generations", [(1024, 1), (4096, 2), (4096, 8)])
+def test_evolve_one_offspring_no_slower_than_above_the_line(P, generations):
+    # 4097 rows take a generation's launches one by one: fewer rows must not take longer for few generations
+    _, g = both(workloads.config("C2"))
+    best = {}
+    for n in (P, 4097):
+        dtfm.reserve(g, n, 1, dtfm.GAIN4)
+        dtfm.evolve(g, 1, generations, n, lam=1, ls_moves=1)
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                dtfm.evolve(g, 1, generations, n, lam=1, ls_moves=1)
+            b.record()
+            b.synchronize()
+            best[n] = min(best.get(n, np.inf), a.elapsed_time(b) / 10)
+    assert best[P] <= 1.15 * best[4097], best
+
+
 def test_evolve_steady_state_lambda_one():
     # the paper's loop: one offspring per generation, inserted iff better than the worst
     _evolve_parity(workloads.config("C1"), 11, 40, 7, lam=1, m_x=2, m_m=1, ls_moves=2, neighbourhood=dtfm.GAIN4)

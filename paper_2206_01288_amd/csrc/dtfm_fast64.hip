@@ -1303,7 +1303,8 @@ int dtfm_fast64_steady_enqueue(const dtfm_problem *pr, dtfm_offspring_src src, i
                                double *cost, double *best_trace, int32_t *order, int32_t *rows, hipStream_t st)
 {
     if (generations <= 0) return DTFM_OK;
-    constexpr int span = 256;   // generations of a launch: some milliseconds
+    // generations of a launch: 512 passes of four rounds, some 8 ms, or a single generation
+    const int passes = moves > DEEP ? (moves - 1) / DEEP + 1 : 1, span = std::max(512 / passes, 1);
     for (int g = 0; g < generations; g += span) {
         src.g = (uint32_t)g;
         hipLaunchKernelGGL(k_steady_fast64, dim3(1), dim3(SP_THREADS), SP_AT + SP_BYTES + (size_t)src.P * 10, st, pr->W_dp, pr->W_pp,

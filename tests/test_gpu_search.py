@@ -275,7 +275,7 @@ def test_gain4_rounds_ahead_up_to_a_workgroup_a_cu():
 @pytest.mark.parametrize("name,P,generations,moves", [("C2", 1, 5, 8), ("C2", 2, 1, 0), ("C2b", 7, 259, 3), ("C2", 300, 12, 8),
                                                       ("C3h", 33, 20, 9)])
 def test_evolve_one_offspring_a_generation(name, P, generations, moves):
-    # all generations in a launch (256 of them in the first); members of equal cost, the first ranking, a population of one
+    # all generations in a launch; members of equal cost, the first ranking, a population of one
     o, g = both(workloads.config(name))
     ref = o.evolve(5, generations, P, lam=1, ls_moves=moves)
     got = dtfm.evolve(g, 5, generations, P, lam=1, ls_moves=moves)
@@ -319,6 +319,39 @@ def test_evolve_one_offspring_no_slower_than_above_the_line(P, generations):
             b.synchronize()
             best[n] = min(best.get(n, np.inf), a.elapsed_time(b) / 10)
     assert best[P] <= 1.15 * best[4097], best
+
+
+def _kernels_of_a_capture(call):
+    """kernel nodes of the HIP graph that `call` is captured into (not run)"""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so")
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        out = call()
+    handle, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
+    del out
+    return count.value
+
+
+def test_evolve_one_offspring_launches_of_bounded_length():
+    # 512 passes of four rounds a launch: with 1000 rounds a generation, two generations
+    _, g = both(workloads.config("C2"))
+    dtfm.reserve(g, 8, 1, dtfm.GAIN4)
+    torch.cuda.synchronize()
+    few = _kernels_of_a_capture(lambda: dtfm.evolve(g, 1, 2, 8, lam=1, ls_moves=1000))
+    assert _kernels_of_a_capture(lambda: dtfm.evolve(g, 1, 40, 8, lam=1, ls_moves=1000)) == few + 19
+    assert _kernels_of_a_capture(lambda: dtfm.evolve(g, 1, 256, 8, lam=1, ls_moves=8)) == few
+    assert _kernels_of_a_capture(lambda: dtfm.evolve(g, 1, 257, 8, lam=1, ls_moves=8)) == few + 1
+
+
+@pytest.mark.parametrize("generations,moves", [(66, 32), (130, 31), (5, 1030)])
+def test_evolve_one_offspring_across_launches(generations, moves):
+    # 64 generations a launch, and two
+    o, g = both(workloads.config("C2"))
+    ref = o.evolve(6, generations, 3, lam=1, ls_moves=moves)
+    got = dtfm.evolve(g, 6, generations, 3, lam=1, ls_moves=moves)
+    assert all(np.array_equal(host(a), b) for a, b in zip(got, ref))
 
 
 def test_evolve_steady_state_lambda_one():

@@ -14,7 +14,8 @@
 // A swap inside a stage changes only the order of that stage's DataP sums.
 // The unchanged edges and the F tables are also where the round's own coarsened graph comes from
 // (replacing a row by itself), so a round costs 448 seven-row programmes, 1792 eight-row programmes
-// and 225 Held-Karp passes instead of 2016 full evaluations (56,448 eight-row programmes).
+// and, where every swap is priced (dtfm_move_costs), 225 Held-Karp passes instead of 2016 full evaluations (56,448 eight-row
+// programmes); the bounds leave a search 4 to 9 of the passes.
 #include "dtfm_fast64_device.h"
 
 namespace {
@@ -80,6 +81,8 @@ __device__ __forceinline__ void keep_best(double &bc, uint32_t &bk, double c, ui
     }
 }
 
+// PRICE: one round that writes the cost of every swap instead of applying the cheapest
+template <bool PRICE>
 __global__ void __launch_bounds__(WAVES_PER_BLOCK * 64)
 k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict__ rank_tab,
                      const double *__restrict__ rank_val_g, int32_t *__restrict__ perm, size_t P, int moves,
@@ -160,11 +163,10 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                 pp_base = hk_registers<false>(G, lane);
             }
             cur_cost = __dadd_rn(dp_base, pp_base);
-            const bool prune = move_cost == nullptr;   // pricing every swap: nothing may be left out
             // 28 batches (j < j') of 64 swaps, and an end that empties the queue
             int head = 0, queued = 0;
 #pragma nounroll
-            for (int batch = 0; batch <= 28; batch++) {
+            for (int batch = 0; batch <= (PRICE ? 27 : 28); batch++) {
                 int j = 0, jp = 1, cnt = 0;
                 double thr = INFINITY;
                 const int scr = (batch & 1) ? AP_EDGE_SCR_ODD : AP_EDGE_SCR;
@@ -221,8 +223,7 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                 // whose bound is strictly above the cheapest cost so far (or the row's own) can neither be applied nor
                 // tie with the winner, and is left out. 6 to 14 % of the swaps of random rows stay (by the m_v alone, each stage
                 // but the first entered by an edge of its own, 32 to 37 %; 1.5 to 2.7 % are cheaper than the threshold).
-                cnt = 64;
-                if (prune) {
+                if constexpr (!PRICE) {
                     thr = bestc;
 #pragma unroll
                     for (int o = 32; o >= 1; o >>= 1) thr = fmin(thr, __shfl_xor(thr, o));
@@ -253,6 +254,22 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                     WAVE_LDS_SYNC();
                 }
                 }
+                if constexpr (PRICE) {   // nothing may be left out, so nothing is queued (256 rows 1105 us, through the queue 1412)
+#pragma nounroll
+                    for (int pass = 0; pass < 8; pass++) {
+                        const int mv = pass * 8 + hm;
+                        double G[8];
+                        G[0] = 0.0;
+#pragma unroll
+                        for (int d = 1; d < 8; d++) G[d] = rank_val[edge[edge_index(mv, hv, hv ^ d)]];
+                        const double pp = hk_registers<false>(G, lane);
+                        const uint32_t a = 8 * j + (mv >> 3), b = 8 * jp + (mv & 7);
+                        if (hv == 0)
+                            move_cost[cand * (size_t)N_MOVES + (a * NDEV - a * (a + 1) / 2 + (b - a - 1))] = __dadd_rn(dpm[mv], pp);
+                    }
+                    WAVE_LDS_SYNC();   // the next batch overwrites the slice
+                    continue;
+                }
                 // ---- the swaps left, eight at a time: priced by a minimum spanning tree, which a path is no cheaper than (the
                 // same roundings), and queued for Held-Karp if that bound leaves them too (a quarter of them), so that its passes are
                 // full: 1,900 instructions against 280 of a pass here. 4096 rows, 20 rounds: 27.8 -> 23.8 ms ----
@@ -260,31 +277,29 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                 for (;;) {
                     const int slot = pass * 8 + hm;
                     if (pass * 8 < cnt && queued + 8 <= AP_QUEUE) {
-                        const int mv = prune ? list[min(slot, cnt - 1)] : slot;
+                        const int mv = list[min(slot, cnt - 1)];
                         uint32_t e[8];
 #pragma unroll
                         for (int d = 1; d < 8; d++) e[d] = edge[edge_index(mv, hv, hv ^ d)];
                         bool keep = slot < cnt;
-                        if (prune) {
-                            double tree = 0.0;
-                            uint32_t key = hv == 0 ? ~0u : 0x7FFFFFFFu;   // rank of the cheapest edge to the tree, and the stage
-                            int b = 0;
+                        double tree = 0.0;
+                        uint32_t key = hv == 0 ? ~0u : 0x7FFFFFFFu;   // rank of the cheapest edge to the tree, and the stage
+                        int b = 0;
 #pragma unroll
-                            for (int t = 0; t < 7; t++) {
-                                const int d = hv ^ b;   // 0: the stage that joined last
-                                const uint32_t x0 = (d & 1) ? e[1] : 0u, x1 = (d & 1) ? e[3] : e[2], x2 = (d & 1) ? e[5] : e[4],
-                                               x3 = (d & 1) ? e[7] : e[6];
-                                const uint32_t y0 = (d & 2) ? x1 : x0, y1 = (d & 2) ? x3 : x2, w = (d & 4) ? y1 : y0;
-                                key = d == 0 ? ~0u : key == ~0u ? ~0u : min(key, w << 3 | (uint32_t)hv);
-                                uint32_t k = key;
-                                k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_XOR1, 0xF, 0xF, true));
-                                k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_XOR2, 0xF, 0xF, true));
-                                k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_HALF_MIRROR, 0xF, 0xF, true));
-                                b = (int)(k & 7u);
-                                tree = __dadd_rn(tree, rank_val[k >> 3]);
-                            }
-                            keep = keep && !(__dadd_rn(dpm[mv], __dmul_rn(tree, 1.0 - 1e-12)) > thr);
+                        for (int t = 0; t < 7; t++) {
+                            const int d = hv ^ b;   // 0: the stage that joined last
+                            const uint32_t x0 = (d & 1) ? e[1] : 0u, x1 = (d & 1) ? e[3] : e[2], x2 = (d & 1) ? e[5] : e[4],
+                                           x3 = (d & 1) ? e[7] : e[6];
+                            const uint32_t y0 = (d & 2) ? x1 : x0, y1 = (d & 2) ? x3 : x2, w = (d & 4) ? y1 : y0;
+                            key = d == 0 ? ~0u : key == ~0u ? ~0u : min(key, w << 3 | (uint32_t)hv);
+                            uint32_t k = key;
+                            k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_XOR1, 0xF, 0xF, true));
+                            k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_XOR2, 0xF, 0xF, true));
+                            k = min(k, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)k, DPP_HALF_MIRROR, 0xF, 0xF, true));
+                            b = (int)(k & 7u);
+                            tree = __dadd_rn(tree, rank_val[k >> 3]);
                         }
+                        keep = keep && !(__dadd_rn(dpm[mv], __dmul_rn(tree, 1.0 - 1e-12)) > thr);
                         const uint64_t kept = __ballot(keep && hv == 0);
                         if (keep) {
                             const int q = (head + queued + __popcll(kept & ((1ull << (lane & 56)) - 1ull))) % AP_QUEUE;
@@ -319,8 +334,6 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                         const double total = __dadd_rn(*reinterpret_cast<const double *>(entry + 28), pp);
                         const uint32_t a = qkey[2 * q], b = qkey[2 * q + 1];
                         if (valid) keep_best(bestc, bestk, total, 64 * a + b);
-                        if (move_cost != nullptr && valid && hv == 0)
-                            move_cost[cand * (size_t)N_MOVES + (a * NDEV - a * (a + 1) / 2 + (b - a - 1))] = total;
                         head = (head + now) % AP_QUEUE;
                         queued -= now;
                         WAVE_LDS_SYNC();
@@ -347,10 +360,11 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                     if (q != s) d = fmax(d, dpb[q]);
                 const uint32_t a = 8 * s + i, b = 8 * s + k;
                 const double total = __dadd_rn(d, pp_base);
-                if (valid) keep_best(bestc, bestk, total, 64 * a + b);
-                if (move_cost != nullptr && valid)
+                if (!PRICE && valid) keep_best(bestc, bestk, total, 64 * a + b);
+                if (PRICE && valid)
                     move_cost[cand * (size_t)N_MOVES + (a * NDEV - a * (a + 1) / 2 + (b - a - 1))] = total;
             }
+            if constexpr (PRICE) break;   // the row stays as it is
             // ---- cheapest swap of the round (lowest index on ties); applied iff strictly cheaper ----
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) {
@@ -358,7 +372,6 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
                 const uint32_t ok = (uint32_t)__shfl_xor((int)bestk, o);
                 keep_best(bestc, bestk, oc, ok);
             }
-            if (move_cost != nullptr) break;   // pricing only: the row stays as it is
             const bool take = bestc < cur_cost;
             const int a = (int)(bestk >> 6), b = (int)(bestk & 63);
             if (applied != nullptr && lane == 0)
@@ -375,7 +388,7 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
             }
             WAVE_LDS_SYNC();
         }
-        if (move_cost == nullptr) {
+        if constexpr (!PRICE) {
             perm[cand * NDEV + lane] = cur[lane];
             if (lane == 0) cost[cand] = cur_cost;
         }
@@ -387,7 +400,9 @@ k_ls_allpairs_fast64(const double *__restrict__ W_dp, const uint16_t *__restrict
 
 int dtfm_fast64_allpairs_prepare()
 {
-    DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ls_allpairs_fast64),
+    DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ls_allpairs_fast64<false>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, AP_LDS_TOTAL));
+    DTFM_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_ls_allpairs_fast64<true>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, AP_LDS_TOTAL));
     return DTFM_OK;
 }
@@ -410,7 +425,7 @@ int dtfm_fast64_ls_allpairs_enqueue(const dtfm_problem *pr, int32_t *perm, size_
     const int wpb = ap_waves_per_block(pr, rows);
     size_t blocks = (rows + wpb - 1) / wpb;
     if (blocks > (size_t)pr->f64_grid) blocks = pr->f64_grid;
-    hipLaunchKernelGGL(k_ls_allpairs_fast64, dim3((unsigned)blocks), dim3(wpb * 64), LDS_TABLES + wpb * AP_WAVE_BYTES, st, pr->W_dp,
+    hipLaunchKernelGGL(k_ls_allpairs_fast64<false>, dim3((unsigned)blocks), dim3(wpb * 64), LDS_TABLES + wpb * AP_WAVE_BYTES, st, pr->W_dp,
                        pr->f64_rank, pr->f64_rank_val, perm, rows, moves, cost, applied, (double *)nullptr);
     DTFM_HIP(hipGetLastError());
     return DTFM_OK;
@@ -424,7 +439,7 @@ int dtfm_fast64_move_costs_enqueue(const dtfm_problem *pr, const int32_t *perm, 
     const int wpb = ap_waves_per_block(pr, rows);
     size_t blocks = (rows + wpb - 1) / wpb;
     if (blocks > (size_t)pr->f64_grid) blocks = pr->f64_grid;
-    hipLaunchKernelGGL(k_ls_allpairs_fast64, dim3((unsigned)blocks), dim3(wpb * 64), LDS_TABLES + wpb * AP_WAVE_BYTES, st, pr->W_dp,
+    hipLaunchKernelGGL(k_ls_allpairs_fast64<true>, dim3((unsigned)blocks), dim3(wpb * 64), LDS_TABLES + wpb * AP_WAVE_BYTES, st, pr->W_dp,
                        pr->f64_rank, pr->f64_rank_val, const_cast<int32_t *>(perm), rows, 1, (double *)nullptr,
                        (int64_t *)nullptr, move_cost);
     DTFM_HIP(hipGetLastError());

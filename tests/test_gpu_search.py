@@ -174,6 +174,29 @@ def test_gain4_odd_shapes(D_dp, D_pp):
     _ls_parity(custom(N, D_dp, D_pp, seed=N), workloads.random_population(20, N, seed=4), 12, dtfm.GAIN4)
 
 
+def test_pricing_every_swap_does_not_go_through_the_queue():
+    # 224 passes of Held-Karp against the few that the bounds leave a round of the search: 2.4 times its time, not 3.0
+    _, g = both(workloads.config("C2"))
+    rows = dev(workloads.random_population(256, 64, seed=1))
+    out, cost = dtfm.move_costs(g, rows), torch.empty(256, dtype=torch.float64, device="cuda")
+
+    def search():
+        dtfm.local_search(g, rows.clone(), 1, dtfm.ALL_PAIRS, cost=cost)
+
+    best = {}
+    for name, call in (("price", lambda: dtfm.move_costs(g, rows, out)), ("search", search)):
+        call()
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                call()
+            b.record()
+            b.synchronize()
+            best[name] = min(best.get(name, np.inf), a.elapsed_time(b) / 10)
+    assert best["price"] <= 2.65 * best["search"], best
+
+
 @pytest.mark.parametrize("neighbourhood", [dtfm.GAIN4, dtfm.BEST4])
 @pytest.mark.parametrize("values", [1, 3, 2000])
 @pytest.mark.parametrize("D_dp,D_pp", [(17, 3), (31, 2), (32, 3), (33, 2), (48, 3), (49, 2), (63, 3), (64, 2)])

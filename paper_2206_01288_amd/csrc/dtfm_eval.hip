@@ -987,11 +987,20 @@ static size_t datap_slice(const dtfm_problem *pr, size_t rows)
 // search of its own per wavefront ends earlier than the longest of four, the more so the longer the searches are. Evaluation time
 // with k_match over that with k_match16 at 10,300 / 14,000 / 20,500 / 24,000 / 33,000 blocks, devices in regions: 16 rows (3 stages)
 // 0.86 / 0.83 / 0.94 / 0.98 / 1.05, (8 stages) 0.95 / 0.96 / 1.04 / 1.02 / 1.09; 12 rows (7 stages) 0.96 / 0.97 / 1.07 / 1.09 / 1.17.
-// Blocks of at most 8 rows go to k_match_lanes, one launch's time whatever their number (20 rows of 9 stages of 5 20.6 us by k_match,
-// 18.2; of 16 stages of 8 104.5 and 105.8).
 static bool four_blocks_a_wavefront(const dtfm_problem *pr, size_t blocks)
 {
     return blocks > (size_t)1536 * pr->D_dp;
+}
+
+// Blocks of at most 8 rows go to k_match_lanes, whose programme and table take the same time whatever their number; a wavefront each
+// (k_match) is done sooner where there are few and the programme is long, or the table large. Kernel times by lanes (by wavefronts)
+// at some 20 / 300 / 1500 / 4500 blocks: 16 stages of 8 9.7 / 9.9 / 10.5 / 10.7 (6.6 / 6.7 / 7.2 / 10.3) us, 12 of 8 8.0 / 8.6 / 8.9 / 9.0
+// (5.0 / 5.8 / 7.2 / 9.3), 16 of 7 7.0 / 7.3 / 7.8 / 7.9 (5.5 / 5.8 / 6.4 / 8.8), 16 of 6 5.4 / 5.7 / 6.2 / 6.3 (4.8 / 4.9 / 6.2 / 8.2), 12 of 7
+// 5.7 / 6.0 / 6.5 / 6.6 (5.3 / 5.9 / 7.0 / 9.6), 9 of 8 7.6 / 7.5 / 8.2 / 8.8 (6.2 / 7.0 / 8.0 / 11.7), 7 of 8 7.0 / 7.0 / 8.1 / 8.3 (6.1 /
+// 8.0 / 8.4 / 12.1), 7 of 5 2.9 / 3.2 / 3.8 / 4.4 (4.8 / 5.0 / 5.9 / 8.3).
+static bool two_blocks_a_lane(const dtfm_problem *pr, size_t blocks)
+{
+    return pr->D_dp <= 8 && blocks > (pr->N >= 96 && pr->D_dp >= 6 ? 1536u : pr->D_dp == 8 ? (pr->N >= 72 ? 512u : 64u) : 0u);
 }
 
 dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t rows, size_t hk_grid_cap, bool lean)
@@ -1092,7 +1101,7 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         if (pr->D_dp > 16) {
             const int rc = dtfm_match_bits_enqueue(pr, perm, rows, match_pairs, b.ghat, inc_j, inc_jp, st);
             if (rc != DTFM_OK) return rc;
-        } else if (pr->D_dp <= 8) {
+        } else if (two_blocks_a_lane(pr, rows * (size_t)match_pairs)) {
             const int rc = dtfm_match_lanes_enqueue(pr, perm, rows, match_pairs, b.ghat, inc_j, inc_jp, st);
             if (rc != DTFM_OK) return rc;
         } else if (four_blocks_a_wavefront(pr, rows * (size_t)match_pairs)) {

@@ -43,14 +43,16 @@
 namespace {
 
 constexpr int WAVES = 4;               // candidates (= wavefronts) per workgroup
-constexpr int CAP = 224;               // states per layer and wavefront (see tour_lds)
+// states per layer and wavefront; PER: candidates of the workgroup. With one of them four workgroups share a CU's LDS (tour_lds).
+template <int PER>
+constexpr int CAP = PER == 1 ? 224 : 256;
 constexpr int SLOTS = 512;             // hash slots per wavefront
 constexpr int LOG_SLOTS = 9;
 constexpr int RSTR = 16;               // words between rows of the edge table
 constexpr int NARROW = 40;             // layers wider than this go to the whole workgroup
 constexpr int BATCH = 16 * 15;         // new states of one pass of a wavefront: 16 states, at most 15 successors each
 // a pass is begun at no more than NARROW states (a wavefront alone) or WAVES * CAP (each wavefront of a workgroup)
-static_assert(NARROW + BATCH < SLOTS && WAVES * (CAP + BATCH) < WAVES * SLOTS, "a search needs a free slot");
+static_assert(NARROW + BATCH < SLOTS && WAVES * (CAP<WAVES> + BATCH) < WAVES * SLOTS, "a search needs a free slot");
 constexpr int STEPS = 18;              // subgradient steps
 constexpr int LONE_STEPS = 16;         // the same where four step lengths go side by side
 constexpr int REFINE_STEPS = 60;       // of a candidate whose layers outgrow the workgroup's tables
@@ -64,10 +66,10 @@ constexpr double DOWN = 1.0 - 0x1p-50, UP = 1.0 + 0x1p-50;
 template <int PER>
 struct tour_lds {
     double G[PER][16][16];
-    double F[WAVES * CAP];
+    double F[WAVES * CAP<PER>];
     unsigned long long hF[WAVES * SLOTS];
     alignas(16) uint32_t hkey[WAVES * SLOTS];         // ascend() writes its edge tables 16 bytes at a time: here and T
-    uint32_t key[WAVES * CAP];         // set << 4 | last stage
+    uint32_t key[WAVES * CAP<PER>];         // set << 4 | last stage
     alignas(16) uint32_t T[PER][16][RSTR];            // (g_ij + pi_i) << 4
     int pi[PER][16];
     double scale[PER], U[PER], cap[PER], top[PER];
@@ -75,7 +77,7 @@ struct tour_lds {
     double lo[PER], thr[PER], grow[PER];   // where a wavefront's own threshold loop stopped
     int L[PER], state[PER], values[PER];   // values: see edge_values
     int count;
-    uint16_t slot[WAVES * CAP];
+    uint16_t slot[WAVES * CAP<PER>];
 };
 static_assert(sizeof(tour_lds<1>) <= 40960, "four workgroups a CU");
 enum { SEARCH = 0, SETTLED = 1, DENSE = 2, WIDE = 3, SOLVED = 4 };
@@ -364,7 +366,7 @@ __device__ __forceinline__ void expand(tour_lds<PER> &sm, int k, int n, int base
                                        const double *F, unsigned long long *hF, uint32_t *hkey, uint16_t *slot,
                                        const double (*G)[16], const uint32_t (*E)[RSTR], int &made)
 {
-    constexpr int cap = TEAM * CAP, slots = TEAM * SLOTS;
+    constexpr int cap = TEAM * CAP<PER>, slots = TEAM * SLOTS;
     constexpr int shift = 32 - LOG_SLOTS - (TEAM == 4 ? 2 : 0);
     const int i = tid & 15, lane = tid & 63;
     uint32_t S[NJ], dead[NJ], m[NJ], sum[NJ];
@@ -447,7 +449,7 @@ __device__ __forceinline__ void expand(tour_lds<PER> &sm, int k, int n, int base
     }
 }
 
-// The states of a search, layer by layer, for the back-tracking: n layers of up to WAVES * CAP.
+// The states of a search, layer by layer, for the back-tracking: n layers of up to WAVES * CAP<PER>.
 struct tour_record {
     double *F;
     uint32_t *key;
@@ -464,12 +466,12 @@ __device__ __forceinline__ int tour_search(tour_lds<PER> &sm, int cd, int tid, i
                                            const tour_record &rec)
 {
     constexpr int slots = TEAM * SLOTS, NG = TEAM * 4;
-    const int limit = TEAM == 1 ? NARROW : !RECORD && sm.values[cd] <= n / 2 ? 40 * n : TEAM * CAP;
+    const int limit = TEAM == 1 ? NARROW : !RECORD && sm.values[cd] <= n / 2 ? 40 * n : TEAM * CAP<PER>;
     const int at = TEAM == 1 ? cd : 0;
-    double *F = sm.F + at * CAP;
+    double *F = sm.F + at * CAP<PER>;
     unsigned long long *hF = sm.hF + at * SLOTS;
-    uint32_t *hkey = sm.hkey + at * SLOTS, *key = sm.key + at * CAP;
-    uint16_t *slot = sm.slot + at * CAP;
+    uint32_t *hkey = sm.hkey + at * SLOTS, *key = sm.key + at * CAP<PER>;
+    uint16_t *slot = sm.slot + at * CAP<PER>;
     const double (*G)[16] = sm.G[cd];
     const uint32_t (*E)[RSTR] = sm.T[cd];
     auto sync = [&]() {
@@ -516,8 +518,8 @@ __device__ __forceinline__ int tour_search(tour_lds<PER> &sm, int cd, int tid, i
             key[e] = hkey[h];
             F[e] = __longlong_as_double((long long)hF[h]);
             if (RECORD) {
-                rec.key[k * (WAVES * CAP) + e] = hkey[h];
-                rec.F[k * (WAVES * CAP) + e] = __longlong_as_double((long long)hF[h]);
+                rec.key[k * (WAVES * CAP<PER>) + e] = hkey[h];
+                rec.F[k * (WAVES * CAP<PER>) + e] = __longlong_as_double((long long)hF[h]);
             }
             hkey[h] = EMPTY;
             hF[h] = ~0ull;
@@ -740,8 +742,8 @@ k_tour_path(const double *__restrict__ ghat, int n, size_t P, double *__restrict
     __shared__ tour_lds<1> sm;
     const int tid = threadIdx.x, lane = tid & 63;
     double *slot = tab + (size_t)blockIdx.x * ((size_t)n << n);   // n * 2^n doubles hold the layers from n = 11 on
-    const tour_record rec = {slot, reinterpret_cast<uint32_t *>(slot + n * WAVES * CAP),
-                             reinterpret_cast<int *>(slot + n * WAVES * CAP + n * WAVES * CAP / 2)};
+    const tour_record rec = {slot, reinterpret_cast<uint32_t *>(slot + n * WAVES * CAP<1>),
+                             reinterpret_cast<int *>(slot + n * WAVES * CAP<1> + n * WAVES * CAP<1> / 2)};
     for (size_t p = blockIdx.x; p < P; p += gridDim.x) {
         __syncthreads();
         {
@@ -791,8 +793,8 @@ k_tour_path(const double *__restrict__ ghat, int n, size_t P, double *__restrict
                 double val = 0.0;
                 const int m = rec.count[k];
                 for (int e = lane; e < m; e += 64) {
-                    const uint32_t ky = rec.key[k * (WAVES * CAP) + e];
-                    const double f = rec.F[k * (WAVES * CAP) + e];
+                    const uint32_t ky = rec.key[k * (WAVES * CAP<1>) + e];
+                    const double f = rec.F[k * (WAVES * CAP<1>) + e];
                     const uint32_t u = ky & 15u;
                     if (ky >> 4 == S && u < best && (v < 0 ? f : __dadd_rn(f, sm.G[0][u][v])) == F) {
                         best = u;

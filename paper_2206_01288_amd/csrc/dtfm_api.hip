@@ -167,12 +167,13 @@ extern "C" int dtfm_create_problem(const double *latency, const double *bandwidt
         pr->weights = (int)vals.size();
         std::vector<uint32_t> rk(w.size());
         for (size_t i = 0; i < w.size(); i++) rk[i] = (uint32_t)(std::lower_bound(vals.begin(), vals.end(), w[i]) - vals.begin());
-        if (D_dp <= 16) {
+        if (D_dp <= 16 || (D_dp <= 48 && vals.size() <= 65533u)) {
             std::vector<uint16_t> code(w.size());
             for (size_t i = 0; i < w.size(); i++) code[i] = (uint16_t)(2u + rk[i]);
             CREATE_HIP(hipMalloc((void **)&pr->W_code, code.size() * sizeof(uint16_t)));
             CREATE_HIP(hipMemcpy(pr->W_code, code.data(), code.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
-        } else {
+        }
+        if (D_dp > 16) {
             CREATE_HIP(hipMalloc((void **)&pr->W_rank, rk.size() * sizeof(uint32_t)));
             CREATE_HIP(hipMemcpy(pr->W_rank, rk.data(), rk.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
         }

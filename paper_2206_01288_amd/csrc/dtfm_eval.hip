@@ -2,8 +2,9 @@
 //   k_weights     Sec. 2 symmetrisation + the per-link terms of Eqs. 2 and 3
 //   k_datap       Eq. 2 per stage and the max over stages (Sec. 3.2); for matrices beyond an XCD's L2
 //                 k_datap_sliced (by slice of devices) or k_positions + k_datap_rows + k_datap_reduce (by device)
-//   k_match       Eq. 3, stages of 9 to 16 devices: bottleneck perfect matching of one stage pair per wavefront; k_match16: of
-//                 four, when there are many (smaller stages: dtfm_match_lanes.hip, larger ones: dtfm_match.hip)
+//   k_match       Eq. 3: bottleneck perfect matching of one stage pair per wavefront, stages of 9 to 16 devices, few of smaller ones
+//                 and many of up to 48 on some networks; k_match16: of four, when there are many (smaller stages:
+//                 dtfm_match_lanes.hip, larger ones: dtfm_match.hip)
 //   k_held_karp   Eq. 4: open-loop TSP over the coarsened graph, exact, by subset dynamic
 //                 programming; adds the two parts (Eq. 1); k_held_karp_blocked from 11 stages on
 //   k_trial_shortcut   trials of the local search that the coarsened graph settles without Eq. 4
@@ -257,8 +258,8 @@ __global__ void k_zero_f64(double *__restrict__ dst, size_t n)
 //
 // Lane c keeps its column of the block in registers for the steps whose row index is known at compile time
 // (1 and 2). For the search, where the row comes from a lane, the wavefront keeps the block in LDS,
-// s_E[r * 64 + c] (all lanes read one row: no bank conflicts). Registers and LDS hold codes, 2 + rank in 16 bits (N <= 256
-// here: at most 32,641 ranks), pad 0xffff.
+// s_E[r * 64 + c] (all lanes read one row: no bank conflicts). Registers and LDS hold codes, 2 + rank in 16 bits (at most
+// 65,533 ranks), pad 0xffff.
 // dist carries, in its low 7 bits, the column whose matched row gave it (127: the inserted row), so relaxing is
 // one shift-OR and one unsigned minimum; a visited column parks that field in `parked` and holds dist = 0 from
 // then on, which no minimum changes. Lanes c >= D_dp hold the pad code and never take part.
@@ -294,16 +295,17 @@ __device__ __forceinline__ uint64_t dtfm_clear_bit(uint64_t m, int bit)
 // All steps for one block, by one wavefront. E: the lane's column as codes (pad 0xffff for the rows and lanes outside the
 // block); tile: room for the block's LDS copy, entry (row r, this lane) at tile[r * 64] (the caller passes its lane's base).
 // Returns the optimum's rank, or 0xffffffff if a search fails (cannot happen for a finite block).
-__device__ __forceinline__ uint32_t match_block(uint16_t *tile, const uint32_t (&E)[16], int lane, bool active, int D_dp)
+// R: 16, 32 or 48 rows, of which the first R - 16 exist for every D_dp.
+template <int R>
+__device__ __forceinline__ uint32_t match_block(uint16_t *tile, const uint32_t (&E)[R], int lane, bool active, int D_dp)
 {
-    constexpr int R = 16;
     uint32_t colmin = 0xffffu;
 #pragma unroll
     for (int r = 0; r < R; r++) colmin = min(colmin, E[r]);
     // the largest column minimum = ~ the smallest of the complements (idle lanes: complement of 0)
     uint32_t theta = ~dtfm_wave_min_u32(active ? ~colmin : 0xffffffffu);   // the threshold, as a code
 
-    const uint64_t allcols = D_dp >= 64 ? ~0ull : ((1ull << D_dp) - 1ull);
+    const uint64_t allcols = (1ull << D_dp) - 1ull;
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int r = 0; r < R; r++) tile[r * DTFM_WAVE] = (uint16_t)E[r];
@@ -315,7 +317,7 @@ __device__ __forceinline__ uint32_t match_block(uint16_t *tile, const uint32_t (
     int match_row = 0;   // row matched to this lane's column (meaningful when not free)
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        if (r < D_dp) {
+        if (r < R - 16 || r < D_dp) {
             uint64_t m = __ballot(E[r] <= theta);
             if (m == 0ull) {
                 theta = dtfm_wave_min_u32(E[r]);
@@ -395,25 +397,28 @@ __device__ __forceinline__ uint32_t match_block(uint16_t *tile, const uint32_t (
 // The lane's column of a block from the table of codes (pad 0xffff outside the block); rowdev(r): the device of row r. All
 // loads are in flight before the first is used: where only the lanes of the block need an entry the compiler otherwise gives
 // each load a branch for them and waits for one after another (1 allocation of 7 stages of 12: k_match 9.8 us, 8.1 so).
-template <typename RowDev>
+template <int R, typename RowDev>
 __device__ __forceinline__ void gather_column(const uint16_t *__restrict__ Wcode, RowDev rowdev, int N, uint32_t coldev, bool active,
-                                              int D_dp, uint32_t (&E)[16])
+                                              int D_dp, uint32_t (&E)[R])
 {
 #pragma unroll
-    for (int r = 0; r < 16; r++) E[r] = Wcode[rowdev(r < D_dp ? r : 0) * (uint32_t)N + coldev];
-    asm volatile("" : "+v"(E[0]), "+v"(E[1]), "+v"(E[2]), "+v"(E[3]), "+v"(E[4]), "+v"(E[5]), "+v"(E[6]), "+v"(E[7]));
-    asm volatile("" : "+v"(E[8]), "+v"(E[9]), "+v"(E[10]), "+v"(E[11]), "+v"(E[12]), "+v"(E[13]), "+v"(E[14]), "+v"(E[15]));
+    for (int r = 0; r < R; r++) E[r] = Wcode[rowdev(r < R - 16 || r < D_dp ? r : 0) * (uint32_t)N + coldev];
 #pragma unroll
-    for (int r = 0; r < 16; r++) E[r] = active && r < D_dp ? E[r] : 0xffffu;
+    for (int r = 0; r < R; r += 8)
+        asm volatile("" : "+v"(E[r]), "+v"(E[r + 1]), "+v"(E[r + 2]), "+v"(E[r + 3]), "+v"(E[r + 4]), "+v"(E[r + 5]), "+v"(E[r + 6]),
+                          "+v"(E[r + 7]));
+#pragma unroll
+    for (int r = 0; r < R; r++) E[r] = active && (r < R - 16 || r < D_dp) ? E[r] : 0xffffu;
 }
 
 // One wavefront (= one workgroup) per (candidate, stage pair): the lane gathers its column of the block from the
 // table of codes, 2 bytes an entry (pad 0xffff outside the block), and keeps the block's LDS copy as s_E[r * 64 + c].
-__global__ void __launch_bounds__(DTFM_WAVE)
+template <int R>
+__global__ void __launch_bounds__(DTFM_WAVE) __attribute__((amdgpu_waves_per_eu(5)))
 k_match(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_val, const int32_t *__restrict__ perm, int N, int D_dp,
         int D_pp, double *__restrict__ ghat, int inc_j, int inc_jp)
 {
-    __shared__ uint16_t s_E[16 * DTFM_WAVE];
+    __shared__ uint16_t s_E[R * DTFM_WAVE];
     const int lane = threadIdx.x;
     const bool active = lane < D_dp;
     const size_t p = blockIdx.x;   // candidate
@@ -422,7 +427,7 @@ k_match(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_val,
     const int32_t *row = perm + p * N;
     const int32_t *Ca = row + j1 * D_dp;   // wavefront-uniform: read through the scalar cache
     const uint32_t coldev = active ? (uint32_t)row[j2 * D_dp + lane] : 0u;
-    uint32_t E[16];
+    uint32_t E[R];
     gather_column(Wcode, [&](int r) { return (uint32_t)Ca[r]; }, N, coldev, active, D_dp, E);
     const uint32_t result = match_block(s_E + lane, E, lane, active, D_dp);
     if (lane == 0) {
@@ -1003,6 +1008,20 @@ static bool two_blocks_a_lane(const dtfm_problem *pr, size_t blocks)
     return pr->D_dp <= 8 && blocks > (pr->N >= 96 && pr->D_dp >= 6 ? 1536u : pr->D_dp == 8 ? (pr->N >= 72 ? 512u : 64u) : 0u);
 }
 
+// Blocks of 17 to 48 rows by smallest entries (k_match) instead of bit masks (k_match_bits), where a weight's rank fits a code: in
+// numbers, on networks whose links are all of their own, whose optimum is hardly above the largest row or column minimum that
+// these searches begin at; up to 18 rows on all networks. Kernel times by masks (by entries), links of their own, 30 / 4000 /
+// 10,000 / 140,000 blocks: 8 stages of 17 9.9 / 16.9 / 26.2 / 276 (7.8 / 15.2 / 22.4 / 186) us, of 22 9.3 / 18.7 / 28.5 / 295 (8.5 / 18.0 / 26.5 / 219);
+// 4000 / 10,000 / 140,000: of 28 21.1 / 33.4 / 325 (19.9 / 30.6 /
+// 256), of 33 27.2 / 43.6 / 406 (24.9 / 37.3 / 316), of 40 30.0 / 45.4 / 438 (29.4 / 45.9 / 357); in regions, 20,000 / 40,000 / 140,000: of 17 43 / 84 /
+// 276 (43 / 74 / 233), of 18 44 / 83 / 277 (45 / 78 / 241), of 20 46 / 86 / 285 (50 / 85 / 267), 2 of 17 33 / 60 / 191 (45 / 75 / 230).
+static bool match_by_codes(const dtfm_problem *pr, size_t blocks)
+{
+    if (pr->D_dp <= 16 || pr->W_code == nullptr) return false;
+    if (pr->digits.own) return blocks > (pr->D_dp <= 24 ? 0u : pr->D_dp <= 32 ? 2048u : 8192u);
+    return pr->D_dp <= 18 && pr->D_pp > 2 && blocks > 32768u;
+}
+
 dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t rows, size_t hk_grid_cap, bool lean)
 {
     dtfm_eval_bufs b;
@@ -1098,7 +1117,10 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
         const int match_pairs = inc_j >= 0 ? (inc_j == inc_jp ? 0 : 2 * n - 3) : pr->npairs;
         if (rows > 0x7fffffffu) return DTFM_ERR_ARG;
         if (match_pairs > 0) {
-        if (pr->D_dp > 16) {
+        if (match_by_codes(pr, rows * (size_t)match_pairs)) {
+            hipLaunchKernelGGL(pr->D_dp <= 32 ? k_match<32> : k_match<48>, dim3((unsigned)rows, (unsigned)match_pairs), dim3(DTFM_WAVE), 0,
+                               st, pr->W_code, pr->rank_val, perm, N, pr->D_dp, n, b.ghat, inc_j, inc_jp);
+        } else if (pr->D_dp > 16) {
             const int rc = dtfm_match_bits_enqueue(pr, perm, rows, match_pairs, b.ghat, inc_j, inc_jp, st);
             if (rc != DTFM_OK) return rc;
         } else if (two_blocks_a_lane(pr, rows * (size_t)match_pairs)) {
@@ -1109,7 +1131,7 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
                                pr->rank_val, perm, N, pr->D_dp, n, b.ghat, rows, inc_j, inc_jp);
         } else {
             // one wavefront per (candidate, stage pair)
-            hipLaunchKernelGGL(k_match, dim3((unsigned)rows, (unsigned)match_pairs), dim3(DTFM_WAVE), 0, st, pr->W_code, pr->rank_val,
+            hipLaunchKernelGGL(k_match<16>, dim3((unsigned)rows, (unsigned)match_pairs), dim3(DTFM_WAVE), 0, st, pr->W_code, pr->rank_val,
                                perm, N, pr->D_dp, n, b.ghat, inc_j, inc_jp);
         }
         DTFM_HIP(hipGetLastError());

@@ -39,6 +39,7 @@ struct dtfm_digits {
     int levels;        // digits of a rank
     int top[3];        // largest value of each
     int usual;         // leading digit that the optimum of a block usually has
+    bool own;          // as small as where every link is of its own (dtfm_match_usual)
 };
 
 struct dtfm_problem {
@@ -49,7 +50,7 @@ struct dtfm_problem {
     double *W_pp;           // device, N*N
     uint32_t *hk_subsets;   // device, 2^D_pp - 1 subsets ordered by (popcount, value)
     uint32_t *W_rank;       // device, N*N: dense rank of W_pp[d][d'] among all entries (stages of more than 16 devices)
-    uint16_t *W_code;       // device, N*N: 2 + rank (stages of at most 16 devices, N <= 256)
+    uint16_t *W_code;       // device, N*N: 2 + rank (stages of at most 16 devices, of up to 48 if there are at most 65,533 ranks)
     double *rank_val;       // device: rank -> weight
     dtfm_digits digits;     // stages of more than 16 devices
     int weights;            // different entries of W_pp

@@ -372,40 +372,47 @@ __global__ void k_digit_first(const double *__restrict__ rank_val, int ranks, in
 
 }  // namespace
 
-// The digit that the searches begin at: the usual one of the blocks of a random allocation (D_pp (D_pp - 1) / 2 of them).
+// The digit that the searches begin at: the usual one of the blocks of random allocations (32 blocks or more); and whether it is
+// that of a network whose links are all of their own.
 static int dtfm_match_usual(dtfm_problem *pr)
 {
-    const int N = pr->N, n = pr->D_pp;
-    if (pr->npairs < 1) {
+    const size_t N = pr->N, n = pr->D_pp, rows = pr->npairs < 1 ? 0 : (32 + pr->npairs - 1) / pr->npairs;
+    if (rows == 0) {
         DTFM_HIP(hipDeviceSynchronize());
         return DTFM_OK;
     }
-    std::vector<int32_t> row(N);
+    std::vector<int32_t> perm(rows * N);
     uint32_t x = 1u;
-    for (int q = 0; q < N; q++) {
-        x = x * 1664525u + 1013904223u;
-        const int at = (int)(((uint64_t)x * (uint64_t)(q + 1)) >> 32);
-        row[q] = row[at];
-        row[at] = q;
-    }
-    std::vector<double> first(128), graph((size_t)n * n), edges;
+    for (size_t p = 0; p < rows; p++)
+        for (size_t q = 0; q < N; q++) {   // a random device of those before gives way
+            x = x * 1664525u + 1013904223u;
+            const size_t at = (size_t)(((uint64_t)x * (uint64_t)(q + 1)) >> 32);
+            perm[p * N + q] = perm[p * N + at];
+            perm[p * N + at] = (int32_t)q;
+        }
+    std::vector<double> first(128), graph(rows * n * n), edges;
     char *mem = nullptr;
-    DTFM_HIP(hipMalloc((void **)&mem, graph.size() * sizeof(double) + row.size() * sizeof(int32_t)));
+    DTFM_HIP(hipMalloc((void **)&mem, graph.size() * sizeof(double) + perm.size() * sizeof(int32_t)));
     double *ghat = reinterpret_cast<double *>(mem);
-    int32_t *perm = reinterpret_cast<int32_t *>(mem + graph.size() * sizeof(double));
+    int32_t *perm_dev = reinterpret_cast<int32_t *>(mem + graph.size() * sizeof(double));
     int rc = DTFM_OK;
-    hipError_t e = hipMemcpy(perm, row.data(), row.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) rc = dtfm_match_bits_enqueue(pr, perm, 1, pr->npairs, ghat, -1, -1, (hipStream_t) nullptr);
+    hipError_t e = hipMemcpy(perm_dev, perm.data(), perm.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) rc = dtfm_match_bits_enqueue(pr, perm_dev, rows, pr->npairs, ghat, -1, -1, (hipStream_t) nullptr);
     if (e == hipSuccess && rc == DTFM_OK) e = hipMemcpy(graph.data(), ghat, graph.size() * sizeof(double), hipMemcpyDeviceToHost);
     if (e == hipSuccess && rc == DTFM_OK) e = hipMemcpy(first.data(), pr->digits.first, 128 * sizeof(double), hipMemcpyDeviceToHost);
     (void)hipFree(mem);
     if (rc != DTFM_OK) return rc;
     DTFM_HIP(e);
-    for (int a = 0; a < n; a++)
-        for (int b = a + 1; b < n; b++) edges.push_back(graph[a * n + b]);
+    for (size_t p = 0; p < rows; p++)
+        for (size_t a = 0; a < n; a++)
+            for (size_t b = a + 1; b < n; b++) edges.push_back(graph[(p * n + a) * n + b]);
     std::nth_element(edges.begin(), edges.begin() + edges.size() / 2, edges.end());
     const double usual = edges[edges.size() / 2];
-    pr->digits.usual = (int)std::max<ptrdiff_t>(std::upper_bound(first.begin(), first.end(), usual) - first.begin() - 1, 0);
+    dtfm_digits &dg = pr->digits;
+    dg.usual = (int)std::max<ptrdiff_t>(std::upper_bound(first.begin(), first.end(), usual) - first.begin() - 1, 0);
+    // D x D links of their own have a perfect matching about when no row and no column is left without one: at a share ln(2 D) / D
+    // of the weights. Found 0.16 to 0.21 at 17 devices (regions, tied or not: 0.31 to 0.7), 0.08 to 0.11 at 48 (0.24 to 0.34).
+    dg.own = (dg.usual + 0.5) / (dg.top[0] + 1) <= 1.4 * log(2.0 * pr->D_dp) / pr->D_dp;
     return DTFM_OK;
 }
 

@@ -1005,7 +1005,7 @@ static bool four_blocks_a_wavefront(const dtfm_problem *pr, size_t blocks)
 // 8.0 / 8.4 / 12.1), 7 of 5 2.9 / 3.2 / 3.8 / 4.4 (4.8 / 5.0 / 5.9 / 8.3).
 static bool two_blocks_a_lane(const dtfm_problem *pr, size_t blocks)
 {
-    return pr->D_dp <= 8 && blocks > (pr->N >= 96 && pr->D_dp >= 6 ? 1536u : pr->D_dp == 8 ? (pr->N >= 72 ? 512u : 64u) : 0u);
+    return pr->D_dp <= 8 && blocks > (pr->N >= 96 && pr->D_dp >= 6 ? 1280u * (pr->D_dp - 5) : pr->D_dp == 8 ? (pr->N >= 72 ? 512u : 64u) : 0u);
 }
 
 // Blocks of 17 to 48 rows by smallest entries (k_match) instead of bit masks (k_match_bits), where a weight's rank fits a code: in

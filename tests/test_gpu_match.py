@@ -144,11 +144,11 @@ def test_small_evaluations_in_one_launch(ties, D_dp, D_pp):
 
 
 @pytest.mark.parametrize("D_dp,D_pp,P", [(1, 7, 1), (2, 7, 3), (3, 7, 171), (4, 8, 2), (5, 11, 40), (6, 9, 700), (7, 8, 5), (8, 7, 90),
-                                         (8, 16, 60), (8, 16, 12), (8, 16, 13), (6, 16, 12), (6, 16, 13), (8, 9, 14), (8, 9, 15)])
+                                         (8, 16, 140), (8, 16, 32), (8, 16, 33), (7, 14, 28), (7, 14, 29), (6, 16, 10), (6, 16, 11), (8, 9, 14), (8, 9, 15)])
 @pytest.mark.parametrize("ties", [0, 3])
 def test_two_blocks_to_a_lane(ties, D_dp, D_pp, P):
     # odd and even numbers of stage pairs (the odd one out is matched twice) and of trial pairs; 16 x 8: codes up to 8130; the last
-    # six: numbers of blocks on both sides of the line below which a block has a wavefront
+    # eight: numbers of blocks on both sides of the line below which a block has a wavefront
     N = D_dp * D_pp
     rng = np.random.default_rng(D_dp + 100 * D_pp)
     lat = rng.uniform(1e-3, 0.1, (N, N)) if ties == 0 else rng.integers(1, ties + 1, (N, N)) * 0.01

@@ -949,7 +949,8 @@ k_trial_shortcut(const double *__restrict__ ghat, const double *__restrict__ dat
     }
     __syncthreads();
     if (wave != 0) return;
-    const bool open = lane < SHORTCUT_TRIALS && s_open[lane < SHORTCUT_TRIALS ? lane : 0] != 0;
+    const int waves = (int)blockDim.x / DTFM_WAVE;
+    const bool open = lane < waves && s_open[lane < waves ? lane : 0] != 0;
     const uint64_t all = __ballot(open);
     int first = lane == 0 && all != 0ull ? atomicAdd(count, __popcll(all)) : 0;
     first = __builtin_amdgcn_readfirstlane(first);
@@ -1140,8 +1141,10 @@ int dtfm_eval_inc_enqueue(const dtfm_problem *pr, const dtfm_eval_bufs &b, const
     if (cost == nullptr) return DTFM_OK;
     const int32_t *list = nullptr, *count = nullptr;
     if (ref != nullptr) {   // trials of the local search: Held-Karp only where the coarsened graph does not settle the trial
-        hipLaunchKernelGGL(k_trial_shortcut, dim3((unsigned)((rows + SHORTCUT_TRIALS - 1) / SHORTCUT_TRIALS)), dim3(SHORTCUT_TRIALS * DTFM_WAVE), 0, st, b.ghat, b.datap,
-                           n * n, ref->ghat_cur, ref->pp_cur, ref->cur, cost, b.pp, b.list, b.count, rows, ref->trials_per_row);
+        const size_t waves = rows < SHORTCUT_TRIALS ? rows : SHORTCUT_TRIALS;   // one trial: 2.2 us, as a workgroup of sixteen 2.6
+        hipLaunchKernelGGL(k_trial_shortcut, dim3((unsigned)((rows + SHORTCUT_TRIALS - 1) / SHORTCUT_TRIALS)),
+                           dim3((unsigned)waves * DTFM_WAVE), 0, st, b.ghat, b.datap, n * n, ref->ghat_cur, ref->pp_cur, ref->cur, cost,
+                           b.pp, b.list, b.count, rows, ref->trials_per_row);
         DTFM_HIP(hipGetLastError());
         list = b.list;
         count = b.count;

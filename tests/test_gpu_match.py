@@ -1,6 +1,7 @@
 """Matchings of blocks of 9 to 16 rows: four to a wavefront from 1536 blocks for each row on, one to a wavefront below; of at most
-8 rows a lane for two; of more on bit masks. Populations that leave the last wavefront with one, two and three candidates, all block sizes at the edges, weights with
-many ties and without any, whole evaluations and the trials of the local search, against the oracle to the bit."""
+8 rows a lane for two, few of them one to a wavefront; of more on bit masks or by smallest entries. Populations that leave the last
+wavefront with one, two and three candidates, all block sizes at the edges, weights with many ties and without any, whole
+evaluations and the trials of the local search, against the oracle to the bit."""
 import numpy as np
 import pytest
 import torch
@@ -13,11 +14,12 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("ties", [0, 2, 40])
-@pytest.mark.parametrize("D_dp,D_pp,P", [(1, 4, 1709), (2, 3, 3415), (3, 9, 289), (7, 8, 387), (8, 5, 1231), (9, 12, 213),
-                                         (15, 6, 1537), (16, 4, 4098), (16, 16, 207)])
-def test_four_blocks_to_a_wavefront(ties, D_dp, D_pp, P):
+@pytest.mark.parametrize("D_dp,D_pp,P", [(1, 4, 1709), (2, 3, 3415), (3, 9, 289), (7, 8, 387), (8, 5, 1231), (9, 12, 213), (10, 3, 5121),
+                                         (11, 9, 470), (13, 8, 714), (15, 6, 1537), (16, 4, 4098), (16, 16, 207)])
+def test_many_blocks_of_at_most_16_rows(ties, D_dp, D_pp, P):
+    # 9 to 16 rows: four blocks to a wavefront, the first rows alone one to a wavefront; fewer rows: two to a lane
     N, pairs = D_dp * D_pp, D_pp * (D_pp - 1) // 2
-    assert P * pairs > max(10240, 1536 * D_dp)
+    assert P * pairs > max(10240, 1536 * D_dp) and (D_dp <= 8 or 3 * pairs <= 1536 * D_dp)
     rng = np.random.default_rng(1000 * D_dp + D_pp + ties)
     lat = rng.uniform(1e-3, 0.1, (N, N)) if ties == 0 else rng.integers(1, ties + 1, (N, N)) * 0.01
     bw = 10.0 ** rng.uniform(7, 9, (N, N)) if ties == 0 else np.full((N, N), 1e9)
@@ -26,8 +28,8 @@ def test_four_blocks_to_a_wavefront(ties, D_dp, D_pp, P):
     o, g = both(workloads.Workload("match", N, D_dp, D_pp, 1e8, 1e7, lat, bw, 0))
     perms = workloads.random_population(P, N, seed=D_pp)
     cost = host(dtfm.eval_population(g, dev(perms)))
-    few = host(dtfm.eval_population(g, dev(perms[:3])))          # one block to a wavefront
-    assert np.array_equal(cost[:3], few)
+    graphs = host(dtfm.coarsened_graph(g, dev(perms))[0])
+    assert np.array_equal(graphs[:3], host(dtfm.coarsened_graph(g, dev(perms[:3]))[0]))
     some = np.arange(P) if D_pp <= 9 else np.r_[0:32, P - 8:P]   # the oracle's full recursion is slow from 12 stages on
     assert np.array_equal(cost[some], oracle_eval_threaded(o, perms[some]))
     if D_dp > 1 and D_pp <= 9:                                   # trials: 2 D_pp - 3 blocks of each of 4 P rows
@@ -63,8 +65,7 @@ def test_four_blocks_to_a_wavefront_of_many_stages(D_dp, D_pp, P):
     dtfm.destroy_problem(g)
 
 
-@pytest.mark.parametrize("D_dp,D_pp", [(12, 7), (16, 3)])
-@pytest.mark.parametrize("blocks", [10240, 1536 * 12, 1536 * 16])
+@pytest.mark.parametrize("D_dp,D_pp,blocks", [(9, 12, 1536 * 9), (12, 7, 1536 * 12), (16, 3, 1536 * 16), (17, 4, 32768), (18, 8, 32768)])
 def test_no_jump_where_the_kernel_changes(D_dp, D_pp, blocks):
     # one per cent more rows on the other side cost at most a tenth more
     N, pairs = D_dp * D_pp, D_pp * (D_pp - 1) // 2
@@ -191,3 +192,36 @@ def test_links_of_their_own_take_no_longer(D_dp):
             best[kind] = min(best.get(kind, np.inf), a.elapsed_time(b))
         dtfm.destroy_problem(g)
     assert best["own"] <= 1.25 * best["regions"], best
+
+
+@pytest.mark.parametrize("D_dp,D_pp,below,moves", [(2, 4, 512, None), (8, 5, 512, None), (16, 5, 512, None), (16, 6, 256, None), (16, 16, 1024, None),
+                                                   (4, 13, 1024, None), (1, 14, 512, None), (8, 16, 32, None), (8, 8, 256, 1),
+                                                   (8, 8, 256, 4), (8, 8, 256, 8)])
+def test_few_rows_take_no_longer_than_more(D_dp, D_pp, below, moves):
+    # launches of few rows go ways of their own up to a line (evaluation in one launch, lone tours, wavefronts for blocks of 8 rows,
+    # rounds priced ahead): never more time there than for a row, or a tenth of the rows, beyond it
+    N = D_dp * D_pp
+    w = workloads.Workload("few", N, D_dp, D_pp, 1e8, 1e7, *workloads.network_iid(N, seed=1), 0)
+    g = dtfm.create_problem(w.latency, w.bandwidth, w.c_dp, w.c_pp, D_dp, D_pp)
+    perms = dev(workloads.random_population(below + 1 if moves else below + below // 10, N, seed=2))
+    best = {}
+    for P in (below, len(perms)):
+        rows, out = perms[:P].clone(), torch.empty(P, dtype=torch.float64, device="cuda")
+
+        def call():
+            if moves:
+                dtfm.local_search(g, rows, moves, dtfm.GAIN4, cost=out)
+            else:
+                dtfm.eval_population(g, rows, out)
+
+        call()
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best[P] = min(best.get(P, np.inf), a.elapsed_time(b) / 20)
+    assert best[below] <= 1.1 * best[len(perms)] + 0.001, best
+    dtfm.destroy_problem(g)

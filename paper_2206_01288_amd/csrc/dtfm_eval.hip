@@ -5,6 +5,7 @@
 //   k_match       Eq. 3: bottleneck perfect matching of one stage pair per wavefront, stages of 9 to 16 devices, few of smaller ones
 //                 and many of up to 48 on some networks; k_match16: of four, when there are many (smaller stages:
 //                 dtfm_match_lanes.hip, larger ones: dtfm_match.hip)
+//   k_eval_small  Eqs. 1-4 in one launch, few candidates of at most 6 stages of at most 16 devices
 //   k_held_karp   Eq. 4: open-loop TSP over the coarsened graph, exact, by subset dynamic
 //                 programming; adds the two parts (Eq. 1); k_held_karp_blocked from 11 stages on
 //   k_trial_shortcut   trials of the local search that the coarsened graph settles without Eq. 4
@@ -579,9 +580,8 @@ k_match16(const uint16_t *__restrict__ Wcode, const double *__restrict__ rank_va
 // ------------------------------------------------------------------------------------------------
 // a5/a6: Held-Karp. tab[S*n + v] = cheapest path visiting exactly the stage set S and ending in v,
 // each candidate value formed as fl(tab[S \ v][u] + Ghat[u][v]). Subsets are processed in layers
-// of equal size (list `subsets` ordered by popcount), one (S, v) item per thread, with a workgroup
-// barrier between layers. The table is in LDS when it fits, else in this workgroup's slice of an
-// HBM scratch area. One workgroup walks over candidates p = blockIdx.x, += gridDim.x.
+// of equal size (list `subsets` ordered by popcount), one (S, v) item per thread, with a barrier between
+// layers and the table in LDS (up to DTFM_HK_LDS_MAX_DPP stages).
 // The layers of one candidate (tab and G in LDS), by `threads` threads, which sync() brings together; returns Eq. 4 in all of them.
 template <typename Sync>
 __device__ __forceinline__ double held_karp_layers(double *tab, const double *G, int n, const uint32_t *subsets,
@@ -613,6 +613,7 @@ __device__ __forceinline__ double held_karp_layers(double *tab, const double *G,
     return m;
 }
 
+// One workgroup walks over candidates p = blockIdx.x, += gridDim.x.
 __global__ void k_held_karp(const double *__restrict__ ghat, const double *__restrict__ datap, int n,
                             const uint32_t *__restrict__ subsets, dtfm_layer_off lo, double *__restrict__ cost, size_t P,
                             const int32_t *__restrict__ list, const int32_t *__restrict__ count,

@@ -444,7 +444,8 @@ int dtfm_match_prepare(dtfm_problem *pr)
 int dtfm_match_bits_enqueue(const dtfm_problem *pr, const int32_t *perm, size_t rows, int pairs, double *ghat, int inc_j, int inc_jp,
                             hipStream_t st)
 {
-    // twice the wavefronts that the chip holds, each with as many candidates of one stage pair as that takes
+    // 16,384 wavefronts, of which the chip holds 7,168 (28 a CU by their registers), each with as many candidates of one stage
+    // pair as that takes
     const size_t share = ((size_t)2 * 256 * 32 + pairs - 1) / pairs, chunks = rows < share ? rows : share;
     const unsigned waves = (unsigned)(chunks * pairs), w = waves <= 2048u ? 1u : WAVES;
     auto kern = pr->D_dp <= 24 ? k_match_bits<24> : pr->D_dp <= 32 ? k_match_bits<32> : pr->D_dp <= 48 ? k_match_bits<48> : k_match_bits<64>;

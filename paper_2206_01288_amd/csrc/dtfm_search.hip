@@ -149,11 +149,6 @@ __global__ void k_pick_apply(int32_t *__restrict__ perm, int N, long long M, siz
 }
 
 // ------------------------------------------------------------------------------------------------
-// GAIN4 proposal for round r, one wavefront per candidate. Stage pair (j, j') = pair number
-// r mod D_pp(D_pp-1)/2; fastest link inside each stage = lexicographically first minimiser of W_pp
-// over slot pairs; the four end-point swaps ranked by the paper's Gain (sums over the pre-swap
-// sets in slot order from +0.0, divided by D_dp, four terms combined left to right), first
-// maximiser wins. Writes the swapped allocation and the two positions.
 // The fastest link inside the stage of devices C[0 .. D): the first minimiser of W_pp over slot pairs, by one wavefront.
 __device__ __forceinline__ void fastest_link(const double *__restrict__ W_pp, const int32_t *C, int N, int D, int lane, int (&slot)[2],
                                              double &link)
@@ -233,6 +228,11 @@ __device__ __forceinline__ void fastest_link_digits(const uint8_t *__restrict__ 
     link = best;
 }
 
+// GAIN4 proposal for round r, one wavefront per candidate. Stage pair (j, j') = pair number
+// r mod D_pp(D_pp-1)/2; fastest link inside each stage = lexicographically first minimiser of W_pp
+// over slot pairs; the four end-point swaps ranked by the paper's Gain (sums over the pre-swap
+// sets in slot order from +0.0, divided by D_dp, four terms combined left to right), first
+// maximiser wins. Writes the swapped allocation and the two positions.
 template <bool DIGITS>
 __global__ void k_gain4_propose(const double *__restrict__ W_pp, const uint8_t *__restrict__ code, const int32_t *__restrict__ perm,
                                 int N, int D_dp, int D_pp, int r, int32_t *__restrict__ tmp_perm,

@@ -24,7 +24,7 @@
 //              too short for its entries, their next digits are gathered and searched first.
 // The result is mapped back through rank_val: no rounding is involved, and the way taken does not change the value.
 // Evaluation of 4096 candidates of 16 stages of 64: 4258 -> 2290 us against greedy pass and search by smallest entries on
-// 16-bit codes (3,220 scalar and 2,670 vector instructions a block; here 1,240 and 1,370, and a gather of half the bytes,
+// 16-bit codes (3,220 scalar and 2,670 vector instructions a block; here 1,240 and 1,450, and a gather of half the bytes,
 // which moves one cache line where that one moved two: 1.43 of the kernel's 1.9 ms are bare gathers).
 #include "dtfm_internal.h"
 

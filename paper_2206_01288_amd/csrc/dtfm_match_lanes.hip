@@ -1,7 +1,7 @@
 // Eq. 3 for stages of at most 8 devices: a lane takes two blocks of a candidate by the min-max programme over
 // column subsets that the 64-device kernels use (g[S] = min over c in S of max(g[S - c], w[row][c]), row by row; the table in
 // registers with compile-time indices, the two blocks in the halves of each). Its length does not depend on the data: 1016
-// maxima and 448 minima for two blocks of 8 rows in every lane, some 12 instructions of a wavefront a block, where the searches
+// maxima and 448 minima for two blocks of 8 rows in every lane, 18 vector instructions of a wavefront a block with the gathers, where the searches
 // of k_match16, four blocks a wavefront, take 200 to 300. Codes (2 + rank, N <= 128: at most 8130) are halves in the order of the
 // integers; the table of them is in LDS. Whole evaluations, by k_match and k_match16 (this way): 4000 allocations of 9 stages of 8
 // 120 (63) us, 30,000 of 5 stages of 8 177 (57), 30,000 of 16 stages of 8 2719 (1496), 4000 of 8 stages of 4 53 (30).

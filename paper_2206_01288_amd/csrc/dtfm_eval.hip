@@ -1012,16 +1012,16 @@ static bool two_blocks_a_lane(const dtfm_problem *pr, size_t blocks)
 
 // Blocks of 17 to 48 rows by smallest entries (k_match) instead of bit masks (k_match_bits), where a weight's rank fits a code: in
 // numbers, on networks whose links are all of their own, whose optimum is hardly above the largest row or column minimum that
-// these searches begin at; up to 18 rows on all networks. Kernel times by masks (by entries), links of their own, 30 / 4000 /
+// these searches begin at; up to 19 rows on all networks. Kernel times by masks (by entries), links of their own, 30 / 4000 /
 // 10,000 / 140,000 blocks: 8 stages of 17 9.9 / 16.9 / 26.2 / 276 (7.8 / 15.2 / 22.4 / 186) us, of 22 9.3 / 18.7 / 28.5 / 295 (8.5 / 18.0 / 26.5 / 219);
 // 4000 / 10,000 / 140,000: of 28 21.1 / 33.4 / 325 (19.9 / 30.6 /
 // 256), of 33 27.2 / 43.6 / 406 (24.9 / 37.3 / 316), of 40 30.0 / 45.4 / 438 (29.4 / 45.9 / 357); in regions, 20,000 / 40,000 / 140,000: of 17 43 / 84 /
-// 276 (43 / 74 / 233), of 18 44 / 83 / 277 (45 / 78 / 241), of 20 46 / 86 / 285 (50 / 85 / 267), 2 of 17 33 / 60 / 191 (45 / 75 / 230).
+// 276 (43 / 74 / 233), of 18 44 / 83 / 277 (45 / 78 / 241), of 19 45 / 87 / 288 (47 / 82 / 256), of 20 46 / 86 / 285 (50 / 85 / 267), 2 of 17 33 / 60 / 191 (45 / 75 / 230).
 static bool match_by_codes(const dtfm_problem *pr, size_t blocks)
 {
     if (pr->D_dp <= 16 || pr->W_code == nullptr) return false;
     if (pr->digits.own) return blocks > (pr->D_dp <= 24 ? 0u : pr->D_dp <= 32 ? 2048u : 8192u);
-    return pr->D_dp <= 18 && pr->D_pp > 2 && blocks > 32768u;
+    return pr->D_dp <= (pr->D_pp > 4 ? 19 : pr->D_pp > 2 ? 18 : 0) && blocks > 32768u;
 }
 
 dtfm_eval_bufs dtfm_eval_carve(const dtfm_problem *pr, dtfm_arena &ar, size_t rows, size_t hk_grid_cap, bool lean)

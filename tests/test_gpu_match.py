@@ -65,7 +65,7 @@ def test_four_blocks_to_a_wavefront_of_many_stages(D_dp, D_pp, P):
     dtfm.destroy_problem(g)
 
 
-@pytest.mark.parametrize("D_dp,D_pp,blocks", [(9, 12, 1536 * 9), (12, 7, 1536 * 12), (16, 3, 1536 * 16), (17, 4, 32768), (18, 8, 32768)])
+@pytest.mark.parametrize("D_dp,D_pp,blocks", [(9, 12, 1536 * 9), (12, 7, 1536 * 12), (16, 3, 1536 * 16), (17, 4, 32768), (18, 8, 32768), (19, 8, 32768)])
 def test_no_jump_where_the_kernel_changes(D_dp, D_pp, blocks):
     # one per cent more rows on the other side cost at most a tenth more
     N, pairs = D_dp * D_pp, D_pp * (D_pp - 1) // 2
@@ -90,10 +90,10 @@ def test_no_jump_where_the_kernel_changes(D_dp, D_pp, blocks):
 
 
 @pytest.mark.parametrize("D_dp,D_pp,P", [(17, 3, 9), (31, 4, 40), (32, 3, 700), (33, 4, 9), (47, 3, 40), (63, 4, 3), (64, 4, 40),
-                                         (64, 2, 900), (18, 3, 10930), (24, 2, 7), (32, 2, 2048), (33, 3, 2740), (48, 2, 8193)])
+                                         (64, 2, 900), (18, 3, 10930), (19, 5, 3277), (24, 2, 7), (32, 2, 2048), (33, 3, 2740), (48, 2, 8193)])
 @pytest.mark.parametrize("kind", ["equal", "few", "thousand", "all", "near"])
 def test_blocks_of_more_than_16_rows(kind, D_dp, D_pp, P):
-    # the last five: many blocks, which go by smallest entries on all networks (18 rows) or on those whose links are all of their
+    # the last six: many blocks, which go by smallest entries on all networks (18 and 19 rows) or on those whose links are all of their
     # own (all). Ranks of one digit (2 and 61 weights), two (1000) and three (16,130 and more); near: the blocks between two halves of
     # the network hold weights of neighbouring ranks only, so that columns hold many entries of the optimum's leading digit
     N = D_dp * D_pp
